@@ -34,6 +34,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E, vendor figure
 FP32_MFMA_PEAK_TFLOPS = 157.3     # MI355X, dense fp32 matrix rate
+BF16_MFMA_PEAK_TFLOPS = 2500.0    # MI355X, dense bf16 matrix rate
 FUSED_GATHER_MAX_PERCENT = 11     # curdkv_compress: above this share of rows kept, the fused kernel only scores
 
 
@@ -369,17 +370,19 @@ def main():
         "three_calls": calls,
     }
 
-    # An fp32 cache with a wide sketch is bound by the fp32 matrix rate, not by HBM: 4*d*r flop per
-    # token (2*d*r for key-only / value-only) against 8*d bytes.  The scoring kernel is then the
-    # dominant one and is priced against the fp32 MFMA peak; the HBM view stays beside it.
+    # An fp32 cache with a wide sketch can be bound by the matrix units rather than by HBM: 4*d*r flop per
+    # token (2*d*r for key-only / value-only) against 8*d bytes, on the fp32 units up to 32 columns, as six
+    # bf16 products each beyond.  The scoring kernel is then the dominant one and is priced against those
+    # units; the HBM view stays beside it.
     if cfg.dtype == "fp32" and not args.no_projection:
         flops = (4 if args.source == "kv" else 2) * d * cfg.r * heads * n
-        if flops / (FP32_MFMA_PEAK_TFLOPS * 1e12) > ab["total"] / (HBM_PEAK_GBS * 1e9):
+        peak = FP32_MFMA_PEAK_TFLOPS if cfg.r <= 32 else BF16_MFMA_PEAK_TFLOPS / 6
+        if flops / (peak * 1e12) > ab["total"] / (HBM_PEAK_GBS * 1e9):
             sc_ms = calls["ms"]["scores"]
             tf = flops / (sc_ms * 1e-3) / 1e12
             out["roofline"] = {"bound": "mfma", "kernel": "scores_f32_kernel (curdkv_scores: scoring kernel + normalisation)",
-                               "achieved": tf, "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
-                               "frac": tf / FP32_MFMA_PEAK_TFLOPS, "traffic": None,
+                               "achieved": tf, "peak": peak, "unit": "TFLOP/s",
+                               "frac": tf / peak, "traffic": None,
                                "algorithmic_flops_per_launch": flops, "avg_ms": sc_ms,
                                "whole_path_against_hbm": out["roofline"]}
 

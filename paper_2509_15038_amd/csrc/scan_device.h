@@ -245,29 +245,30 @@ __device__ __forceinline__ float scan_tiles(const SketchRegs<CB>& G, const uint4
     return acc_sum;
 }
 
-// ---- fp32 storage -----------------------------------------------------------------------
+// ---- fp32 storage, at most 32 sketch columns ---------------------------------------------
 // The same walk and the same lane roles as above with mfma_f32_16x16x4f32: lane L holds token
 // L%16 and, of every 64-byte stretch of its row, the 16 bytes (four floats) number L/16, so a
 // load instruction again asks for 64 contiguous bytes per row.  One MFMA takes one of the four
 // floats as the token operand; its sketch operand in lane L is
-// G[(4*s + L/16)*4 + e][16*cb + L%16] for step s = 0..7 and float e = 0..3.  The sketch lives
-// in registers up to 64 columns (32*CB floats per lane) and in LDS beyond (gs: the packed
-// sketch as it lies in memory, [cb][s][lane] float4).
+// G[(4*s + L/16)*4 + e][16*cb + L%16] for step s = 0..7 and float e = 0..3, 32*CB floats per
+// lane in registers.  HBM is the bound here (32 columns are 16 flop/B): splitting the products
+// over the bf16 matrix units, as the wider sketches do, measured 2 % slower (256 heads of 16384
+// tokens, r = 20: 746 us against 729).
 struct TileRegsF32 {    // one 32-token tile of K and of V as seen by a lane
     float4 k[2][8];
     float4 v[2][8];
 };
 
-template <int CB, bool IN_REGS>
+template <int CB>
 struct SketchF32 {
-    float4 g[IN_REGS ? CB : 1][8];
+    float4 g[CB][8];
 };
 
-template <int CB, bool IN_REGS, int SRC = kSrcKV, bool PROJ = true>
-__device__ __forceinline__ float scan_tiles_f32(const SketchF32<CB, IN_REGS>& G, const float4* __restrict__ gs,
-                                                const float4* __restrict__ Kh, const float4* __restrict__ Vh,
-                                                int32_t n, int32_t t_begin, int32_t t_end, float* lds_rows,
-                                                int32_t row0, int lane, uint32_t phase = 0) {
+template <int CB, int SRC = kSrcKV, bool PROJ = true>
+__device__ __forceinline__ float scan_tiles_f32(const SketchF32<CB>& G, const float4* __restrict__ Kh,
+                                                const float4* __restrict__ Vh, int32_t n, int32_t t_begin,
+                                                int32_t t_end, float* lds_rows, int32_t row0, int lane,
+                                                uint32_t phase = 0) {
     const int tok = lane & 15, q = lane >> 4;
     float acc_sum = 0.f;
     float pend = 0.f;
@@ -293,10 +294,6 @@ __device__ __forceinline__ float scan_tiles_f32(const SketchF32<CB, IN_REGS>& G,
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2) {
             float lk = SRC == kSrcV ? 0.25f : 0.f, lv = SRC == kSrcK ? 0.25f : 0.f;
-            // a sketch in LDS is read again for every sub-tile: the lane's offset is made opaque
-            // here, or the compiler lifts all of the loads out of the walk and runs out of registers
-            int gl = lane;
-            if (!IN_REGS) asm volatile("" : "+v"(gl));
             if (!PROJ) {                        // squared norm of the stored row: 32 of its 128 floats per lane
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {
@@ -315,7 +312,7 @@ __device__ __forceinline__ float scan_tiles_f32(const SketchF32<CB, IN_REGS>& G,
                 f32x4 ak = f32x4{0.f, 0.f, 0.f, 0.f}, av = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {
-                    const float4 g = IN_REGS ? G.g[IN_REGS ? cb : 0][s] : gs[(cb * 8 + s) * 64 + gl];
+                    const float4 g = G.g[cb][s];
                     if (SRC != kSrcV) {
                         const float4 x = r.k[t2][s];
                         ak = __builtin_amdgcn_mfma_f32_16x16x4f32(g.x, x.x, ak, 0, 0, 0);
@@ -349,6 +346,210 @@ __device__ __forceinline__ float scan_tiles_f32(const SketchF32<CB, IN_REGS>& G,
         }
     };
     walk_tiles<TileRegsF32>(n, t_begin, t_end, phase, load_tile, compute_tile, store_pair);
+    return acc_sum;
+}
+
+// ---- fp32 storage, more than 32 sketch columns -------------------------------------------
+// Lane roles as above; the products go through the bf16 matrix units.  A float is split into three bf16 numbers,
+// x = x1 + x2 + x3 exactly (rounded to nearest each time: 8 significant bits and a sign per part
+// hold 24 bits), the sketch likewise, and x*g is taken as the six products whose size is at
+// least 2^-18 of it:
+//     x3*g1 + x1*g3 + x2*g2  +  x1*g2 + x2*g1  +  x1*g1,
+// smallest first, accumulated in fp32.  What is left out (x2*g3, x3*g2, x3*g3) is below 2^-26 of
+// |x*g|, a quarter of the rounding of one fp32 product, and a product of bf16 numbers is exact:
+// the matrix unit rounds once per 32 terms instead of once per 4.  Error of the scores against 64
+// bits, relative 2-norm: r = 64 1.4e-7 with fp32 products, 0.9e-7 split; r = 128 1.3e-7 and 1.0e-7.
+// A float whose first part is infinite turns its row into NaN here; rescore_row then does such
+// a row again in plain fp32.
+//
+// Why: 4*d*r flop per 1024 bytes of a token's K and V rows made the fp32 matrix units the bound
+// from r = 64 on; six bf16 products take 6/16 of their time.  256 heads of 16384
+// tokens: r = 64 1148 -> 820 us (HBM alone: 720), r = 128 2146 -> 1260 us (the bf16 units are busy
+// two thirds of the time).
+//
+// The token operand of MFMA step s (0..3) in lane L are the floats of stretches 2s and 2s + 1,
+// d = (2s + e/4)*16 + (L/16)*4 + e%4 for e = 0..7, the sketch operand G[d][16*cb + L%16]: two
+// neighbouring float4 of the packed sketch.  The sketch's parts live in LDS
+// ([cb][s][part][lane], 12 KB per 16 columns) and are read once per 16 tokens of K and V.
+union Parts {           // eight floats as three bf16 operands, largest first
+    bf16x8 p[3];
+    uint32_t w[3][4];
+};
+
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+
+// two floats rounded to bf16 (nearest even), packed
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+
+__device__ __forceinline__ Parts split_bf16(const float4& a, const float4& b) {
+    const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    Parts r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float lo = x[2 * e], hi = x[2 * e + 1];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const uint32_t h = pack_bf16(lo, hi);
+            r.w[j][e] = h;
+            // exact: at most 16 bits remain after the first part, at most 8 after the second
+            lo -= __uint_as_float(h << 16);
+            hi -= __uint_as_float(h & 0xFFFF0000u);
+        }
+    }
+    return r;
+}
+
+template <int CB> constexpr int kSketchF32Chunks = CB * 4 * 3 * 64;     // 16-byte words in LDS
+
+// The whole workgroup splits the head's packed sketch ([cb][step 0..7][lane] float4) into LDS.
+template <int CB, int THREADS>
+__device__ __forceinline__ void split_sketch_to_lds(bf16x8* gs, const float4* __restrict__ Gh) {
+    for (int i = threadIdx.x; i < CB * 4 * 64; i += THREADS) {          // i = (cb*4 + s)*64 + lane
+        const int l = i & 63, cs = i >> 6;
+        const Parts p = split_bf16(Gh[cs * 128 + l], Gh[cs * 128 + 64 + l]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) gs[(cs * 3 + j) * 64 + l] = p.p[j];
+    }
+    __syncthreads();
+}
+
+// One row's squared projected norm in plain fp32, all lanes of a wave on the row's columns.
+template <int CB>
+__device__ float rescore_row(const bf16x8* gs, const float* __restrict__ row, int lane) {
+    float l = 0.f;
+    for (int c = lane; c < 16 * CB; c += 64) {
+        float y = 0.f;
+        for (int d = 0; d < kHeadDim; ++d) {
+            const int at = ((c >> 4) * 4 + (d >> 5)) * 3 * 64 + ((d >> 2) & 3) * 16 + (c & 15);
+            const int e = ((d >> 4) & 1) * 4 + (d & 3);
+            const float g = ((float)gs[at + 128][e] + (float)gs[at + 64][e]) + (float)gs[at][e];   // exact
+            y = fmaf(row[d], g, y);
+        }
+        l = fmaf(y, y, l);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) l += __shfl_xor(l, off, 64);
+    return l;
+}
+
+struct TileF32 {        // 16 tokens of K and of V as seen by a lane
+    float4 k[8];
+    float4 v[8];
+};
+
+// Scores tiles [t_begin, t_end) (32 tokens each, as elsewhere) of one head, 64 tokens at a time;
+// t_begin must be even, and t_end even or equal to ceil(n/32).  16 tokens are split into parts,
+// then the loads of the next 16 go out into the registers just freed and stay in flight while
+// the matrix units work on the parts: one buffer of 64 registers and 96 of parts, so that two
+// waves share a SIMD and one's splitting runs beside the other's products.  (One wave of two
+// 32-token buffers per SIMD took turns at the two: 950 us at r = 64, 1460 at r = 128.  Two chains
+// of products per 16 columns and wave, K's and V's, are enough: four measured 3 to 5 % slower.)
+template <int CB, int SRC = kSrcKV>
+__device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const float4* __restrict__ Kh,
+                                                const float4* __restrict__ Vh,
+                                                int32_t n, int32_t t_begin, int32_t t_end, float* lds_rows,
+                                                int32_t row0, int lane, uint32_t phase) {
+    const int tok = lane & 15, q = lane >> 4;
+    const int32_t groups = (t_end - t_begin + 1) >> 1;          // of 64 tokens
+    if (groups <= 0) return 0.f;
+    float acc_sum = 0.f;
+    float pend = 0.f;                                           // this lane's score of the current group
+    TileF32 r;
+    // rows past the end reload the last one; their scores are dropped
+    auto load = [&](int32_t first) {
+        int32_t row = first + tok;
+        row = row < n ? row : n - 1;
+        const size_t off = (size_t)(uint32_t)row * 32 + q;      // 32 float4 per row
+        if (SRC != kSrcV) {
+#pragma unroll
+            for (int s = 0; s < 8; ++s) r.k[s] = Kh[off + s * 4];
+        }
+        if (SRC != kSrcK) {
+#pragma unroll
+            for (int s = 0; s < 8; ++s) r.v[s] = Vh[off + s * 4];
+        }
+    };
+    auto step = [&](int part, int32_t next) {                   // scores the 16 tokens in r, loads those from `next`
+        Parts xk[4], xv[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (SRC != kSrcV) xk[s] = split_bf16(r.k[2 * s], r.k[2 * s + 1]);
+            if (SRC != kSrcK) xv[s] = split_bf16(r.v[2 * s], r.v[2 * s + 1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load(next);
+        __builtin_amdgcn_sched_barrier(0);
+        float lk = SRC == kSrcV ? 0.25f : 0.f, lv = SRC == kSrcK ? 0.25f : 0.f;
+        // the lane's offset is made opaque, or the compiler lifts the sketch's loads out of the walk
+        int gl = lane;
+        asm volatile("" : "+v"(gl));
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            f32x4 ak = f32x4{0.f, 0.f, 0.f, 0.f}, av = f32x4{0.f, 0.f, 0.f, 0.f};
+            bf16x8 g[4][3];
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) g[s][j] = gs[((cb * 4 + s) * 3 + j) * 64 + gl];
+            auto mac = [&](int s, int jg, int jx) {
+                if (SRC != kSrcV) ak = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[s][jg], xk[s].p[jx], ak, 0, 0, 0);
+                if (SRC != kSrcK) av = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[s][jg], xv[s].p[jx], av, 0, 0, 0);
+            };
+#pragma unroll
+            for (int s = 0; s < 4; ++s) { mac(s, 0, 2); mac(s, 2, 0); mac(s, 1, 1); }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) { mac(s, 1, 0); mac(s, 0, 1); }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) mac(s, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (SRC != kSrcV) lk = fmaf(ak[e], ak[e], lk);
+                if (SRC != kSrcK) lv = fmaf(av[e], av[e], lv);
+            }
+            __builtin_amdgcn_sched_barrier(0);                  // or several blocks' loads pile up in registers
+        }
+        const float lkv = combine_rows(lk, lv);
+        pend = q == part ? lkv : pend;
+    };
+    // the walk starts at a rotated group, as in walk_tiles (whole groups only)
+    const int32_t rot = (t_begin + 2 * groups) * kTileTokens <= n && groups >= 4 ? (int32_t)(phase % (uint32_t)groups) : 0;
+    const int32_t base = t_begin * kTileTokens;
+    int32_t g = rot;
+    load(base + g * 64);
+    for (int32_t i = 0; i < groups; ++i) {
+        const int32_t first = base + g * 64;
+        g = g + 1 == groups ? 0 : g + 1;
+        step(0, first + 16);
+        step(1, first + 32);
+        step(2, first + 48);
+        step(3, i + 1 < groups ? base + g * 64 : first + 48);   // (at the end these rows once more, from the L2, unused)
+        const int32_t row = first + lane;
+        if (row < n) {
+            lds_rows[row - row0] = pend;
+            acc_sum += pend;
+        }
+    }
+    if (__any(acc_sum != acc_sum)) {                            // some row is not a number: do those again
+        acc_sum = 0.f;
+        for (int32_t j = base; j < base + groups * 64; j += 64) {
+            const int32_t row = j + lane;
+            float v = row < n ? lds_rows[row - row0] : 0.f;
+            for (uint64_t bad = __ballot(v != v); bad; bad &= bad - 1) {
+                const int b = __ffsll((unsigned long long)bad) - 1;
+                const size_t at = (size_t)(uint32_t)(j + b) * kHeadDim;
+                const float lk = SRC == kSrcV ? 1.f : rescore_row<CB>(gs, (const float*)Kh + at, lane);
+                const float lv = SRC == kSrcK ? 1.f : rescore_row<CB>(gs, (const float*)Vh + at, lane);
+                if (lane == b) v = lk * lv;
+            }
+            if (row < n) {
+                lds_rows[row - row0] = v;
+                acc_sum += v;
+            }
+        }
+    }
     return acc_sum;
 }
 

@@ -13,17 +13,19 @@
 
 namespace curdkv {
 
-// Sum the four wave totals of a 256-thread block in a fixed order and store it.  A head
+// Sum the wave totals of a block (four or eight) in a fixed order and store it.  A head
 // scored by a single block (few new tokens during generation) can fold the total into the
 // head's running sum right here: sum = (restart ? 0 : sum) + total, in double, which is
 // what accumulate_sums_kernel computes from one partial.
+template <int WAVES>
 __device__ __forceinline__ void block_partial_store(float wave_total, float* dst, double* running, int restart) {
-    __shared__ float wsum[4];
+    __shared__ float wsum[WAVES];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) wsum[wave] = wave_total;
     __syncthreads();
     if (threadIdx.x == 0) {
-        const float total = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+        float total = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+        if (WAVES == 8) total += (wsum[WAVES - 4] + wsum[WAVES - 3]) + (wsum[WAVES - 2] + wsum[WAVES - 1]);
         *dst = total;
         if (running) *running = (restart ? 0.0 : *running) + (double)total;
     }
@@ -77,53 +79,54 @@ __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
         for (int32_t r = r0 + lane; r < r1; r += 64) __builtin_nontemporal_store(mine[r - r0], &sh[r]);
     }
-    block_partial_store(wave_sum(acc_sum), partial + (size_t)head * kMaxBlocksPerHead + blk,
-                        sums ? sums + head : nullptr, restart);
+    block_partial_store<4>(wave_sum(acc_sum), partial + (size_t)head * kMaxBlocksPerHead + blk,
+                           sums ? sums + head : nullptr, restart);
 }
 
 // ---------------------------------------------------------------------------
-// fp32 storage: the same structure with mfma_f32_16x16x4f32 (scan_device.h).  A lane's two
-// tile buffers take 256 registers, so a SIMD holds one wave and a compute unit one workgroup.
-// CB = 16-column blocks of the padded sketch: 2 and 4 keep the sketch in registers, 8 reads it
-// from LDS.  Up to 32 columns the kernel is bound by HBM, from 64 on by the fp32 matrix rate
-// (4*d*r flop per 1024 bytes of a token's K and V rows is 32 flop/B at r = 64).
+// fp32 storage: the same structure (scan_device.h).  CB = 16-column blocks of the padded sketch.
+// Up to 32 columns (CB = 2, and the ablation without projection) the sketch is in registers and a
+// lane's two tile buffers take 256 more: a SIMD holds one wave and a compute unit one workgroup
+// of four.  Wider sketches split the products over the bf16 matrix units: the sketch's parts share
+// the LDS with the score stages, and a workgroup has eight waves, two to a SIMD.
 // ---------------------------------------------------------------------------
-template <int CB> struct StageF32 {
-    static constexpr int kTiles = CB > 4 ? 128 : 256;     // 64 KB beside a 64 KB sketch, else 128 KB
+template <int CB> struct ShapeF32 {
+    static constexpr bool kSplit = CB > 2;
+    static constexpr int kWaves = kSplit ? 8 : 4;
+    static constexpr int kTiles = CB > 4 ? 48 : CB > 2 ? 96 : 256;    // per wave between bursts: 48, 96 or 128 KB in all
 };
 
 template <int CB, int SRC, bool PROJ>
-__global__ __launch_bounds__(256, 1) void scores_f32_kernel(
+__global__ __launch_bounds__((ShapeF32<CB>::kWaves * 64), (ShapeF32<CB>::kSplit ? 2 : 1)) void scores_f32_kernel(
     const float4* __restrict__ K, const float4* __restrict__ V, const float4* __restrict__ Gp,
     float* __restrict__ scores, float* __restrict__ partial, int64_t n, int blocks_per_head,
     int64_t out_stride, int64_t out_offset, double* __restrict__ sums, int restart) {
-    constexpr bool kInRegs = CB <= 4;             // (PROJ = false comes with CB = 2 and never touches the sketch)
-    constexpr int kStageTiles = StageF32<CB>::kTiles;
-    __shared__ float stage[4][kStageTiles * kTileTokens];
-    __shared__ float4 gs[kInRegs ? 1 : CB * 8 * 64];
+    constexpr bool kSplit = ShapeF32<CB>::kSplit;  // (PROJ = false comes with CB = 2 and never touches the sketch)
+    constexpr int kWaves = ShapeF32<CB>::kWaves;
+    constexpr int kStageTiles = ShapeF32<CB>::kTiles;
+    __shared__ float stage[kWaves][kStageTiles * kTileTokens];
+    __shared__ bf16x8 gs[kSplit ? kSketchF32Chunks<CB> : 1];
     const int head = blockIdx.x / blocks_per_head;
     const int blk = blockIdx.x - head * blocks_per_head;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
     const float4* Gh = Gp + (size_t)head * (CB * 8 * 64);
-    SketchF32<CB, kInRegs> G;
-    if (!PROJ) {
-    } else if (kInRegs) {
+    SketchF32<kSplit ? 1 : CB> G;
+    if (kSplit) {
+        split_sketch_to_lds<CB, kWaves * 64>(gs, Gh);
+    } else if (PROJ) {
 #pragma unroll
-        for (int cb = 0; cb < (kInRegs ? CB : 1); ++cb)
+        for (int cb = 0; cb < (kSplit ? 1 : CB); ++cb)
 #pragma unroll
             for (int s = 0; s < 8; ++s) G.g[cb][s] = Gh[(cb * 8 + s) * 64 + lane];
-    } else {
-        for (int i = threadIdx.x; i < CB * 8 * 64; i += 256) gs[i] = Gh[i];
-        __syncthreads();
     }
 
     const int32_t n32 = (int32_t)n;
     const int32_t tiles = (n32 + kTileTokens - 1) / kTileTokens;
-    const int32_t waves_per_head = blocks_per_head * 4;
+    const int32_t waves_per_head = blocks_per_head * kWaves;
     int32_t per_wave = (tiles + waves_per_head - 1) / waves_per_head;
     per_wave += per_wave & 1;                                   // whole pairs
-    const int32_t t_begin = (blk * 4 + wave) * per_wave;
+    const int32_t t_begin = (blk * kWaves + wave) * per_wave;
     const int32_t t_end = t_begin + per_wave < tiles ? t_begin + per_wave : tiles;
     const float4* Kh = K + (size_t)head * n * 32;               // 32 chunks of 16 bytes per row
     const float4* Vh = V + (size_t)head * n * 32;
@@ -133,13 +136,14 @@ __global__ __launch_bounds__(256, 1) void scores_f32_kernel(
     for (int32_t seg = t_begin; seg < t_end; seg += kStageTiles) {
         const int32_t seg_end = seg + kStageTiles < t_end ? seg + kStageTiles : t_end;
         const int32_t r0 = seg * kTileTokens;
-        acc_sum += scan_tiles_f32<CB, kInRegs, SRC, PROJ>(G, gs, Kh, Vh, n32, seg, seg_end, mine, r0, lane,
-                                                          scan_phase(head, blk * 4 + wave));
+        const uint32_t phase = scan_phase(head, blk * kWaves + wave);
+        if constexpr (kSplit) acc_sum += scan_tiles_f32_split<CB, SRC>(gs, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase);
+        else acc_sum += scan_tiles_f32<CB, SRC, PROJ>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase);
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
         for (int32_t r = r0 + lane; r < r1; r += 64) __builtin_nontemporal_store(mine[r - r0], &sh[r]);
     }
-    block_partial_store(wave_sum(acc_sum), partial + (size_t)head * kMaxBlocksPerHead + blk,
-                        sums ? sums + head : nullptr, restart);
+    block_partial_store<kWaves>(wave_sum(acc_sum), partial + (size_t)head * kMaxBlocksPerHead + blk,
+                                sums ? sums + head : nullptr, restart);
 }
 
 // ---------------------------------------------------------------------------
@@ -212,12 +216,14 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
     const int64_t tiles = (n + kTileTokens - 1) / kTileTokens;
     const bool wide = ctx->cfg.dtype == CURDKV_DTYPE_BF16 && ctx->col_blocks > 2 && !ctx->cfg.no_projection;
     const bool f32 = ctx->cfg.dtype == CURDKV_DTYPE_F32;         // one workgroup per compute unit, like the wide kernel
-    const int64_t stage = f32 ? (ctx->col_blocks > 2 && !ctx->cfg.no_projection ? StageF32<8>::kTiles : StageF32<4>::kTiles)
+    const int cb = ctx->cfg.no_projection ? 1 : ctx->col_blocks;
+    const int waves = f32 && cb > 1 ? ShapeF32<4>::kWaves : 4;       // per workgroup
+    const int64_t stage = f32 ? (cb == 1 ? ShapeF32<2>::kTiles : cb == 2 ? ShapeF32<4>::kTiles : ShapeF32<8>::kTiles)
                               : (wide ? Stage<8>::kTiles : Stage<4>::kTiles);
     const int64_t slots = (int64_t)ctx->num_cu * ((wide || f32 || ctx->heads <= ctx->num_cu) ? 1 : 2);
-    int64_t cap = (tiles + 3) / 4;                                     // at least one tile per wave
+    int64_t cap = (tiles + waves - 1) / waves;                                     // at least one tile per wave
     if (cap > kMaxBlocksPerHead) cap = kMaxBlocksPerHead;
-    int64_t lo = (tiles + 4 * stage - 1) / (4 * stage);
+    int64_t lo = (tiles + waves * stage - 1) / (waves * stage);
     if (lo > cap) lo = cap;
     if (lo < 1) lo = 1;
     if (!wide && !f32 && lo <= 2 && ctx->heads <= 2 * (int64_t)ctx->num_cu) {
@@ -227,7 +233,7 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
     const int64_t hi = lo + 15 < cap ? lo + 15 : cap;
     auto cost = [&](int64_t b) {                                       // rounds x tiles a wave works through
         const int64_t rounds = ((int64_t)ctx->heads * b + slots - 1) / slots;
-        int64_t per_wave = (tiles + 4 * b - 1) / (4 * b);
+        int64_t per_wave = (tiles + waves * b - 1) / (waves * b);
         per_wave += per_wave & 1;                                      // whole pairs, as in the kernel
         return rounds * per_wave;
     };
@@ -253,12 +259,12 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
     if (bph != 1) sums = nullptr;                 // several blocks per head: the caller adds the partials
     if (summed) *summed = sums != nullptr;
     const int rs = restart ? 1 : 0;
-    const dim3 grid((unsigned)(ctx->heads * bph)), block(256);
+    const dim3 grid((unsigned)(ctx->heads * bph));
     if (ctx->cfg.dtype == CURDKV_DTYPE_BF16) {
         const uint4* k = (const uint4*)K; const uint4* v = (const uint4*)V; const uint4* g = (const uint4*)ctx->d_G;
         float* part = ctx->d_partial;
 #define CURDKV_LAUNCH(CBV, SRCV, PROJV) \
-    scores_bf16_kernel<CBV, SRCV, PROJV><<<grid, block, 0, stream>>>(k, v, g, scores, part, n, bph, out_stride, out_offset, sums, rs)
+    scores_bf16_kernel<CBV, SRCV, PROJV><<<grid, 256, 0, stream>>>(k, v, g, scores, part, n, bph, out_stride, out_offset, sums, rs)
 #define CURDKV_BY_SRC(CBV, PROJV)                                                   \
     switch (ctx->cfg.score_source) {                                                \
         case CURDKV_SCORE_KEY: CURDKV_LAUNCH(CBV, kSrcK, PROJV); break;             \
@@ -280,7 +286,7 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
         const float4* k = (const float4*)K; const float4* v = (const float4*)V; const float4* g = (const float4*)ctx->d_G;
         float* part = ctx->d_partial;
 #define CURDKV_LAUNCH(CBV, SRCV, PROJV) \
-    scores_f32_kernel<CBV, SRCV, PROJV><<<grid, block, 0, stream>>>(k, v, g, scores, part, n, bph, out_stride, out_offset, sums, rs)
+    scores_f32_kernel<CBV, SRCV, PROJV><<<grid, ShapeF32<CBV>::kWaves * 64, 0, stream>>>(k, v, g, scores, part, n, bph, out_stride, out_offset, sums, rs)
 #define CURDKV_BY_SRC(CBV, PROJV)                                                   \
     switch (ctx->cfg.score_source) {                                                \
         case CURDKV_SCORE_KEY: CURDKV_LAUNCH(CBV, kSrcK, PROJV); break;             \
