@@ -45,13 +45,15 @@ bool on_own_device(const curdkv_ctx* ctx) {
 
 // Checks offsets (host) and makes the device copy current on `stream`.
 int sync_offsets(curdkv_ctx* ctx, const int64_t* offsets, const int32_t* budgets, int64_t n,
-                 hipStream_t stream, int64_t* total) {
+                 hipStream_t stream, int64_t* total, int64_t* max_budget) {
     const int heads = ctx->heads;
     if (offsets[0] != 0) return CURDKV_ERR_INVALID_ARG;
+    *max_budget = 0;
     for (int i = 0; i < heads; ++i) {
         const int64_t k = offsets[i + 1] - offsets[i];
         if (k < 0 || k > n) return CURDKV_ERR_INVALID_ARG;
         if (budgets && (int64_t)budgets[i] != k) return CURDKV_ERR_INVALID_ARG;
+        if (k > *max_budget) *max_budget = k;
     }
     *total = offsets[heads];
     Plan& pl = ctx->plan;
@@ -101,6 +103,7 @@ void release(curdkv_ctx* ctx) {
     if (!ctx) return;
     if (ctx->d_G) (void)hipFree(ctx->d_G);
     if (ctx->d_partial) (void)hipFree(ctx->d_partial);
+    if (ctx->d_split_ws) (void)hipFree(ctx->d_split_ws);
     if (ctx->d_scores_ws) (void)hipFree(ctx->d_scores_ws);
     if (ctx->d_adaptive_ws) (void)hipFree(ctx->d_adaptive_ws);
     if (ctx->d_adaptive_blocks) (void)hipFree(ctx->d_adaptive_blocks);
@@ -199,6 +202,12 @@ int curdkv_create(curdkv_ctx** out, const curdkv_config* cfg) {
         release(ctx);
         return CURDKV_ERR_OOM;
     }
+    // workspace of the split selection, where a call can be long enough for it
+    if (split_wanted(ctx) && hipMalloc(&ctx->d_split_ws, split_workspace_bytes(ctx)) != hipSuccess) {
+        (void)hipGetLastError();
+        release(ctx);
+        return CURDKV_ERR_OOM;
+    }
     ctx->plan.d_offsets = reinterpret_cast<int64_t*>(ctx->plan.d_buf);
     ctx->plan.d_block_info = reinterpret_cast<BlockInfo*>(ctx->plan.d_buf + off_bytes);
     if (hipEventCreateWithFlags(&ctx->plan.copied, hipEventDisableTiming) != hipSuccess) {
@@ -286,12 +295,13 @@ int curdkv_select(curdkv_ctx* ctx, const float* scores, int64_t n, const int32_t
     if (!ctx || !scores || !budgets || !offsets) return CURDKV_ERR_INVALID_ARG;
     if (!on_own_device(ctx)) return CURDKV_ERR_INVALID_ARG;
     if (n < 1 || n > ctx->cfg.max_tokens || n_sink < 0) return CURDKV_ERR_INVALID_ARG;
-    int64_t total = 0;
-    const int rc = sync_offsets(ctx, offsets, budgets, n, (hipStream_t)stream, &total);
+    int64_t total = 0, max_budget = 0;
+    const int rc = sync_offsets(ctx, offsets, budgets, n, (hipStream_t)stream, &total, &max_budget);
     if (rc != CURDKV_OK) return rc;
     if (total == 0) return CURDKV_OK;
     if (!indices) return CURDKV_ERR_INVALID_ARG;
-    return launch_select(ctx, const_cast<float*>(scores), n, n_sink, ctx->plan.d_offsets, indices, (hipStream_t)stream) == hipSuccess
+    return launch_select(ctx, const_cast<float*>(scores), n, n_sink, ctx->plan.d_offsets, max_budget, indices,
+                         (hipStream_t)stream) == hipSuccess
                ? CURDKV_OK : CURDKV_ERR_HIP;
 }
 
@@ -301,8 +311,8 @@ int curdkv_compact(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, con
     if (!on_own_device(ctx)) return CURDKV_ERR_INVALID_ARG;
     if (n < 1 || n > ctx->cfg.max_tokens) return CURDKV_ERR_INVALID_ARG;
     if (((uintptr_t)K | (uintptr_t)V | (uintptr_t)K_out | (uintptr_t)V_out) & 15u) return CURDKV_ERR_INVALID_ARG;
-    int64_t total = 0;
-    const int rc = sync_offsets(ctx, offsets, nullptr, n, (hipStream_t)stream, &total);
+    int64_t total = 0, max_budget = 0;
+    const int rc = sync_offsets(ctx, offsets, nullptr, n, (hipStream_t)stream, &total, &max_budget);
     if (rc != CURDKV_OK) return rc;
     if (total == 0) return CURDKV_OK;
     if (!indices || !K_out || !V_out) return CURDKV_ERR_INVALID_ARG;
@@ -318,8 +328,8 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     if (n < 1 || n > ctx->cfg.max_tokens || n_sink < 0) return CURDKV_ERR_INVALID_ARG;
     if (((uintptr_t)K | (uintptr_t)V | (uintptr_t)K_out | (uintptr_t)V_out) & 15u) return CURDKV_ERR_INVALID_ARG;
     hipStream_t st = (hipStream_t)stream;
-    int64_t total = 0;
-    const int rc = sync_offsets(ctx, offsets, budgets, n, st, &total);
+    int64_t total = 0, max_budget = 0;
+    const int rc = sync_offsets(ctx, offsets, budgets, n, st, &total, &max_budget);
     if (rc != CURDKV_OK) return rc;
     if (total > 0 && (!indices || !K_out || !V_out)) return CURDKV_ERR_INVALID_ARG;
     // One kernel for everything when it applies and about a tenth of the rows or fewer are kept.
@@ -346,7 +356,7 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     }
     if (fusable) {      // scores from the fused kernel's first phases, then select and gather kernels
         if (launch_fused(ctx, K, V, n, 0, ctx->d_zero_offsets, scores, nullptr, nullptr, nullptr, st) != hipSuccess ||
-            launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, indices, st) != hipSuccess ||
+            launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st) != hipSuccess ||
             launch_compact(ctx, K, V, n, indices, ctx->plan.d_offsets, total, K_out, V_out, st) != hipSuccess)
             return CURDKV_ERR_HIP;
         return CURDKV_OK;
@@ -354,9 +364,12 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     // the selection kernel normalises on the fly (and writes the normalised scores
     // back), which saves the separate pass over the scores
     int bph = 0;
-    if (launch_scores(ctx, K, V, n, scores, st, /*normalise=*/false, &bph) != hipSuccess) return CURDKV_ERR_HIP;
-    if (launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, indices, st, bph, scores_wanted) != hipSuccess) return CURDKV_ERR_HIP;
-    if (total == 0) return CURDKV_OK;
+    if (launch_scores(ctx, K, V, n, scores, st, /*normalise=*/false, &bph, 0, 0, nullptr, false, nullptr,
+                      /*with_hist=*/split_applicable(ctx, n, true), n_sink) != hipSuccess) return CURDKV_ERR_HIP;
+    SelectGather gather{K, V, K_out, V_out, total, false};
+    if (launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st, bph, scores_wanted, nullptr, &gather) != hipSuccess)
+        return CURDKV_ERR_HIP;
+    if (total == 0 || gather.done) return CURDKV_OK;
     return launch_compact(ctx, K, V, n, indices, ctx->plan.d_offsets, total, K_out, V_out, st) == hipSuccess
                ? CURDKV_OK : CURDKV_ERR_HIP;
 }
@@ -441,7 +454,7 @@ int curdkv_compress_adaptive(curdkv_ctx* ctx, const void* K, const void* V, int6
         return CURDKV_ERR_HIP;
     if (total == 0) return CURDKV_OK;
     // (`planned`: budgets were allotted layer-wide, and the allocation has left every head's threshold)
-    if (launch_select(ctx, scores, n, n_sink, offsets_out, indices, st, 0, true,
+    if (launch_select(ctx, scores, n, n_sink, offsets_out, /*max_budget=*/n, indices, st, 0, true,
                       planned ? adaptive_thresholds(ctx, ctx->d_adaptive_ws) : nullptr) != hipSuccess ||
         launch_compact(ctx, K, V, n, indices, offsets_out, total, K_out, V_out, st, ctx->d_adaptive_blocks) != hipSuccess)
         return CURDKV_ERR_HIP;

@@ -59,6 +59,7 @@ struct curdkv_ctx {
     int64_t* d_zero_offsets = nullptr; // [heads + 1] zeros: "keep nothing", for the scores-only use of the fused kernel
     void* d_adaptive_ws = nullptr;     // histograms, key segments and per-layer state of the head-wise budget allocation
     curdkv::BlockInfo* d_adaptive_blocks = nullptr;  // gather block table built on the device (curdkv_compress_adaptive)
+    void* d_split_ws = nullptr;        // histograms and bitmaps of the split selection (split_select.hip)
     float* d_scores_ws = nullptr;      // [heads, max_tokens], allocated when curdkv_compress needs it
     int lds_limit = 0;                 // max dynamic LDS per workgroup, bytes
     int num_cu = 0;
@@ -80,7 +81,10 @@ size_t packed_elems(int col_blocks);
 hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n,
                          float* scores, hipStream_t stream, bool normalise = true,
                          int* blocks_per_head = nullptr, int64_t out_stride = 0, int64_t out_offset = 0,
-                         double* sums = nullptr, bool restart = false, bool* summed = nullptr);
+                         double* sums = nullptr, bool restart = false, bool* summed = nullptr,
+                         bool with_hist = false, int32_t n_sink = 0);
+// with_hist: every workgroup also leaves its counts of the products of tokens n_sink and up for the
+// split selection (split_select.hip), which must apply to n.
 // sums (device, [heads]) given: where one block scores a whole head, the kernel itself adds the
 // head's total to sums[head] (after zeroing it if `restart`) and *summed is set; otherwise the
 // caller adds the partial sums (launch_accumulate).
@@ -95,12 +99,32 @@ hipError_t launch_fold(const curdkv_ctx* ctx, const float* scores_q, int64_t n, 
 // result and writes it back, which is what normalisation followed by selection gives
 // (write_scaled = false: selects on the divided values but leaves `scores` as they are, for
 // callers that do not want the scores).
+// max_budget: the largest of the heads' budgets, or an upper bound of it.
 // known_thresholds (device, one {key, need} pair per head as the budget allocation leaves them,
 // adaptive_thresholds): heads whose entry is valid skip the search for their threshold.
+struct SelectGather {
+    const void *K, *V;
+    void *K_out, *V_out;
+    int64_t total;                     // rows kept, all heads
+    bool done;
+};
 hipError_t launch_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
-                         const int64_t* d_offsets, int32_t* indices, hipStream_t stream,
+                         const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
                          int scale_blocks = 0, bool write_scaled = true,
-                         const void* known_thresholds = nullptr);
+                         const void* known_thresholds = nullptr, SelectGather* gather = nullptr);
+// gather given: the selection may copy the kept rows itself; gather->done says whether it has.
+// split_select.hip: the same for long heads, several workgroups per head (workspace ctx->d_split_ws).
+// scale_blocks > 0: step 1's histograms, scale_blocks of them per head, have been made by launch_scores.
+bool split_wanted(const curdkv_ctx* ctx);              // some n <= max_tokens may take it: the context needs the workspace
+bool split_applicable(const curdkv_ctx* ctx, int64_t n, bool one_call);   // one_call: scores not normalised yet, histograms from launch_scores
+size_t split_workspace_bytes(const curdkv_ctx* ctx);
+int split_hists(const curdkv_ctx* ctx);                // histograms per head there is room for
+uint32_t* split_hist(const curdkv_ctx* ctx);           // [heads][split_hists][2048], two counts to a word
+uint32_t* split_coarse(const curdkv_ctx* ctx);         // [heads][split_hists][256]
+constexpr int kSplitMaxHeads = 128;                    // (layer, group) pairs the split is used for (its workspace is about 0.3 MB per pair)
+hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
+                               const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
+                               int scale_blocks, bool write_scaled, SelectGather* gather);
 hipError_t launch_compact(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n,
                           const int32_t* indices, const int64_t* d_offsets, int64_t total,
                           void* K_out, void* V_out, hipStream_t stream,

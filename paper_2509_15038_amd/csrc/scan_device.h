@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "curdkv_internal.h"
+#include "raw_hist.h"
 
 namespace curdkv {
 
@@ -171,11 +172,13 @@ __device__ __forceinline__ void walk_tiles(int32_t n, int32_t t_begin, int32_t t
     }
 }
 
-template <int CB, int SRC = kSrcKV, bool PROJ = true>
+// COUNT: every score is also counted in `hist` (raw_hist_count), those of the first n_sink rows as nothing:
+// one LDS atomic per 64 tokens, hidden behind the stream like the LDS store beside it.
+template <int CB, int SRC = kSrcKV, bool PROJ = true, bool COUNT = false>
 __device__ __forceinline__ float scan_tiles(const SketchRegs<CB>& G, const uint4* __restrict__ Kh,
                                             const uint4* __restrict__ Vh, int32_t n, int32_t t_begin,
                                             int32_t t_end, float* lds_rows, int32_t row0, int lane,
-                                            uint32_t phase = 0) {
+                                            uint32_t phase = 0, uint32_t* hist = nullptr, int32_t n_sink = 0) {
     const int tok = lane & 15, q = lane >> 4;
     float acc_sum = 0.f;
     float pend = 0.f;                                           // this lane's score of the current pair
@@ -238,6 +241,7 @@ __device__ __forceinline__ float scan_tiles(const SketchRegs<CB>& G, const uint4
         const int32_t row = tile * kTileTokens + lane;
         if (!decltype(check)::value || row < n) {
             lds_rows[row - row0] = pend;
+            if (COUNT) raw_hist_count(hist, pend, row >= n_sink);
             acc_sum += pend;
         }
     };
@@ -264,11 +268,11 @@ struct SketchF32 {
     float4 g[CB][8];
 };
 
-template <int CB, int SRC = kSrcKV, bool PROJ = true>
+template <int CB, int SRC = kSrcKV, bool PROJ = true, bool COUNT = false>
 __device__ __forceinline__ float scan_tiles_f32(const SketchF32<CB>& G, const float4* __restrict__ Kh,
                                                 const float4* __restrict__ Vh, int32_t n, int32_t t_begin,
                                                 int32_t t_end, float* lds_rows, int32_t row0, int lane,
-                                                uint32_t phase = 0) {
+                                                uint32_t phase, uint32_t* hist, int32_t n_sink) {
     const int tok = lane & 15, q = lane >> 4;
     float acc_sum = 0.f;
     float pend = 0.f;
@@ -342,6 +346,7 @@ __device__ __forceinline__ float scan_tiles_f32(const SketchF32<CB>& G, const fl
         const int32_t row = tile * kTileTokens + lane;
         if (!decltype(check)::value || row < n) {
             lds_rows[row - row0] = pend;
+            if (COUNT) raw_hist_count(hist, pend, row >= n_sink);
             acc_sum += pend;
         }
     };
@@ -447,11 +452,12 @@ struct TileF32 {        // 16 tokens of K and of V as seen by a lane
 // waves share a SIMD and one's splitting runs beside the other's products.  (One wave of two
 // 32-token buffers per SIMD took turns at the two: 950 us at r = 64, 1460 at r = 128.  Two chains
 // of products per 16 columns and wave, K's and V's, are enough: four measured 3 to 5 % slower.)
-template <int CB, int SRC = kSrcKV>
+template <int CB, int SRC = kSrcKV, bool COUNT = false>
 __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const float4* __restrict__ Kh,
                                                 const float4* __restrict__ Vh,
                                                 int32_t n, int32_t t_begin, int32_t t_end, float* lds_rows,
-                                                int32_t row0, int lane, uint32_t phase) {
+                                                int32_t row0, int lane, uint32_t phase, uint32_t* hist,
+                                                int32_t n_sink) {
     const int tok = lane & 15, q = lane >> 4;
     const int32_t groups = (t_end - t_begin + 1) >> 1;          // of 64 tokens
     if (groups <= 0) return 0.f;
@@ -529,6 +535,7 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
         const int32_t row = first + lane;
         if (row < n) {
             lds_rows[row - row0] = pend;
+            if (COUNT) raw_hist_count(hist, pend, row >= n_sink);
             acc_sum += pend;
         }
     }
@@ -542,7 +549,10 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
                 const size_t at = (size_t)(uint32_t)(j + b) * kHeadDim;
                 const float lk = SRC == kSrcV ? 1.f : rescore_row<CB>(gs, (const float*)Kh + at, lane);
                 const float lv = SRC == kSrcK ? 1.f : rescore_row<CB>(gs, (const float*)Vh + at, lane);
-                if (lane == b) v = lk * lv;
+                if (lane == b) {
+                    v = lk * lv;
+                    if (COUNT) raw_hist_count(hist, v, row >= n_sink);  // (it stays counted as a NaN as well)
+                }
             }
             if (row < n) {
                 lds_rows[row - row0] = v;

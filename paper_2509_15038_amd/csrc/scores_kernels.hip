@@ -10,6 +10,7 @@
 // never leave registers.  The bf16 inner loop lives in scan_device.h.
 
 #include "scan_device.h"
+#include "select_device.h"
 
 namespace curdkv {
 
@@ -45,19 +46,26 @@ template <int CB> struct Stage {    // tiles (of 32 tokens) a wave collects betw
     static constexpr int kTiles = CB > 4 ? 256 : 128;     // one workgroup per CU: 128 KB; two: 64 KB each
 };
 
-template <int CB, int SRC, bool PROJ>
+// COUNT: the workgroup also leaves its histogram of scores for the split selection (split_select.hip).
+template <int CB, int SRC, bool PROJ, bool COUNT>
 __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
     const uint4* __restrict__ K, const uint4* __restrict__ V, const uint4* __restrict__ Gp,
     float* __restrict__ scores, float* __restrict__ partial, int64_t n, int blocks_per_head,
-    int64_t out_stride, int64_t out_offset, double* __restrict__ sums, int restart) {
+    int64_t out_stride, int64_t out_offset, double* __restrict__ sums, int restart,
+    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, int hists, int32_t n_sink) {
     constexpr int kStageTiles = Stage<CB>::kTiles;
     __shared__ float stage[4][kStageTiles * kTileTokens];
+    __shared__ uint32_t hist[COUNT ? kRawHistWords : 1];
     const int head = blockIdx.x / blocks_per_head;
     const int blk = blockIdx.x - head * blocks_per_head;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
     SketchRegs<CB> G;
     if (PROJ) load_sketch<CB>(G, Gp + (size_t)head * (CB * 4 * 64), lane);
+    if (COUNT) {
+        for (int i = threadIdx.x; i < kRawHistWords; i += 256) hist[i] = 0;
+        __syncthreads();
+    }
 
     const int32_t n32 = (int32_t)n;
     const int32_t tiles = (n32 + kTileTokens - 1) / kTileTokens;
@@ -74,13 +82,14 @@ __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
     for (int32_t seg = t_begin; seg < t_end; seg += kStageTiles) {
         const int32_t seg_end = seg + kStageTiles < t_end ? seg + kStageTiles : t_end;
         const int32_t r0 = seg * kTileTokens;
-        acc_sum += scan_tiles<CB, SRC, PROJ>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane,
-                                             scan_phase(head, blk * 4 + wave));
+        acc_sum += scan_tiles<CB, SRC, PROJ, COUNT>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane,
+                                                   scan_phase(head, blk * 4 + wave), hist, n_sink);
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
         for (int32_t r = r0 + lane; r < r1; r += 64) __builtin_nontemporal_store(mine[r - r0], &sh[r]);
     }
     block_partial_store<4>(wave_sum(acc_sum), partial + (size_t)head * kMaxBlocksPerHead + blk,
                            sums ? sums + head : nullptr, restart);
+    if (COUNT) raw_hist_store<256>(hist, hist_out, coarse_out, head * hists + blk);
 }
 
 // ---------------------------------------------------------------------------
@@ -96,20 +105,26 @@ template <int CB> struct ShapeF32 {
     static constexpr int kTiles = CB > 4 ? 48 : CB > 2 ? 96 : 256;    // per wave between bursts: 48, 96 or 128 KB in all
 };
 
-template <int CB, int SRC, bool PROJ>
+template <int CB, int SRC, bool PROJ, bool COUNT>
 __global__ __launch_bounds__((ShapeF32<CB>::kWaves * 64), (ShapeF32<CB>::kSplit ? 2 : 1)) void scores_f32_kernel(
     const float4* __restrict__ K, const float4* __restrict__ V, const float4* __restrict__ Gp,
     float* __restrict__ scores, float* __restrict__ partial, int64_t n, int blocks_per_head,
-    int64_t out_stride, int64_t out_offset, double* __restrict__ sums, int restart) {
+    int64_t out_stride, int64_t out_offset, double* __restrict__ sums, int restart,
+    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, int hists, int32_t n_sink) {
     constexpr bool kSplit = ShapeF32<CB>::kSplit;  // (PROJ = false comes with CB = 2 and never touches the sketch)
     constexpr int kWaves = ShapeF32<CB>::kWaves;
     constexpr int kStageTiles = ShapeF32<CB>::kTiles;
     __shared__ float stage[kWaves][kStageTiles * kTileTokens];
     __shared__ bf16x8 gs[kSplit ? kSketchF32Chunks<CB> : 1];
+    __shared__ uint32_t hist[COUNT ? kRawHistWords : 1];
     const int head = blockIdx.x / blocks_per_head;
     const int blk = blockIdx.x - head * blocks_per_head;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
+    if (COUNT) {
+        for (int i = threadIdx.x; i < kRawHistWords; i += kWaves * 64) hist[i] = 0;
+        __syncthreads();
+    }
     const float4* Gh = Gp + (size_t)head * (CB * 8 * 64);
     SketchF32<kSplit ? 1 : CB> G;
     if (kSplit) {
@@ -137,13 +152,14 @@ __global__ __launch_bounds__((ShapeF32<CB>::kWaves * 64), (ShapeF32<CB>::kSplit 
         const int32_t seg_end = seg + kStageTiles < t_end ? seg + kStageTiles : t_end;
         const int32_t r0 = seg * kTileTokens;
         const uint32_t phase = scan_phase(head, blk * kWaves + wave);
-        if constexpr (kSplit) acc_sum += scan_tiles_f32_split<CB, SRC>(gs, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase);
-        else acc_sum += scan_tiles_f32<CB, SRC, PROJ>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase);
+        if constexpr (kSplit) acc_sum += scan_tiles_f32_split<CB, SRC, COUNT>(gs, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink);
+        else acc_sum += scan_tiles_f32<CB, SRC, PROJ, COUNT>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink);
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
         for (int32_t r = r0 + lane; r < r1; r += 64) __builtin_nontemporal_store(mine[r - r0], &sh[r]);
     }
     block_partial_store<kWaves>(wave_sum(acc_sum), partial + (size_t)head * kMaxBlocksPerHead + blk,
                                 sums ? sums + head : nullptr, restart);
+    if (COUNT) raw_hist_store<kWaves * 64>(hist, hist_out, coarse_out, head * hists + blk);
 }
 
 // ---------------------------------------------------------------------------
@@ -230,7 +246,11 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
         const int64_t in_last = ctx->heads - (ctx->heads > ctx->num_cu ? ctx->num_cu : 0);   // heads in the last round
         if (in_last * 4 >= 3 * (int64_t)ctx->num_cu) return 1;
     }
-    const int64_t hi = lo + 15 < cap ? lo + 15 : cap;
+    // (up to one workgroup per place where the heads are few: 8 heads of 131072 tokens 105 us on 184 units, 99 on 256;
+    // the whole call for 1 head of 32768 tokens 52 us with 17 workgroups, 33 with 64)
+    const int64_t fill = (slots + ctx->heads - 1) / ctx->heads;
+    const int64_t most = lo + 15 > fill ? lo + 15 : fill;
+    const int64_t hi = most < cap ? most : cap;
     auto cost = [&](int64_t b) {                                       // rounds x tiles a wave works through
         const int64_t rounds = ((int64_t)ctx->heads * b + slots - 1) / slots;
         int64_t per_wave = (tiles + waves * b - 1) / (waves * b);
@@ -252,58 +272,54 @@ hipError_t configure_kernels(curdkv_ctx* ctx) {
 hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n,
                          float* scores, hipStream_t stream, bool normalise, int* blocks_per_head,
                          int64_t out_stride, int64_t out_offset, double* sums, bool restart,
-                         bool* summed) {
+                         bool* summed, bool with_hist, int32_t n_sink) {
     if (out_stride <= 0) out_stride = n;
     const int bph = pick_blocks_per_head(ctx, n);
     if (blocks_per_head) *blocks_per_head = bph;
     if (bph != 1) sums = nullptr;                 // several blocks per head: the caller adds the partials
     if (summed) *summed = sums != nullptr;
     const int rs = restart ? 1 : 0;
+    const int hists = with_hist ? split_hists(ctx) : 0;
+    if (with_hist) {
+        // a workgroup's tokens (at most two stages of its waves here) must stay below 65536: 16-bit counts
+        const int64_t tiles = (n + kTileTokens - 1) / kTileTokens;
+        if (bph > hists || (tiles + bph - 1) / bph + 16 > 65535 / kTileTokens) return hipErrorInvalidValue;
+    }
+    uint32_t* hist = with_hist ? split_hist(ctx) : nullptr;
+    uint32_t* coarse = with_hist ? split_coarse(ctx) : nullptr;
     const dim3 grid((unsigned)(ctx->heads * bph));
-    if (ctx->cfg.dtype == CURDKV_DTYPE_BF16) {
-        const uint4* k = (const uint4*)K; const uint4* v = (const uint4*)V; const uint4* g = (const uint4*)ctx->d_G;
-        float* part = ctx->d_partial;
-#define CURDKV_LAUNCH(CBV, SRCV, PROJV) \
-    scores_bf16_kernel<CBV, SRCV, PROJV><<<grid, 256, 0, stream>>>(k, v, g, scores, part, n, bph, out_stride, out_offset, sums, rs)
-#define CURDKV_BY_SRC(CBV, PROJV)                                                   \
-    switch (ctx->cfg.score_source) {                                                \
-        case CURDKV_SCORE_KEY: CURDKV_LAUNCH(CBV, kSrcK, PROJV); break;             \
-        case CURDKV_SCORE_VALUE: CURDKV_LAUNCH(CBV, kSrcV, PROJV); break;           \
-        default: CURDKV_LAUNCH(CBV, kSrcKV, PROJV); break;                          \
-    }
-        if (ctx->cfg.no_projection) {
-            CURDKV_BY_SRC(2, false)
-        } else {
-            switch (ctx->col_blocks) {   // 16-column MFMA blocks = 2 per 32 padded columns
-                case 1: CURDKV_BY_SRC(2, true) break;
-                case 2: CURDKV_BY_SRC(4, true) break;
-                default: CURDKV_BY_SRC(8, true) break;
-            }
+    float* part = ctx->d_partial;
+    auto launch = [&](auto cb, auto src, auto proj, auto count) {
+        constexpr int CB = decltype(cb)::value, SRC = decltype(src)::value;
+        constexpr bool PROJ = decltype(proj)::value, COUNT = decltype(count)::value;
+        if (ctx->cfg.dtype == CURDKV_DTYPE_BF16)
+            scores_bf16_kernel<CB, SRC, PROJ, COUNT><<<grid, 256, 0, stream>>>(
+                (const uint4*)K, (const uint4*)V, (const uint4*)ctx->d_G, scores, part, n, bph, out_stride, out_offset, sums, rs,
+                hist, coarse, hists, n_sink);
+        else
+            scores_f32_kernel<CB, SRC, PROJ, COUNT><<<grid, ShapeF32<CB>::kWaves * 64, 0, stream>>>(
+                (const float4*)K, (const float4*)V, (const float4*)ctx->d_G, scores, part, n, bph, out_stride, out_offset, sums, rs,
+                hist, coarse, hists, n_sink);
+    };
+    auto by_count = [&](auto cb, auto src, auto proj) {
+        if (with_hist) launch(cb, src, proj, std::true_type{});
+        else launch(cb, src, proj, std::false_type{});
+    };
+    auto by_source = [&](auto cb, auto proj) {
+        switch (ctx->cfg.score_source) {
+            case CURDKV_SCORE_KEY: by_count(cb, std::integral_constant<int, kSrcK>{}, proj); break;
+            case CURDKV_SCORE_VALUE: by_count(cb, std::integral_constant<int, kSrcV>{}, proj); break;
+            default: by_count(cb, std::integral_constant<int, kSrcKV>{}, proj); break;
         }
-#undef CURDKV_BY_SRC
-#undef CURDKV_LAUNCH
+    };
+    if (ctx->cfg.no_projection) {
+        by_source(std::integral_constant<int, 2>{}, std::false_type{});
     } else {
-        const float4* k = (const float4*)K; const float4* v = (const float4*)V; const float4* g = (const float4*)ctx->d_G;
-        float* part = ctx->d_partial;
-#define CURDKV_LAUNCH(CBV, SRCV, PROJV) \
-    scores_f32_kernel<CBV, SRCV, PROJV><<<grid, ShapeF32<CBV>::kWaves * 64, 0, stream>>>(k, v, g, scores, part, n, bph, out_stride, out_offset, sums, rs)
-#define CURDKV_BY_SRC(CBV, PROJV)                                                   \
-    switch (ctx->cfg.score_source) {                                                \
-        case CURDKV_SCORE_KEY: CURDKV_LAUNCH(CBV, kSrcK, PROJV); break;             \
-        case CURDKV_SCORE_VALUE: CURDKV_LAUNCH(CBV, kSrcV, PROJV); break;           \
-        default: CURDKV_LAUNCH(CBV, kSrcKV, PROJV); break;                          \
-    }
-        if (ctx->cfg.no_projection) {
-            CURDKV_BY_SRC(2, false)
-        } else {
-            switch (ctx->col_blocks) {   // 16-column MFMA blocks = 2 per 32 padded columns
-                case 1: CURDKV_BY_SRC(2, true) break;
-                case 2: CURDKV_BY_SRC(4, true) break;
-                default: CURDKV_BY_SRC(8, true) break;
-            }
+        switch (ctx->col_blocks) {   // 16-column MFMA blocks = 2 per 32 padded columns
+            case 1: by_source(std::integral_constant<int, 2>{}, std::true_type{}); break;
+            case 2: by_source(std::integral_constant<int, 4>{}, std::true_type{}); break;
+            default: by_source(std::integral_constant<int, 8>{}, std::true_type{}); break;
         }
-#undef CURDKV_BY_SRC
-#undef CURDKV_LAUNCH
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !normalise) return e;

@@ -34,6 +34,8 @@
 // can write them out, or gather by them, with coalesced accesses.
 #pragma once
 
+#include <type_traits>
+
 #include "curdkv_internal.h"
 
 namespace curdkv {
@@ -69,8 +71,13 @@ struct HeadScale {
 __device__ __forceinline__ HeadScale head_scale(const float* __restrict__ partial, int blocks, int64_t n) {
     HeadScale h;
     h.on = blocks > 0;
+    // the partial sums (at most 64, kMaxBlocksPerHead) in one load, a lane each, then added in index
+    // order: a load per addition left the whole selection waiting for a chain of them
+    static_assert(kMaxBlocksPerHead <= 64, "a lane per partial sum");
+    const int lane = threadIdx.x & 63;
+    const int mine = lane < blocks ? __float_as_int(partial[lane]) : 0;
     double tot = 0.0;
-    for (int i = 0; i < blocks; ++i) tot += (double)partial[i];
+    for (int i = 0; i < blocks; ++i) tot += (double)__int_as_float(__builtin_amdgcn_readlane(mine, i));
     h.zero = !(tot > 0.0);
     h.inv = h.zero ? 0.f : (float)(1.0 / tot);
     h.uniform = (float)(1.0 / (double)n);
@@ -85,6 +92,23 @@ struct Threshold {
     uint32_t need;
 };
 constexpr uint32_t kNoThreshold = 0xFFFFFFFFu;
+
+// Inclusive prefix sum over the 64 lanes of a wave, in registers: shifts inside the rows of 16 lanes,
+// then each row's last value to the rows behind it.  (A chain of __shfl_up goes through the LDS
+// unit six times, about 0.3 us when nothing else runs.)
+__device__ __forceinline__ uint32_t wave_inclusive(uint32_t x) {
+    auto add = [&](auto ctrl, auto rows) {
+        x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+    };
+    using std::integral_constant;
+    add(integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});      // row_shr:1
+    add(integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});      // row_shr:2
+    add(integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});      // row_shr:4
+    add(integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});      // row_shr:8
+    add(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});      // row_bcast:15 into rows 1 and 3
+    add(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});      // row_bcast:31 into rows 2 and 3
+    return x;
+}
 
 // What find_bin_from_top reports (in LDS).
 struct BinFound {
@@ -109,12 +133,7 @@ __device__ __forceinline__ void find_bin_from_top(const uint32_t* hist, uint32_t
         c[i] = hist[BINS - 1 - (tid * kPer + i)];
         tot += c[i];
     }
-    uint32_t incl = tot;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t t = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += t;
-    }
+    uint32_t incl = wave_inclusive(tot);
     if (lane == 63) wave_tot[wave] = incl;
     __syncthreads();
     uint32_t before = 0;
@@ -230,12 +249,7 @@ __device__ __forceinline__ uint32_t threshold_by_radix(uint32_t (&x)[KPT], int32
             uint32_t c[4], tot = 0;
 #pragma unroll
             for (int i = 0; i < 4; ++i) { c[i] = sm.bin_count[255 - 4 * lane - i]; tot += c[i]; }
-            uint32_t incl = tot;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t t = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += t;
-            }
+            uint32_t incl = wave_inclusive(tot);
             uint32_t run = incl - tot;             // keys in higher bins
             if (run < want && want <= incl) {
 #pragma unroll
@@ -285,12 +299,7 @@ __device__ __forceinline__ uint32_t threshold_on_list(const int32_t* pairs, uint
         __syncthreads();
         if (wave == 0) {                           // lane L looks at digit 63 - L
             const uint32_t c = hist64[63 - lane];
-            uint32_t incl = c;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t t = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += t;
-            }
+            uint32_t incl = wave_inclusive(c);
             if (incl - c < want && want <= incl) { *digit = 63 - lane; *want_s = want - (incl - c); }
             hist64[63 - lane] = 0;
         }
@@ -406,12 +415,7 @@ __device__ __forceinline__ void select_core(uint32_t (&x)[KPT], int32_t n, int32
             keep[i] = w < kWords ? sm.emask[w] : 0ull;
             ne += (uint32_t)__popcll(keep[i]);
         }
-        uint32_t incl = ne;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t t = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += t;
-        }
+        uint32_t incl = wave_inclusive(ne);
         uint32_t eq_before = incl - ne, nk = 0;
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
@@ -425,12 +429,7 @@ __device__ __forceinline__ void select_core(uint32_t (&x)[KPT], int32_t n, int32
             keep[i] = (w < kWords ? sm.gmask[w] : 0ull) | e;
             nk += (uint32_t)__popcll(keep[i]);
         }
-        incl = nk;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t t = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += t;
-        }
+        incl = wave_inclusive(nk);
         uint32_t pos = (uint32_t)s + incl - nk;
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {

@@ -151,12 +151,7 @@ __global__ __launch_bounds__(kSelThreads) void select_stream_kernel(float* __res
                 const int w = lane * kPer + i;
                 ne += w < words ? (uint32_t)__popcll(sm.emask[w]) : 0u;
             }
-            uint32_t incl = ne;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t t = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += t;
-            }
+            uint32_t incl = wave_inclusive(ne);
             uint32_t eq_before = eq_carry + incl - ne, nk = 0;
             const uint32_t eq_total = __shfl(incl, 63, 64);
 #pragma unroll 1
@@ -173,12 +168,7 @@ __global__ __launch_bounds__(kSelThreads) void select_stream_kernel(float* __res
                 sm.gmask[w] = keep;
                 nk += (uint32_t)__popcll(keep);
             }
-            incl = nk;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t t = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += t;
-            }
+            incl = wave_inclusive(nk);
             uint32_t pos = pos_carry + incl - nk;
 #pragma unroll 1
             for (int i = 0; i < kPer; ++i) {
@@ -418,11 +408,13 @@ hipError_t configure_select(curdkv_ctx* ctx) {
 }
 
 hipError_t launch_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
-                         const int64_t* d_offsets, int32_t* indices, hipStream_t stream,
-                         int scale_blocks, bool write_scaled, const void* known_thresholds) {
+                         const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
+                         int scale_blocks, bool write_scaled, const void* known_thresholds, SelectGather* gather) {
     const Threshold* known = static_cast<const Threshold*>(known_thresholds);
     const int32_t n32 = (int32_t)n;
     const int ws = write_scaled ? 1 : 0;
+    if (!known && split_applicable(ctx, n, scale_blocks > 0))
+        return launch_split_select(ctx, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, write_scaled, gather);
     if (n <= 4 * kSelThreads) return launch_reg<4>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);
     if (n <= 8 * kSelThreads) return launch_reg<8>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);
     if (n <= 16 * kSelThreads) return launch_reg<16>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);

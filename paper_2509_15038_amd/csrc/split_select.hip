@@ -1,0 +1,531 @@
+// Selection of long heads by several workgroups per (layer, group), for gfx950: the sink, top-k
+// and union steps of Algorithm 1 where one workgroup per head (select_kernels.hip) would leave
+// most of the chip idle, or would stream a head that does not fit its registers through one
+// compute unit.  Three steps, each a barrier for the next:
+//   1. histograms of the scores over 4096 bins (exponent and top four mantissa bits), one per
+//      workgroup that makes them: the scoring kernel, on the one-call path, while it has the
+//      (un-normalised) scores in LDS, or split_hist_kernel from scores in memory;
+//   2. split_flag_kernel, workgroup (part, head): every workgroup finds the bin that holds the
+//      cut (the same small sums in each: exponents first, then the sixteen bins of one
+//      exponent), turns it into a range [lo, hi] of normalised scores and writes one bit per
+//      token of its part to two bitmaps, "above hi" and "in the range".  On the one-call
+//      path it also normalises the scores;
+//   3. split_emit_kernel, workgroup (share, head): reads the head's bitmaps (n/4 bytes), resolves
+//      the threshold on the few keys in the range, scans the popcounts into output positions
+//      and lists its share of the output rows.  Resolving and scanning are repeated
+//      by every workgroup of a head: they are small, and it saves a launch and a trip through
+//      memory.
+// What is kept and in which order is exactly what select_core (select_device.h) keeps.
+//
+// Normalising multiplies by one factor and rounds, so it keeps the order of two products or makes
+// them equal.  The m-th largest score is therefore the normalised m-th largest product, and
+// lies in the normalised range of that product's bin; products of neighbouring bins that round
+// onto the range's ends are inside the range too, so that ties between them are
+// decided by token number as everywhere.
+//
+// A range with more keys than the list takes (a head of equal scores, say) is resolved by
+// reading its scores again, a digit per pass: slow and exact.
+//
+// (One histogram per head, added up with atomics, took 15 us for 8 heads of 131072 tokens where
+// writing and summing one per workgroup takes about 1: atomics of many workgroups on one address
+// go through memory one after the other on this chip.)
+
+#include "raw_hist.h"
+#include "select_device.h"
+
+namespace curdkv {
+
+constexpr int kSplitThreads = 512;
+constexpr int kSplitWaves = kSplitThreads / 64;
+constexpr int kSplitList = 4096;                   // keys in the range that step 3 resolves in LDS
+constexpr int kSplitMinTokens = 24 * 1024;          // one call, at most 32 heads
+constexpr int kSplitMinTokensElse = 36 * 1024;      // beyond: one workgroup's registers hold a head up to here
+constexpr int kSplitMaxTokens = 131072;            // tokens per head the bitmaps and their scan are laid out for
+constexpr int kSplitMaxWords = kSplitMaxTokens / 64;
+constexpr int kSplitWordsPerThread = kSplitMaxWords / kSplitThreads;   // 4
+constexpr int kSplitShare = 1024;                  // output rows a workgroup of step 3 lists at most, where it also gathers them
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+struct SplitWorkspace {                            // device pointers into one allocation; nothing survives a call
+    uint32_t* hist;                                // [heads][hists][2048], two 16-bit counts to a word
+    uint32_t* coarse;                              // [heads][hists][256], per exponent
+    unsigned long long* gmask;                     // [heads][words]
+    unsigned long long* emask;                     // [heads][words]
+    uint2* range;                                  // [heads] keys lo, hi (without the top bit)
+    int words, hists;                              // allocated per head
+};
+
+static int words_for(int64_t max_tokens) {
+    const int64_t t = max_tokens < kSplitMaxTokens ? max_tokens : kSplitMaxTokens;
+    return (int)(((t + 63) / 64 + 1) & ~(int64_t)1);
+}
+
+// histograms per head: what pick_blocks_per_head (scores_kernels.hip) can ask for; fewer heads, more workgroups each
+int split_hists(const curdkv_ctx* ctx) { return ctx->heads <= 32 ? kMaxBlocksPerHead : 32; }
+
+static SplitWorkspace carve(const curdkv_ctx* ctx) {
+    SplitWorkspace w;
+    const size_t heads = (size_t)ctx->heads;
+    w.words = words_for(ctx->cfg.max_tokens);
+    w.hists = split_hists(ctx);
+    w.hist = reinterpret_cast<uint32_t*>(ctx->d_split_ws);
+    w.coarse = w.hist + heads * w.hists * kRawHistWords;
+    w.gmask = reinterpret_cast<unsigned long long*>(w.coarse + heads * w.hists * 256);
+    w.emask = w.gmask + heads * w.words;
+    w.range = reinterpret_cast<uint2*>(w.emask + heads * w.words);
+    return w;
+}
+
+size_t split_workspace_bytes(const curdkv_ctx* ctx) {
+    return (size_t)ctx->heads * ((size_t)split_hists(ctx) * (kRawHistWords + 256) * 4 + (size_t)words_for(ctx->cfg.max_tokens) * 16 + sizeof(uint2));
+}
+
+struct SplitArgs {
+    SplitWorkspace ws;
+    float* scores;
+    int32_t n, n_sink;
+    const int64_t* offsets;
+    const float* partial;
+    int scale_blocks, write_scaled;                // as in launch_select
+    int part;                                      // tokens per workgroup of step 2, a multiple of 512
+    int hists;                                     // histograms per head
+};
+
+// k - s' and whether anything has to be searched (not all of the candidates are kept, nor none)
+__device__ __forceinline__ bool needs_search(int32_t k, int32_t n, int32_t s, uint32_t* m) {
+    *m = (uint32_t)(k - s);
+    return k > s && *m < (uint32_t)(n - s);
+}
+
+__device__ __forceinline__ uint32_t key31(float x) { return order_key(x) & 0x7FFFFFFFu; }
+
+// Step 1 from scores in memory: workgroup (blockIdx.x, head) counts an equal share of the head.
+__global__ __launch_bounds__(kSplitThreads) void split_hist_kernel(SplitArgs a) {
+    __shared__ uint32_t hist[kRawHistWords];
+    const int head = blockIdx.y, tid = threadIdx.x;
+    const int32_t n = a.n, s = a.n_sink < n ? a.n_sink : n;
+    uint32_t m;
+    if (!needs_search((int32_t)(a.offsets[head + 1] - a.offsets[head]), n, s, &m)) return;
+    const int32_t part = (n + a.hists - 1) / a.hists;
+    const int32_t j0 = (int32_t)blockIdx.x * part;
+    const int32_t j1 = j0 + part < n ? j0 + part : n;
+    const float* sc = a.scores + (size_t)head * n;
+    for (int i = tid; i < kRawHistWords; i += kSplitThreads) hist[i] = 0;
+    __syncthreads();
+    constexpr int kU = 8;
+    for (int32_t b = j0; b < j1; b += kU * kSplitThreads) {
+        float v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int32_t j = b + u * kSplitThreads + tid;
+            v[u] = j < j1 ? sc[j] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int32_t j = b + u * kSplitThreads + tid;
+            if (j >= s && j < j1) raw_hist_count(hist, v[u]);
+        }
+    }
+    __syncthreads();
+    raw_hist_store<kSplitThreads>(hist, a.ws.hist, a.ws.coarse, head * a.ws.hists + blockIdx.x);
+}
+
+// The bin in which the running count from the top of 64*PER counts reaches `want`: called by one
+// wave, lane L holds counts 64*PER-1 - (L*PER + i) in c[i].  The lane that finds it writes
+// {bin, want left inside it} to LDS.
+template <int PER>
+__device__ __forceinline__ void wave_find(const uint32_t (&c)[PER], uint32_t want, uint32_t* out) {
+    const int lane = threadIdx.x & 63;
+    uint32_t tot = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) tot += c[i];
+    uint32_t incl = wave_inclusive(tot);
+    uint32_t run = incl - tot;
+    if (run < want && want <= incl) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (want <= run + c[i]) { out[0] = (uint32_t)(64 * PER - 1 - (lane * PER + i)); out[1] = want - run; break; }
+            run += c[i];
+        }
+    }
+}
+
+__global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) {
+    __shared__ uint32_t exps[256], fine[64], found[2];
+    const int head = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int32_t n = a.n, s = a.n_sink < n ? a.n_sink : n;
+    const int64_t o0 = a.offsets[head], o1 = a.offsets[head + 1];
+    const int32_t j0 = (int32_t)blockIdx.x * a.part;
+    const int32_t j1 = j0 + a.part < n ? j0 + a.part : n;
+    float* sc = a.scores + (size_t)head * n;
+    // all of the first loads go out together, before anything is decided
+    uint32_t ce = 0;                               // thread (half, exponent): half of the histograms each
+    const uint32_t* co = a.ws.coarse + (size_t)head * a.ws.hists * 256 + (tid & 255);
+#pragma unroll 8
+    for (int h = tid >> 8; h < a.hists; h += 2) ce += co[h * 256];
+    constexpr int kU = 8;
+    float v[kU];
+    auto load = [&](int32_t b) {
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int32_t j = b + u * kSplitThreads + tid;
+            v[u] = j < j1 ? sc[j] : 0.f;
+        }
+    };
+    uint32_t m;
+    const bool search = needs_search((int32_t)(o1 - o0), n, s, &m);
+    const bool write = a.scale_blocks > 0 && a.write_scaled;
+    if (!search && !write) return;
+    load(j0);
+    const HeadScale scale = head_scale(a.partial + (size_t)head * kMaxBlocksPerHead, a.scale_blocks, n);
+    uint32_t lo = 0, hi = 0;
+    if (search) {
+        if (tid < 64) fine[tid] = 0;
+        if (tid < 256) exps[tid] = ce;
+        __syncthreads();
+        if (tid >= 256) atomicAdd(&exps[tid & 255], ce);
+        __syncthreads();
+        if (tid < 64) {
+            const uint32_t c[4] = {exps[255 - 4 * lane], exps[254 - 4 * lane], exps[253 - 4 * lane], exps[252 - 4 * lane]};
+            wave_find<4>(c, m, found);
+        }
+        __syncthreads();
+        const uint32_t ex = found[0], want = found[1];
+        for (int i = tid; i < a.hists * 16; i += kSplitThreads) {       // a thread per histogram and bin of the exponent
+            const uint32_t bin = ex * 16 + (i & 15);
+            const uint32_t w = a.ws.hist[((size_t)head * a.ws.hists + (i >> 4)) * kRawHistWords + (bin >> 1)];
+            atomicAdd(&fine[i & 15], (bin & 1u) ? w >> 16 : w & 0xFFFFu);
+        }
+        __syncthreads();
+        if (tid < 64) {
+            const uint32_t c[1] = {fine[63 - lane]};
+            wave_find<1>(c, want, found);
+        }
+        __syncthreads();
+        const uint32_t bin = ex * 16 + (found[0] & 15u);
+        lo = key31(scale(__uint_as_float(bin << kRawShift)));
+        hi = key31(scale(__uint_as_float((bin << kRawShift) | ((1u << kRawShift) - 1u))));
+        if (ex >= 255u || (scale.on && scale.zero)) { lo = 0u; hi = 0x7FFFFFFFu; }   // beyond the finite range, or all zero: everything
+        if (blockIdx.x == 0 && tid == 0) a.ws.range[head] = uint2{lo, hi};
+    }
+    unsigned long long* g = a.ws.gmask + (size_t)head * a.ws.words;
+    unsigned long long* e = a.ws.emask + (size_t)head * a.ws.words;
+    for (int32_t b = j0; b < j1; b += kU * kSplitThreads) {
+        if (b > j0) load(b);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int32_t j = b + u * kSplitThreads + tid;
+            const float x = scale(v[u]);
+            if (write && j < j1) sc[j] = x;
+            if (search) {
+                const bool cd = j >= s && j < j1;
+                const uint32_t k = key31(x);
+                const unsigned long long bg = __ballot(cd && k > hi), be = __ballot(cd && k >= lo && k <= hi);
+                const int32_t w0 = j - lane;       // first token of the wave's word
+                if (lane == 0 && w0 < j1) { g[w0 >> 6] = bg; e[w0 >> 6] = be; }
+            }
+        }
+    }
+}
+
+struct EmitShared {
+    unsigned long long gmask[kSplitMaxWords];      // kept tokens
+    uint32_t wpos[kSplitMaxWords];                 // output position of a word's first kept token
+    unsigned long long emask[kSplitMaxWords];      // candidates in the range, then those equal to the threshold
+    uint32_t list[2 * kSplitList];                 // (key - lo, token) of the candidates in the range
+    uint32_t hist[256];
+    uint32_t wave_tot[2][kSplitWaves];
+    uint32_t list_count, digit, want;
+};
+
+// exclusive prefix of x over the workgroup's threads; the total goes to *total
+__device__ __forceinline__ uint32_t block_exclusive(uint32_t x, uint32_t* wave_tot, uint32_t* total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t incl = wave_inclusive(x);
+    if (lane == 63) wave_tot[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kSplitWaves; ++w) {
+        const uint32_t t = wave_tot[w];
+        before += w < wave ? t : 0u;
+        all += t;
+    }
+    *total = all;
+    return before + incl - x;
+}
+
+// One digit of the search for the threshold: hist[0..255] counts the digit's values (zeroed
+// again), *want becomes the rank inside the chosen value.  Ends with a barrier.
+__device__ __forceinline__ void pick_digit(uint32_t* hist, uint32_t* digit, uint32_t* want) {
+    if (threadIdx.x < 64) {                        // lane L looks at values 255-4L .. 252-4L
+        const int lane = threadIdx.x;
+        uint32_t c[4], tot = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { c[i] = hist[255 - 4 * lane - i]; tot += c[i]; hist[255 - 4 * lane - i] = 0; }
+        uint32_t incl = wave_inclusive(tot);
+        uint32_t run = incl - tot;
+        const uint32_t w = *want;
+        if (run < w && w <= incl) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (w <= run + c[i]) { *digit = 255 - 4 * lane - i; *want = w - run; break; }
+                run += c[i];
+            }
+        }
+    }
+    __syncthreads();
+}
+
+struct GatherArgs {                                // rows of ROW_U4 16-byte chunks
+    const u32x4 *K, *V;
+    u32x4 *K_out, *V_out;
+};
+
+// ROW_U4 > 0: the workgroup also copies its share's rows of K and V (gather step of Algorithm 1);
+// share <= kSplitShare then.
+template <int ROW_U4>
+__global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, int32_t* __restrict__ indices, int share,
+                                                                   GatherArgs ga) {
+    __shared__ EmitShared sm;
+    __shared__ int32_t stage[ROW_U4 ? kSplitShare : 1];
+    const int head = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int32_t n = a.n, s = a.n_sink < n ? a.n_sink : n;
+    const int64_t o0 = a.offsets[head], o1 = a.offsets[head + 1];
+    // all of the first loads go out together, before anything is decided
+    const int words = (n + 63) >> 6;
+    const int w0 = tid * kSplitWordsPerThread;
+    unsigned long long g[kSplitWordsPerThread], e[kSplitWordsPerThread];
+    {
+        const unsigned long long* gp = a.ws.gmask + (size_t)head * a.ws.words;
+        const unsigned long long* ep = a.ws.emask + (size_t)head * a.ws.words;
+#pragma unroll
+        for (int i = 0; i < kSplitWordsPerThread; ++i) {
+            g[i] = w0 + i < words ? gp[w0 + i] : 0ull;
+            e[i] = w0 + i < words ? ep[w0 + i] : 0ull;
+        }
+    }
+    const uint2 range = a.ws.range[head];
+    const HeadScale scale = head_scale(a.partial + (size_t)head * kMaxBlocksPerHead, a.write_scaled ? 0 : a.scale_blocks, n);
+    const float* sc = a.scores + (size_t)head * n;
+    const int32_t k = (int32_t)(o1 - o0);
+    const int32_t r0 = (int32_t)blockIdx.x * share;
+    const int32_t r1 = r0 + share < k ? r0 + share : k;            // output rows r0 .. r1-1 are this workgroup's
+    uint32_t m;
+    const bool search = needs_search(k, n, s, &m);
+    if (r0 >= r1) return;
+    int32_t* out = indices + o0;
+    auto put = [&](int32_t p, int32_t j) {                         // row p of the head is token j
+        if (ROW_U4) stage[p - r0] = j; else out[p] = j;
+    };
+    auto gather = [&]() {
+        if constexpr (ROW_U4 > 0) {
+            __syncthreads();
+            for (int32_t p = r0 + tid; p < r1; p += kSplitThreads) out[p] = stage[p - r0];
+            constexpr int kRows = kSplitThreads / ROW_U4, kFlight = 8;     // rows per instruction, and in flight per thread
+            const int c = tid % ROW_U4, rsub = tid / ROW_U4;
+            const int32_t count = r1 - r0;
+#pragma unroll 1
+            for (int which = 0; which < 2; ++which) {
+                const u32x4* src = (which ? ga.V : ga.K) + (size_t)head * n * ROW_U4 + c;
+                u32x4* dst = (which ? ga.V_out : ga.K_out) + (size_t)(o0 + r0) * ROW_U4 + c;
+#pragma unroll 1
+                for (int32_t p0 = 0; p0 < count; p0 += kRows * kFlight) {
+                    u32x4 v[kFlight];
+#pragma unroll
+                    for (int it = 0; it < kFlight; ++it) {
+                        const int32_t p = p0 + it * kRows + rsub;
+                        const uint32_t j = (uint32_t)stage[p < count ? p : count - 1];
+                        // every place holds a token by construction; never read outside the cache whatever the scores were
+                        v[it] = __builtin_nontemporal_load(src + (size_t)(j < (uint32_t)n ? j : 0u) * ROW_U4);
+                    }
+#pragma unroll
+                    for (int it = 0; it < kFlight; ++it) {
+                        const int32_t p = p0 + it * kRows + rsub;
+                        if (p < count) __builtin_nontemporal_store(v[it], dst + (size_t)p * ROW_U4);
+                    }
+                }
+            }
+        }
+    };
+    if (!search) {                                                 // tokens 0 .. k-1: sinks only, or everything
+        for (int32_t j = r0 + tid; j < r1; j += kSplitThreads) put(j, j);
+        gather();
+        return;
+    }
+    // ---- the bitmaps -------------------------------------------------------------------------------
+    uint32_t ng = 0, ne = 0, total_g, total_e;
+#pragma unroll
+    for (int i = 0; i < kSplitWordsPerThread; ++i) {
+        ng += (uint32_t)__popcll(g[i]);
+        ne += (uint32_t)__popcll(e[i]);
+        sm.gmask[w0 + i] = g[i];
+        sm.emask[w0 + i] = e[i];
+    }
+    for (int i = tid; i < 256; i += kSplitThreads) sm.hist[i] = 0;
+    block_exclusive(ng, sm.wave_tot[0], &total_g);
+    uint32_t slot = block_exclusive(ne, sm.wave_tot[1], &total_e);
+    uint32_t need = m - total_g;                                   // how many of the range are kept (>= 1)
+    // ---- the threshold among the keys in the range ---------------------------------------------------
+    if (need < total_e) {
+        const bool listed = total_e <= (uint32_t)kSplitList;
+        // f(word, token is in the range, its key - lo), a wave per word, eight words' scores in flight
+        auto for_each_in_range = [&](auto f) {
+            constexpr int kU = 8;
+            for (int wb = wave * kU; wb < words; wb += kSplitWaves * kU) {
+                bool mine[kU];
+                float x[kU];
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    mine[u] = wb + u < words && ((sm.emask[wb + u] >> lane) & 1ull);
+                    x[u] = mine[u] ? sc[(wb + u) * 64 + lane] : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < kU; ++u) f(wb + u, mine[u], key31(scale(x[u])) - range.x);
+            }
+        };
+        if (listed) {                                              // tokens first, then all their keys at once
+#pragma unroll
+            for (int i = 0; i < kSplitWordsPerThread; ++i)
+                for (unsigned long long x = e[i]; x; x &= x - 1) sm.list[2 * slot++ + 1] = (uint32_t)((w0 + i) * 64 + __ffsll(x) - 1);
+            __syncthreads();
+            for (uint32_t i = tid; i < total_e; i += kSplitThreads) sm.list[2 * i] = key31(scale(sc[sm.list[2 * i + 1]])) - range.x;
+        }
+        if (tid == 0) sm.want = need;
+        __syncthreads();
+        const uint32_t width = range.y - range.x;
+        int rem = width ? 32 - __clz((int)width) : 0;              // bits of key - lo not yet decided
+        uint32_t fixed = 0;
+        while (rem > 0) {
+            const int w = rem < 8 ? rem : 8, shift = rem - w;
+            const uint32_t mask = (1u << w) - 1u;
+            if (listed) {
+                for (uint32_t i = tid; i < total_e; i += kSplitThreads) {
+                    const uint32_t key = sm.list[2 * i];
+                    if ((key >> rem) == fixed) atomicAdd(&sm.hist[(key >> shift) & mask], 1u);
+                }
+            } else {
+                for_each_in_range([&](int, bool mine, uint32_t key) {
+                    if (mine && (key >> rem) == fixed) atomicAdd(&sm.hist[(key >> shift) & mask], 1u);
+                });
+            }
+            __syncthreads();
+            pick_digit(sm.hist, &sm.digit, &sm.want);
+            fixed = (fixed << w) | sm.digit;
+            rem = shift;
+        }
+        need = sm.want;                                            // keys equal to the threshold still to be kept
+        // the range's members above the threshold join the kept ones, those equal to it stay flagged
+        if (listed) {
+            for (uint32_t i = tid; i < total_e; i += kSplitThreads) {
+                const uint32_t key = sm.list[2 * i], j = sm.list[2 * i + 1];
+                if (key > fixed) atomicOr(&sm.gmask[j >> 6], 1ull << (j & 63u));
+                if (key != fixed) atomicAnd(&sm.emask[j >> 6], ~(1ull << (j & 63u)));
+            }
+        } else {
+            for_each_in_range([&](int w1, bool mine, uint32_t key) {
+                const unsigned long long above = __ballot(mine && key > fixed), equal = __ballot(mine && key == fixed);
+                if (lane == 0 && w1 < words) { sm.gmask[w1] |= above; sm.emask[w1] = equal; }
+            });
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kSplitWordsPerThread; ++i) { g[i] = sm.gmask[w0 + i]; e[i] = sm.emask[w0 + i]; }
+    }
+    // ---- the first `need` flagged tokens join the kept ones; output positions -------------------------
+    ne = 0;
+#pragma unroll
+    for (int i = 0; i < kSplitWordsPerThread; ++i) ne += (uint32_t)__popcll(e[i]);
+    __syncthreads();                                               // the totals have been read by everyone
+    uint32_t eq_before = block_exclusive(ne, sm.wave_tot[0], &total_e), nk = 0;
+#pragma unroll
+    for (int i = 0; i < kSplitWordsPerThread; ++i) {
+        const uint32_t c = (uint32_t)__popcll(e[i]);
+        unsigned long long keep = e[i];
+        if (eq_before >= need) keep = 0ull;                        // quota already used up
+        else if (eq_before + c > need)                             // the word where it runs out
+            for (uint32_t drop = eq_before + c - need; drop; --drop) keep &= ~(1ull << (63 - __clzll((long long)keep)));
+        eq_before += c;
+        g[i] |= keep;
+        nk += (uint32_t)__popcll(g[i]);
+    }
+    uint32_t pos = (uint32_t)s + block_exclusive(nk, sm.wave_tot[1], &total_g);
+#pragma unroll
+    for (int i = 0; i < kSplitWordsPerThread; ++i) {
+        sm.gmask[w0 + i] = g[i];
+        sm.wpos[w0 + i] = pos;
+        pos += (uint32_t)__popcll(g[i]);
+    }
+    __syncthreads();
+    // ---- this workgroup's share ----------------------------------------------------------------------------
+    for (int32_t j = r0 + tid; j < r1 && j < s; j += kSplitThreads) put(j, j);
+    for (int q = tid; q < words * 4; q += kSplitThreads) {         // a thread per quarter word (16 tokens)
+        const int w = q >> 2, part = q & 3;
+        const unsigned long long word = sm.gmask[w];
+        uint32_t mm = (uint32_t)(word >> (16 * part)) & 0xFFFFu;
+        int32_t p = (int32_t)sm.wpos[w] + (int32_t)__popcll(word & ((1ull << (16 * part)) - 1ull));
+        if (p >= r1 || p + 16 <= r0) continue;
+        while (mm) {
+            const int bit = __ffs(mm) - 1;
+            mm &= mm - 1;
+            if (p >= r0 && p < r1) put(p, w * 64 + 16 * part + bit);
+            ++p;
+        }
+    }
+    gather();
+}
+
+// Which heads take this route.  One call, this against one workgroup per head (us): 1 head of 32768
+// tokens 31 against 33, 8 heads 47 against 50, 32 heads 133 against 137; 8 heads of 16384 33.8 against 32, 64 heads
+// of 32768 247 against 246: hence 24576 and 32 heads.  Longer heads would otherwise be streamed twice by one
+// workgroup (8 heads of 131072 tokens: 188 -> 136, 1 head 157 -> 54, 64 heads 933 -> 902, 256 heads no
+// difference).  The separate selection needs a launch more (32 heads of 32768: 147 against 137 for the three
+// calls), so it stays with one workgroup as long as its registers hold the head.
+bool split_wanted(const curdkv_ctx* ctx) { return ctx->cfg.max_tokens > kSplitMinTokens && ctx->heads <= kSplitMaxHeads; }
+
+bool split_applicable(const curdkv_ctx* ctx, int64_t n, bool one_call) {
+    if (!ctx->d_split_ws || n > kSplitMaxTokens) return false;
+    return n > (one_call && ctx->heads <= 32 ? kSplitMinTokens : kSplitMinTokensElse);
+}
+
+uint32_t* split_hist(const curdkv_ctx* ctx) { return carve(ctx).hist; }
+uint32_t* split_coarse(const curdkv_ctx* ctx) { return carve(ctx).coarse; }
+
+// One-call path: whether step 3 should gather as well.  It saves a launch and the indices' trip
+// through memory; the stand-alone gather kernel's many small workgroups move long lists faster.
+static bool emit_gathers(const curdkv_ctx* ctx, int64_t total) { return total <= (int64_t)ctx->num_cu * 1024; }
+
+hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
+                               const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
+                               int scale_blocks, bool write_scaled, SelectGather* gather) {
+    SplitArgs a{carve(ctx), scores, (int32_t)n, n_sink, d_offsets, ctx->d_partial, scale_blocks, write_scaled ? 1 : 0, 0, scale_blocks};
+    if (scale_blocks == 0) {
+        int64_t h = ((int64_t)ctx->num_cu * 2 + ctx->heads - 1) / ctx->heads;
+        const int64_t least = (n + 8191) / 8192;
+        if (h < least) h = least;
+        a.hists = (int)(h < a.ws.hists ? h : a.ws.hists);
+        split_hist_kernel<<<dim3((unsigned)a.hists, (unsigned)ctx->heads), kSplitThreads, 0, stream>>>(a);
+    }
+    int64_t parts = ((int64_t)ctx->num_cu * 2 + ctx->heads - 1) / ctx->heads;
+    int64_t part = (n + parts - 1) / parts;
+    if (part > 16384) part = 16384;
+    a.part = (int)((part + kSplitThreads - 1) / kSplitThreads * kSplitThreads);
+    split_flag_kernel<<<dim3((unsigned)((n + a.part - 1) / a.part), (unsigned)ctx->heads), kSplitThreads, 0, stream>>>(a);
+    const bool with_gather = gather && gather->total > 0 && emit_gathers(ctx, gather->total);
+    // shares such that there are about two workgroups per compute unit
+    int64_t share = with_gather ? (gather->total + ctx->num_cu * 2 - 1) / (ctx->num_cu * 2) : 4096;
+    if (with_gather) share = share < 64 ? 64 : share > kSplitShare ? kSplitShare : (share + 31) / 32 * 32;
+    const int64_t shares = (max_budget + share - 1) / share;
+    const dim3 grid((unsigned)(shares > 0 ? shares : 1), (unsigned)ctx->heads);
+    GatherArgs ga{};
+    if (with_gather) {
+        ga = GatherArgs{(const u32x4*)gather->K, (const u32x4*)gather->V, (u32x4*)gather->K_out, (u32x4*)gather->V_out};
+        gather->done = true;
+    }
+    if (!with_gather) split_emit_kernel<0><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga);
+    else if (ctx->cfg.dtype == CURDKV_DTYPE_BF16) split_emit_kernel<16><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga);
+    else split_emit_kernel<32><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga);
+    return hipGetLastError();
+}
+
+}  // namespace curdkv

@@ -1,0 +1,96 @@
+"""The selection of long heads by several workgroups per head: against the oracle's selection on the very
+scores the library stored, so that every index has to agree, ties included."""
+import numpy as np
+import pytest
+
+from oracle import curdkv_oracle as orc
+from paper_2509_15038_amd import binding as B
+from paper_2509_15038_amd import workloads as wl
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(scores, idx, off, budgets, s):
+    for i, k in enumerate(budgets):
+        want = orc.select(scores[i].astype(np.float64), int(k), s)
+        assert np.array_equal(idx[off[i]:off[i + 1]], want), (i, int(k), s)
+
+
+def _select(scores, budgets, s):
+    import torch
+    heads, n = scores.shape
+    off = wl.offsets_for(budgets)
+    with B.Context(1, heads, 4, 128, 32, "bf16", n, 1) as ctx:
+        g = gu.Guarded((max(int(off[-1]), 1),), torch.int32, -7)
+        ctx.select(torch.from_numpy(scores).cuda(), n, budgets, s, off, g.t)
+        torch.cuda.synchronize()
+        g.check("indices")
+        return g.t.cpu().numpy().astype(np.int64), off
+
+
+# (36864: the longest head one workgroup takes; 131072: the longest the bitmaps take)
+@pytest.mark.parametrize("n", [36864, 36865, 40960, 65537, 131071, 131072, 131073])
+def test_given_scores(n):
+    rng = np.random.default_rng(n)
+    x = np.exp(rng.standard_normal((9, n)) * 2.0)
+    x[1] = 1.0                                                # one value: every candidate ties
+    x[2] = rng.integers(0, 3, n)                              # three values, zero among them
+    x[3] = np.round(rng.random(n) * 7000) + 1                 # ties everywhere
+    x[4] = 1.0 + rng.random(n) * 1e-3                         # one bin holds the whole head
+    x[5] *= 1e-33                                             # normalised scores below 1e-37 among them
+    x[6, : n // 2] = 0.0
+    x[7] = rng.random(n) * 3.0                                # (not normalised below: scores of 2 and above)
+    x[8, n - 5:] = 1e6                                        # a block at the end
+    norm = x.sum(1, keepdims=True)
+    norm[7] = 1.0
+    scores = (x / norm).astype(np.float32)
+    for budgets, s in ((np.array([n // 10] * 9), 4), (np.array([0, 1, 4, 5, n - 1, n, n // 2, n // 3, 6]), 4),
+                       (np.array([n // 2] * 9), 0), (np.array([70, n - 64, 130, 4096, 4097, 64, 65, 1, n]), 64)):
+        budgets = budgets.astype(np.int32)
+        idx, off = _select(scores, budgets, s)
+        _check(scores, idx, off, budgets, s)
+
+
+def _one_call(K, V, dtype, r, budgets, s, with_scores=True):
+    import torch
+    L, H, n, d = K.shape
+    off = wl.offsets_for(budgets)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    total = int(off[-1])
+    with B.Context(L, H, 4, d, r, dtype, n, 7) as ctx:
+        Kd, Vd = gu.to_device(K, dtype), gu.to_device(V, dtype)
+        sc = gu.Guarded((L * H, n), torch.float32, float("nan"))
+        ix = gu.Guarded((max(total, 1),), torch.int32, -7)
+        Ko = gu.Guarded((max(total, 1), d), tdt, float("nan"))
+        Vo = gu.Guarded((max(total, 1), d), tdt, float("nan"))
+        ctx.compress(Kd, Vd, n, budgets, s, off, sc.t if with_scores else None, ix.t, Ko.t, Vo.t)
+        torch.cuda.synchronize()
+        for g in (sc, ix, Ko, Vo):
+            g.check()
+        idx = ix.t.cpu().numpy().astype(np.int64)[:total]
+        ko, vo = gu.to_host(Ko.t, dtype)[:total], gu.to_host(Vo.t, dtype)[:total]
+        for i in range(L * H):
+            rows = idx[off[i]:off[i + 1]]
+            assert np.array_equal(ko[off[i]:off[i + 1]], K.reshape(L * H, n, d)[i][rows])
+            assert np.array_equal(vo[off[i]:off[i + 1]], V.reshape(L * H, n, d)[i][rows])
+        return sc.t.cpu().numpy(), idx, off
+
+
+# 1 to 33 heads on both sides of the lengths at which the route changes; 128 columns and fp32 have other scoring kernels
+@pytest.mark.parametrize("heads,n,r,dtype", [(1, 24576, 20, "bf16"), (1, 24577, 20, "bf16"), (3, 30001, 64, "bf16"), (33, 36865, 20, "bf16"),
+                                             (2, 131072, 128, "bf16"), (1, 50000, 20, "fp32"), (2, 33333, 64, "fp32"), (1, 40000, 128, "fp32")])
+def test_one_call(heads, n, r, dtype):
+    cfg = wl.scaled(wl.CONFIGS["c2"], kv_heads=heads, n=n, r=r, dtype=dtype)
+    K, V = wl.host_cache(cfg)
+    if heads > 1:                                             # a head of few distinct rows: ties by the thousand, also at the bins' ends
+        few = np.random.default_rng(1).integers(0, 40, n)
+        K[0, 1], V[0, 1] = K[0, 1][few], V[0, 1][few]
+    if heads > 2:
+        V[0, 2] = 0                                           # a head of zeros: uniform scores
+    budgets = np.array([n // 10, n // 3, n // 2, 0, 3, n, n - 1, 64][:heads] + [n // 7] * max(0, heads - 8), dtype=np.int32)
+    scores, idx, off = _one_call(K, V, dtype, r, budgets, 4)
+    assert np.all(np.isfinite(scores))
+    _check(scores, idx, off, budgets, 4)
+    _, idx2, _ = _one_call(K, V, dtype, r, budgets, 4, with_scores=False)
+    assert np.array_equal(idx, idx2)
