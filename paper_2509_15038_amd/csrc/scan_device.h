@@ -354,6 +354,72 @@ __device__ __forceinline__ float scan_tiles_f32(const SketchF32<CB>& G, const fl
     return acc_sum;
 }
 
+// ---- fp32 storage, few tokens in all -----------------------------------------------------
+// A workgroup takes 16 tokens at a time and its waves share the products: wave w has tensor w / CB
+// (where both are scored) and the 16 sketch columns of block w % CB.  With a few thousand tokens per
+// call the walks above leave most of the chip idle behind serial chains: a wave of scan_tiles_f32 works
+// through 64 tokens of K and V, 512 fp32 MFMAs of 32 cycles (7 us) at 32 columns; here 32 (0.4 us).
+// The products are plain fp32 at every width.  Scoring, us per call before and after: 1 head of 1024
+// tokens 17.4 -> 8.5 at r = 20, 23.7 -> 9.6 at r = 64, 34.7 -> 12.0 at r = 128; 8 heads of 2048 tokens
+// 17.9 -> 12.1, 23.8 -> 16.4, 34.9 -> 21.6; 256 heads of one token 7.9 -> 3.4, 15.0 -> 4.2, 23.6 -> 7.1.
+// first, last: the workgroup's range of 16-token
+// steps; `put(row, score)` is called by the lanes 0..15 of wave 0, once for each row below n.
+// red: LDS, two sets of WAVES x 16 floats, taken in turn so that one barrier per step is enough.
+template <int CB, int SRC, class Put>
+__device__ __forceinline__ void scan_few_f32(const float4* __restrict__ Gh, const float4* __restrict__ Kh,
+                                             const float4* __restrict__ Vh, int32_t n, int32_t first, int32_t last,
+                                             float (*red)[(SRC == kSrcKV ? 2 : 1) * CB][16], Put put) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int tok = lane & 15, q = lane >> 4;
+    const int cb = wave % CB;
+    const float4* src = SRC == kSrcK || (SRC == kSrcKV && wave < CB) ? Kh : Vh;
+    float4 x[8], g[8];
+    auto load = [&](int32_t step) {
+        int32_t row = step * 16 + tok;
+        row = row < n ? row : n - 1;                            // rows past the end reload the last one
+        const float4* p = src + (size_t)(uint32_t)row * 32 + q;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) x[s] = p[s * 4];
+    };
+    if (first < last) load(first);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) g[s] = Gh[(cb * 8 + s) * 64 + lane];
+    for (int32_t t = first; t < last; ++t) {
+        f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            a = __builtin_amdgcn_mfma_f32_16x16x4f32(g[s].x, x[s].x, a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_16x16x4f32(g[s].y, x[s].y, a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_16x16x4f32(g[s].z, x[s].z, a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_16x16x4f32(g[s].w, x[s].w, a, 0, 0, 0);
+        }
+        if (t + 1 < last) load(t + 1);      // (sent out ahead of the products: slower, the barrier waits for loads as well)
+        float l = a[0] * a[0];
+#pragma unroll
+        for (int e = 1; e < 4; ++e) l = fmaf(a[e], a[e], l);
+        float m = l;
+        swap_rows(l, m);                                        // l = rows 0,0,2,2; m = rows 1,1,3,3
+        l += m;
+        m = l;
+        swap_halves(l, m);                                      // l = rows 0,1 (twice), m = rows 2,3
+        l += m;
+        auto& out = red[(t - first) & 1];
+        if (lane < 16) out[wave][lane] = l;
+        __syncthreads();
+        if (wave == 0 && lane < 16) {
+            float score = 1.f;
+#pragma unroll
+            for (int tensor = 0; tensor < (SRC == kSrcKV ? 2 : 1); ++tensor) {
+                float sum = out[tensor * CB][lane];
+#pragma unroll
+                for (int c = 1; c < CB; ++c) sum += out[tensor * CB + c][lane];
+                score *= sum;
+            }
+            if (t * 16 + lane < n) put(t * 16 + lane, score);
+        }
+    }
+}
+
 // ---- fp32 storage, more than 32 sketch columns -------------------------------------------
 // Lane roles as above; the products go through the bf16 matrix units.  A float is split into three bf16 numbers,
 // x = x1 + x2 + x3 exactly (rounded to nearest each time: 8 significant bits and a sign per part
