@@ -201,11 +201,11 @@ __global__ __launch_bounds__(256) void normalise_kernel(float* __restrict__ scor
                                                         int chunks_per_head) {
     const int head = blockIdx.x / chunks_per_head;
     const int chunk = blockIdx.x - head * chunks_per_head;
-    double tot = 0.0;
-    for (int i = 0; i < blocks_per_head; ++i) tot += (double)partial[(size_t)head * kMaxBlocksPerHead + i];
-    const bool zero = !(tot > 0.0);
-    const float inv = zero ? 0.f : (float)(1.0 / tot);
-    const float uniform = (float)(1.0 / (double)n);
+    partial += (size_t)head * kMaxBlocksPerHead;
+    // one or two sums (many heads) come through scalar loads: 256 heads of 131072 tokens 42 us, 57 with all lanes adding
+    const HeadScale scale = blocks_per_head <= 2
+        ? scale_by((double)partial[0] + (blocks_per_head == 2 ? (double)partial[1] : 0.0), n)
+        : head_scale(head_partial(partial, blocks_per_head), blocks_per_head, n);
     float* sh = scores + (size_t)head * n;
     constexpr int kInFlight = 8;                   // loads issued before the first store
     const int64_t stride = (int64_t)chunks_per_head * blockDim.x;
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256) void normalise_kernel(float* __restrict__ scor
 #pragma unroll
         for (int u = 0; u < kInFlight; ++u) {
             const int64_t j = j0 + u * stride;
-            if (j < n) sh[j] = zero ? uniform : v[u] * inv;
+            if (j < n) sh[j] = scale(v[u]);
         }
     }
 }
@@ -388,14 +388,13 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
 }
 
 // Decode-phase bookkeeping: running sum of a head's un-normalised scores, and the
-// normalisation by it.  Partial sums are added in index order, in double.
-__global__ void accumulate_sums_kernel(const float* __restrict__ partial, int blocks_per_head,
-                                       double* __restrict__ sums, int heads, int reset) {
-    const int head = blockIdx.x * blockDim.x + threadIdx.x;
+// normalisation by it.  A wave per head adds the partial sums in a fixed order, in double.
+__global__ __launch_bounds__(256) void accumulate_sums_kernel(const float* __restrict__ partial, int blocks_per_head,
+                                                              double* __restrict__ sums, int heads, int reset) {
+    const int head = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (head >= heads) return;
-    double tot = reset ? 0.0 : sums[head];
-    for (int i = 0; i < blocks_per_head; ++i) tot += (double)partial[(size_t)head * kMaxBlocksPerHead + i];
-    sums[head] = tot;
+    const double total = wave_total((double)head_partial(partial + (size_t)head * kMaxBlocksPerHead, blocks_per_head));
+    if ((threadIdx.x & 63) == 0) sums[head] = (reset ? 0.0 : sums[head]) + total;
 }
 
 __global__ __launch_bounds__(256) void normalise_sums_kernel(const float* __restrict__ raw,
@@ -406,19 +405,31 @@ __global__ __launch_bounds__(256) void normalise_sums_kernel(const float* __rest
     const int head = blockIdx.x / chunks_per_head;
     const int chunk = blockIdx.x - head * chunks_per_head;
     const double tot = sums[head];
-    const bool zero = !(tot > 0.0);
-    const float inv = zero ? 0.f : (float)(1.0 / tot);
-    const float uniform = (float)(1.0 / (double)n);
     const float* src = raw + (size_t)head * stride;
     float* dst = scores + (size_t)head * n;
-    for (int64_t j = (int64_t)chunk * blockDim.x + threadIdx.x; j < n;
-         j += (int64_t)chunks_per_head * blockDim.x)
-        dst[j] = zero ? uniform : src[j] * inv;
+    constexpr int kInFlight = 4;                   // loads issued before the first store: all there are up to 65536 tokens
+    const int64_t step = (int64_t)chunks_per_head * blockDim.x;
+    for (int64_t j0 = (int64_t)chunk * blockDim.x + threadIdx.x; j0 < n; j0 += kInFlight * step) {
+        float v[kInFlight];
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+            const int64_t j = j0 + u * step;
+            v[u] = j < n ? src[j] : 0.f;
+        }
+        const bool zero = !(tot > 0.0);
+        const float inv = zero ? 0.f : (float)(1.0 / tot);
+        const float uniform = (float)(1.0 / (double)n);
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+            const int64_t j = j0 + u * step;
+            if (j < n) dst[j] = zero ? uniform : v[u] * inv;
+        }
+    }
 }
 
 hipError_t launch_accumulate(const curdkv_ctx* ctx, int blocks_per_head, double* sums, bool reset,
                              hipStream_t stream) {
-    accumulate_sums_kernel<<<dim3((unsigned)((ctx->heads + 255) / 256)), 256, 0, stream>>>(
+    accumulate_sums_kernel<<<dim3((unsigned)((ctx->heads + 3) / 4)), 256, 0, stream>>>(
         ctx->d_partial, blocks_per_head, sums, ctx->heads, reset ? 1 : 0);
     return hipGetLastError();
 }

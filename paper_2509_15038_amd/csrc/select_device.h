@@ -59,7 +59,7 @@ __device__ __forceinline__ uint32_t bin12(uint32_t key) {
 }
 
 // The normalisation step of Algorithm 1 applied on the fly: v -> v / (sum of the head), the
-// sum being the per-block partial sums added in index order in double; 1/n when the sum
+// sum being the per-block partial sums added in a fixed order in double; 1/n when the sum
 // is 0.  The arithmetic is the one of the stand-alone normalisation kernel.
 struct HeadScale {
     float inv, uniform;
@@ -68,20 +68,50 @@ struct HeadScale {
         return !on ? v : (zero ? uniform : v * inv);
     }
 };
-__device__ __forceinline__ HeadScale head_scale(const float* __restrict__ partial, int blocks, int64_t n) {
-    HeadScale h;
-    h.on = blocks > 0;
-    // the partial sums (at most 64, kMaxBlocksPerHead) in one load, a lane each, then added in index
-    // order: a load per addition left the whole selection waiting for a chain of them
+// A head's partial sums, a lane each (at most 64); the load can go out long before head_scale needs it.
+__device__ __forceinline__ float head_partial(const float* __restrict__ partial, int blocks) {
     static_assert(kMaxBlocksPerHead <= 64, "a lane per partial sum");
     const int lane = threadIdx.x & 63;
-    const int mine = lane < blocks ? __float_as_int(partial[lane]) : 0;
-    double tot = 0.0;
-    for (int i = 0; i < blocks; ++i) tot += (double)__int_as_float(__builtin_amdgcn_readlane(mine, i));
+    return lane < blocks ? partial[lane] : 0.f;
+}
+// The sum of a double over the 64 lanes, in every lane: neighbours first, then pairs, and so on, by
+// lane exchanges in registers.  All 64 lanes must be there.
+__device__ __forceinline__ double wave_total(double x) {
+    auto add = [&](auto ctrl) {
+        const int lo = __double2loint(x), hi = __double2hiint(x);
+        x += __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, decltype(ctrl)::value, 0xF, 0xF, true),
+                              __builtin_amdgcn_update_dpp(0, lo, decltype(ctrl)::value, 0xF, 0xF, true));
+    };
+    using std::integral_constant;
+    add(integral_constant<int, 0xB1>{});           // quad_perm 1,0,3,2
+    add(integral_constant<int, 0x4E>{});           // quad_perm 2,3,0,1
+    add(integral_constant<int, 0x141>{});          // row_half_mirror: the other quad of eight lanes
+    add(integral_constant<int, 0x140>{});          // row_mirror: the other half of the row of 16
+    {
+        const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(x), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(x), false, false);
+        x = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    }
+    {
+        const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(x), false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(x), false, false);
+        x = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    }
+    return x;
+}
+// Every wave of every kernel that scales a head adds the same way, so they all agree to the bit.  (One
+// after the other, 64 additions that wait for one another take 0.6 us.)
+__device__ __forceinline__ HeadScale scale_by(double tot, int64_t n) {
+    HeadScale h;
+    h.on = true;
     h.zero = !(tot > 0.0);
     h.inv = h.zero ? 0.f : (float)(1.0 / tot);
     h.uniform = (float)(1.0 / (double)n);
     return h;
+}
+__device__ __forceinline__ HeadScale head_scale(float mine, int blocks, int64_t n) {
+    if (blocks <= 0) return HeadScale{0.f, 0.f, false, false};
+    return scale_by(wave_total((double)mine), n);
 }
 
 // A threshold the caller already knows (the head-wise budget allocation finds one per layer):
@@ -289,6 +319,28 @@ __device__ __forceinline__ uint32_t threshold_on_list(const int32_t* pairs, uint
                                                       uint32_t want, uint32_t* hist64, uint32_t* digit,
                                                       uint32_t* want_s, uint32_t* need) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (count <= 32u) {
+        // a short list (heads up to some 8000 tokens): one wave compares every key with every other, which costs
+        // one barrier instead of six (selection of 64 heads of 4096 tokens 6.3 -> 5.9 us; with lists of 50 keys,
+        // 32 heads of 20000 tokens, it would be 13.7 -> 14.3)
+        if (wave == 0) {
+            const uint32_t key = lane < (int)count ? (uint32_t)pairs[2 * lane] & 0x7FFFFFFFu : 0u;
+            uint32_t above = 0, equal = 0;
+            for (uint32_t i = 0; i < count; i += 8) {          // (lanes past the list hold 0: above nothing)
+#pragma unroll
+                for (uint32_t u = 0; u < 8; ++u) {
+                    const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)key, (int)(i + u));
+                    above += other > key ? 1u : 0u;
+                    equal += other == key ? 1u : 0u;
+                }
+            }
+            // (equal keys all write the same)
+            if (lane < (int)count && above < want && want <= above + equal) { *digit = key; *want_s = want - above; }
+        }
+        __syncthreads();
+        *need = *want_s;
+        return *digit;
+    }
     uint32_t fixed = bin;                          // decided high part of (key & 0x7FFFFFFF): >> rem
     for (int rem = kBinShift; rem > 0; rem -= 6) {
         const int shift = rem - 6;

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kSelThreads) void select_stream_kernel(float* __res
     int32_t* out = indices + o0;
     float* sc = scores + (size_t)head * n;
     const uint32_t s = (uint32_t)n_sink < n ? (uint32_t)n_sink : n;
-    const HeadScale scale = head_scale(partial + (size_t)head * kMaxBlocksPerHead, scale_blocks, n64);
+    const HeadScale scale = head_scale(head_partial(partial + (size_t)head * kMaxBlocksPerHead, scale_blocks), scale_blocks, n64);
     auto scale_all = [&]() {                       // heads that need no selection still get normalised
         if (scale.on && write_scaled)
             for (uint32_t j = tid; j < n; j += kSelThreads) sc[j] = scale(sc[j]);
@@ -345,22 +345,26 @@ __global__ __launch_bounds__(kSelThreads) void select_reg_kernel(float* __restri
     __shared__ SelectShared<kSelThreads, KPT> sm;
     const int head = blockIdx.x;
     const int tid = threadIdx.x;
+    float* sc = scores + (size_t)head * n;
+    // all loads go out together, before anything is decided: offsets, partial sums and scores fetched one
+    // after the other each cost a trip to memory (one call, 8 heads of 8192 tokens: 21.0 -> 19.7 us together with
+    // the sum of the partials)
+    const float mine = head_partial(partial + (size_t)head * kMaxBlocksPerHead, scale_blocks);
+    float v[KPT];
+#pragma unroll
+    for (int it = 0; it < KPT; ++it) {
+        const int32_t j = it * kSelThreads + tid;
+        v[it] = j < n ? sc[j] : 0.f;
+    }
     const int64_t o0 = offsets[head];
     const int32_t k = (int32_t)(offsets[head + 1] - o0);
     if (k <= 0 && (scale_blocks <= 0 || !write_scaled)) return;
     int32_t* out = indices + o0;
-    float* sc = scores + (size_t)head * n;
     const int32_t s = n_sink < n ? n_sink : n;
-    const HeadScale scale = head_scale(partial + (size_t)head * kMaxBlocksPerHead, scale_blocks, n);
 
     uint32_t x[KPT];
     {
-        float v[KPT];
-#pragma unroll
-        for (int it = 0; it < KPT; ++it) {
-            const int32_t j = it * kSelThreads + tid;
-            v[it] = j < n ? sc[j] : 0.f;
-        }
+        const HeadScale scale = head_scale(mine, scale_blocks, n);
 #pragma unroll
         for (int it = 0; it < KPT; ++it) {
             v[it] = scale(v[it]);

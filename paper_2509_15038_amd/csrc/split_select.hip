@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) 
     const bool write = a.scale_blocks > 0 && a.write_scaled;
     if (!search && !write) return;
     load(j0);
-    const HeadScale scale = head_scale(a.partial + (size_t)head * kMaxBlocksPerHead, a.scale_blocks, n);
+    const HeadScale scale = head_scale(head_partial(a.partial + (size_t)head * kMaxBlocksPerHead, a.scale_blocks), a.scale_blocks, n);
     uint32_t lo = 0, hi = 0;
     if (search) {
         if (tid < 64) fine[tid] = 0;
@@ -306,7 +306,8 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
         }
     }
     const uint2 range = a.ws.range[head];
-    const HeadScale scale = head_scale(a.partial + (size_t)head * kMaxBlocksPerHead, a.write_scaled ? 0 : a.scale_blocks, n);
+    const int scale_blocks = a.write_scaled ? 0 : a.scale_blocks;
+    const HeadScale scale = head_scale(head_partial(a.partial + (size_t)head * kMaxBlocksPerHead, scale_blocks), scale_blocks, n);
     const float* sc = a.scores + (size_t)head * n;
     const int32_t k = (int32_t)(o1 - o0);
     const int32_t r0 = (int32_t)blockIdx.x * share;
