@@ -354,44 +354,58 @@ __device__ __forceinline__ float scan_tiles_f32(const SketchF32<CB>& G, const fl
     return acc_sum;
 }
 
-// ---- fp32 storage, few tokens in all -----------------------------------------------------
+// ---- few tokens in all, either storage ---------------------------------------------------
 // A workgroup takes 16 tokens at a time and its waves share the products: wave w has tensor w / CB
 // (where both are scored) and the 16 sketch columns of block w % CB.  With a few thousand tokens per
-// call the walks above leave most of the chip idle behind serial chains: a wave of scan_tiles_f32 works
-// through 64 tokens of K and V, 512 fp32 MFMAs of 32 cycles (7 us) at 32 columns; here 32 (0.4 us).
-// The products are plain fp32 at every width.  Scoring, us per call before and after: 1 head of 1024
-// tokens 17.4 -> 8.5 at r = 20, 23.7 -> 9.6 at r = 64, 34.7 -> 12.0 at r = 128; 8 heads of 2048 tokens
-// 17.9 -> 12.1, 23.8 -> 16.4, 34.9 -> 21.6; 256 heads of one token 7.9 -> 3.4, 15.0 -> 4.2, 23.6 -> 7.1.
-// first, last: the workgroup's range of 16-token
-// steps; `put(row, score)` is called by the lanes 0..15 of wave 0, once for each row below n.
-// red: LDS, two sets of WAVES x 16 floats, taken in turn so that one barrier per step is enough.
-template <int CB, int SRC, class Put>
-__device__ __forceinline__ void scan_few_f32(const float4* __restrict__ Gh, const float4* __restrict__ Kh,
-                                             const float4* __restrict__ Vh, int32_t n, int32_t first, int32_t last,
-                                             float (*red)[(SRC == kSrcKV ? 2 : 1) * CB][16], Put put) {
+// call the walks above and below leave most of the chip idle behind serial chains: a wave of scan_tiles_f32
+// works through 64 tokens of K and V, 512 fp32 MFMAs of 32 cycles (7 us) at 32 columns; here 32 (0.4 us).
+// A wave of scan_tiles loads the whole sketch (16 KB at 64 columns) and 64 rows where one or sixteen are new.
+// The products are plain fp32 for fp32 storage at every width.  Scoring, us per call before and after,
+// fp32: 1 head of 1024 tokens 17.4 -> 8.5 at r = 20, 23.7 -> 9.6 at r = 64, 34.7 -> 12.0 at r = 128; 8
+// heads of 2048 tokens 17.9 -> 12.1, 23.8 -> 16.4, 34.9 -> 21.6; 256 heads of one token 7.9 -> 3.4,
+// 15.0 -> 4.2, 23.6 -> 7.1; bf16: 1 head of 1024 tokens 7.9 -> 4.3, 8.5 -> 4.9, 10.3 -> 6.0; 256 heads of one
+// token 4.4 -> 2.8, 4.7 -> 3.1, 5.5 -> 3.6.
+// first, last: the workgroup's range of 16-token steps; `put(row, score)` is called by the lanes
+// 0..15 of wave 0, once for each row below n.  red: LDS, two sets of WAVES x 16 floats, taken in turn so
+// that one barrier per step is enough.
+template <bool F32> struct FewOperand {             // a lane's quarter of a row, 16 bytes at a time
+    static constexpr int kSteps = F32 ? 8 : 4;
+    using Word = std::conditional_t<F32, float4, Chunk>;
+};
+
+template <bool F32, int CB, int SRC, class Put>
+__device__ __forceinline__ void scan_few(const typename FewOperand<F32>::Word* __restrict__ Gh,
+                                         const typename FewOperand<F32>::Word* __restrict__ Kh,
+                                         const typename FewOperand<F32>::Word* __restrict__ Vh, int32_t n, int32_t first,
+                                         int32_t last, float (*red)[(SRC == kSrcKV ? 2 : 1) * CB][16], Put put) {
+    constexpr int kSteps = FewOperand<F32>::kSteps;             // a row is 4 * kSteps words
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int tok = lane & 15, q = lane >> 4;
     const int cb = wave % CB;
-    const float4* src = SRC == kSrcK || (SRC == kSrcKV && wave < CB) ? Kh : Vh;
-    float4 x[8], g[8];
+    const auto* src = SRC == kSrcK || (SRC == kSrcKV && wave < CB) ? Kh : Vh;
+    typename FewOperand<F32>::Word x[kSteps], g[kSteps];
     auto load = [&](int32_t step) {
         int32_t row = step * 16 + tok;
         row = row < n ? row : n - 1;                            // rows past the end reload the last one
-        const float4* p = src + (size_t)(uint32_t)row * 32 + q;
+        const auto* p = src + (size_t)(uint32_t)row * (4 * kSteps) + q;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) x[s] = p[s * 4];
+        for (int s = 0; s < kSteps; ++s) x[s] = p[s * 4];
     };
     if (first < last) load(first);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) g[s] = Gh[(cb * 8 + s) * 64 + lane];
+    for (int s = 0; s < kSteps; ++s) g[s] = Gh[(cb * kSteps + s) * 64 + lane];
     for (int32_t t = first; t < last; ++t) {
         f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            a = __builtin_amdgcn_mfma_f32_16x16x4f32(g[s].x, x[s].x, a, 0, 0, 0);
-            a = __builtin_amdgcn_mfma_f32_16x16x4f32(g[s].y, x[s].y, a, 0, 0, 0);
-            a = __builtin_amdgcn_mfma_f32_16x16x4f32(g[s].z, x[s].z, a, 0, 0, 0);
-            a = __builtin_amdgcn_mfma_f32_16x16x4f32(g[s].w, x[s].w, a, 0, 0, 0);
+        for (int s = 0; s < kSteps; ++s) {
+            if constexpr (F32) {
+                a = __builtin_amdgcn_mfma_f32_16x16x4f32(g[s].x, x[s].x, a, 0, 0, 0);
+                a = __builtin_amdgcn_mfma_f32_16x16x4f32(g[s].y, x[s].y, a, 0, 0, 0);
+                a = __builtin_amdgcn_mfma_f32_16x16x4f32(g[s].z, x[s].z, a, 0, 0, 0);
+                a = __builtin_amdgcn_mfma_f32_16x16x4f32(g[s].w, x[s].w, a, 0, 0, 0);
+            } else {
+                a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[s].v, x[s].v, a, 0, 0, 0);
+            }
         }
         if (t + 1 < last) load(t + 1);      // (sent out ahead of the products: slower, the barrier waits for loads as well)
         float l = a[0] * a[0];

@@ -162,12 +162,13 @@ __global__ __launch_bounds__((ShapeF32<CB>::kWaves * 64), (ShapeF32<CB>::kSplit 
     if (COUNT) raw_hist_store<kWaves * 64>(hist, hist_out, coarse_out, head * hists + blk);
 }
 
-// fp32 storage, few tokens in all (scan_few_f32): `steps` of 16 tokens to a workgroup.
-template <int CB, int SRC>
-__global__ __launch_bounds__(((SRC == kSrcKV ? 2 : 1) * CB * 64)) void scores_f32_few_kernel(
-    const float4* __restrict__ K, const float4* __restrict__ V, const float4* __restrict__ Gp,
-    float* __restrict__ scores, float* __restrict__ partial, int32_t n, int32_t blocks_per_head, int32_t steps,
-    int64_t out_stride, int64_t out_offset, double* __restrict__ sums, int restart) {
+// Few tokens in all (scan_few): `steps` of 16 tokens to a workgroup.
+template <bool F32, int CB, int SRC>
+__global__ __launch_bounds__(((SRC == kSrcKV ? 2 : 1) * CB * 64)) void scores_few_kernel(
+    const typename FewOperand<F32>::Word* __restrict__ K, const typename FewOperand<F32>::Word* __restrict__ V,
+    const typename FewOperand<F32>::Word* __restrict__ Gp, float* __restrict__ scores, float* __restrict__ partial, int32_t n,
+    int32_t blocks_per_head, int32_t steps, int64_t out_stride, int64_t out_offset, double* __restrict__ sums, int restart) {
+    constexpr int kRow = 4 * FewOperand<F32>::kSteps;           // 16-byte words per row
     __shared__ float red[2][(SRC == kSrcKV ? 2 : 1) * CB][16];
     const int head = blockIdx.x / blocks_per_head;
     const int blk = blockIdx.x - head * blocks_per_head;
@@ -176,11 +177,11 @@ __global__ __launch_bounds__(((SRC == kSrcKV ? 2 : 1) * CB * 64)) void scores_f3
     const int32_t last = first + steps < all ? first + steps : all;
     float* sh = scores + (size_t)head * out_stride + out_offset;
     float acc = 0.f;
-    scan_few_f32<CB, SRC>(Gp + (size_t)head * (CB * 8 * 64), K + (size_t)head * n * 32, V + (size_t)head * n * 32,
-                          n, first, last, red, [&](int32_t row, float score) {
-                              sh[row] = score;
-                              acc += score;
-                          });
+    scan_few<F32, CB, SRC>(Gp + (size_t)head * (CB * FewOperand<F32>::kSteps * 64), K + (size_t)head * n * kRow,
+                           V + (size_t)head * n * kRow, n, first, last, red, [&](int32_t row, float score) {
+                               sh[row] = score;
+                               acc += score;
+                           });
     if (threadIdx.x < 64) {
         const float total = wave_sum(acc);
         if (threadIdx.x == 0) {
@@ -292,28 +293,37 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
     return (int)lo;
 }
 
-// As many workgroups as the chip holds at once (16 waves per compute unit), a step each at least.
-static int few_f32_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
+// As many workgroups as the chip holds at once (16 waves per compute unit), a step each at least.  Two
+// steps stay in one workgroup, which can add a head's running sum by itself: one launch instead of two.
+static int few_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
     const int waves = (ctx->cfg.score_source == CURDKV_SCORE_KV ? 2 : 1) * 2 * ctx->col_blocks;
     const int64_t slots = (int64_t)ctx->num_cu * (16 / waves);
     int64_t b = (slots + ctx->heads - 1) / ctx->heads;
     const int64_t steps = (n + 15) / 16;
+    if (steps <= 2) return 1;
     b = b < steps ? b : steps;
     return (int)(b < kMaxBlocksPerHead ? b : kMaxBlocksPerHead);
 }
 
-// fp32 calls of few tokens in all take scan_few_f32.  Measured at r = 20 / 64 / 128 (us per call, the
-// other kernel -> this one): 16384 tokens in 8 heads 17.9 -> 12.1 / 23.8 -> 16.4 / 34.9 -> 21.6, 32768 tokens in 8
-// heads 18.4 -> 16.1 / 24.7 -> 24.1 / 36.5 -> 36.4; in 256 heads level at 16384 tokens (13.2 -> 13.9 at
+// Calls of few tokens in all take scan_few.  Measured, us per curdkv_scores_append, the other kernel -> this one.
+// fp32, r = 20 / 64 / 128: 16384 tokens in 8 heads 17.9 -> 12.1 / 23.8 -> 16.4 / 34.9 -> 21.6, 32768 tokens in 8
+// heads 18.4 -> 16.1 / 24.7 -> 24.1 / 36.5 -> 36.4; in 256 heads level at 16384 tokens (13.2 -> 13.2 at
 // r = 64) and behind at 32768 (15.3 -> 23.4).  One long head has at most 64 workgroups: 4096
 // tokens, 4 steps each, 18.0 -> 11.3 / 23.8 -> 15.5 / 34.7 -> 23.2; 16384 tokens, 16 steps each,
 // 20.7 -> 22.1 / 25.3 -> 36.2 / 36.2 -> 64.6.
-constexpr int64_t kFewF32Tokens = 16384, kFewF32Steps = 6;
+// bf16: 256 heads of one token 4.4 -> 2.8 / 4.7 -> 3.1 / 5.5 -> 3.6; 8192 tokens in 8 heads 7.9 -> 5.1 / 8.6 -> 6.2 / 10.4 -> 8.0;
+// 16384 in 8 heads 8.2 -> 5.9 / 9.0 -> 7.9 / 10.6 -> 11.4 and in 64 heads 6.6 -> 6.4 / 7.3 -> 8.1 / 9.0 -> 11.5; one head
+// of 4096 tokens 8.6 -> 5.5 / 9.3 -> 7.4 / 11.1 -> 11.1.  128 columns in many heads end earlier: 256 heads of 16
+// tokens 4.6 -> 4.8 (each row goes to sixteen waves).
+constexpr int64_t kFewF32Tokens = 16384, kFewF32Steps = 6, kFewBf16Tokens = 8192, kFewBf16Wide = 2048, kFewBf16Steps = 4;
 
-static bool few_f32(const curdkv_ctx* ctx, int64_t n) {
-    if (ctx->cfg.dtype != CURDKV_DTYPE_F32 || ctx->cfg.no_projection || n * ctx->heads > kFewF32Tokens) return false;
+static bool few_tokens(const curdkv_ctx* ctx, int64_t n) {
+    if (ctx->cfg.no_projection) return false;
+    const bool f32 = ctx->cfg.dtype == CURDKV_DTYPE_F32;
+    const bool wide = ctx->col_blocks > 2 && ctx->heads > ctx->num_cu / 4;
+    if (n * ctx->heads > (f32 ? kFewF32Tokens : wide ? kFewBf16Wide : kFewBf16Tokens)) return false;
     const int64_t steps = (n + 15) / 16;
-    return steps <= kFewF32Steps * few_f32_blocks_per_head(ctx, n);
+    return steps <= (f32 ? kFewF32Steps : kFewBf16Steps) * few_blocks_per_head(ctx, n);
 }
 
 hipError_t configure_kernels(curdkv_ctx* ctx) {
@@ -326,8 +336,8 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
                          int64_t out_stride, int64_t out_offset, double* sums, bool restart,
                          bool* summed, bool with_hist, int32_t n_sink) {
     if (out_stride <= 0) out_stride = n;
-    const bool few = few_f32(ctx, n) && !with_hist;
-    const int bph = few ? few_f32_blocks_per_head(ctx, n) : pick_blocks_per_head(ctx, n);
+    const bool few = few_tokens(ctx, n) && !with_hist;
+    const int bph = few ? few_blocks_per_head(ctx, n) : pick_blocks_per_head(ctx, n);
     if (blocks_per_head) *blocks_per_head = bph;
     if (bph != 1) sums = nullptr;                 // several blocks per head: the caller adds the partials
     if (summed) *summed = sums != nullptr;
@@ -345,16 +355,22 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
     auto launch = [&](auto cb, auto src, auto proj, auto count) {
         constexpr int CB = decltype(cb)::value, SRC = decltype(src)::value;
         constexpr bool PROJ = decltype(proj)::value, COUNT = decltype(count)::value;
-        if (ctx->cfg.dtype == CURDKV_DTYPE_BF16)
+        const int64_t steps = (n + 15) / 16;
+        const bool bf16 = ctx->cfg.dtype == CURDKV_DTYPE_BF16;
+        if (PROJ && !COUNT && few) {
+            auto launch_few = [&](auto f32) {
+                using Word = typename FewOperand<decltype(f32)::value>::Word;
+                scores_few_kernel<decltype(f32)::value, CB, SRC><<<grid, (SRC == kSrcKV ? 2 : 1) * CB * 64, 0, stream>>>(
+                    (const Word*)K, (const Word*)V, (const Word*)ctx->d_G, scores, part, (int32_t)n, bph,
+                    (int32_t)((steps + bph - 1) / bph), out_stride, out_offset, sums, rs);
+            };
+            if (bf16) launch_few(std::false_type{});
+            else launch_few(std::true_type{});
+        } else if (bf16)
             scores_bf16_kernel<CB, SRC, PROJ, COUNT><<<grid, 256, 0, stream>>>(
                 (const uint4*)K, (const uint4*)V, (const uint4*)ctx->d_G, scores, part, n, bph, out_stride, out_offset, sums, rs,
                 hist, coarse, hists, n_sink);
-        else if (PROJ && !COUNT && few) {
-            const int64_t steps = (n + 15) / 16;
-            scores_f32_few_kernel<CB, SRC><<<grid, (SRC == kSrcKV ? 2 : 1) * CB * 64, 0, stream>>>(
-                (const float4*)K, (const float4*)V, (const float4*)ctx->d_G, scores, part, (int32_t)n, bph,
-                (int32_t)((steps + bph - 1) / bph), out_stride, out_offset, sums, rs);
-        } else
+        else
             scores_f32_kernel<CB, SRC, PROJ, COUNT><<<grid, ShapeF32<CB>::kWaves * 64, 0, stream>>>(
                 (const float4*)K, (const float4*)V, (const float4*)ctx->d_G, scores, part, n, bph, out_stride, out_offset, sums, rs,
                 hist, coarse, hists, n_sink);

@@ -1,0 +1,44 @@
+"""bf16 calls of few tokens in all: workgroups of 16 tokens whose waves share the products.  Scores and
+running sums against the float64 oracle at the edges of the 16-token steps, with one step and several
+per workgroup, and on both sides of the lines where the kernel of longer calls takes over."""
+import numpy as np
+import pytest
+
+from oracle import curdkv_oracle as orc
+from paper_2509_15038_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+SEED = 0xC0DE0011
+# products of bf16 numbers are exact; a projected coordinate is rounded once per 32 of them, then squared,
+# summed over r, multiplied and normalised: some 200 roundings of 2^-24 at random, and the sums' own
+NORM_TOL = 1e-6
+
+
+# one token; edges of a step; two steps in one workgroup and three in three; 64 workgroups of 1 and 4 steps and
+# one step too many; many heads, up to the last sizes of either width and beyond them
+@pytest.mark.parametrize("n,heads", [(1, 1), (16, 1), (17, 3), (32, 2), (33, 2), (1025, 1), (4096, 1), (4097, 1), (1, 256),
+                                     (8, 256), (9, 256), (32, 256), (33, 256), (1024, 8), (1025, 8)])
+@pytest.mark.parametrize("r,source", [(20, "kv"), (33, "v"), (64, "kv"), (128, "k"), (128, "kv")])
+def test_scores_and_sums(n, heads, r, source):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n * 512 + heads)
+    K = torch.randn((heads, n, 128), generator=g, device="cuda").to(torch.bfloat16)
+    V = torch.randn((heads, n, 128), generator=g, device="cuda").to(torch.bfloat16)
+    with B.Context(heads, 1, 4, 128, r, "bf16", n + 7, SEED, source) as ctx:
+        got = torch.full((heads, n), float("nan"), device="cuda")
+        ctx.scores(K, V, n, got)
+        # behind five tokens scored before, in rows of n + 7 places: only the new ones are written
+        raw = torch.full((heads, n + 7), -1.0, device="cuda")
+        sums = torch.full((heads,), 3.0, dtype=torch.float64, device="cuda")
+        ctx.scores_append(K, V, n, 5, n + 7, raw, sums)
+        got, raw, sums = got.cpu().numpy(), raw.cpu().numpy(), sums.cpu().numpy()
+    assert np.all(raw[:, :5] == -1.0) and np.all(raw[:, n + 5:] == -1.0)
+    assert np.allclose(sums - 3.0, raw[:, 5:n + 5].astype(np.float64).sum(1), rtol=1e-6)
+    for i in range(heads) if heads < 8 else (0, heads // 2, heads - 1):
+        G = orc.sketch(SEED, i, 0, 1, 128, r, "bf16")
+        want = orc.scores(K[i].double().cpu().numpy(), V[i].double().cpu().numpy(), G, source)
+        assert np.linalg.norm(got[i] - want) <= NORM_TOL * np.linalg.norm(want), (n, heads, r, source, i)
+        new = raw[i, 5:n + 5].astype(np.float64)
+        assert np.linalg.norm(new / new.sum() - want) <= NORM_TOL * np.linalg.norm(want)
