@@ -265,7 +265,15 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
     const int waves = f32 && cb > 1 ? ShapeF32<4>::kWaves : 4;       // per workgroup
     const int64_t stage = f32 ? (cb == 1 ? ShapeF32<2>::kTiles : cb == 2 ? ShapeF32<4>::kTiles : ShapeF32<8>::kTiles)
                               : (wide ? Stage<8>::kTiles : Stage<4>::kTiles);
-    const int64_t slots = (int64_t)ctx->num_cu * ((wide || f32 || ctx->heads <= ctx->num_cu) ? 1 : 2);
+    int64_t slots = (int64_t)ctx->num_cu * ((wide || f32 || ctx->heads <= ctx->num_cu) ? 1 : 2);
+    // Few, long heads: a sixteenth of the units is left idle, and the ranges of the waves, which otherwise lie
+    // powers of two apart where n is one, fall between.  Scoring, us with all 256 units and with 240 at most:
+    // 8 heads of 131072 tokens 97.7 and 94.2, of 65536 51.5 and 49.9, of 32768 29.7 and 28.6, of 100000 74.1 and 73.6; 4 heads
+    // of 131072 51.4 and 49.3; 16 of 32768 52.0 and 49.6; 32 of 32768 96.4 and 95.6, not worth a rule; 128 columns, 8 heads
+    // of 131072 104.3 and 97.5.  Below eight tiles a wave the rounding to whole pairs costs more (8 heads of 8192:
+    // 11.2 and 13.1).
+    const bool spare = ctx->cfg.dtype == CURDKV_DTYPE_BF16 && ctx->heads * 16 <= ctx->num_cu && (int64_t)ctx->heads * tiles >= 8 * waves * slots;
+    if (spare) slots -= slots / 16;
     int64_t cap = (tiles + waves - 1) / waves;                                     // at least one tile per wave
     if (cap > kMaxBlocksPerHead) cap = kMaxBlocksPerHead;
     int64_t lo = (tiles + waves * stage - 1) / (waves * stage);
@@ -279,7 +287,8 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
     // the whole call for 1 head of 32768 tokens 52 us with 17 workgroups, 33 with 64)
     const int64_t fill = (slots + ctx->heads - 1) / ctx->heads;
     const int64_t most = lo + 15 > fill ? lo + 15 : fill;
-    const int64_t hi = most < cap ? most : cap;
+    int64_t hi = most < cap ? most : cap;
+    if (spare && hi > slots / ctx->heads) hi = slots / ctx->heads > lo ? slots / ctx->heads : lo;     // one round
     auto cost = [&](int64_t b) {                                       // rounds x tiles a wave works through
         const int64_t rounds = ((int64_t)ctx->heads * b + slots - 1) / slots;
         int64_t per_wave = (tiles + waves * b - 1) / (waves * b);
