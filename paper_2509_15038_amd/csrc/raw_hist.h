@@ -19,6 +19,13 @@ __device__ __forceinline__ void raw_hist_count(uint32_t* hist, float v, bool cou
     atomicAdd(&hist[(bits >> (kRawShift + 1)) & (kRawHistWords - 1)], counts ? one : 0u);
 }
 
+// Takes back what raw_hist_count added for the same v and `counts`.
+__device__ __forceinline__ void raw_hist_uncount(uint32_t* hist, float v, bool counts = true) {
+    const uint32_t bits = __float_as_uint(v);
+    const uint32_t one = (bits >> kRawShift) & 1u ? 0x10000u : 1u;
+    atomicSub(&hist[(bits >> (kRawShift + 1)) & (kRawHistWords - 1)], counts ? one : 0u);
+}
+
 // Writes the workgroup's histogram (complete, in LDS) and its sums per exponent to place `at`.
 template <int THREADS>
 __device__ __forceinline__ void raw_hist_store(const uint32_t* hist, uint32_t* __restrict__ out,

@@ -630,8 +630,9 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
                 const float lk = SRC == kSrcV ? 1.f : rescore_row<CB>(gs, (const float*)Kh + at, lane);
                 const float lv = SRC == kSrcK ? 1.f : rescore_row<CB>(gs, (const float*)Vh + at, lane);
                 if (lane == b) {
+                    if (COUNT) raw_hist_uncount(hist, v, row >= n_sink);
                     v = lk * lv;
-                    if (COUNT) raw_hist_count(hist, v, row >= n_sink);  // (it stays counted as a NaN as well)
+                    if (COUNT) raw_hist_count(hist, v, row >= n_sink);
                 }
             }
             if (row < n) {

@@ -52,13 +52,15 @@ def test_given_scores(n):
         _check(scores, idx, off, budgets, s)
 
 
-def _one_call(K, V, dtype, r, budgets, s, with_scores=True):
+def _one_call(K, V, dtype, r, budgets, s, with_scores=True, sketch=None):
     import torch
     L, H, n, d = K.shape
     off = wl.offsets_for(budgets)
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
     total = int(off[-1])
     with B.Context(L, H, 4, d, r, dtype, n, 7) as ctx:
+        for h in range(H if sketch is not None else 0):
+            ctx.set_sketch(0, h, sketch)
         Kd, Vd = gu.to_device(K, dtype), gu.to_device(V, dtype)
         sc = gu.Guarded((L * H, n), torch.float32, float("nan"))
         ix = gu.Guarded((max(total, 1),), torch.int32, -7)
@@ -94,3 +96,27 @@ def test_one_call(heads, n, r, dtype):
     _check(scores, idx, off, budgets, 4)
     _, idx2, _ = _one_call(K, V, dtype, r, budgets, 4, with_scores=False)
     assert np.array_equal(idx, idx2)
+
+
+@pytest.mark.parametrize("r", [64, 128])
+def test_rows_scored_again(r):
+    """fp32 rows whose split into bf16 parts overflows (a float above the largest bf16, in a dimension that
+    the sketch leaves out) but whose score is finite: counted once, in the bin of that score."""
+    n, s = 30002, 4
+    cfg = wl.scaled(wl.CONFIGS["c2"], kv_heads=6, n=n, r=r, dtype="fp32")
+    K, V = wl.host_cache(cfg)
+    rng = np.random.default_rng(r)
+    G = (rng.standard_normal((128, r)) / np.sqrt(r)).astype(np.float32)
+    G[[9, 100]] = 0.0
+    for h in range(6):
+        rows = rng.permutation(n)[:(0, 1, 300, 300, 300, 3000)[h]]
+        (K if h % 2 else V)[0, h, rows, 9] = np.finfo(np.float32).max
+        K[0, h, rows[::3], 100] = -np.finfo(np.float32).max
+        K[0, h, 2, 9] = np.finfo(np.float32).max              # a sink: counted nowhere
+    for frac in (7, 40, 1000):
+        budgets = np.array([s + 1, n // frac, s + 1, s + 2, n // frac, n // frac], dtype=np.int32)
+        scores, idx, off = _one_call(K, V, "fp32", r, budgets, s, sketch=G)
+        _check(scores, idx, off, budgets, s)
+    for h in range(6):
+        want = orc.scores(K[0, h].astype(np.float64), V[0, h].astype(np.float64), G.astype(np.float64), "kv")
+        gu.check_scores(scores[h], want, h)
