@@ -61,7 +61,7 @@ __global__ __launch_bounds__(kFusedThreads, 2) void fused_kernel(
 #pragma unroll
     for (int w = 0; w < kFusedWaves; ++w) tot += (double)wsum[w];
     const bool zero = !(tot > 0.0);
-    const float inv = zero ? 0.f : (float)(1.0 / tot);
+    const float inv = zero ? 0.f : head_reciprocal(tot);
     const float uniform = (float)(1.0 / (double)n);
 
     // ---- 3. normalise, write out, keys into registers ----------------------------------

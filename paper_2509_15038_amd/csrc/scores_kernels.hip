@@ -442,7 +442,7 @@ __global__ __launch_bounds__(256) void normalise_sums_kernel(const float* __rest
             v[u] = j < n ? src[j] : 0.f;
         }
         const bool zero = !(tot > 0.0);
-        const float inv = zero ? 0.f : (float)(1.0 / tot);
+        const float inv = zero ? 0.f : head_reciprocal(tot);
         const float uniform = (float)(1.0 / (double)n);
 #pragma unroll
         for (int u = 0; u < kInFlight; ++u) {

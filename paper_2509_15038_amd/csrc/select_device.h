@@ -99,13 +99,18 @@ __device__ __forceinline__ double wave_total(double x) {
     }
     return x;
 }
+// What a head's products are multiplied by, tot > 0.  A sum below 2.9e-39, whose reciprocal is no float, must not
+// make zeros NaN, which have no place in the order: the largest float instead.
+__device__ __forceinline__ float head_reciprocal(double tot) {
+    return fminf((float)(1.0 / tot), 3.40282347e38f);
+}
 // Every wave of every kernel that scales a head adds the same way, so they all agree to the bit.  (One
 // after the other, 64 additions that wait for one another take 0.6 us.)
 __device__ __forceinline__ HeadScale scale_by(double tot, int64_t n) {
     HeadScale h;
     h.on = true;
     h.zero = !(tot > 0.0);
-    h.inv = h.zero ? 0.f : (float)(1.0 / tot);
+    h.inv = h.zero ? 0.f : head_reciprocal(tot);
     h.uniform = (float)(1.0 / (double)n);
     return h;
 }

@@ -120,3 +120,37 @@ def test_rows_scored_again(r):
     for h in range(6):
         want = orc.scores(K[0, h].astype(np.float64), V[0, h].astype(np.float64), G.astype(np.float64), "kv")
         gu.check_scores(scores[h], want, h)
+
+
+# several workgroups per head, one, a head in parts, the fused kernel; and the two separate normalisations
+@pytest.mark.parametrize("heads,n,dtype", [(2, 30001, "fp32"), (33, 30001, "bf16"), (129, 37001, "bf16"), (256, 700, "bf16"), (2, 300, "fp32")])
+def test_sum_too_small_to_divide_by(heads, n, dtype):
+    """A head whose scores add up to less than the smallest number with a finite reciprocal (2.9e-39) keeps
+    finite scores, in their order."""
+    import torch
+    s = 4
+    K = torch.zeros((heads, n, 128), dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda")
+    V = torch.zeros_like(K)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    rows = torch.randperm(n, generator=g, device="cuda")[:100].sort().values
+    K[:2, rows] = 1e-11
+    V[:2, rows] = (2e-13 * (1 + torch.arange(100, device="cuda") % 7)[:, None]).to(V.dtype)
+    with B.Context(1, heads, 4, 128, 20, dtype, n, 7) as ctx:
+        sc = torch.empty((heads, n), device="cuda")
+        Ko, Vo = torch.empty((2 * n, 128), dtype=K.dtype, device="cuda"), torch.empty((2 * n, 128), dtype=K.dtype, device="cuda")
+        for k in (5, 60, 104, n // 2, n - 1):
+            budgets = np.array([k, k] + [0] * (heads - 2), np.int32)
+            off = wl.offsets_for(budgets)
+            ix = torch.full((2 * k,), -7, dtype=torch.int32, device="cuda")
+            ctx.compress(K, V, n, budgets, s, off, sc, ix, Ko, Vo)
+            got = sc[:2].cpu().numpy()
+            assert np.all(np.isfinite(got)) and np.count_nonzero(got) == 200 and len(np.unique(got[0])) > 4
+            _check(got, ix.cpu().numpy(), off, budgets[:2], s)
+        raw, sums, two = torch.empty_like(sc), torch.zeros((heads,), dtype=torch.float64, device="cuda"), torch.empty_like(sc)
+        ctx.scores_append(K, V, n, 0, n, raw, sums)
+        assert 0 < float(sums[0]) < 2.9e-39
+        ctx.normalise(raw, sums, n, n, two)
+        ctx.scores(K, V, n, sc)
+        for x in (two, sc):
+            assert bool(torch.isfinite(x[:2]).all()) and int(torch.count_nonzero(x[:2])) == 200
