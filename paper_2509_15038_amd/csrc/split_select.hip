@@ -123,7 +123,8 @@ __global__ __launch_bounds__(kSplitThreads) void split_hist_kernel(SplitArgs a) 
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int32_t j = b + u * kSplitThreads + tid;
-            if (j >= s && j < j1) raw_hist_count(hist, v[u]);
+            // by the key, as the flags of step 2: the two agree whatever the caller's scores are
+            if (j >= s && j < j1) raw_hist_count(hist, __uint_as_float(key31(v[u])));
         }
     }
     __syncthreads();
@@ -132,9 +133,9 @@ __global__ __launch_bounds__(kSplitThreads) void split_hist_kernel(SplitArgs a) 
 
 // The bin in which the running count from the top of 64*PER counts reaches `want`: called by one
 // wave, lane L holds counts 64*PER-1 - (L*PER + i) in c[i].  The lane that finds it writes
-// {bin, want left inside it} to LDS.
+// {bin, want left inside it} to LDS.  Returns the sum of all counts.
 template <int PER>
-__device__ __forceinline__ void wave_find(const uint32_t (&c)[PER], uint32_t want, uint32_t* out) {
+__device__ __forceinline__ uint32_t wave_find(const uint32_t (&c)[PER], uint32_t want, uint32_t* out) {
     const int lane = threadIdx.x & 63;
     uint32_t tot = 0;
 #pragma unroll
@@ -148,6 +149,7 @@ __device__ __forceinline__ void wave_find(const uint32_t (&c)[PER], uint32_t wan
             run += c[i];
         }
     }
+    return (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
 }
 
 __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) {
@@ -187,7 +189,8 @@ __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) 
         __syncthreads();
         if (tid < 64) {
             const uint32_t c[4] = {exps[255 - 4 * lane], exps[254 - 4 * lane], exps[253 - 4 * lane], exps[252 - 4 * lane]};
-            wave_find<4>(c, m, found);
+            // step 3 takes for granted that the range holds the cut: if counts went missing, everything is in it
+            if (wave_find<4>(c, m, found) != (uint32_t)(n - s) && lane == 0) { found[0] = 255u; found[1] = 1u; }
         }
         __syncthreads();
         const uint32_t ex = found[0], want = found[1];

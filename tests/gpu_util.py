@@ -3,6 +3,9 @@ host-generated cache and compare with the oracle.  Not collected by pytest."""
 
 from __future__ import annotations
 
+import os
+import re
+
 import numpy as np
 
 from oracle import curdkv_oracle as orc
@@ -10,6 +13,15 @@ from paper_2509_15038_amd import binding as B
 from paper_2509_15038_amd import workloads as wl
 
 RTOL = 1e-3     # relative tolerance on scores: fp32 accumulation of exact bf16 products
+
+
+def limit(source: str, name: str) -> int:
+    """An integer constant of the library's sources (paper_2509_15038_amd/csrc): where a test has to lie on a
+    certain side of a dispatch rule, it takes the rule's own number."""
+    text = open(os.path.join(os.path.dirname(B.__file__), "csrc", source)).read()
+    found = re.search(r"\b%s = ([0-9* ]+)[,;]" % name, text)
+    assert found, (source, name)
+    return int(np.prod([int(f) for f in found.group(1).split("*")]))
 
 
 def to_device(a: np.ndarray, dtype: str):

@@ -122,6 +122,28 @@ def test_rows_scored_again(r):
         gu.check_scores(scores[h], want, h)
 
 
+def test_scores_out_of_the_ordinary():
+    """Scores that curdkv_scores itself can leave (an infinite product gives NaN), and zeros of either sign, keep the
+    same tokens as in a context of more heads than this route takes; scores that have no business
+    here (negative ones) have no order, but keep as many tokens as asked for."""
+    n, s, most = 40001, 4, gu.limit("curdkv_internal.h", "kSplitMaxHeads")
+    rng = np.random.default_rng(9)
+    x = np.exp(rng.standard_normal((most + 1, n)) * 2.0).astype(np.float32)
+    x[0, rng.permutation(n)[:50]] = np.nan
+    x[1, rng.permutation(n)[:50]] = np.inf
+    x[2, ::2] = -0.0
+    x[3] *= np.where(rng.random(n) < 0.3, -1, 1)
+    x[4, ::3] = -np.float32(np.nan)
+    x[5] = -x[5]
+    budgets = np.full((most + 1,), 9, np.int32)
+    for k in (5, 30, 60, n // 3, n - 1):
+        budgets[:6] = k
+        want, off = _select(x, budgets, s)                    # one workgroup per head
+        got, off6 = _select(np.ascontiguousarray(x[:6]), budgets[:6].copy(), s)
+        assert np.array_equal(got[:off[3]], want[:off[3]])
+        assert got.min() == 0 and got.max() < n and np.all(np.diff(got.reshape(6, k)) > 0)
+
+
 # several workgroups per head, one, a head in parts, the fused kernel; and the two separate normalisations
 @pytest.mark.parametrize("heads,n,dtype", [(2, 30001, "fp32"), (33, 30001, "bf16"), (129, 37001, "bf16"), (256, 700, "bf16"), (2, 300, "fp32")])
 def test_sum_too_small_to_divide_by(heads, n, dtype):
