@@ -97,7 +97,11 @@ __device__ __forceinline__ bool needs_search(int32_t k, int32_t n, int32_t s, ui
     return k > s && *m < (uint32_t)(n - s);
 }
 
-__device__ __forceinline__ uint32_t key31(float x) { return order_key(x) & 0x7FFFFFFFu; }
+// order_key without its top bit
+__device__ __forceinline__ uint32_t key31(float x) {
+    const int32_t b = __float_as_int(x + 0.0f);                    // -0 -> +0
+    return (uint32_t)(b ^ (b >> 31)) & 0x7FFFFFFFu;
+}
 
 // Step 1 from scores in memory: workgroup (blockIdx.x, head) counts an equal share of the head.
 __global__ __launch_bounds__(kSplitThreads) void split_hist_kernel(SplitArgs a) {
@@ -118,7 +122,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_hist_kernel(SplitArgs a) 
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int32_t j = b + u * kSplitThreads + tid;
-            v[u] = j < j1 ? sc[j] : 0.f;
+            v[u] = sc[j < j1 ? j : j1 - 1];        // (not as a branch, or each load is waited for inside it)
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
