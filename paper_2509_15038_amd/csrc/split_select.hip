@@ -23,8 +23,11 @@
 // onto the range's ends are inside the range too, so that ties between them are
 // decided by token number as everywhere.
 //
-// A range with more keys than the list takes (a head of equal scores, say) is resolved by
-// reading its scores again, a digit per pass: slow and exact.
+// The range is a sixteenth of a binade: a few hundred to a few thousand tokens of a long head whose scores spread
+// over decades, but a tenth or more of one whose scores lie together (rows of like norm).  Step 3 takes up to 4096 keys in
+// LDS, up to 20480 in registers, and narrows a fuller range by reading its scores again, a digit per pass.
+// Without the registers, us per call: 8 heads of 131072 normal rows, 64 columns, half kept, 361, with them 210 (one
+// workgroup per head: 271); 128 columns, a tenth kept, 309 and 147 (208); 64 heads of 65536, 64 columns, half kept, 807 and 739 (750).
 //
 // (One histogram per head, added up with atomics, took 15 us for 8 heads of 131072 tokens where
 // writing and summing one per workgroup takes about 1: atomics of many workgroups on one address
@@ -37,7 +40,8 @@ namespace curdkv {
 
 constexpr int kSplitThreads = 512;
 constexpr int kSplitWaves = kSplitThreads / 64;
-constexpr int kSplitList = 4096;                   // keys in the range that step 3 resolves in LDS
+constexpr int kSplitPairs = 4096;                  // keys in the range that step 3 resolves in LDS,
+constexpr int kSplitList = 20480;                  // and in registers: two workgroups still share a unit's LDS
 constexpr int kSplitMinTokens = 24 * 1024;          // one call, at most 32 heads
 constexpr int kSplitMinTokensElse = 36 * 1024;      // beyond: one workgroup's registers hold a head up to here
 constexpr int kSplitMaxTokens = 131072;            // tokens per head the bitmaps and their scan are laid out for
@@ -212,7 +216,8 @@ __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) 
         const uint32_t bin = ex * 16 + (found[0] & 15u);
         lo = key31(scale(__uint_as_float(bin << kRawShift)));
         hi = key31(scale(__uint_as_float((bin << kRawShift) | ((1u << kRawShift) - 1u))));
-        if (ex >= 255u || (scale.on && scale.zero)) { lo = 0u; hi = 0x7FFFFFFFu; }   // beyond the finite range, or all zero: everything
+        if (ex >= 255u) { lo = 0u; hi = 0x7FFFFFFFu; }                      // beyond the finite range: everything
+        if (scale.on && scale.zero) lo = hi = key31(scale.uniform);         // all scores are this one
         if (blockIdx.x == 0 && tid == 0) a.ws.range[head] = uint2{lo, hi};
     }
     unsigned long long* g = a.ws.gmask + (size_t)head * a.ws.words;
@@ -237,12 +242,18 @@ __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) 
 
 struct EmitShared {
     unsigned long long gmask[kSplitMaxWords];      // kept tokens
-    uint32_t wpos[kSplitMaxWords];                 // output position of a word's first kept token
     unsigned long long emask[kSplitMaxWords];      // candidates in the range, then those equal to the threshold
-    uint32_t list[2 * kSplitList];                 // (key - lo, token) of the candidates in the range
+    union {
+        struct {
+            uint32_t pairs[2 * kSplitPairs];       // (key - lo, token) of the candidates in the range,
+            uint32_t wpos[kSplitMaxWords];         // later: output position of a word's first kept token
+        };
+        uint16_t list[kSplitList];                 // or the candidates' tokens, ascending, without bit 16
+    };
     uint32_t hist[256];
     uint32_t wave_tot[2][kSplitWaves];
-    uint32_t list_count, digit, want;
+    uint32_t digit, want, count;
+    uint32_t low;                                  // place in the list of the first token from 65536 on
 };
 
 // exclusive prefix of x over the workgroup's threads; the total goes to *total
@@ -262,9 +273,21 @@ __device__ __forceinline__ uint32_t block_exclusive(uint32_t x, uint32_t* wave_t
     return before + incl - x;
 }
 
+// Counts a digit per lane in hist (LDS); lanes of the same digit as the first one, as equal scores have, in
+// one addition.  All 64 lanes must be there.
+__device__ __forceinline__ void count_digit(uint32_t* hist, uint32_t digit, bool counts) {
+    const unsigned long long all = __ballot(counts);
+    if (!all) return;
+    const int leader = __ffsll(all) - 1;
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)digit, leader);
+    const unsigned long long same = __ballot(counts && digit == first);
+    if ((threadIdx.x & 63) == leader) atomicAdd(&hist[first], (uint32_t)__popcll(same));
+    else if (counts && digit != first) atomicAdd(&hist[digit], 1u);
+}
+
 // One digit of the search for the threshold: hist[0..255] counts the digit's values (zeroed
-// again), *want becomes the rank inside the chosen value.  Ends with a barrier.
-__device__ __forceinline__ void pick_digit(uint32_t* hist, uint32_t* digit, uint32_t* want) {
+// again), *want becomes the rank inside the chosen value, *count that value's count.  Ends with a barrier.
+__device__ __forceinline__ void pick_digit(uint32_t* hist, uint32_t* digit, uint32_t* want, uint32_t* count) {
     if (threadIdx.x < 64) {                        // lane L looks at values 255-4L .. 252-4L
         const int lane = threadIdx.x;
         uint32_t c[4], tot = 0;
@@ -276,7 +299,7 @@ __device__ __forceinline__ void pick_digit(uint32_t* hist, uint32_t* digit, uint
         if (run < w && w <= incl) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if (w <= run + c[i]) { *digit = 255 - 4 * lane - i; *want = w - run; break; }
+                if (w <= run + c[i]) { *digit = 255 - 4 * lane - i; *want = w - run; *count = c[i]; break; }
                 run += c[i];
             }
         }
@@ -375,68 +398,134 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
     uint32_t slot = block_exclusive(ne, sm.wave_tot[1], &total_e);
     uint32_t need = m - total_g;                                   // how many of the range are kept (>= 1)
     // ---- the threshold among the keys in the range ---------------------------------------------------
-    if (need < total_e) {
-        const bool listed = total_e <= (uint32_t)kSplitList;
-        // f(word, token is in the range, its key - lo), a wave per word, eight words' scores in flight
-        auto for_each_in_range = [&](auto f) {
-            constexpr int kU = 8;
-            for (int wb = wave * kU; wb < words; wb += kSplitWaves * kU) {
-                bool mine[kU];
-                float x[kU];
+    const uint32_t width = range.y - range.x;
+    int rem = width ? 32 - __clz((int)width) : 0;                  // bits of key - lo not yet decided
+    if (need < total_e && rem > 0) {
+        uint32_t fixed = 0;
+        if (tid == 0) sm.want = need;
+        if (total_e > (uint32_t)kSplitList) {
+            // digit by digit from memory until the rest fits the list, then one pass that keeps what is above and leaves
+            // the rest flagged (8 heads of 131072 equal scores, a tenth kept, curdkv_select: 450 -> 210 us)
+            // f(word, token is in the range, its key - lo), a wave per word, kU words' scores and flags in flight
+            auto for_each_in_range = [&](auto f) {
+                constexpr int kU = 32;
+                const uint32_t* half = reinterpret_cast<const uint32_t*>(sm.emask) + (lane >> 5);
+                for (int wb = wave * kU; wb < words; wb += kSplitWaves * kU) {
+                    float x[kU];
+                    uint32_t mine[kU];
 #pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                    mine[u] = wb + u < words && ((sm.emask[wb + u] >> lane) & 1ull);
-                    x[u] = mine[u] ? sc[(wb + u) * 64 + lane] : 0.f;
+                    for (int u = 0; u < kU; ++u) {
+                        const int32_t j = (wb + u) * 64 + lane;
+                        x[u] = sc[j < n ? j : n - 1];
+                        mine[u] = half[2 * (wb + u)];              // (zero beyond the head)
+                    }
+#pragma unroll
+                    for (int u = 0; u < kU; ++u) f(wb + u, ((mine[u] >> (lane & 31)) & 1u) != 0, key31(scale(x[u])) - range.x);
                 }
-#pragma unroll
-                for (int u = 0; u < kU; ++u) f(wb + u, mine[u], key31(scale(x[u])) - range.x);
+            };
+            __syncthreads();
+            while (rem > 0 && total_e > (uint32_t)kSplitList) {
+                const int w = rem < 8 ? rem : 8, shift = rem - w;
+                for_each_in_range([&](int, bool mine, uint32_t key) {
+                    count_digit(sm.hist, (key >> shift) & ((1u << w) - 1u), mine && (key >> rem) == fixed);
+                });
+                __syncthreads();
+                pick_digit(sm.hist, &sm.digit, &sm.want, &sm.count);
+                fixed = (fixed << w) | sm.digit;
+                total_e = sm.count;
+                rem = shift;
             }
-        };
-        if (listed) {                                              // tokens first, then all their keys at once
+            for_each_in_range([&](int w1, bool mine, uint32_t key) {
+                const unsigned long long above = __ballot(mine && (key >> rem) > fixed), rest = __ballot(mine && (key >> rem) == fixed);
+                if (lane == 0) { atomicOr(&sm.gmask[w1], above); sm.emask[w1] = rest; }
+            });
+            __syncthreads();
+            ne = 0;
+#pragma unroll
+            for (int i = 0; i < kSplitWordsPerThread; ++i) {
+                e[i] = sm.emask[w0 + i];
+                ne += (uint32_t)__popcll(e[i]);
+            }
+            slot = block_exclusive(ne, sm.wave_tot[1], &total_e);
+        }
+        if (rem > 0 && total_e <= (uint32_t)kSplitPairs) {         // tokens first, then all their keys at once
 #pragma unroll
             for (int i = 0; i < kSplitWordsPerThread; ++i)
-                for (unsigned long long x = e[i]; x; x &= x - 1) sm.list[2 * slot++ + 1] = (uint32_t)((w0 + i) * 64 + __ffsll(x) - 1);
+                for (unsigned long long x = e[i]; x; x &= x - 1) sm.pairs[2 * slot++ + 1] = (uint32_t)((w0 + i) * 64 + __ffsll(x) - 1);
             __syncthreads();
-            for (uint32_t i = tid; i < total_e; i += kSplitThreads) sm.list[2 * i] = key31(scale(sc[sm.list[2 * i + 1]])) - range.x;
-        }
-        if (tid == 0) sm.want = need;
-        __syncthreads();
-        const uint32_t width = range.y - range.x;
-        int rem = width ? 32 - __clz((int)width) : 0;              // bits of key - lo not yet decided
-        uint32_t fixed = 0;
-        while (rem > 0) {
-            const int w = rem < 8 ? rem : 8, shift = rem - w;
-            const uint32_t mask = (1u << w) - 1u;
-            if (listed) {
+            for (uint32_t i = tid; i < total_e; i += kSplitThreads) sm.pairs[2 * i] = key31(scale(sc[sm.pairs[2 * i + 1]])) - range.x;
+            __syncthreads();
+            while (rem > 0) {
+                const int w = rem < 8 ? rem : 8, shift = rem - w;
                 for (uint32_t i = tid; i < total_e; i += kSplitThreads) {
-                    const uint32_t key = sm.list[2 * i];
-                    if ((key >> rem) == fixed) atomicAdd(&sm.hist[(key >> shift) & mask], 1u);
+                    const uint32_t key = sm.pairs[2 * i];
+                    if ((key >> rem) == fixed) atomicAdd(&sm.hist[(key >> shift) & ((1u << w) - 1u)], 1u);
                 }
-            } else {
-                for_each_in_range([&](int, bool mine, uint32_t key) {
-                    if (mine && (key >> rem) == fixed) atomicAdd(&sm.hist[(key >> shift) & mask], 1u);
-                });
+                __syncthreads();
+                pick_digit(sm.hist, &sm.digit, &sm.want, &sm.count);
+                fixed = (fixed << w) | sm.digit;
+                rem = shift;
             }
-            __syncthreads();
-            pick_digit(sm.hist, &sm.digit, &sm.want);
-            fixed = (fixed << w) | sm.digit;
-            rem = shift;
-        }
-        need = sm.want;                                            // keys equal to the threshold still to be kept
-        // the range's members above the threshold join the kept ones, those equal to it stay flagged
-        if (listed) {
+            // the list's members above the threshold join the kept ones, those equal to it stay flagged
             for (uint32_t i = tid; i < total_e; i += kSplitThreads) {
-                const uint32_t key = sm.list[2 * i], j = sm.list[2 * i + 1];
+                const uint32_t key = sm.pairs[2 * i], j = sm.pairs[2 * i + 1];
                 if (key > fixed) atomicOr(&sm.gmask[j >> 6], 1ull << (j & 63u));
                 if (key != fixed) atomicAnd(&sm.emask[j >> 6], ~(1ull << (j & 63u)));
             }
-        } else {
-            for_each_in_range([&](int w1, bool mine, uint32_t key) {
-                const unsigned long long above = __ballot(mine && key > fixed), equal = __ballot(mine && key == fixed);
-                if (lane == 0 && w1 < words) { sm.gmask[w1] |= above; sm.emask[w1] = equal; }
+            __syncthreads();
+        } else if (rem > 0) {                                      // tokens in LDS, keys in registers
+            if (w0 == 65536 / 64) sm.low = slot;
+#pragma unroll
+            for (int i = 0; i < kSplitWordsPerThread; ++i)
+                for (unsigned long long x = e[i]; x; x &= x - 1) sm.list[slot++] = (uint16_t)((w0 + i) * 64 + __ffsll(x) - 1);
+            __syncthreads();
+            const uint32_t low = sm.low;
+            auto token = [&](uint32_t p) { return (uint32_t)sm.list[p] | (p >= low ? 65536u : 0u); };
+            constexpr int kGroup = 8;                              // keys of a thread fetched together
+            uint32_t key[kSplitList / kSplitThreads];
+#pragma unroll
+            for (int u0 = 0; u0 < kSplitList / kSplitThreads; u0 += kGroup) {
+                if ((uint32_t)(u0 * kSplitThreads) < total_e) {
+                    float x[kGroup];
+#pragma unroll
+                    for (int u = 0; u < kGroup; ++u) {
+                        const uint32_t p = (uint32_t)((u0 + u) * kSplitThreads + tid);
+                        x[u] = sc[token(p < total_e ? p : total_e - 1)];
+                    }
+#pragma unroll
+                    for (int u = 0; u < kGroup; ++u) {
+                        const uint32_t p = (uint32_t)((u0 + u) * kSplitThreads + tid);
+                        key[u0 + u] = p < total_e ? key31(scale(x[u])) - range.x : 0xFFFFFFFFu;   // (nobody's digits)
+                    }
+                }
+            }
+            // f(number in the list, key - lo)
+            auto for_each_listed = [&](auto f) {
+#pragma unroll
+                for (int u = 0; u < kSplitList / kSplitThreads; ++u) {
+                    int count = __builtin_amdgcn_readfirstlane((int)total_e);
+                    asm volatile("" : "+s"(count));                // or 32 comparisons are kept in scalar registers from the start
+                    if (u * kSplitThreads < count) f((uint32_t)(u * kSplitThreads + tid), key[u]);
+                }
+            };
+            while (rem > 0) {
+                const int w = rem < 8 ? rem : 8, shift = rem - w;
+                for_each_listed([&](uint32_t, uint32_t k1) { count_digit(sm.hist, (k1 >> shift) & ((1u << w) - 1u), (k1 >> rem) == fixed); });
+                __syncthreads();
+                pick_digit(sm.hist, &sm.digit, &sm.want, &sm.count);
+                fixed = (fixed << w) | sm.digit;
+                rem = shift;
+            }
+            for_each_listed([&](uint32_t p, uint32_t k1) {
+                if (p < total_e && k1 != fixed) {
+                    const uint32_t j = token(p);
+                    if (k1 > fixed) atomicOr(&sm.gmask[j >> 6], 1ull << (j & 63u));
+                    atomicAnd(&sm.emask[j >> 6], ~(1ull << (j & 63u)));
+                }
             });
+            __syncthreads();
         }
-        __syncthreads();
+        need = sm.want;                                            // keys equal to the threshold still to be kept
 #pragma unroll
         for (int i = 0; i < kSplitWordsPerThread; ++i) { g[i] = sm.gmask[w0 + i]; e[i] = sm.emask[w0 + i]; }
     }

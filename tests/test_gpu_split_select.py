@@ -52,6 +52,36 @@ def test_given_scores(n):
         _check(scores, idx, off, budgets, s)
 
 
+PAIRS, LIST = gu.limit("split_select.hip", "kSplitPairs"), gu.limit("split_select.hip", "kSplitList")
+
+
+# keys that share the cut's bin [1, 1 + 1/16): as many as are resolved in LDS, in registers, and by reading the scores
+# again, and one more; tokens on both sides of 65536 or not
+@pytest.mark.parametrize("n", [50000, 131072])
+@pytest.mark.parametrize("inside", [1, 511, PAIRS, PAIRS + 1, 8192, LIST, LIST + 1, 40000])
+def test_range_of_every_size(n, inside):
+    rng = np.random.Generator(np.random.PCG64([n, inside]))
+    above, heads = 300, 8
+    scores = rng.uniform(0.0, 0.5, (heads, n)).astype(np.float32)
+    budgets = np.zeros((heads,), np.int32)
+    for h in range(heads):
+        place = rng.permutation(np.arange(4, n))
+        scores[h, place[:above]] = rng.uniform(1.5, 1.9, above)
+        fine = (1.0 + rng.integers(0, 2 ** 19, inside) * 2.0 ** -23).astype(np.float32)
+        if h in (2, 3):                                       # half of them from eight values
+            fine = np.where(rng.random(inside) < 0.5, 1.0 + rng.integers(0, 8, inside) / 128.0, fine)
+        if h in (4, 5):                                       # three neighbouring floats, at the end of the bin
+            fine = 1.0625 - (1 + rng.integers(0, 3, inside)) * 2.0 ** -23
+        if h == 6:                                            # one value
+            fine = 1.03125
+        scores[h, place[above:above + inside]] = fine
+        if h == 7:                                            # all in one stretch
+            scores[h, 4:] = np.concatenate([scores[h, place[above:above + inside]], np.delete(scores[h], place[above:above + inside])[4:]])
+        budgets[h] = 4 + above + (1, inside, (inside + 1) // 2, inside // 3 + 1, (inside + 1) // 2, inside // 5 + 1, inside // 2 + 1, inside // 7 + 1)[h]
+    idx, off = _select(scores, budgets, 4)
+    _check(scores, idx, off, budgets, 4)
+
+
 def _one_call(K, V, dtype, r, budgets, s, with_scores=True, sketch=None):
     import torch
     L, H, n, d = K.shape
