@@ -302,14 +302,14 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
     return (int)lo;
 }
 
-// As many workgroups as the chip holds at once (16 waves per compute unit), a step each at least.  Two
-// steps stay in one workgroup, which can add a head's running sum by itself: one launch instead of two.
-static int few_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
+// As many workgroups as the chip holds at once (16 waves per compute unit), a step each at least.  Where a
+// running sum is wanted two steps stay in one workgroup, which adds it by itself: one launch instead of two.
+static int few_blocks_per_head(const curdkv_ctx* ctx, int64_t n, bool running) {
     const int waves = (ctx->cfg.score_source == CURDKV_SCORE_KV ? 2 : 1) * 2 * ctx->col_blocks;
     const int64_t slots = (int64_t)ctx->num_cu * (16 / waves);
     int64_t b = (slots + ctx->heads - 1) / ctx->heads;
     const int64_t steps = (n + 15) / 16;
-    if (steps <= 2) return 1;
+    if (running && steps <= 2) return 1;
     b = b < steps ? b : steps;
     return (int)(b < kMaxBlocksPerHead ? b : kMaxBlocksPerHead);
 }
@@ -326,13 +326,22 @@ static int few_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
 // tokens 4.6 -> 4.8 (each row goes to sixteen waves).
 constexpr int64_t kFewF32Tokens = 16384, kFewF32Steps = 6, kFewBf16Tokens = 8192, kFewBf16Wide = 2048, kFewBf16Steps = 4;
 
-static bool few_tokens(const curdkv_ctx* ctx, int64_t n) {
+// running: a running sum is wanted (curdkv_scores_append).
+static bool few_tokens(const curdkv_ctx* ctx, int64_t n, bool running) {
     if (ctx->cfg.no_projection) return false;
     const bool f32 = ctx->cfg.dtype == CURDKV_DTYPE_F32;
     const bool wide = ctx->col_blocks > 2 && ctx->heads > ctx->num_cu / 4;
     if (n * ctx->heads > (f32 ? kFewF32Tokens : wide ? kFewBf16Wide : kFewBf16Tokens)) return false;
     const int64_t steps = (n + 15) / 16;
-    return steps <= (f32 ? kFewF32Steps : kFewBf16Steps) * few_blocks_per_head(ctx, n);
+    // bf16 appends that the other kernel gives one workgroup per head (up to 256 tokens) are one launch there.  Two
+    // steps in one workgroup are slower here beyond 32 columns (8 heads of 32 tokens, r = 20 / 64 / 128, replayed graph:
+    // 3.6 -> 3.4 / 3.9 -> 4.3 / 4.7 -> 6.3; of 16 tokens 3.5 -> 3.0 / 3.8 -> 3.5 / 4.5 -> 4.6; of 8 4.4 -> 3.9 at r = 128), and
+    // several workgroups take a second launch for the sum: 8 heads of 64 tokens 4.2 -> 4.5 / 4.7 -> 5.0 / 6.0 -> 6.0
+    // replayed, 5.2 -> 8.2 / 5.2 -> 8.4 / 6.1 -> 7.8 launched call by call, 8 heads of 256 6.6 -> 4.6 / 7.3 -> 5.1 / 8.9 -> 6.2 and
+    // 6.7 -> 8.2 / 7.4 -> 8.5 / 9.0 -> 7.9: with 128 columns from 129 tokens on the split wins either way.
+    if (running && !f32 && n > 32 / ctx->col_blocks && !(ctx->col_blocks > 2 && n > 128) && pick_blocks_per_head(ctx, n) == 1)
+        return false;
+    return steps <= (f32 ? kFewF32Steps : kFewBf16Steps) * few_blocks_per_head(ctx, n, running);
 }
 
 hipError_t configure_kernels(curdkv_ctx* ctx) {
@@ -345,8 +354,8 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
                          int64_t out_stride, int64_t out_offset, double* sums, bool restart,
                          bool* summed, bool with_hist, int32_t n_sink) {
     if (out_stride <= 0) out_stride = n;
-    const bool few = few_tokens(ctx, n) && !with_hist;
-    const int bph = few ? few_blocks_per_head(ctx, n) : pick_blocks_per_head(ctx, n);
+    const bool few = few_tokens(ctx, n, sums != nullptr) && !with_hist;
+    const int bph = few ? few_blocks_per_head(ctx, n, sums != nullptr) : pick_blocks_per_head(ctx, n);
     if (blocks_per_head) *blocks_per_head = bph;
     if (bph != 1) sums = nullptr;                 // several blocks per head: the caller adds the partials
     if (summed) *summed = sums != nullptr;

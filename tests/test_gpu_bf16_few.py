@@ -42,3 +42,45 @@ def test_scores_and_sums(n, heads, r, source):
         assert np.linalg.norm(got[i] - want) <= NORM_TOL * np.linalg.norm(want), (n, heads, r, source, i)
         new = raw[i, 5:n + 5].astype(np.float64)
         assert np.linalg.norm(new / new.sum() - want) <= NORM_TOL * np.linalg.norm(want)
+
+
+def _launches(call):
+    """Kernels that `call` launches, as nodes of a captured graph."""
+    import ctypes
+    import torch
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    count = ctypes.c_size_t()
+    assert ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    return count.value
+
+
+# both sides of the tokens from which the kernel of longer calls takes appends (8, 16 or 32 by width), of the step from one
+# workgroup per head to several in it (256), and of the line where 128 columns are split all the same (128)
+@pytest.mark.parametrize("r", [20, 33, 64, 128])
+@pytest.mark.parametrize("n", [1, 8, 9, 16, 17, 32, 33, 64, 128, 129, 256, 257])
+@pytest.mark.parametrize("heads", [1, 8])
+def test_short_appends(n, heads, r):
+    """Raw scores and running sums, and a single launch wherever one workgroup per head can add its sum by itself."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n * 512 + r)
+    K = torch.randn((heads, n, 128), generator=g, device="cuda").to(torch.bfloat16)
+    V = torch.randn((heads, n, 128), generator=g, device="cuda").to(torch.bfloat16)
+    with B.Context(heads, 1, 4, 128, r, "bf16", n + 5, SEED) as ctx:
+        raw = torch.full((heads, n + 5), -1.0, device="cuda")
+        sums = torch.full((heads,), 3.0, dtype=torch.float64, device="cuda")
+        ctx.scores_append(K, V, n, 5, n + 5, raw, sums)
+        torch.cuda.synchronize()
+        scores, total = raw.cpu().numpy(), sums.cpu().numpy()
+        launches = _launches(lambda: ctx.scores_append(K, V, n, 5, n + 5, raw, sums))
+    assert launches == (1 if n <= (256 if r <= 64 else 128) else 2)
+    assert np.all(scores[:, :5] == -1.0)
+    assert np.allclose(total - 3.0, scores[:, 5:].astype(np.float64).sum(1), rtol=1e-6)
+    for i in (0, heads - 1):
+        G = orc.sketch(SEED, i, 0, 1, 128, r, "bf16")
+        want = orc.scores(K[i].double().cpu().numpy(), V[i].double().cpu().numpy(), G)
+        new = scores[i, 5:].astype(np.float64)
+        assert np.linalg.norm(new / new.sum() - want) <= NORM_TOL * np.linalg.norm(want)
