@@ -422,7 +422,21 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
 }
 
 // Decode-phase bookkeeping: running sum of a head's un-normalised scores, and the
-// normalisation by it.  A wave per head adds the partial sums in a fixed order, in double.
+// normalisation by it.  Partial sums are added in a fixed order, in double: up to four one after the other, a thread
+// per head, so that one or two workgroups do it all; more by a wave per head.  A chain of loads against waves spread
+// over the chip, us per curdkv_scores_append: 64 heads of 512 tokens (2 sums each) 8.4 against 8.7, of 2048 (4 sums)
+// 15.8 and 16.2; 8 heads of 2048 (8 sums) 8.45 and 8.2, of 8192 (32 sums) 10.3 and 9.1; 1 head of 16384 (64 sums) 11.5 and 8.0.
+constexpr int kFewPartials = 4;
+
+__global__ __launch_bounds__(256) void accumulate_few_kernel(const float* __restrict__ partial, int blocks_per_head,
+                                                             double* __restrict__ sums, int heads, int reset) {
+    const int head = blockIdx.x * 256 + threadIdx.x;
+    if (head >= heads) return;
+    double total = 0.0;
+    for (int i = 0; i < blocks_per_head; ++i) total += (double)partial[(size_t)head * kMaxBlocksPerHead + i];
+    sums[head] = (reset ? 0.0 : sums[head]) + total;
+}
+
 __global__ __launch_bounds__(256) void accumulate_sums_kernel(const float* __restrict__ partial, int blocks_per_head,
                                                               double* __restrict__ sums, int heads, int reset) {
     const int head = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -463,8 +477,12 @@ __global__ __launch_bounds__(256) void normalise_sums_kernel(const float* __rest
 
 hipError_t launch_accumulate(const curdkv_ctx* ctx, int blocks_per_head, double* sums, bool reset,
                              hipStream_t stream) {
-    accumulate_sums_kernel<<<dim3((unsigned)((ctx->heads + 3) / 4)), 256, 0, stream>>>(
-        ctx->d_partial, blocks_per_head, sums, ctx->heads, reset ? 1 : 0);
+    if (blocks_per_head <= kFewPartials)
+        accumulate_few_kernel<<<dim3((unsigned)((ctx->heads + 255) / 256)), 256, 0, stream>>>(
+            ctx->d_partial, blocks_per_head, sums, ctx->heads, reset ? 1 : 0);
+    else
+        accumulate_sums_kernel<<<dim3((unsigned)((ctx->heads + 3) / 4)), 256, 0, stream>>>(
+            ctx->d_partial, blocks_per_head, sums, ctx->heads, reset ? 1 : 0);
     return hipGetLastError();
 }
 
