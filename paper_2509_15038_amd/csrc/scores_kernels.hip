@@ -422,11 +422,11 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
 }
 
 // Decode-phase bookkeeping: running sum of a head's un-normalised scores, and the
-// normalisation by it.  Partial sums are added in a fixed order, in double: up to four one after the other, a thread
+// normalisation by it.  Partial sums are added in a fixed order, in double: up to seven one after the other, a thread
 // per head, so that one or two workgroups do it all; more by a wave per head.  A chain of loads against waves spread
 // over the chip, us per curdkv_scores_append: 64 heads of 512 tokens (2 sums each) 8.4 against 8.7, of 2048 (4 sums)
-// 15.8 and 16.2; 8 heads of 2048 (8 sums) 8.45 and 8.2, of 8192 (32 sums) 10.3 and 9.1; 1 head of 16384 (64 sums) 11.5 and 8.0.
-constexpr int kFewPartials = 4;
+// 15.8 and 16.2; 8 heads of 1159 (5 sums) 8.3 and 8.7, of 2048 (8 sums) 8.45 and 8.2, of 8192 (32 sums) 10.3 and 9.1; 1 head of 16384 (64 sums) 11.5 and 8.0.
+constexpr int kFewPartials = 7;
 
 __global__ __launch_bounds__(256) void accumulate_few_kernel(const float* __restrict__ partial, int blocks_per_head,
                                                              double* __restrict__ sums, int heads, int reset) {
