@@ -302,15 +302,17 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
     return (int)lo;
 }
 
-// As many workgroups as the chip holds at once (16 waves per compute unit), a step each at least.  Where a
-// running sum is wanted two steps stay in one workgroup, which adds it by itself: one launch instead of two.
+// As many workgroups as the chip holds at once (16 waves per compute unit), a step each at least: one more per head
+// and some wait for a place (12 heads of 576 tokens, bf16, r = 128, 22 workgroups each 11.3 us per curdkv_scores_append, 21
+// each 7.8).  Two steps stay in one workgroup in bf16, and in fp32 where a running sum is wanted, which it then adds by
+// itself: one launch instead of two.
 static int few_blocks_per_head(const curdkv_ctx* ctx, int64_t n, bool running) {
     const int waves = (ctx->cfg.score_source == CURDKV_SCORE_KV ? 2 : 1) * 2 * ctx->col_blocks;
     const int64_t slots = (int64_t)ctx->num_cu * (16 / waves);
-    int64_t b = (slots + ctx->heads - 1) / ctx->heads;
     const int64_t steps = (n + 15) / 16;
-    if (running && steps <= 2) return 1;
-    b = b < steps ? b : steps;
+    if (steps <= 2 && (running || ctx->cfg.dtype == CURDKV_DTYPE_BF16)) return 1;
+    int64_t b = slots / ctx->heads;
+    b = b < 1 ? 1 : b < steps ? b : steps;
     return (int)(b < kMaxBlocksPerHead ? b : kMaxBlocksPerHead);
 }
 
@@ -322,25 +324,27 @@ static int few_blocks_per_head(const curdkv_ctx* ctx, int64_t n, bool running) {
 // 20.7 -> 22.1 / 25.3 -> 36.2 / 36.2 -> 64.6.
 // bf16: 256 heads of one token 4.4 -> 2.8 / 4.7 -> 3.1 / 5.5 -> 3.6; 8192 tokens in 8 heads 7.9 -> 5.1 / 8.6 -> 6.2 / 10.4 -> 8.0;
 // 16384 in 8 heads 8.2 -> 5.9 / 9.0 -> 7.9 / 10.6 -> 11.4 and in 64 heads 6.6 -> 6.4 / 7.3 -> 8.1 / 9.0 -> 11.5; one head
-// of 4096 tokens 8.6 -> 5.5 / 9.3 -> 7.4 / 11.1 -> 11.1.  128 columns in many heads end earlier: 256 heads of 16
-// tokens 4.6 -> 4.8 (each row goes to sixteen waves).
-constexpr int64_t kFewF32Tokens = 16384, kFewF32Steps = 6, kFewBf16Tokens = 8192, kFewBf16Wide = 2048, kFewBf16Steps = 4;
+// of 4096 tokens 8.6 -> 5.5 / 9.3 -> 7.4 / 11.1 -> 11.1.  Wide sketches in many heads end earlier, as each row goes to more
+// waves: curdkv_scores, r = 64, 100 heads of 64 tokens 6.3 -> 6.7, 128 columns, 256 heads of 16 4.6 -> 4.8.
+constexpr int64_t kFewF32Tokens = 16384, kFewF32Steps = 6, kFewBf16Tokens = 8192, kFewBf16Steps = 4;
 
 // running: a running sum is wanted (curdkv_scores_append).
 static bool few_tokens(const curdkv_ctx* ctx, int64_t n, bool running) {
     if (ctx->cfg.no_projection) return false;
     const bool f32 = ctx->cfg.dtype == CURDKV_DTYPE_F32;
-    const bool wide = ctx->col_blocks > 2 && ctx->heads > ctx->num_cu / 4;
-    if (n * ctx->heads > (f32 ? kFewF32Tokens : wide ? kFewBf16Wide : kFewBf16Tokens)) return false;
-    const int64_t steps = (n + 15) / 16;
-    // bf16 appends that the other kernel gives one workgroup per head (up to 256 tokens) are one launch there.  Two
-    // steps in one workgroup are slower here beyond 32 columns (8 heads of 32 tokens, r = 20 / 64 / 128, replayed graph:
-    // 3.6 -> 3.4 / 3.9 -> 4.3 / 4.7 -> 6.3; of 16 tokens 3.5 -> 3.0 / 3.8 -> 3.5 / 4.5 -> 4.6; of 8 4.4 -> 3.9 at r = 128), and
-    // several workgroups take a second launch for the sum: 8 heads of 64 tokens 4.2 -> 4.5 / 4.7 -> 5.0 / 6.0 -> 6.0
-    // replayed, 5.2 -> 8.2 / 5.2 -> 8.4 / 6.1 -> 7.8 launched call by call, 8 heads of 256 6.6 -> 4.6 / 7.3 -> 5.1 / 8.9 -> 6.2 and
+    const int64_t most = f32 ? kFewF32Tokens : kFewBf16Tokens / (ctx->heads > ctx->num_cu / 4 ? ctx->col_blocks : 1);
+    if (n * ctx->heads > most) return false;
+    // bf16, two steps of a wide sketch: the other kernel's waves hold all of it and take 32 tokens at once.  8 heads, r = 20 /
+    // 64 / 128, replayed graph: 32 tokens 3.6 -> 3.4 / 3.9 -> 4.3 / 4.7 -> 6.3, 16 tokens 3.5 -> 3.0 / 3.8 -> 3.5 / 4.5 -> 4.6, 8
+    // tokens 4.4 -> 3.9 at r = 128; curdkv_scores of 224 heads of 19 tokens, r = 64, in two workgroups 6.2 -> 6.8.
+    const int64_t one_step = 32 / ctx->col_blocks;
+    if (!f32 && n > one_step && n <= 32) return false;
+    // bf16 appends that the other kernel gives one workgroup per head (up to 256 tokens) are one launch there, several
+    // workgroups take a second one for the sum: 8 heads of 64 tokens 4.2 -> 4.5 / 4.7 -> 5.0 / 6.0 -> 6.0 replayed, 5.2 ->
+    // 8.2 / 5.2 -> 8.4 / 6.1 -> 7.8 launched call by call, 8 heads of 256 6.6 -> 4.6 / 7.3 -> 5.1 / 8.9 -> 6.2 and
     // 6.7 -> 8.2 / 7.4 -> 8.5 / 9.0 -> 7.9: with 128 columns from 129 tokens on the split wins either way.
-    if (running && !f32 && n > 32 / ctx->col_blocks && !(ctx->col_blocks > 2 && n > 128) && pick_blocks_per_head(ctx, n) == 1)
-        return false;
+    if (!f32 && running && n > 32 && !(ctx->col_blocks > 2 && n > 128) && pick_blocks_per_head(ctx, n) == 1) return false;
+    const int64_t steps = (n + 15) / 16;
     return steps <= (f32 ? kFewF32Steps : kFewBf16Steps) * few_blocks_per_head(ctx, n, running);
 }
 

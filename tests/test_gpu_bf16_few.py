@@ -84,3 +84,28 @@ def test_short_appends(n, heads, r):
         want = orc.scores(K[i].double().cpu().numpy(), V[i].double().cpu().numpy(), G)
         new = scores[i, 5:].astype(np.float64)
         assert np.linalg.norm(new / new.sum() - want) <= NORM_TOL * np.linalg.norm(want)
+
+
+# numbers of heads that do not divide the chip's places; two steps; 64 columns in many heads on both sides of 4096 tokens
+@pytest.mark.parametrize("heads,n", [(12, 576), (17, 300), (4, 25), (224, 19), (100, 40), (100, 41), (129, 31)])
+@pytest.mark.parametrize("r", [20, 64, 128])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_numbers_of_heads(heads, n, r, dtype):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n * 512 + r)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    K = torch.randn((heads, n, 128), generator=g, device="cuda").to(tdt)
+    V = torch.randn((heads, n, 128), generator=g, device="cuda").to(tdt)
+    with B.Context(heads, 1, 4, 128, r, dtype, n, SEED) as ctx:
+        got, raw = torch.full((heads, n), float("nan"), device="cuda"), torch.full((heads, n), float("nan"), device="cuda")
+        sums = torch.zeros((heads,), dtype=torch.float64, device="cuda")
+        ctx.scores(K, V, n, got)
+        ctx.scores_append(K, V, n, 0, n, raw, sums)
+        got, raw, sums = got.cpu().numpy(), raw.cpu().numpy().astype(np.float64), sums.cpu().numpy()
+    assert np.allclose(sums, raw.sum(1), rtol=1e-6)
+    for i in (0, heads // 2, heads - 1):
+        G = orc.sketch(SEED, i, 0, 1, 128, r, dtype)
+        want = orc.scores(K[i].double().cpu().numpy(), V[i].double().cpu().numpy(), G)
+        for x in (got[i], raw[i] / raw[i].sum()):
+            assert np.linalg.norm(x - want) <= NORM_TOL * np.linalg.norm(want)
