@@ -17,7 +17,7 @@ namespace curdkv {
 // Sum the wave totals of a block (four or eight) in a fixed order and store it.  A head
 // scored by a single block (few new tokens during generation) can fold the total into the
 // head's running sum right here: sum = (restart ? 0 : sum) + total, in double, which is
-// what accumulate_sums_kernel computes from one partial.
+// what accumulate_few_kernel computes from one partial.
 template <int WAVES>
 __device__ __forceinline__ void block_partial_store(float wave_total, float* dst, double* running, int restart) {
     __shared__ float wsum[WAVES];
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(((SRC == kSrcKV ? 2 : 1) * CB * 64)) void scores_fe
 
 // ---------------------------------------------------------------------------
 // Normalisation step of Algorithm 1: divide by the sum over all n rows of the head.  The per-block
-// partial sums are added in index order in double, so the result does not
+// partial sums are added in a fixed order in double, so the result does not
 // depend on scheduling.  A zero sum gives 1/n everywhere.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void normalise_kernel(float* __restrict__ scores,
@@ -342,8 +342,9 @@ static bool few_tokens(const curdkv_ctx* ctx, int64_t n, bool running) {
     // bf16 appends that the other kernel gives one workgroup per head (up to 256 tokens) are one launch there, several
     // workgroups take a second one for the sum: 8 heads of 64 tokens 4.2 -> 4.5 / 4.7 -> 5.0 / 6.0 -> 6.0 replayed, 5.2 ->
     // 8.2 / 5.2 -> 8.4 / 6.1 -> 7.8 launched call by call, 8 heads of 256 6.6 -> 4.6 / 7.3 -> 5.1 / 8.9 -> 6.2 and
-    // 6.7 -> 8.2 / 7.4 -> 8.5 / 9.0 -> 7.9: with 128 columns from 129 tokens on the split wins either way.
-    if (!f32 && running && n > 32 && !(ctx->col_blocks > 2 && n > 128) && pick_blocks_per_head(ctx, n) == 1) return false;
+    // 6.7 -> 8.2 / 7.4 -> 8.5 / 9.0 -> 7.9: with 128 columns beyond 192 tokens the split wins either way (48 heads of 130
+    // tokens 7.3 -> 7.9 and 7.7 -> 8.1).
+    if (!f32 && running && n > 32 && !(ctx->col_blocks > 2 && n > 192) && pick_blocks_per_head(ctx, n) == 1) return false;
     const int64_t steps = (n + 15) / 16;
     return steps <= (f32 ? kFewF32Steps : kFewBf16Steps) * few_blocks_per_head(ctx, n, running);
 }

@@ -58,9 +58,9 @@ def _launches(call):
 
 
 # both sides of the tokens from which the kernel of longer calls takes appends (8, 16 or 32 by width), of the step from one
-# workgroup per head to several in it (256), and of the line where 128 columns are split all the same (128)
+# workgroup per head to several in it (256), and of the line where 128 columns are split all the same (192)
 @pytest.mark.parametrize("r", [20, 33, 64, 128])
-@pytest.mark.parametrize("n", [1, 8, 9, 16, 17, 32, 33, 64, 128, 129, 256, 257])
+@pytest.mark.parametrize("n", [1, 8, 9, 16, 17, 32, 33, 64, 128, 192, 193, 256, 257])
 @pytest.mark.parametrize("heads", [1, 8])
 def test_short_appends(n, heads, r):
     """Raw scores and running sums, and a single launch wherever one workgroup per head can add its sum by itself."""
@@ -76,7 +76,7 @@ def test_short_appends(n, heads, r):
         torch.cuda.synchronize()
         scores, total = raw.cpu().numpy(), sums.cpu().numpy()
         launches = _launches(lambda: ctx.scores_append(K, V, n, 5, n + 5, raw, sums))
-    assert launches == (1 if n <= (256 if r <= 64 else 128) else 2)
+    assert launches == (1 if n <= (256 if r <= 64 else 192) else 2)
     assert np.all(scores[:, :5] == -1.0)
     assert np.allclose(total - 3.0, scores[:, 5:].astype(np.float64).sum(1), rtol=1e-6)
     for i in (0, heads - 1):
