@@ -18,8 +18,9 @@
  *     read before the call returns.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).  The
  *     compute calls only enqueue work on it and do not synchronise.
- *   - The context owns the sketches, the per-block partial sums and the device
- *     copy of the offsets, all on the device that was current at curdkv_create;
+ *   - The context owns the sketches, the per-block partial sums, the device
+ *     copy of the offsets and the workspaces of the selection and of the budget
+ *     allocation, all on the device that was current at curdkv_create;
  *     that device must be current for every later call (else INVALID_ARG).
  *     Calls on one context must not overlap in time on different streams.
  *   - Capturing a compute call in a HIP graph: run the same call (same offsets,
@@ -86,7 +87,7 @@ typedef struct curdkv_config {
 
 /* Create a context on the current HIP device: generates the sketch G of every
  * (layer, group) on the host, uploads it in the kernels' operand layout and
- * allocates the reduction workspace.  Synchronous.  *out is set only on success. */
+ * allocates the workspaces.  Synchronous.  *out is set only on success. */
 int curdkv_create(curdkv_ctx** out, const curdkv_config* cfg);
 
 /* Free everything the context owns.  Synchronises the device first.  NULL is accepted. */

@@ -121,7 +121,7 @@ size_t split_workspace_bytes(const curdkv_ctx* ctx);
 int split_hists(const curdkv_ctx* ctx);                // histograms per head there is room for
 uint32_t* split_hist(const curdkv_ctx* ctx);           // [heads][split_hists][2048], two counts to a word
 uint32_t* split_coarse(const curdkv_ctx* ctx);         // [heads][split_hists][256]
-constexpr int kSplitMaxHeads = 128;                    // (layer, group) pairs the split is used for (its workspace is about 0.3 MB per pair)
+constexpr int kSplitMaxHeads = 128;                    // (layer, group) pairs the split is used for (its workspace takes 9 KB per histogram, 64 per pair up to 32 pairs and 32 beyond, and 32 KB of bitmaps at most: 0.62 or 0.33 MB a pair)
 hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
                                const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
                                int scale_blocks, bool write_scaled, SelectGather* gather);

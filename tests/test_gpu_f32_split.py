@@ -1,6 +1,7 @@
 """fp32 caches with more than 32 sketch columns: every float goes through the bf16 matrix units as
-three bf16 numbers.  Scores against the float64 oracle at the edges of the 16-token steps, the
-64-token groups and the waves' ranges, and rows that are not finite."""
+three bf16 numbers.  Scores against the float64 oracle, and rows that are not finite.  (Calls of few tokens in all,
+the smaller sizes here, take a kernel of plain fp32 products; the edges of this one's steps, groups and
+ranges beyond that limit are in test_gpu_dispatch_sides.py.)"""
 import numpy as np
 import pytest
 
@@ -11,8 +12,9 @@ from paper_2509_15038_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 # 2-norm error of a head's scores: a projected coordinate is 128 exact products, summed with one
-# rounding per 32 of them over six passes (24 roundings), the parts left out weigh 2^-26; squared and
-# summed over r, multiplied and normalised (about 30 roundings of 2^-24 relative, at random)
+# rounding per 32 of them over six passes (24 roundings), the parts left out weigh 2^-24 of a product at most
+# and 2^-27 at root mean square; squared and summed over r, multiplied and normalised (about 30 roundings
+# of 2^-24 relative, at random)
 NORM_TOL = 1e-6
 
 
