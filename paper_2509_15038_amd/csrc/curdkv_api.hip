@@ -104,6 +104,7 @@ void release(curdkv_ctx* ctx) {
     if (ctx->d_G) (void)hipFree(ctx->d_G);
     if (ctx->d_partial) (void)hipFree(ctx->d_partial);
     if (ctx->d_split_ws) (void)hipFree(ctx->d_split_ws);
+    if (ctx->d_raw_ws) (void)hipFree(ctx->d_raw_ws);
     if (ctx->d_scores_ws) (void)hipFree(ctx->d_scores_ws);
     if (ctx->d_adaptive_ws) (void)hipFree(ctx->d_adaptive_ws);
     if (ctx->d_adaptive_blocks) (void)hipFree(ctx->d_adaptive_blocks);
@@ -204,6 +205,11 @@ int curdkv_create(curdkv_ctx** out, const curdkv_config* cfg) {
     }
     // workspace of the split selection, where a call can be long enough for it
     if (split_wanted(ctx) && hipMalloc(&ctx->d_split_ws, split_workspace_bytes(ctx)) != hipSuccess) {
+        (void)hipGetLastError();
+        release(ctx);
+        return CURDKV_ERR_OOM;
+    }
+    if (select_gather_wanted(ctx) && hipMalloc((void**)&ctx->d_raw_ws, select_gather_workspace_bytes(ctx)) != hipSuccess) {
         (void)hipGetLastError();
         release(ctx);
         return CURDKV_ERR_OOM;
@@ -345,7 +351,9 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
         return launch_fused(ctx, K, V, n, n_sink, ctx->plan.d_offsets, scores, indices, K_out, V_out, st) == hipSuccess
                    ? CURDKV_OK : CURDKV_ERR_HIP;
     const bool scores_wanted = scores != nullptr;
-    if (!scores) {
+    const bool with_hist = !fusable && split_applicable(ctx, n, true);
+    const bool together = !fusable && !with_hist && select_gather_applicable(ctx, n, total);
+    if (!scores && !together) {
         if (!ctx->d_scores_ws &&
             hipMalloc((void**)&ctx->d_scores_ws, (size_t)ctx->heads * (size_t)ctx->cfg.max_tokens * sizeof(float)) != hipSuccess) {
             (void)hipGetLastError();
@@ -364,9 +372,12 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     // the selection kernel normalises on the fly (and writes the normalised scores
     // back), which saves the separate pass over the scores
     int bph = 0;
-    if (launch_scores(ctx, K, V, n, scores, st, /*normalise=*/false, &bph, 0, 0, nullptr, false, nullptr,
-                      /*with_hist=*/split_applicable(ctx, n, true), n_sink) != hipSuccess) return CURDKV_ERR_HIP;
+    if (launch_scores(ctx, K, V, n, together ? ctx->d_raw_ws : scores, st, /*normalise=*/false, &bph, 0, 0, nullptr, false, nullptr,
+                      with_hist, n_sink) != hipSuccess) return CURDKV_ERR_HIP;
     SelectGather gather{K, V, K_out, V_out, total, false};
+    if (together)
+        return launch_select_gather(ctx, ctx->d_raw_ws, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st, bph, gather) == hipSuccess
+                   ? CURDKV_OK : CURDKV_ERR_HIP;
     if (launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st, bph, scores_wanted, nullptr, &gather) != hipSuccess)
         return CURDKV_ERR_HIP;
     if (total == 0 || gather.done) return CURDKV_OK;

@@ -60,6 +60,7 @@ struct curdkv_ctx {
     void* d_adaptive_ws = nullptr;     // histograms, key segments and per-layer state of the head-wise budget allocation
     curdkv::BlockInfo* d_adaptive_blocks = nullptr;  // gather block table built on the device (curdkv_compress_adaptive)
     void* d_split_ws = nullptr;        // histograms and bitmaps of the split selection (split_select.hip)
+    float* d_raw_ws = nullptr;         // products of few, short heads on their way to select_gather_kernel
     float* d_scores_ws = nullptr;      // [heads, max_tokens], allocated when curdkv_compress needs it
     int lds_limit = 0;                 // max dynamic LDS per workgroup, bytes
     int num_cu = 0;
@@ -112,6 +113,14 @@ hipError_t launch_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_
                          const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
                          int scale_blocks = 0, bool write_scaled = true,
                          const void* known_thresholds = nullptr, SelectGather* gather = nullptr);
+// Few, short heads, one call: selection and gather in one launch.  `raw`: the un-normalised products (ctx->d_raw_ws);
+// scores: where the normalised ones go, or nullptr.
+bool select_gather_wanted(const curdkv_ctx* ctx);      // the context needs the workspace
+size_t select_gather_workspace_bytes(const curdkv_ctx* ctx);
+bool select_gather_applicable(const curdkv_ctx* ctx, int64_t n, int64_t total);
+hipError_t launch_select_gather(const curdkv_ctx* ctx, const float* raw, float* scores, int64_t n, int32_t n_sink,
+                                const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
+                                int scale_blocks, const SelectGather& gather);
 // gather given: the selection may copy the kept rows itself; gather->done says whether it has.
 // split_select.hip: the same for long heads, several workgroups per head (workspace ctx->d_split_ws).
 // scale_blocks > 0: step 1's histograms, scale_blocks of them per head, have been made by launch_scores.

@@ -44,6 +44,14 @@ constexpr int kHistRep = 8;                       // general case: replicated bi
 constexpr int kBins12 = 4096;
 constexpr int kBinShift = 18;                     // key bits below the bin number (for bins other than the last)
 
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// What a selection that copies the kept rows itself is given: rows of 16-byte chunks.
+struct GatherArgs {
+    const u32x4 *K, *V;
+    u32x4 *K_out, *V_out;
+};
+
 __device__ __forceinline__ uint32_t order_key(float x) {
     x = x + 0.0f;                                 // -0 -> +0
     const uint32_t b = __float_as_uint(x);
@@ -376,16 +384,19 @@ __device__ __forceinline__ uint32_t threshold_on_list(const int32_t* pairs, uint
 // is complete.  0 <= k <= n, 0 <= s <= n, n <= THREADS*KPT < 65536, cap >= 0.
 // `given`: the threshold, where the caller knows it (then k - s must be the number of
 // candidates above it plus given.need); the search is skipped.
-template <int THREADS, int KPT>
+// SHARE: only positions first .. last-1 are listed, at stage[0 .. last-first), which must be room for them.
+template <int THREADS, int KPT, bool SHARE = false>
 __device__ __forceinline__ void select_core(uint32_t (&x)[KPT], int32_t n, int32_t s, int32_t k,
                                             SelectShared<THREADS, KPT>& sm, int32_t* stage,
                                             int32_t cap, int32_t* out_global,
-                                            Threshold given = Threshold{kNoThreshold, 0u}) {
+                                            Threshold given = Threshold{kNoThreshold, 0u}, int32_t first = 0, int32_t last = 0) {
     constexpr int kWaves = THREADS / 64;
     constexpr int kWords = KPT * kWaves;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto put = [&](uint32_t pos, int32_t j) {
-        if (pos < (uint32_t)cap) stage[pos] = j; else out_global[pos] = j;
+        if (SHARE) {
+            if (pos - (uint32_t)first < (uint32_t)(last - first)) stage[pos - (uint32_t)first] = j;
+        } else if (pos < (uint32_t)cap) stage[pos] = j; else out_global[pos] = j;
     };
 
     const int32_t sinks = s < k ? s : k;           // budget inside the sink block: tokens 0..k-1
@@ -506,6 +517,7 @@ __device__ __forceinline__ void select_core(uint32_t (&x)[KPT], int32_t n, int32
         const uint64_t word = sm.gmask[w];
         uint32_t mm = (uint32_t)(word >> (16 * part)) & 0xFFFFu;
         uint32_t pos = sm.wpos[w] + (uint32_t)__popcll(word & ((1ull << (16 * part)) - 1ull));
+        if (SHARE && (pos >= (uint32_t)last || pos + 16 <= (uint32_t)first)) continue;
         while (mm) {
             const int bit = __ffs(mm) - 1;
             mm &= mm - 1;

@@ -379,6 +379,80 @@ __global__ __launch_bounds__(kSelThreads) void select_reg_kernel(float* __restri
     for (int32_t p = tid; p < staged; p += kSelThreads) out[p] = stage[p];
 }
 
+// ---------------------------------------------------------------------------
+// Selection and gather of short heads where heads are few, one launch: workgroup (share, head).  Every workgroup of a
+// head selects for itself, on a chip that would otherwise be idle, and then copies its share of the rows; the indices
+// need no trip through memory, and no third kernel waits for the second one's end.  The products come from a buffer of
+// the library's own (ctx->d_raw_ws): normalised in place they would change under the other workgroups of the head.
+// ---------------------------------------------------------------------------
+template <int KPT, int ROW_U4>
+__global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float* __restrict__ raw, float* __restrict__ scores,
+                                                                int32_t n, int32_t n_sink, const int64_t* __restrict__ offsets,
+                                                                int32_t* __restrict__ indices, const float* __restrict__ partial,
+                                                                int scale_blocks, int share, GatherArgs ga) {
+    extern __shared__ int32_t stage[];             // [n]
+    __shared__ SelectShared<kSelThreads, KPT> sm;
+    const int head = blockIdx.y;
+    const int tid = threadIdx.x;
+    raw += (size_t)head * n;
+    const float mine = head_partial(partial + (size_t)head * kMaxBlocksPerHead, scale_blocks);
+    float v[KPT];
+#pragma unroll
+    for (int it = 0; it < KPT; ++it) {
+        const int32_t j = it * kSelThreads + tid;
+        v[it] = j < n ? raw[j] : 0.f;
+    }
+    const int64_t o0 = offsets[head];
+    const int32_t k = (int32_t)(offsets[head + 1] - o0);
+    const int32_t s = n_sink < n ? n_sink : n;
+    const int32_t r0 = (int32_t)blockIdx.x * share;
+    const int32_t r1 = r0 + share < k ? r0 + share : k;            // output rows r0 .. r1-1 are this workgroup's
+    if (r0 >= r1 && blockIdx.x > 0) return;
+    uint32_t x[KPT];
+    {
+        const HeadScale scale = head_scale(mine, scale_blocks, n);
+#pragma unroll
+        for (int it = 0; it < KPT; ++it) {
+            v[it] = scale(v[it]);
+            const int32_t j = it * kSelThreads + tid;
+            if (blockIdx.x == 0 && scores && j < n) scores[(size_t)head * n + j] = v[it];
+            x[it] = order_key(v[it]);
+        }
+    }
+    if (r0 >= r1) return;
+    select_core<kSelThreads, KPT, true>(x, n, s, k, sm, stage, n, nullptr, Threshold{kNoThreshold, 0u}, r0, r1);
+    const int32_t count = r1 - r0;
+    for (int32_t p = tid; p < count; p += kSelThreads) indices[o0 + r0 + p] = stage[p];
+    constexpr int kRows = kSelThreads / ROW_U4, kFlight = 4;           // rows per instruction, and of each tensor in flight per thread
+    const int c = tid % ROW_U4, rsub = tid / ROW_U4;
+    const u32x4* K = ga.K + (size_t)head * n * ROW_U4 + c;
+    const u32x4* V = ga.V + (size_t)head * n * ROW_U4 + c;
+    u32x4* K_out = ga.K_out + (size_t)(o0 + r0) * ROW_U4 + c;
+    u32x4* V_out = ga.V_out + (size_t)(o0 + r0) * ROW_U4 + c;
+#pragma unroll 1
+    for (int32_t p0 = rsub; p0 < count; p0 += kRows * kFlight) {
+        u32x4 a[kFlight], b[kFlight];
+#pragma unroll
+        for (int it = 0; it < kFlight; ++it) {
+            const int32_t p = p0 + it * kRows;
+            if (p < count) {
+                // every place holds a token by construction; never read outside the cache whatever the scores were
+                const uint32_t j = (uint32_t)stage[p] < (uint32_t)n ? (uint32_t)stage[p] : 0u;
+                a[it] = __builtin_nontemporal_load(K + (size_t)j * ROW_U4);
+                b[it] = __builtin_nontemporal_load(V + (size_t)j * ROW_U4);
+            }
+        }
+#pragma unroll
+        for (int it = 0; it < kFlight; ++it) {
+            const int32_t p = p0 + it * kRows;
+            if (p < count) {
+                __builtin_nontemporal_store(a[it], K_out + (size_t)p * ROW_U4);
+                __builtin_nontemporal_store(b[it], V_out + (size_t)p * ROW_U4);
+            }
+        }
+    }
+}
+
 template <int KPT>
 static hipError_t launch_reg(const curdkv_ctx* ctx, float* scores, int32_t n, int32_t n_sink,
                              const int64_t* d_offsets, int32_t* indices, hipStream_t stream,
@@ -396,10 +470,76 @@ static hipError_t launch_reg(const curdkv_ctx* ctx, float* scores, int32_t n, in
     return hipGetLastError();
 }
 
+// Which calls take it.  One call, separate kernels -> this, us: 1 head of 1024 tokens (fp32) 12.1 -> 10.2, of 4096 15.4 -> 13.4; 8 heads of
+// 2048 tokens, 30 % kept, 16.7 -> 14.6, of 8192, 20 %, 20.8 -> 18.1, of 24000, 60 %, 54.9 -> 49.8; 32 heads of 4096, 20 %, 27.4 -> 24.1,
+// of 16384, 10 %, 72.8 -> 70.5; 64 heads of 8192, 10 %, 74.6 -> 71.3; 128 heads of 2048, 10 %, 40.6 -> 38.5.  With more rows the
+// gather kernel's many small workgroups make up for its launch: half kept of 64 heads of 8192 tokens (262144 rows)
+// 106.4 -> 105.6, of 128 heads 185.9 -> 190.6; a tenth of 64 heads of 32768 (209664) 241.8 -> 242.5: hence 512 rows a unit.
+// Smaller workgroups for shorter heads give nothing (256 threads: 1024 tokens 9.9, 8192 tokens 21.7).
+constexpr int64_t kGatherMaxTokens = 32 * kSelThreads;             // what a workgroup's registers and LDS hold
+constexpr int64_t kGatherRowsPerUnit = 512;
+
+bool select_gather_wanted(const curdkv_ctx* ctx) { return ctx->heads * 2 <= ctx->num_cu; }
+
+size_t select_gather_workspace_bytes(const curdkv_ctx* ctx) {
+    const int64_t n = ctx->cfg.max_tokens < kGatherMaxTokens ? ctx->cfg.max_tokens : kGatherMaxTokens;
+    return (size_t)ctx->heads * (size_t)n * sizeof(float);
+}
+
+bool select_gather_applicable(const curdkv_ctx* ctx, int64_t n, int64_t total) {
+    return ctx->d_raw_ws && n <= kGatherMaxTokens && n * 4 <= (int64_t)ctx->lds_limit - kSelStaticReserve && total > 0 &&
+           total <= ctx->num_cu * kGatherRowsPerUnit;
+}
+
+template <int KPT, int ROW_U4>
+static hipError_t launch_gather(const curdkv_ctx* ctx, const float* raw, float* scores, int32_t n, int32_t n_sink,
+                                const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
+                                int scale_blocks, const SelectGather& g, int dyn) {
+    if (dyn > 0)
+        return hipFuncSetAttribute((const void*)select_gather_kernel<KPT, ROW_U4>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
+    const int64_t places = ctx->num_cu / ctx->heads;
+    int64_t share = (max_budget + places - 1) / places;
+    if (share < kSelThreads / ROW_U4) share = kSelThreads / ROW_U4;           // every lane has something to copy
+    const GatherArgs ga{(const u32x4*)g.K, (const u32x4*)g.V, (u32x4*)g.K_out, (u32x4*)g.V_out};
+    const dim3 grid((unsigned)((max_budget + share - 1) / share), (unsigned)ctx->heads);
+    select_gather_kernel<KPT, ROW_U4><<<grid, kSelThreads, (size_t)n * 4, stream>>>(
+        raw, scores, n, n_sink, d_offsets, indices, ctx->d_partial, scale_blocks, (int)share, ga);
+    return hipGetLastError();
+}
+
+template <int ROW_U4>
+static hipError_t gather_by_keys(const curdkv_ctx* ctx, const float* raw, float* scores, int32_t n, int32_t n_sink,
+                                 const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
+                                 int scale_blocks, const SelectGather& g, int dyn = 0) {
+    auto go = [&](auto kpt) {
+        return launch_gather<decltype(kpt)::value, ROW_U4>(ctx, raw, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g, dyn);
+    };
+    using std::integral_constant;
+    if (n <= 4 * kSelThreads) return go(integral_constant<int, 4>{});
+    if (n <= 8 * kSelThreads) return go(integral_constant<int, 8>{});
+    if (n <= 16 * kSelThreads) return go(integral_constant<int, 16>{});
+    return go(integral_constant<int, 32>{});
+}
+
+hipError_t launch_select_gather(const curdkv_ctx* ctx, const float* raw, float* scores, int64_t n, int32_t n_sink,
+                                const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
+                                int scale_blocks, const SelectGather& g) {
+    return ctx->cfg.dtype == CURDKV_DTYPE_BF16
+        ? gather_by_keys<16>(ctx, raw, scores, (int32_t)n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g)
+        : gather_by_keys<32>(ctx, raw, scores, (int32_t)n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g);
+}
+
 hipError_t configure_select(curdkv_ctx* ctx) {
     const int dyn = ctx->lds_limit - kSelStaticReserve;   // what the kernels' static LDS leaves
     if (dyn <= 48 * 1024) return hipSuccess;
     hipError_t e;
+    for (int kpt : {4, 8, 16, 32}) {
+        const SelectGather none{};
+        e = ctx->cfg.dtype == CURDKV_DTYPE_BF16
+            ? gather_by_keys<16>(ctx, nullptr, nullptr, kpt * kSelThreads, 0, nullptr, 0, nullptr, nullptr, 0, none, dyn)
+            : gather_by_keys<32>(ctx, nullptr, nullptr, kpt * kSelThreads, 0, nullptr, 0, nullptr, nullptr, 0, none, dyn);
+        if (e != hipSuccess) return e;
+    }
     e = hipFuncSetAttribute((const void*)select_reg_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void*)select_reg_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);

@@ -48,7 +48,6 @@ constexpr int kSplitMaxTokens = 131072;            // tokens per head the bitmap
 constexpr int kSplitMaxWords = kSplitMaxTokens / 64;
 constexpr int kSplitWordsPerThread = kSplitMaxWords / kSplitThreads;   // 4
 constexpr int kSplitShare = 1024;                  // output rows a workgroup of step 3 lists at most, where it also gathers them
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 struct SplitWorkspace {                            // device pointers into one allocation; nothing survives a call
     uint32_t* hist;                                // [heads][hists][2048], two 16-bit counts to a word
@@ -306,11 +305,6 @@ __device__ __forceinline__ void pick_digit(uint32_t* hist, uint32_t* digit, uint
     }
     __syncthreads();
 }
-
-struct GatherArgs {                                // rows of ROW_U4 16-byte chunks
-    const u32x4 *K, *V;
-    u32x4 *K_out, *V_out;
-};
 
 // ROW_U4 > 0: the workgroup also copies its share's rows of K and V (gather step of Algorithm 1);
 // share <= kSplitShare then.

@@ -1,0 +1,78 @@
+"""Few, short heads in one call: the selection whose workgroups copy their share of the rows.  Indices against the oracle's
+selection on the very scores the library stored, rows against torch's indexing, scores against the separate calls."""
+import numpy as np
+import pytest
+
+from oracle import curdkv_oracle as orc
+from paper_2509_15038_amd import binding as B
+from paper_2509_15038_amd import workloads as wl
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+ROWS = gu.limit("select_kernels.hip", "kGatherRowsPerUnit") * 256       # rows kept, all heads, up to which this route is taken
+LONGEST = gu.limit("split_select.hip", "kSplitMinTokens")               # up to 32 heads; beyond, what the registers hold
+
+
+def _cache(heads, n, dtype, seed):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    K, V = (torch.randn((heads, n, 128), generator=g, device="cuda") * torch.randn((heads, n, 1), generator=g, device="cuda").exp() for _ in range(2))
+    if heads > 1:
+        V[1] = V[1, :1]                                       # rows of one value: every candidate ties,
+        K[1] = K[1, :1]
+    if heads > 2:
+        V[2] = 0                                              # scores of 1/n,
+    if heads > 4:
+        K[4, n // 3:] = K[4, n // 3].clone()                  # and a stretch of equal scores
+        V[4, n // 3:] = V[4, n // 3].clone()
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    return (x.to(dt).view(1, heads, n, 128) for x in (K, V))
+
+
+def _check(heads, n, dtype, budgets, s, r=20, source="kv", projection=True, seed=3):
+    import torch
+    budgets = np.minimum(np.asarray(budgets), n).astype(np.int32)
+    K, V = _cache(heads, n, dtype, seed)
+    with B.Context(1, heads, 4, 128, r, dtype, n, 77, source, projection) as ctx:
+        sc, idx, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, s, dtype, one_call=True)
+        apart = torch.empty_like(sc)
+        ctx.scores(K, V, n, apart)
+        assert torch.allclose(sc, apart, rtol=1e-6, atol=0)            # (the sum is added in the same order or not: 2^-24 each)
+        scores, where = sc.cpu().numpy().astype(np.float64), idx.long()
+        got = where.cpu().numpy()
+        for h in range(heads):
+            a, b = int(off[h]), int(off[h + 1])
+            assert np.array_equal(got[a:b], orc.select(scores[h], int(budgets[h]), s)), (h, int(budgets[h]))
+            assert torch.equal(Ko[a:b], K[0, h, where[a:b]]) and torch.equal(Vo[a:b], V[0, h, where[a:b]]), h
+        # without the scores the rows are the same ones
+        i2, k2, v2 = (torch.zeros_like(x) for x in (idx, Ko, Vo))
+        ctx.compress(K, V, n, budgets, s, off, None, i2, k2, v2)
+        assert torch.equal(i2, idx) and torch.equal(k2, Ko) and torch.equal(v2, Vo)
+
+
+# (lengths at the edges of the bitmap's words, of a thread's 4, 8, 16 and 32 keys, and of the route)
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("heads,n", [(1, 1), (1, 63), (5, 65), (6, 1000), (3, 1024), (8, 4096), (8, 4097), (5, 8193), (7, 16385), (3, LONGEST), (128, 300), (100, 1023)])
+def test_budgets_of_every_kind(heads, n, dtype):
+    kinds = [n // 5, n // 3 + 1, 1, 0, n, n - 1, 5, 64, 65]   # some heads keep next to nothing, some everything
+    for s in (0, 4, 64):
+        _check(heads, n, dtype, [kinds[h % len(kinds)] for h in range(heads)], s)
+    _check(heads, n, dtype, [n // 4 + 1] * heads, 4, r=64, seed=9)
+
+
+@pytest.mark.parametrize("source,projection", [("k", True), ("v", True), ("kv", False)])
+def test_other_scores(source, projection):
+    _check(6, 1500, "bf16", [300] * 6, 4, source=source, projection=projection)
+
+
+# 33 heads: more than the split selection takes below 36864 tokens; budgets on both sides of the limit of rows
+@pytest.mark.parametrize("heads,n,total", [(33, 32768, 33 * 200), (64, 8192, ROWS), (64, 8192, ROWS + 64), (128, 2048, ROWS)])
+def test_both_sides_of_the_rule(heads, n, total):
+    _check(heads, n, "bf16", [total // heads] * heads, 4)
+
+
+def test_nothing_kept():
+    """All budgets zero: scores only."""
+    _check(4, 2000, "bf16", [0] * 4, 4)
