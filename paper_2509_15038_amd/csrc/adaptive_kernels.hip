@@ -10,23 +10,25 @@
 //     sum_h max(0, c_h(t) - g) = R,      R = H*(k - s') - H*g.
 // The counting functions c_h come from per-head histograms of the order-
 // preserving keys over the 4096 bins of the selection (bin12, select_device.h):
-//   * the histograms are made by the fused kernel while it has a head's keys in
-//     registers, or by ada_hist_kernel from scores in memory, one workgroup per
-//     (layer, head);
-//   * ada_resolve_kernel, again one workgroup per (layer, head): every workgroup
-//     scans the H histograms of its layer for the bin in which the sum above reaches
-//     R (the same small computation in each of them, which saves a launch and a
-//     trip through memory), copies its own head's keys inside that bin (a fraction
-//     of a percent of the head) to the workspace and counts itself done; the
-//     workgroup that finds itself the last of its layer resolves the remaining key
-//     bits on those few keys in LDS, allots keys equal to the threshold head by
-//     head, and writes the budgets, their prefix sums and the gather's block table
+//   * the histograms, and their sums per exponent, are made by the fused kernel while it has a
+//     head's keys in registers, or by ada_hist_kernel from scores in memory, several workgroups per
+//     (layer, head) where heads are few, each a histogram of its part;
+//   * ada_cut_kernel, workgroup (part, head): every workgroup finds the bin in which the sum above reaches R (the same
+//     small computation in each of them: first over the layer's sums per exponent, then over the 32 bins of one exponent),
+//     and copies its own part's keys inside that bin (a fraction of a percent of the head) to the workspace;
+//   * ada_allot_kernel, one workgroup per layer, resolves the remaining key bits on those few keys in LDS, allots keys equal to the
+//     threshold head by head, and writes the budgets, their prefix sums and the gather's block table
 //     for the layer (every layer keeps H*k rows, so a layer's first row is known).
-// Nobody waits for anybody: a workgroup that is not the last simply ends.  Bins
-// too full for the lists (a layer of equal scores, say) and scores of 2 and above
-// make the last workgroup refine the threshold by reading the layer's scores
+// Bins too full for the lists (a layer of equal scores, say) and scores of 2 and above
+// make the layer's workgroup refine the threshold by reading the layer's scores
 // itself, a few bits per pass: slow, and exact all the same.
 // No token order is needed anywhere.
+//
+// What bounds these kernels is latency: loads, barriers and LDS round trips in a chain.  Two launches instead of one whose last workgroup
+// of a layer went on: a device-scope fence, which such a hand-over needs, is a cache-wide operation here (eight L2s) and dearer
+// than the boundary between two kernels.  With all H histograms of 4096 bins scanned by every workgroup and that hand-over, 8 heads of
+// 1024 tokens took 19.6 us, 256 of 32768 29.2; the two kernels take 4.8 + 5.3 and 12.4 + 7.0.  Histograms in parts (8 heads of
+// 131072 tokens): 19.4 -> 5.7 us, normalisation (5.1) included.
 
 #include <mutex>
 
@@ -37,14 +39,19 @@ namespace curdkv {
 constexpr int kAdaThreads = 1024;
 constexpr int kAdaWaves = kAdaThreads / 64;
 constexpr int kAdaU = 8;                          // scores per thread in flight
-constexpr int kAdaOwn = 32;                       // resolve kernel: scores per thread loaded up front
-constexpr int kAdaSeg = 2048;                     // in-bin keys a head hands to its layer's last workgroup
+constexpr int kAdaOwn = 32;                       // cut kernel: scores per thread loaded up front, at most
+constexpr int kAdaSeg = 1920;                     // in-bin keys a head hands to its layer's workgroup
 constexpr int kAdaList = 4096;                    // (key, head) pairs that workgroup resolves in LDS
 constexpr int kAdaDigWords = 8192;                // its per-head digit histograms: H << bits words
-constexpr int kAdaMaxHeads = 1024;                // kv_heads the resolve kernel is laid out for
+constexpr int kAdaMaxHeads = 1024;                // kv_heads these kernels are laid out for
+constexpr int kAdaSlots = 256;                    // histograms there is room for, or one per head where there are more
+constexpr int kAdaMaxParts = 32;                  // histograms per head
+constexpr int kAdaPartTokens = 4096;              // a part is no shorter
+constexpr int kExps = kBins12 / 32;               // sums per exponent: 32 bins each
 
 struct AdaWorkspace {                             // device pointers into one allocation
-    uint32_t* hist;                               // [heads][4096] bin12 histograms of the candidates
+    uint32_t* hist;                               // [heads][parts][4096] bin12 histograms of the candidates
+    uint32_t* coarse;                             // [heads][parts][128] their sums per exponent
     uint32_t* seg;                                // [heads][kAdaSeg] keys (31 bits) inside the layer's cut bin
     uint32_t* above;                              // [heads] candidates in bins above the cut bin
     uint32_t* inbin;                              // [heads] candidates inside it
@@ -52,14 +59,17 @@ struct AdaWorkspace {                             // device pointers into one al
     AdaLayerState* layer;                         // [layers]
 };
 
+static constexpr size_t slots_for(size_t heads) { return heads > (size_t)kAdaSlots ? heads : (size_t)kAdaSlots; }
+
 static constexpr size_t workspace_bytes_for(size_t heads, size_t layers) {
-    return heads * (size_t)kBins12 * 4 + heads * (size_t)kAdaSeg * 4 + heads * 16 + layers * sizeof(AdaLayerState);
+    return slots_for(heads) * (size_t)(kBins12 + kExps) * 4 + heads * (size_t)kAdaSeg * 4 + heads * 16 + layers * sizeof(AdaLayerState);
 }
 
 static AdaWorkspace carve(void* base, size_t heads) {
     AdaWorkspace w;
     w.hist = reinterpret_cast<uint32_t*>(base);
-    w.seg = w.hist + heads * kBins12;
+    w.coarse = w.hist + slots_for(heads) * kBins12;
+    w.seg = w.coarse + slots_for(heads) * kExps;
     w.above = w.seg + heads * kAdaSeg;
     w.inbin = w.above + heads;
     w.known = reinterpret_cast<Threshold*>(w.inbin + heads);
@@ -67,61 +77,198 @@ static AdaWorkspace carve(void* base, size_t heads) {
     return w;
 }
 
-// a load that sees what other workgroups of this kernel have written (after the fences below)
-__device__ __forceinline__ uint32_t load_agent(const uint32_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Histogram of a head's candidate keys (tokens sp and up) over the selection's 4096 bins.
-__global__ __launch_bounds__(kAdaThreads) void ada_hist_kernel(
-    const float* __restrict__ scores, int64_t n, int H, int32_t sp, uint32_t* __restrict__ ws_hist,
-    AdaLayerState* __restrict__ layer_state) {
-    __shared__ uint32_t hist[kBins12];
-    const int head = blockIdx.x;
+// Histogram of a part of a head's candidate keys (tokens sp and up) over the selection's 4096 bins: workgroup (part, head).
+// scale_blocks > 0: `scores` holds un-normalised products, which are normalised on the way.
+__global__ __launch_bounds__(kAdaThreads) void ada_hist_kernel(float* __restrict__ scores, int64_t n, int32_t sp, int64_t part,
+                                                               uint32_t* __restrict__ ws_hist, uint32_t* __restrict__ ws_coarse,
+                                                               const float* __restrict__ partial, int scale_blocks) {
+    __shared__ __align__(16) uint32_t hist[kBins12];
+    const int head = blockIdx.y, slot = head * gridDim.x + blockIdx.x;
     const int tid = threadIdx.x;
-    const float* sc = scores + (size_t)head * n;
-    if (tid == 0 && head % H == 0) {              // a fresh count of finished workgroups for the layer
-        layer_state[head / H].done = 0;
-        layer_state[head / H].overflow = 0;
-    }
-    for (int i = tid; i < kBins12; i += kAdaThreads) hist[i] = 0;
-    __syncthreads();
+    const int64_t j_begin = (int64_t)blockIdx.x * part;
+    const int64_t j_end = j_begin + part < n ? j_begin + part : n;
+    float* sc = scores + (size_t)head * n;
     float cur[kAdaU], nxt[kAdaU];
     auto load = [&](float (&v)[kAdaU], int64_t j0) {
 #pragma unroll
         for (int u = 0; u < kAdaU; ++u) {
             const int64_t j = j0 + (int64_t)u * kAdaThreads;
-            v[u] = j < n ? sc[j] : 0.f;
+            v[u] = j < j_end ? sc[j] : 0.f;
         }
     };
-    load(cur, tid);
-    for (int64_t j0 = tid; j0 < n; j0 += (int64_t)kAdaU * kAdaThreads) {
+    load(cur, j_begin + tid);
+    const HeadScale scale = head_scale(head_partial(partial + (size_t)head * kMaxBlocksPerHead, scale_blocks), scale_blocks, n);
+    for (int i = tid; i < kBins12; i += kAdaThreads) hist[i] = 0;
+    __syncthreads();
+    for (int64_t j0 = j_begin + tid; j0 < j_end; j0 += (int64_t)kAdaU * kAdaThreads) {
         const int64_t jn = j0 + (int64_t)kAdaU * kAdaThreads;
-        if (jn < n) load(nxt, jn);
+        if (jn < j_end) load(nxt, jn);
 #pragma unroll
         for (int u = 0; u < kAdaU; ++u) {
             const int64_t j = j0 + (int64_t)u * kAdaThreads;
-            if (j >= sp && j < n) atomicAdd(&hist[bin12(order_key(cur[u]))], 1u);
+            if (j < j_end) {
+                const float v = scale(cur[u]);
+                if (scale.on) sc[j] = v;
+                if (j >= sp) atomicAdd(&hist[bin12(order_key(v))], 1u);
+            }
         }
 #pragma unroll
         for (int u = 0; u < kAdaU; ++u) cur[u] = nxt[u];
     }
     __syncthreads();
-    uint32_t* dst = ws_hist + (size_t)head * kBins12;
-    for (int i = tid; i < kBins12; i += kAdaThreads) dst[i] = hist[i];
+    hist12_store<kAdaThreads>(hist, ws_hist + (size_t)slot * kBins12, ws_coarse + (size_t)slot * kExps);
 }
 
-constexpr int kAdaHeadsAtOnce = 8;
+constexpr int kAdaHeadsAtOnce = kAdaThreads / kExps;             // 8: a thread per head and exponent
 
-struct AdaShared {
-    uint32_t wave_tot[kAdaHeadsAtOnce][kAdaWaves];
-    unsigned long long best;                      // first position (bins counted from the top) reaching R
-    uint32_t count;                               // keys this workgroup has put into its segment
-    uint32_t last;                                // this workgroup is the last of its layer
-    uint32_t digit;
-    uint32_t total_in;                            // keys inside the cut bin, all heads
-    uint32_t slow;
-};
+// KPT: scores per thread loaded up front.
+template <int KPT>
+__global__ __launch_bounds__(kAdaThreads) void ada_cut_kernel(AdaWorkspace ws, const float* __restrict__ scores, int64_t n, int H,
+                                                              int32_t sp, int32_t g, long long R, int64_t part) {
+    __shared__ uint32_t cum[kAdaHeadsAtOnce][kExps];             // keys of a head in exponents from the top to the i-th
+    __shared__ uint32_t fine[kAdaHeadsAtOnce][32];               // the same over the bins of one exponent
+    __shared__ uint32_t wave_tot[kAdaWaves], own[33], first[2], count;
+    const int parts = gridDim.x, q = blockIdx.x, head = blockIdx.y;
+    const int layer = head / H, my = head - layer * H;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t j_begin = (int64_t)q * part;
+    const int64_t j_end = j_begin + part < n ? j_begin + part : n;
+    const uint32_t len = j_begin < j_end ? (uint32_t)(j_end - j_begin) : 0u;
+    const float* sc = scores + (size_t)head * n + j_begin;
+
+    // the sums per exponent are wanted first, then this part's own scores, which arrive while those are being worked on
+    auto load_counts = [&](int h0) -> uint32_t {
+        const int h = h0 + (tid >> 7);
+        if (h >= H) return 0u;
+        const uint32_t* c = ws.coarse + (size_t)(layer * H + h) * parts * kExps + (kExps - 1 - (tid & 127));
+        uint32_t sum = 0;
+#pragma unroll 8
+        for (int p = 0; p < parts; ++p) sum += c[p * kExps];
+        return sum;
+    };
+    auto accumulate = [&](uint32_t sum) {                        // fills cum
+        uint32_t incl = wave_inclusive(sum);
+        if (lane == 63) wave_tot[wave] = incl;
+        __syncthreads();
+        if (wave & 1) incl += wave_tot[wave - 1];                // (two waves a head)
+        cum[tid >> 7][tid & 127] = incl;
+        __syncthreads();
+    };
+    const uint32_t counts = load_counts(0);
+    if (len == 0) return;                          // (no part is empty by the launcher's rule)
+    float v[KPT];
+#pragma unroll
+    for (int u = 0; u < KPT; ++u) {                // (not as a branch, or each load is waited for inside it)
+        const uint32_t o = (uint32_t)(u * kAdaThreads + tid);
+        v[u] = sc[o < len ? o : len - 1];
+    }
+    // ---- the exponent in which sum_h max(0, c_h - g) reaches R ------------------------------------
+    unsigned long long E = 0;
+    for (int h0 = 0; h0 < H; h0 += kAdaHeadsAtOnce) {
+        accumulate(h0 == 0 ? counts : load_counts(h0));
+        if (tid < kExps) {
+            const int m = H - h0 < kAdaHeadsAtOnce ? H - h0 : kAdaHeadsAtOnce;
+            for (int j = 0; j < m; ++j) {
+                const uint32_t c = cum[j][tid];
+                if (c > (uint32_t)g) E += c - (uint32_t)g;
+            }
+        }
+    }
+    if (wave < 2) {
+        const unsigned long long m = __ballot(E >= (unsigned long long)R);
+        if (lane == 0) first[wave] = m ? (uint32_t)(wave * 64 + __ffsll(m) - 1) : (uint32_t)(kExps - 1);
+    }
+    __syncthreads();
+    // (the lowest bin always reaches R for histograms of n - sp candidates per head; the bounds
+    // keep everything below in range whatever the workspace held)
+    const int pos = (int)(first[0] < first[1] ? first[0] : first[1]);
+    // ---- the bin of that exponent --------------------------------------------------------------------
+    E = 0;
+    for (int h0 = 0; h0 < H; h0 += kAdaHeadsAtOnce) {
+        if (H > kAdaHeadsAtOnce) accumulate(load_counts(h0));
+        const int j = (tid >> 5) & 7, i = tid & 31, slice = tid >> 8, h = h0 + j;      // four slices of the parts
+        uint32_t f = 0;
+        if (h < H) {
+            const uint32_t* c = ws.hist + (size_t)(layer * H + h) * parts * kBins12 + ((kExps - 1 - pos) * 32 + 31 - i);
+#pragma unroll 8
+            for (int p = slice; p < parts; p += 4) f += c[(size_t)p * kBins12];
+        }
+        if (slice == 0) fine[j][i] = f;
+        if (parts > 1) {
+            __syncthreads();
+            if (slice > 0 && f) atomicAdd(&fine[j][i], f);
+            __syncthreads();
+        }
+        if (slice == 0) {
+            uint32_t incl = wave_inclusive(fine[j][i]);
+            const uint32_t low = (uint32_t)__builtin_amdgcn_readlane((int)incl, 31);
+            incl -= lane >= 32 ? low : 0u;
+            const uint32_t before = pos > 0 ? cum[j][pos - 1] : 0u;
+            fine[j][i] = before + incl;
+            if (h == my) {
+                own[i + 1] = before + incl;
+                if (i == 0) own[0] = before;
+            }
+        }
+        __syncthreads();
+        if (tid < 32) {
+            const int m = H - h0 < kAdaHeadsAtOnce ? H - h0 : kAdaHeadsAtOnce;
+            for (int jj = 0; jj < m; ++jj) {
+                const uint32_t c = fine[jj][tid];
+                if (c > (uint32_t)g) E += c - (uint32_t)g;
+            }
+        }
+    }
+    if (wave == 0) {
+        const unsigned long long m = __ballot(lane < 32 && E >= (unsigned long long)R);
+        if (lane == 0) first[0] = m ? (uint32_t)(__ffsll(m) - 1) : 31u;
+    }
+    __syncthreads();
+    const int i0 = (int)first[0];
+    const uint32_t bstar = (uint32_t)((kExps - 1 - pos) * 32 + 31 - i0);
+    const uint32_t above_my = own[i0], inbin_my = own[i0 + 1] - own[i0];
+    if (tid == 0 && q == 0) {
+        ws.above[head] = above_my;
+        ws.inbin[head] = inbin_my;
+        if (my == 0) ws.layer[layer].bin = bstar;
+    }
+    // ---- hand this part's keys inside the bin to the layer ----------------------------------------
+    if (bstar >= (uint32_t)(kBins12 - 1) || inbin_my > (uint32_t)kAdaSeg) return;
+    if (wave == 0) {                               // behind those of the parts before
+        uint32_t before = lane < q ? ws.hist[((size_t)head * parts + lane) * kBins12 + bstar] : 0u;
+        before = wave_inclusive(before);
+        if (lane == 63) count = before;
+    }
+    __syncthreads();
+    uint32_t* seg = ws.seg + (size_t)head * kAdaSeg;
+    auto hand_in = [&](float x, bool cand) {
+        const uint32_t key = order_key(x);
+        if (cand && bin12(key) == bstar) {
+            const uint32_t slot = atomicAdd(&count, 1u);
+            if (slot < (uint32_t)kAdaSeg) seg[slot] = key & 0x7FFFFFFFu;
+        }
+    };
+    const uint32_t lo = j_begin < sp ? (uint32_t)(sp - j_begin) : 0u;        // the part's first candidate
+#pragma unroll
+    for (int u = 0; u < KPT; ++u) {
+        const uint32_t o = (uint32_t)(u * kAdaThreads + tid);
+        hand_in(v[u], o >= lo && o < len);
+    }
+    // parts longer than that: the rest streams through registers
+    for (uint32_t o0 = (uint32_t)(KPT * kAdaThreads); o0 < len; o0 += (uint32_t)(kAdaU * kAdaThreads)) {
+        float x[kAdaU];
+#pragma unroll
+        for (int u = 0; u < kAdaU; ++u) {
+            const uint32_t o = o0 + (uint32_t)(u * kAdaThreads + tid);
+            x[u] = o < len ? sc[o] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kAdaU; ++u) {
+            const uint32_t o = o0 + (uint32_t)(u * kAdaThreads + tid);
+            hand_in(x[u], o >= lo && o < len);
+        }
+    }
+}
 
 // bits per refinement level so that H digit histograms fit kAdaDigWords
 __device__ __forceinline__ int ada_level_bits(int H) {
@@ -130,228 +277,56 @@ __device__ __forceinline__ int ada_level_bits(int H) {
     return bits;
 }
 
-__global__ __launch_bounds__(kAdaThreads) void ada_resolve_kernel(
+struct AdaShared {
+    uint32_t wave_tot[kAdaWaves];
+    uint32_t digit, want;
+    uint32_t total_in;                            // keys inside the cut bin, all heads
+    uint32_t slow;
+    unsigned long long over;                      // sum of the heads' keys above the bin beyond their safeguards
+    uint32_t hist64[64];
+};
+
+__global__ __launch_bounds__(kAdaThreads) void ada_allot_kernel(
     AdaWorkspace ws, const float* __restrict__ scores, int64_t n, int H, int32_t sp, int32_t g, long long R,
     int32_t k, int32_t* __restrict__ budgets, int64_t* __restrict__ offsets, BlockInfo* __restrict__ block_info,
     int layers) {
     extern __shared__ __align__(16) uint32_t dyn[];
     __shared__ AdaShared sm;
-    // Workgroups are dealt to the chip's eight dies (each with an L2 of its own) round-robin by
-    // their number, and the H workgroups of a layer all read that layer's H histograms: where
-    // the layers come in multiples of eight, a layer's workgroups are numbered so that they
-    // share a die, and the histograms cross the fabric once instead of H times.  (Placement
-    // only: any numbering is correct.)
-    int head = blockIdx.x;
-    if (layers % 8 == 0) {
-        const int die = head & 7, q = head >> 3;
-        head = ((q / H) * 8 + die) * H + q % H;
-    }
-    const int layer = head / H, my = head - layer * H;
+    const int layer = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t* lhist = ws.hist + (size_t)layer * H * kBins12;     // the layer's H histograms
-
-    if (tid == 0) { sm.best = ~0ull; sm.count = 0; sm.slow = 0; }
-
-    // ---- the bin in which sum_h max(0, c_h - g) reaches R -------------------------------------
-    // Thread t looks at positions 4t .. 4t+3 counted from the top bin (bin = 4095 - position).
-    // kAdaHeadsAtOnce heads go through the workgroup-wide prefix sums together.  The loads of
-    // the first heads' histograms go out first, then those of this head's own scores, which
-    // are wanted further down (the keys inside the layer's cut bin) and arrive while the
-    // histograms are being worked on.
-    auto load_counts = [&](uint4 (&v)[kAdaHeadsAtOnce], int h0) {
-#pragma unroll
-        for (int j = 0; j < kAdaHeadsAtOnce; ++j) {
-            const int h = h0 + j < H ? h0 + j : H - 1;
-            v[j] = *reinterpret_cast<const uint4*>(lhist + (size_t)h * kBins12 + (kBins12 - 4 - 4 * tid));
-        }
-    };
-    uint4 raw[kAdaHeadsAtOnce];
-    load_counts(raw, 0);
-    const float* sc = scores + (size_t)head * n;
-    float* own = reinterpret_cast<float*>(dyn);    // [kAdaOwn * 1024] staged here: registers are short
-    const uint32_t n_first = n < (int64_t)kAdaOwn * kAdaThreads ? (uint32_t)n : (uint32_t)(kAdaOwn * kAdaThreads);
-    {
-        float v[kAdaOwn];
-#pragma unroll
-        for (int u = 0; u < kAdaOwn; ++u) {
-            const uint32_t o = (uint32_t)(u * kAdaThreads + tid);      // 32-bit offsets from a uniform base
-            v[u] = o < n_first ? sc[o] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < kAdaOwn; ++u) own[u * kAdaThreads + tid] = v[u];
-    }
-    __syncthreads();
-    unsigned long long E[4] = {0, 0, 0, 0};
-    uint32_t mine[4] = {0, 0, 0, 0};               // this head's counts at the thread's positions
-    for (int h0 = 0; h0 < H; h0 += kAdaHeadsAtOnce) {
-        uint32_t c[kAdaHeadsAtOnce][4], tot[kAdaHeadsAtOnce], incl[kAdaHeadsAtOnce];
-        if (h0 > 0) load_counts(raw, h0);
-#pragma unroll
-        for (int j = 0; j < kAdaHeadsAtOnce; ++j) {
-            const bool on = h0 + j < H;
-            const uint4 v = raw[j];
-            c[j][0] = on ? v.w : 0u; c[j][1] = on ? v.z : 0u; c[j][2] = on ? v.y : 0u; c[j][3] = on ? v.x : 0u;
-            tot[j] = c[j][0] + c[j][1] + c[j][2] + c[j][3];
-            incl[j] = tot[j];
-            if (on && h0 + j == my) { mine[0] = c[j][0]; mine[1] = c[j][1]; mine[2] = c[j][2]; mine[3] = c[j][3]; }
-        }
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1)
-#pragma unroll
-            for (int j = 0; j < kAdaHeadsAtOnce; ++j) {
-                const uint32_t t = __shfl_up(incl[j], off, 64);
-                if (lane >= off) incl[j] += t;
-            }
-        if (lane == 63) {
-#pragma unroll
-            for (int j = 0; j < kAdaHeadsAtOnce; ++j) sm.wave_tot[j][wave] = incl[j];
-        }
-        __syncthreads();
-        // exclusive prefix of the wave totals, per head: thread (j, w) of the first
-        // kAdaHeadsAtOnce*16 threads scans inside its group of 16 lanes
-        if (tid < kAdaHeadsAtOnce * kAdaWaves) {
-            const int j = tid / kAdaWaves, w = tid % kAdaWaves;
-            const uint32_t own_tot = sm.wave_tot[j][w];
-            uint32_t inc = own_tot;
-#pragma unroll
-            for (int off = 1; off < kAdaWaves; off <<= 1) {
-                const uint32_t t = __shfl_up(inc, off, kAdaWaves);
-                if (w >= off) inc += t;
-            }
-            sm.wave_tot[j][w] = inc - own_tot;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kAdaHeadsAtOnce; ++j) {
-            if (h0 + j >= H) break;
-            const uint32_t before = sm.wave_tot[j][wave];
-            uint32_t run = before + incl[j] - tot[j];              // keys of this head in higher bins
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                run += c[j][i];
-                if (run > (uint32_t)g) E[i] += run - (uint32_t)g;
-            }
-        }
-        __syncthreads();                                        // wave_tot is reused by the next heads
-    }
-    {
-        // E grows with the position, so every thread beyond the crossing qualifies: the minimum is
-        // taken inside each wave first, one atomic per wave instead of one per thread
-        uint32_t first = 0xFFFFFFFFu;
-#pragma unroll
-        for (int i = 3; i >= 0; --i)
-            if (E[i] >= (unsigned long long)R) first = (uint32_t)(tid * 4 + i);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            const uint32_t o = __shfl_xor(first, off, 64);
-            first = o < first ? o : first;
-        }
-        if (lane == 0 && first != 0xFFFFFFFFu) atomicMin(&sm.best, (unsigned long long)first);
-    }
-    __syncthreads();
-    // (the lowest bin always reaches R for histograms of n - sp candidates per head; the bound
-    // keeps everything below in range whatever the workspace held)
-    const int best = sm.best < (unsigned long long)kBins12 ? (int)sm.best : kBins12 - 1;
-    const uint32_t bstar = (uint32_t)(kBins12 - 1 - best);
-
-    // ---- this head: candidates above the bin, candidates inside it ------------------------------
-    uint32_t above_my, inbin_my;
-    {
-        uint32_t part = 0, inb = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int pos = tid * 4 + i;
-            part += pos < best ? mine[i] : 0u;
-            inb += pos == best ? mine[i] : 0u;
-        }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) { part += __shfl_xor(part, off, 64); inb += __shfl_xor(inb, off, 64); }
-        if (lane == 0) { sm.wave_tot[0][wave] = part; sm.wave_tot[1][wave] = inb; }
-        __syncthreads();
-        above_my = 0; inbin_my = 0;
-#pragma unroll
-        for (int w = 0; w < kAdaWaves; ++w) { above_my += sm.wave_tot[0][w]; inbin_my += sm.wave_tot[1][w]; }
-    }
-    // ---- hand this head's keys inside the bin to the layer -------------------------------------
-    if (bstar < (uint32_t)(kBins12 - 1) && inbin_my <= (uint32_t)kAdaSeg) {
-        uint32_t* seg = ws.seg + (size_t)head * kAdaSeg;
-        auto hand_in = [&](float v, bool cand) {
-            const uint32_t key = order_key(v);
-            if (cand && bin12(key) == bstar) {
-                const uint32_t slot = atomicAdd(&sm.count, 1u);
-                if (slot < (uint32_t)kAdaSeg) seg[slot] = key & 0x7FFFFFFFu;
-            }
-        };
-#pragma unroll 8
-        for (int u = 0; u < kAdaOwn; ++u) {
-            const uint32_t o = (uint32_t)(u * kAdaThreads + tid);
-            hand_in(own[o], o >= (uint32_t)sp && o < n_first);
-        }
-        // heads longer than the staged part: the rest streams through registers
-        for (int64_t j0 = (int64_t)kAdaOwn * kAdaThreads; j0 < n; j0 += (int64_t)kAdaU * kAdaThreads) {
-            const float* cp = sc + j0;                              // uniform base, 32-bit offsets
-            const uint32_t left = n - j0 < (int64_t)kAdaU * kAdaThreads ? (uint32_t)(n - j0) : (uint32_t)(kAdaU * kAdaThreads);
-            float v[kAdaU];
-#pragma unroll
-            for (int u = 0; u < kAdaU; ++u) {
-                const uint32_t o = (uint32_t)(u * kAdaThreads + tid);
-                v[u] = o < left ? cp[o] : 0.f;
-            }
-#pragma unroll
-            for (int u = 0; u < kAdaU; ++u) {
-                const uint32_t o = (uint32_t)(u * kAdaThreads + tid);
-                hand_in(v[u], o < left && j0 + o >= sp);
-            }
-        }
-    } else if (tid == 0) {
-        atomicOr(&ws.layer[layer].overflow, 1u);
-    }
-    if (tid == 0) { ws.above[head] = above_my; ws.inbin[head] = inbin_my; }
-    // ---- the last workgroup of the layer to get here goes on; the others are done ---------------
-    // One thread fences for the workgroup (the barrier orders the others' writes before its
-    // fence, and after the count, its second fence before their reads): a fence at device scope
-    // is a cache-wide operation on this chip, far too dear to issue from every wave.  What every
-    // wave does do is wait until its own stores have been taken by the L2: the barrier by itself
-    // does not wait for stores in flight, and the one write-back must cover them all.
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (tid == 0) {
-        __threadfence();                                        // the workgroup's writes, before the count
-        __builtin_amdgcn_s_waitcnt(0);                          // (the write-back itself included)
-        const uint32_t old = atomicAdd(&ws.layer[layer].done, 1u);
-        sm.last = old == (uint32_t)(H - 1) ? 1u : 0u;
-        if (sm.last) __threadfence();                           // the other workgroups' writes, after the count
-    }
-    __syncthreads();
-    if (!sm.last) return;
-
-    // ---- per-head state in LDS ---------------------------------------------------------------------
     const int B0 = ada_level_bits(H);
     uint32_t* dig = dyn;                           // [H << B] digit histograms, then suffix sums
     uint32_t* above = dyn + kAdaDigWords;          // [H] keys above the prefix decided so far
     uint32_t* inbin = above + kAdaMaxHeads;        // [H] keys inside the cut bin; later: keys equal to the threshold
     uint32_t* base = inbin + kAdaMaxHeads;         // [H + 1] start of a head's keys in the list; later: its first row
     uint32_t* list = base + kAdaMaxHeads + 8;      // [kAdaList][2] (key, head)
-    for (int h = tid; h < H; h += kAdaThreads) {
-        above[h] = load_agent(ws.above + (size_t)layer * H + h);
-        inbin[h] = load_agent(ws.inbin + (size_t)layer * H + h);
-    }
+    const uint32_t bstar = ws.layer[layer].bin;
+    // ---- the heads' counts, the places of their keys in the list (a thread per head) ----------------------
+    const uint32_t my_above = tid < H ? ws.above[(size_t)layer * H + tid] : 0u;
+    const uint32_t my_in = tid < H ? ws.inbin[(size_t)layer * H + tid] : 0u;
+    if (tid == 0) { sm.slow = bstar >= (uint32_t)(kBins12 - 1) ? 1u : 0u; sm.over = 0; }
+    if (tid < 64) sm.hist64[tid] = 0;
+    // A head whose safeguard ends inside the bin counts from there on only.  Usually there is none: heads
+    // beyond their safeguard before the bin count all of its keys, the others none of them, and the threshold is the key
+    // of one rank among the former's.
+    const bool beyond = my_above >= (uint32_t)g;
+    const bool by_rank = !__syncthreads_or(tid < H && !beyond && (unsigned long long)my_above + my_in > (unsigned long long)g);
+    const uint32_t listed = by_rank && !beyond ? 0u : my_in;
+    uint32_t incl = wave_inclusive(listed);        // (wraps only where some head is beyond its segment)
+    if (lane == 63) sm.wave_tot[wave] = incl;
+    if (tid < H && beyond) atomicAdd(&sm.over, (unsigned long long)(my_above - (uint32_t)g));
     __syncthreads();
-    if (tid == 0) {
-        uint32_t run = 0;
-        bool over = bstar == (uint32_t)(kBins12 - 1) || load_agent(&ws.layer[layer].overflow) != 0;
-        for (int h = 0; h < H; ++h) {
-            base[h] = run;
-            over = over || inbin[h] > (uint32_t)kAdaSeg;
-            run += inbin[h] <= (uint32_t)kAdaSeg ? inbin[h] : 0u;
-        }
-        base[H] = run;
-        sm.total_in = run;
-        sm.slow = (over || run > (uint32_t)kAdaList) ? 1u : 0u;
+    for (int w = 0; w < wave; ++w) incl += sm.wave_tot[w];
+    if (tid < H) {
+        above[tid] = my_above;
+        inbin[tid] = listed;
+        base[tid] = incl - listed;
+        if (tid == H - 1) sm.total_in = incl;
+        if (my_in > (uint32_t)kAdaSeg || incl > (uint32_t)kAdaList) sm.slow = 1u;
     }
     __syncthreads();
     const bool slow = sm.slow != 0;
-    const uint32_t total_in = sm.total_in;
+    const uint32_t total_in = slow ? 0u : sm.total_in;
     if (!slow) {
         // gather the heads' segments into one list; threads are dealt to heads so that all
         // heads' loads are in flight together
@@ -362,17 +337,35 @@ __global__ __launch_bounds__(kAdaThreads) void ada_resolve_kernel(
             const uint32_t* seg = ws.seg + ((size_t)layer * H + h) * kAdaSeg;
             const uint32_t cnt = inbin[h], b0 = base[h];
             for (uint32_t i = r; i < cnt; i += per_head) {
-                list[2 * (b0 + i)] = load_agent(seg + i);
+                list[2 * (b0 + i)] = seg[i];
                 list[2 * (b0 + i) + 1] = (uint32_t)h;
             }
         }
         __syncthreads();
     }
 
-    // ---- refine the threshold below the bin: B bits per level -----------------------------------
-    // A key takes part while bin12(key) == bstar and its bits above `rem` equal `fixed`.
+    // ---- the key of a rank among the listed --------------------------------------------------------
     int rem = bstar < (uint32_t)(kBins12 - 1) ? kBinShift : 31;
     uint32_t fixed = bstar < (uint32_t)(kBins12 - 1) ? bstar : 0u;
+    const unsigned long long rank = (unsigned long long)R - sm.over;           // (R is not reached above the bin)
+    if (!slow && by_rank && rank >= 1 && rank <= total_in) {
+        uint32_t need;
+        for (int h = tid; h < H; h += kAdaThreads) dig[h] = 0;
+        fixed = threshold_on_list<kAdaThreads>(reinterpret_cast<const int32_t*>(list), total_in, bstar, (uint32_t)rank, sm.hist64, &sm.digit,
+                                               &sm.want, &need);
+        __syncthreads();
+        for (uint32_t i = tid; i < total_in; i += kAdaThreads) {
+            const uint32_t key = list[2 * i], h = list[2 * i + 1];
+            if (key > fixed) atomicAdd(&above[h], 1u);
+            else if (key == fixed) atomicAdd(&dig[h], 1u);
+        }
+        __syncthreads();
+        for (int h = tid; h < H; h += kAdaThreads) inbin[h] = dig[h];
+        rem = 0;
+        __syncthreads();
+    }
+    // ---- or refined below the bin: B bits per level ---------------------------------------------------
+    // A key takes part while bin12(key) == bstar and its bits above `rem` equal `fixed`.
     const float* lsc = scores + (size_t)layer * H * n;
     while (rem > 0) {
         const int B = rem < B0 ? rem : B0;
@@ -447,7 +440,30 @@ __global__ __launch_bounds__(kAdaThreads) void ada_resolve_kernel(
     }
 
     // ---- exact threshold reached: above[h] keys beat it, inbin[h] keys equal it -------------------
-    if (tid == 0) {
+    if (H <= 64 && (long long)H * n <= 0x7FFFFFFFll) {
+        if (wave == 0) {                            // a lane per head, what the loop below does
+            const bool on = lane < H;
+            const uint32_t cp = on ? above[lane] : 0u, eq = on ? inbin[lane] : 0u, ug = (uint32_t)g;
+            const uint32_t over = on && cp > ug ? cp - ug : 0u;
+            const long long total_over = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive(over), 63);
+            const uint32_t rest = R > total_over ? (uint32_t)(R - total_over) : 0u;
+            const uint32_t kept = cp > ug ? cp : ug;
+            const uint32_t open_eq = on && cp + eq > kept ? cp + eq - kept : 0u;
+            const uint32_t before = wave_inclusive(open_eq) - open_eq;
+            const uint32_t left = rest > before ? rest - before : 0u;
+            const uint32_t take = open_eq < left ? open_eq : left;
+            uint32_t b = (uint32_t)sp + kept + take;
+            b = !on ? 0u : b > (uint32_t)n ? (uint32_t)n : b;
+            const uint32_t layer_rows = (uint32_t)H * (uint32_t)k;
+            const uint32_t run = wave_inclusive(b) - b;
+            if (on) {
+                budgets[(size_t)layer * H + lane] = (int32_t)b;
+                ws.known[(size_t)layer * H + lane] = Threshold{cp >= ug ? fixed : kNoThreshold, take};
+                base[lane] = run < layer_rows ? run : layer_rows;
+            }
+            if (lane == 0) base[H] = layer_rows;
+        }
+    } else if (tid == 0) {
         int32_t* out = budgets + (size_t)layer * H;
         long long rest = R;
         for (int h = 0; h < H; ++h)
@@ -583,23 +599,20 @@ hipError_t launch_adaptive_plan(const curdkv_ctx* ctx, const int32_t* budgets, i
     return hipGetLastError();
 }
 
-// dynamic LDS of ada_resolve_kernel: first the head's own scores; then, in the last workgroup
-// of a layer, digit histograms, three per-head arrays and the key list
-constexpr size_t kAdaLastLds = ((size_t)kAdaDigWords + 3 * (size_t)kAdaMaxHeads + 8 + 2 * (size_t)kAdaList) * 4;
-constexpr size_t kAdaOwnLds = (size_t)kAdaOwn * kAdaThreads * 4;
-constexpr size_t kAdaResolveLds = kAdaOwnLds > kAdaLastLds ? kAdaOwnLds : kAdaLastLds;
+// dynamic LDS of ada_allot_kernel: digit histograms, three per-head arrays and the key list
+constexpr size_t kAdaAllotLds = ((size_t)kAdaDigWords + 3 * (size_t)kAdaMaxHeads + 8 + 2 * (size_t)kAdaList) * 4;
 
 // The layout above holds for every head count the kernel accepts: digit histograms of at least
 // one bit per level, and everything inside the 160 KB of a gfx950 workgroup beside the static
 // part (AdaShared and the compiler's own few words).
 static_assert((kAdaMaxHeads << 1) <= kAdaDigWords, "a level of one bit must fit the digit histograms");
-static_assert(kAdaResolveLds + sizeof(AdaShared) + 1024 <= 160 * 1024, "ada_resolve_kernel's LDS");
+static_assert(kAdaAllotLds + sizeof(AdaShared) + 1024 <= 160 * 1024, "ada_allot_kernel's LDS");
 static_assert(kAdaSeg <= kAdaList, "one head's segment must fit the list");
 
 hipError_t configure_adaptive(curdkv_ctx* ctx) {
-    if ((size_t)ctx->lds_limit < kAdaResolveLds + 4096) return hipSuccess;    // the adaptive calls then report an error
-    return hipFuncSetAttribute((const void*)ada_resolve_kernel,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAdaResolveLds);
+    if ((size_t)ctx->lds_limit < kAdaAllotLds + 4096) return hipSuccess;    // the adaptive calls then report an error
+    return hipFuncSetAttribute((const void*)ada_allot_kernel,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAdaAllotLds);
 }
 
 size_t adaptive_workspace_bytes(const curdkv_ctx* ctx) {
@@ -646,35 +659,49 @@ uint32_t* adaptive_hist_buffer(const curdkv_ctx* ctx, void* workspace) {
     return carve(workspace, (size_t)ctx->heads).hist;
 }
 
+uint32_t* adaptive_coarse_buffer(const curdkv_ctx* ctx, void* workspace) {
+    return carve(workspace, (size_t)ctx->heads).coarse;
+}
+
 const void* adaptive_thresholds(const curdkv_ctx* ctx, void* workspace) {
     return carve(workspace, (size_t)ctx->heads).known;
 }
 
-AdaLayerState* adaptive_layer_state(const curdkv_ctx* ctx, void* workspace) {
-    return carve(workspace, (size_t)ctx->heads).layer;
+// Parts a head is counted in: one per compute unit at most, where heads are fewer than those.
+static int parts_for(const curdkv_ctx* ctx, int64_t n) {
+    int64_t parts = kAdaSlots / ctx->heads;
+    if (parts > (n + kAdaPartTokens - 1) / kAdaPartTokens) parts = (n + kAdaPartTokens - 1) / kAdaPartTokens;
+    return (int)(parts < 1 ? 1 : parts < kAdaMaxParts ? parts : kAdaMaxParts);
 }
 
-hipError_t launch_adaptive(const curdkv_ctx* ctx, void* workspace, const float* scores, int64_t n, int32_t k,
+bool adaptive_allots(int32_t k, int32_t sp, long long R) { return k > sp && R > 0; }
+
+hipError_t launch_adaptive(const curdkv_ctx* ctx, void* workspace, float* scores, int64_t n, int32_t k,
                            int32_t sp, int32_t g, long long R, int32_t* budgets, hipStream_t stream,
-                           bool hist_ready, int64_t* offsets, BlockInfo* block_info, bool* planned) {
+                           bool hist_ready, int scale_blocks, int64_t* offsets, BlockInfo* block_info, bool* planned) {
     const int H = ctx->cfg.kv_heads, L = ctx->cfg.layers;
     if (planned) *planned = false;
-    if (k <= sp || R <= 0) {           // nothing to allot: k each, or all covered by the safeguard
+    if (!adaptive_allots(k, sp, R)) {           // nothing to allot: k each, or all covered by the safeguard
         const int32_t v = k <= sp ? k : sp + g;
         ada_uniform_kernel<<<dim3((unsigned)((ctx->heads + 255) / 256)), 256, 0, stream>>>(budgets, ctx->heads, v);
         return hipGetLastError();
     }
-    if ((size_t)ctx->lds_limit < kAdaResolveLds + 4096 || H > kAdaMaxHeads) return hipErrorInvalidConfiguration;
+    if ((size_t)ctx->lds_limit < kAdaAllotLds + 4096 || H > kAdaMaxHeads) return hipErrorInvalidConfiguration;
     const AdaWorkspace ws = carve(workspace, (size_t)ctx->heads);
-    if (!hist_ready) {
-        ada_hist_kernel<<<dim3((unsigned)ctx->heads), kAdaThreads, 0, stream>>>(scores, n, H, sp, ws.hist, ws.layer);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
+    const int parts = hist_ready ? 1 : parts_for(ctx, n);
+    const int64_t part = (n + parts - 1) / parts;
+    const dim3 grid((unsigned)parts, (unsigned)ctx->heads);
+    if (!hist_ready) ada_hist_kernel<<<grid, kAdaThreads, 0, stream>>>(scores, n, sp, part, ws.hist, ws.coarse, ctx->d_partial, scale_blocks);
+    auto cut = [&](auto kpt) {
+        ada_cut_kernel<decltype(kpt)::value><<<grid, kAdaThreads, 0, stream>>>(ws, scores, n, H, sp, g, R, part);
+    };
+    if (part <= 4 * kAdaThreads) cut(std::integral_constant<int, 4>{});
+    else if (part <= 16 * kAdaThreads) cut(std::integral_constant<int, 16>{});
+    else cut(std::integral_constant<int, kAdaOwn>{});
     // the kernel keeps a head's first row inside its layer in 32 bits: a layer of 2^32 rows or
     // more gets its offsets and block table from the general kernels instead
     if ((long long)H * k > 0xFFFFFFFFll) offsets = nullptr;
-    ada_resolve_kernel<<<dim3((unsigned)ctx->heads), kAdaThreads, kAdaResolveLds, stream>>>(
+    ada_allot_kernel<<<dim3((unsigned)L), kAdaThreads, kAdaAllotLds, stream>>>(
         ws, scores, n, H, sp, g, R, k, budgets, offsets, offsets ? block_info : nullptr, L);
     if (planned) *planned = offsets != nullptr;
     return hipGetLastError();

@@ -190,7 +190,7 @@ int curdkv_create(curdkv_ctx** out, const curdkv_config* cfg) {
         return CURDKV_ERR_OOM;
     }
     // the head-wise budget allocation's workspace and its device-built gather table (a few
-    // tens of KB per head): allocated here so that the adaptive calls are kernel launches only
+    // tens of KB per head, 4 MB at least): allocated here so that the adaptive calls are kernel launches only
     if (hipMalloc(&ctx->d_adaptive_ws, adaptive_workspace_bytes(ctx)) != hipSuccess ||
         hipMalloc((void**)&ctx->d_adaptive_blocks, ctx->plan.max_blocks * sizeof(BlockInfo)) != hipSuccess) {
         (void)hipGetLastError();
@@ -398,7 +398,7 @@ int curdkv_adaptive_budgets(curdkv_ctx* ctx, const float* scores, int64_t n, int
     if (g > n - sp) g = n - sp;
     const long long H = ctx->cfg.kv_heads;
     const long long R = budget > sp ? H * ((long long)budget - sp) - H * g : 0;
-    return launch_adaptive(ctx, ctx->d_adaptive_ws, scores, n, budget, (int32_t)sp, (int32_t)g, R, budgets_out,
+    return launch_adaptive(ctx, ctx->d_adaptive_ws, const_cast<float*>(scores), n, budget, (int32_t)sp, (int32_t)g, R, budgets_out,
                            (hipStream_t)stream) == hipSuccess ? CURDKV_OK : CURDKV_ERR_HIP;
 }
 
@@ -418,7 +418,7 @@ int curdkv_adaptive_budgets_noalloc(curdkv_ctx* ctx, const float* scores, int64_
     if (g > n - sp) g = n - sp;
     const long long H = ctx->cfg.kv_heads;
     const long long R = budget > sp ? H * ((long long)budget - sp) - H * g : 0;
-    return launch_adaptive(ctx, ws, scores, n, budget, (int32_t)sp, (int32_t)g, R, budgets_out,
+    return launch_adaptive(ctx, ws, const_cast<float*>(scores), n, budget, (int32_t)sp, (int32_t)g, R, budgets_out,
                            (hipStream_t)stream) == hipSuccess ? CURDKV_OK : CURDKV_ERR_HIP;
 }
 
@@ -444,32 +444,39 @@ int curdkv_compress_adaptive(curdkv_ctx* ctx, const void* K, const void* V, int6
         scores = ctx->d_scores_ws;
     }
     // normalised scores first: the allocation compares them across the heads of a layer.  The
-    // fused kernel, where it applies, also leaves every head's key histogram in the workspace.
-    const bool fused = fused_applicable(ctx, n);
-    const hipError_t e = fused
-        ? launch_fused(ctx, K, V, n, n_sink, ctx->d_zero_offsets, scores, nullptr, nullptr, nullptr, st,
-                       adaptive_hist_buffer(ctx, ctx->d_adaptive_ws), adaptive_layer_state(ctx, ctx->d_adaptive_ws))
-        : launch_scores(ctx, K, V, n, scores, st);
-    if (e != hipSuccess) return CURDKV_ERR_HIP;
+    // fused kernel, where it applies, also leaves every head's key histogram in the workspace; otherwise
+    // the kernel that makes the histograms normalises on the way.
     const int64_t sp = n_sink < n ? n_sink : n;
     int64_t g = (int64_t)std::floor(alpha * (double)budget) - sp;
     if (g < 0) g = 0;
     if (g > n - sp) g = n - sp;
     const long long H = ctx->cfg.kv_heads;
     const long long R = budget > sp ? H * ((long long)budget - sp) - H * g : 0;
+    const bool fused = fused_applicable(ctx, n), allots = adaptive_allots(budget, (int32_t)sp, R);
+    int bph = 0;
+    const hipError_t e = fused
+        ? launch_fused(ctx, K, V, n, n_sink, ctx->d_zero_offsets, scores, nullptr, nullptr, nullptr, st,
+                       adaptive_hist_buffer(ctx, ctx->d_adaptive_ws), adaptive_coarse_buffer(ctx, ctx->d_adaptive_ws))
+        : launch_scores(ctx, K, V, n, scores, st, /*normalise=*/!allots, &bph);
+    if (e != hipSuccess) return CURDKV_ERR_HIP;
     bool planned = false;
     if (launch_adaptive(ctx, ctx->d_adaptive_ws, scores, n, budget, (int32_t)sp, (int32_t)g, R, budgets_out, st,
-                        fused, offsets_out, ctx->d_adaptive_blocks, &planned) != hipSuccess)
+                        fused, fused ? 0 : bph, offsets_out, ctx->d_adaptive_blocks, &planned) != hipSuccess)
         return CURDKV_ERR_HIP;
     if (!planned && launch_adaptive_plan(ctx, budgets_out, n, total, offsets_out, ctx->d_adaptive_blocks, st) != hipSuccess)
         return CURDKV_ERR_HIP;
     if (total == 0) return CURDKV_OK;
     // (`planned`: budgets were allotted layer-wide, and the allocation has left every head's threshold)
-    if (launch_select(ctx, scores, n, n_sink, offsets_out, /*max_budget=*/n, indices, st, 0, true,
-                      planned ? adaptive_thresholds(ctx, ctx->d_adaptive_ws) : nullptr) != hipSuccess ||
-        launch_compact(ctx, K, V, n, indices, offsets_out, total, K_out, V_out, st, ctx->d_adaptive_blocks) != hipSuccess)
+    const void* known = planned ? adaptive_thresholds(ctx, ctx->d_adaptive_ws) : nullptr;
+    SelectGather gather{K, V, K_out, V_out, total, false};
+    if (select_gather_applicable(ctx, n, total))
+        return launch_select_gather(ctx, scores, nullptr, n, n_sink, offsets_out, /*max_budget=*/-1, indices, st, 0, gather, known) == hipSuccess
+                   ? CURDKV_OK : CURDKV_ERR_HIP;
+    if (launch_select(ctx, scores, n, n_sink, offsets_out, /*max_budget=*/-1, indices, st, 0, true, known, &gather) != hipSuccess)
         return CURDKV_ERR_HIP;
-    return CURDKV_OK;
+    if (gather.done) return CURDKV_OK;
+    return launch_compact(ctx, K, V, n, indices, offsets_out, total, K_out, V_out, st, ctx->d_adaptive_blocks) == hipSuccess
+               ? CURDKV_OK : CURDKV_ERR_HIP;
 }
 
 int curdkv_scores_append(curdkv_ctx* ctx, const void* K_new, const void* V_new, int64_t m,

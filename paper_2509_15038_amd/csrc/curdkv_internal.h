@@ -26,9 +26,8 @@ struct BlockInfo {                     // for gather block b, whose first output
 
 // Per-layer state of the head-wise budget allocation (adaptive_kernels.hip), in its workspace.
 struct AdaLayerState {
-    uint32_t done;                     // workgroups of the layer that have handed in their keys
-    uint32_t overflow;                 // some head's cut bin was too full for its segment
-    uint32_t pad[2];
+    uint32_t bin;                      // the histogram bin that holds the layer's threshold
+    uint32_t pad[3];
 };
 
 // Device copy of the offsets, refreshed when they change, followed by the
@@ -100,7 +99,7 @@ hipError_t launch_fold(const curdkv_ctx* ctx, const float* scores_q, int64_t n, 
 // result and writes it back, which is what normalisation followed by selection gives
 // (write_scaled = false: selects on the divided values but leaves `scores` as they are, for
 // callers that do not want the scores).
-// max_budget: the largest of the heads' budgets, or an upper bound of it.
+// max_budget: the largest of the heads' budgets; negative: they exist on the device only.
 // known_thresholds (device, one {key, need} pair per head as the budget allocation leaves them,
 // adaptive_thresholds): heads whose entry is valid skip the search for their threshold.
 struct SelectGather {
@@ -114,13 +113,13 @@ hipError_t launch_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_
                          int scale_blocks = 0, bool write_scaled = true,
                          const void* known_thresholds = nullptr, SelectGather* gather = nullptr);
 // Few, short heads, one call: selection and gather in one launch.  `raw`: the un-normalised products (ctx->d_raw_ws);
-// scores: where the normalised ones go, or nullptr.
+// scores: where the normalised ones go, or nullptr.  max_budget < 0: the budgets exist on the device only.
 bool select_gather_wanted(const curdkv_ctx* ctx);      // the context needs the workspace
 size_t select_gather_workspace_bytes(const curdkv_ctx* ctx);
 bool select_gather_applicable(const curdkv_ctx* ctx, int64_t n, int64_t total);
 hipError_t launch_select_gather(const curdkv_ctx* ctx, const float* raw, float* scores, int64_t n, int32_t n_sink,
                                 const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
-                                int scale_blocks, const SelectGather& gather);
+                                int scale_blocks, const SelectGather& gather, const void* known_thresholds = nullptr);
 // gather given: the selection may copy the kept rows itself; gather->done says whether it has.
 // split_select.hip: the same for long heads, several workgroups per head (workspace ctx->d_split_ws).
 // scale_blocks > 0: step 1's histograms, scale_blocks of them per head, have been made by launch_scores.
@@ -133,7 +132,7 @@ uint32_t* split_coarse(const curdkv_ctx* ctx);         // [heads][split_hists][2
 constexpr int kSplitMaxHeads = 128;                    // (layer, group) pairs the split is used for (its workspace takes 9 KB per histogram, 64 per pair up to 32 pairs and 32 beyond, and 32 KB of bitmaps at most: 0.62 or 0.33 MB a pair)
 hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
                                const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
-                               int scale_blocks, bool write_scaled, SelectGather* gather);
+                               int scale_blocks, bool write_scaled, const void* known_thresholds, SelectGather* gather);
 hipError_t launch_compact(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n,
                           const int32_t* indices, const int64_t* d_offsets, int64_t total,
                           void* K_out, void* V_out, hipStream_t stream,
@@ -145,22 +144,23 @@ hipError_t configure_adaptive(curdkv_ctx* ctx);
 size_t adaptive_workspace_bytes(const curdkv_ctx* ctx);
 // workspace: adaptive_workspace_bytes(ctx) bytes of device memory; nothing in it has to be
 // cleared beforehand, and its contents mean nothing after the call.
-// hist_ready: the per-head histograms (adaptive_hist_buffer) have been written, and the layers'
-// state (adaptive_layer_state) reset, by a kernel launched earlier on the stream (launch_fused
-// with hist_out); otherwise a kernel of this call makes them from `scores`.
+// hist_ready: the per-head histograms (adaptive_hist_buffer) and their sums per exponent (adaptive_coarse_buffer) have been
+// written by a kernel launched earlier on the stream (launch_fused with hist_out); otherwise a kernel of this call makes them
+// from `scores`, which it normalises first where scale_blocks > 0 (as in launch_select).
 // offsets, block_info (device) given: where budgets are allotted layer-wide, the same launch
 // also writes the budgets' prefix sums (every layer keeps kv_heads*k rows) and the gather's
 // block table, and *planned is set; where every head gets the same budget they are left to
 // launch_adaptive_plan and *planned stays false.
-hipError_t launch_adaptive(const curdkv_ctx* ctx, void* workspace, const float* scores, int64_t n, int32_t k,
+bool adaptive_allots(int32_t k, int32_t sp, long long R);      // otherwise every head gets the same, and `scores` is not looked at
+hipError_t launch_adaptive(const curdkv_ctx* ctx, void* workspace, float* scores, int64_t n, int32_t k,
                            int32_t sp, int32_t g, long long R, int32_t* budgets, hipStream_t stream,
-                           bool hist_ready = false, int64_t* offsets = nullptr, BlockInfo* block_info = nullptr,
-                           bool* planned = nullptr);
+                           bool hist_ready = false, int scale_blocks = 0, int64_t* offsets = nullptr,
+                           BlockInfo* block_info = nullptr, bool* planned = nullptr);
 uint32_t* adaptive_hist_buffer(const curdkv_ctx* ctx, void* workspace);
+uint32_t* adaptive_coarse_buffer(const curdkv_ctx* ctx, void* workspace);
 // per head {threshold key, ties to keep} after launch_adaptive has allotted budgets layer-wide
 // (key 0xFFFFFFFF where a head's budget comes from its safeguard, not from the layer's threshold)
 const void* adaptive_thresholds(const curdkv_ctx* ctx, void* workspace);
-AdaLayerState* adaptive_layer_state(const curdkv_ctx* ctx, void* workspace);
 // The static device array that serves as that workspace for curdkv_adaptive_budgets_noalloc:
 // its address on `device` (looked up by adaptive_static_workspace_init, which curdkv_create
 // calls with the device current), and the number of (layer, group) pairs it is sized for.
@@ -172,12 +172,12 @@ int adaptive_static_max_heads();
 hipError_t launch_adaptive_plan(const curdkv_ctx* ctx, const int32_t* budgets, int64_t n, int64_t total,
                                 int64_t* offsets, BlockInfo* block_info, hipStream_t stream);
 bool fused_applicable(const curdkv_ctx* ctx, int64_t n);
-// hist_out (device, [heads][4096]) given: the kernel also writes every head's histogram of the
+// hist_out (device, [heads][4096]) and coarse_out ([heads][128]) given: the kernel also writes every head's histogram of the
 // candidates' keys (tokens n_sink and up) over the 4096 bins of the selection (select_device.h)
-// and resets layer_state, for the head-wise budget allocation that follows it.
+// and its sums per exponent, for the head-wise budget allocation that follows it.
 hipError_t launch_fused(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n, int32_t n_sink,
                         const int64_t* d_offsets, float* scores, int32_t* indices, void* K_out,
                         void* V_out, hipStream_t stream, uint32_t* hist_out = nullptr,
-                        AdaLayerState* layer_state = nullptr);
+                        uint32_t* coarse_out = nullptr);
 
 }  // namespace curdkv

@@ -31,7 +31,7 @@ __global__ __launch_bounds__(kFusedThreads, 2) void fused_kernel(
     const uint4* __restrict__ K, const uint4* __restrict__ V, const uint4* __restrict__ Gp,
     int32_t n, int32_t n_sink, const int64_t* __restrict__ offsets, float* __restrict__ scores_out,
     int32_t* __restrict__ indices, u32x4* __restrict__ K_out, u32x4* __restrict__ V_out,
-    uint32_t* __restrict__ hist_out, AdaLayerState* __restrict__ layer_state, int heads_per_layer) {
+    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out) {
     extern __shared__ float sc[];                  // [n rounded up to 64]; later int32 stage[n]
     __shared__ SelectShared<kFusedThreads, KPT> sm;
     __shared__ float wsum[kFusedWaves];
@@ -82,12 +82,7 @@ __global__ __launch_bounds__(kFusedThreads, 2) void fused_kernel(
         // for the head-wise budget allocation: the bin12 histogram of this head's candidates,
         // made here because the keys are in registers anyway
         build_hist12<kFusedThreads, KPT>(x, n, s, sm);
-        uint32_t* dst = hist_out + (size_t)head * kBins12;
-        for (int i = tid; i < kBins12; i += kFusedThreads) dst[i] = sm.hist[i];
-        if (tid == 0 && head % heads_per_layer == 0) {       // a fresh count of finished workgroups for the layer
-            layer_state[head / heads_per_layer].done = 0;
-            layer_state[head / heads_per_layer].overflow = 0;
-        }
+        hist12_store<kFusedThreads>(sm.hist, hist_out + (size_t)head * kBins12, coarse_out + (size_t)head * (kBins12 / 32));
     }
     const int64_t o0 = offsets[head];
     const int32_t k = (int32_t)(offsets[head + 1] - o0);
@@ -140,7 +135,7 @@ struct FusedArgs {
     int32_t* indices;
     void *K_out, *V_out;
     uint32_t* hist_out;
-    AdaLayerState* layer_state;
+    uint32_t* coarse_out;
     hipStream_t stream;
     int dyn;                 // >= 0: only raise the kernel's dynamic LDS limit to this, no launch
 };
@@ -153,8 +148,7 @@ static hipError_t one(const FusedArgs& a) {
     const size_t lds = (((size_t)a.n + 63) & ~(size_t)63) * 4;
     fused_kernel<CB, KPT, SRC, PROJ><<<dim3((unsigned)a.ctx->heads), kFusedThreads, lds, a.stream>>>(
         (const uint4*)a.K, (const uint4*)a.V, (const uint4*)a.ctx->d_G, a.n, a.n_sink, a.d_offsets,
-        a.scores, a.indices, (u32x4*)a.K_out, (u32x4*)a.V_out, a.hist_out, a.layer_state,
-        a.ctx->cfg.kv_heads);
+        a.scores, a.indices, (u32x4*)a.K_out, (u32x4*)a.V_out, a.hist_out, a.coarse_out);
     return hipGetLastError();
 }
 
@@ -225,9 +219,9 @@ bool fused_applicable(const curdkv_ctx* ctx, int64_t n) {
 
 hipError_t launch_fused(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n, int32_t n_sink,
                         const int64_t* d_offsets, float* scores, int32_t* indices, void* K_out,
-                        void* V_out, hipStream_t stream, uint32_t* hist_out, AdaLayerState* layer_state) {
-    if (!layer_state) hist_out = nullptr;          // the two go together
-    FusedArgs a{ctx, K, V, (int32_t)n, n_sink, d_offsets, scores, indices, K_out, V_out, hist_out, layer_state, stream, -1};
+                        void* V_out, hipStream_t stream, uint32_t* hist_out, uint32_t* coarse_out) {
+    if (!coarse_out) hist_out = nullptr;           // the two go together
+    FusedArgs a{ctx, K, V, (int32_t)n, n_sink, d_offsets, scores, indices, K_out, V_out, hist_out, coarse_out, stream, -1};
     return dispatch(a, ctx->col_blocks, keys_per_thread(n), ctx->cfg.score_source, !ctx->cfg.no_projection);
 }
 

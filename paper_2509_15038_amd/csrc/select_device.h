@@ -200,7 +200,7 @@ __device__ __forceinline__ void find_bin_from_top(const uint32_t* hist, uint32_t
 template <int THREADS, int KPT>
 struct SelectShared {
     static constexpr int kWaves = THREADS / 64;
-    uint32_t hist[kBins12];                       // bin12 histogram; later the digit histograms (general case: 256 x kHistRep)
+    alignas(16) uint32_t hist[kBins12];           // bin12 histogram; later the digit histograms (general case: 256 x kHistRep)
     unsigned long long gmask[KPT * kWaves];       // bitmaps over the tokens, one 64-token word per (row, wave)
     unsigned long long emask[KPT * kWaves];
     uint32_t wpos[KPT * kWaves];                  // output position of a word's first kept token
@@ -224,6 +224,23 @@ __device__ __forceinline__ void build_hist12(const uint32_t (&x)[KPT], int32_t n
     for (int it = 0; it < KPT; ++it)
         if (jt + (uint32_t)(it * THREADS) < span) atomicAdd(&sm.hist[bin12(x[it])], 1u);
     __syncthreads();
+}
+
+// Writes a bin12 histogram (complete, in LDS) to dst, and its sums per exponent, 32 bins each, to coarse.
+template <int THREADS>
+__device__ __forceinline__ void hist12_store(const uint32_t* hist, uint32_t* __restrict__ dst, uint32_t* __restrict__ coarse) {
+    constexpr int kPer = kBins12 / THREADS;        // neighbouring bins per thread
+    static_assert(kPer % 4 == 0 && 32 % kPer == 0, "an exponent's bins lie in neighbouring lanes");
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < kPer / 4; ++i) {
+        const uint4 c = reinterpret_cast<const uint4*>(hist)[threadIdx.x * (kPer / 4) + i];
+        reinterpret_cast<uint4*>(dst)[threadIdx.x * (kPer / 4) + i] = c;
+        sum += (c.x + c.y) + (c.z + c.w);
+    }
+#pragma unroll
+    for (int off = 1; off < 32 / kPer; off *= 2) sum += __shfl_xor(sum, off, 64);
+    if (threadIdx.x % (32 / kPer) == 0) coarse[threadIdx.x / (32 / kPer)] = sum;
 }
 
 // General case of the threshold search: radix select over the keys in registers.  Fills

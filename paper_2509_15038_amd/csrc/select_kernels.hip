@@ -389,7 +389,8 @@ template <int KPT, int ROW_U4>
 __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float* __restrict__ raw, float* __restrict__ scores,
                                                                 int32_t n, int32_t n_sink, const int64_t* __restrict__ offsets,
                                                                 int32_t* __restrict__ indices, const float* __restrict__ partial,
-                                                                int scale_blocks, int share, GatherArgs ga) {
+                                                                int scale_blocks, int share, GatherArgs ga,
+                                                                const Threshold* __restrict__ known) {
     extern __shared__ int32_t stage[];             // [n]
     __shared__ SelectShared<kSelThreads, KPT> sm;
     const int head = blockIdx.y;
@@ -405,6 +406,7 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float*
     const int64_t o0 = offsets[head];
     const int32_t k = (int32_t)(offsets[head + 1] - o0);
     const int32_t s = n_sink < n ? n_sink : n;
+    if (share == 0) share = (k + (int)gridDim.x - 1) / (int)gridDim.x;
     const int32_t r0 = (int32_t)blockIdx.x * share;
     const int32_t r1 = r0 + share < k ? r0 + share : k;            // output rows r0 .. r1-1 are this workgroup's
     if (r0 >= r1 && blockIdx.x > 0) return;
@@ -420,7 +422,7 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float*
         }
     }
     if (r0 >= r1) return;
-    select_core<kSelThreads, KPT, true>(x, n, s, k, sm, stage, n, nullptr, Threshold{kNoThreshold, 0u}, r0, r1);
+    select_core<kSelThreads, KPT, true>(x, n, s, k, sm, stage, n, nullptr, known ? known[head] : Threshold{kNoThreshold, 0u}, r0, r1);
     const int32_t count = r1 - r0;
     for (int32_t p = tid; p < count; p += kSelThreads) indices[o0 + r0 + p] = stage[p];
     constexpr int kRows = kSelThreads / ROW_U4, kFlight = 4;           // rows per instruction, and of each tensor in flight per thread
@@ -494,25 +496,28 @@ bool select_gather_applicable(const curdkv_ctx* ctx, int64_t n, int64_t total) {
 template <int KPT, int ROW_U4>
 static hipError_t launch_gather(const curdkv_ctx* ctx, const float* raw, float* scores, int32_t n, int32_t n_sink,
                                 const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
-                                int scale_blocks, const SelectGather& g, int dyn) {
+                                int scale_blocks, const SelectGather& g, const Threshold* known, int dyn) {
     if (dyn > 0)
         return hipFuncSetAttribute((const void*)select_gather_kernel<KPT, ROW_U4>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
+    // max_budget < 0: the budgets are on the device, and every workgroup takes an equal share of its head's rows
     const int64_t places = ctx->num_cu / ctx->heads;
     int64_t share = (max_budget + places - 1) / places;
     if (share < kSelThreads / ROW_U4) share = kSelThreads / ROW_U4;           // every lane has something to copy
+    const int64_t shares = max_budget < 0 ? places : (max_budget + share - 1) / share;
+    if (max_budget < 0) share = 0;
     const GatherArgs ga{(const u32x4*)g.K, (const u32x4*)g.V, (u32x4*)g.K_out, (u32x4*)g.V_out};
-    const dim3 grid((unsigned)((max_budget + share - 1) / share), (unsigned)ctx->heads);
+    const dim3 grid((unsigned)shares, (unsigned)ctx->heads);
     select_gather_kernel<KPT, ROW_U4><<<grid, kSelThreads, (size_t)n * 4, stream>>>(
-        raw, scores, n, n_sink, d_offsets, indices, ctx->d_partial, scale_blocks, (int)share, ga);
+        raw, scores, n, n_sink, d_offsets, indices, ctx->d_partial, scale_blocks, (int)share, ga, known);
     return hipGetLastError();
 }
 
 template <int ROW_U4>
 static hipError_t gather_by_keys(const curdkv_ctx* ctx, const float* raw, float* scores, int32_t n, int32_t n_sink,
                                  const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
-                                 int scale_blocks, const SelectGather& g, int dyn = 0) {
+                                 int scale_blocks, const SelectGather& g, const Threshold* known, int dyn = 0) {
     auto go = [&](auto kpt) {
-        return launch_gather<decltype(kpt)::value, ROW_U4>(ctx, raw, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g, dyn);
+        return launch_gather<decltype(kpt)::value, ROW_U4>(ctx, raw, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g, known, dyn);
     };
     using std::integral_constant;
     if (n <= 4 * kSelThreads) return go(integral_constant<int, 4>{});
@@ -523,10 +528,11 @@ static hipError_t gather_by_keys(const curdkv_ctx* ctx, const float* raw, float*
 
 hipError_t launch_select_gather(const curdkv_ctx* ctx, const float* raw, float* scores, int64_t n, int32_t n_sink,
                                 const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
-                                int scale_blocks, const SelectGather& g) {
+                                int scale_blocks, const SelectGather& g, const void* known_thresholds) {
+    const Threshold* known = static_cast<const Threshold*>(known_thresholds);
     return ctx->cfg.dtype == CURDKV_DTYPE_BF16
-        ? gather_by_keys<16>(ctx, raw, scores, (int32_t)n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g)
-        : gather_by_keys<32>(ctx, raw, scores, (int32_t)n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g);
+        ? gather_by_keys<16>(ctx, raw, scores, (int32_t)n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g, known)
+        : gather_by_keys<32>(ctx, raw, scores, (int32_t)n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g, known);
 }
 
 hipError_t configure_select(curdkv_ctx* ctx) {
@@ -536,8 +542,8 @@ hipError_t configure_select(curdkv_ctx* ctx) {
     for (int kpt : {4, 8, 16, 32}) {
         const SelectGather none{};
         e = ctx->cfg.dtype == CURDKV_DTYPE_BF16
-            ? gather_by_keys<16>(ctx, nullptr, nullptr, kpt * kSelThreads, 0, nullptr, 0, nullptr, nullptr, 0, none, dyn)
-            : gather_by_keys<32>(ctx, nullptr, nullptr, kpt * kSelThreads, 0, nullptr, 0, nullptr, nullptr, 0, none, dyn);
+            ? gather_by_keys<16>(ctx, nullptr, nullptr, kpt * kSelThreads, 0, nullptr, 0, nullptr, nullptr, 0, none, nullptr, dyn)
+            : gather_by_keys<32>(ctx, nullptr, nullptr, kpt * kSelThreads, 0, nullptr, 0, nullptr, nullptr, 0, none, nullptr, dyn);
         if (e != hipSuccess) return e;
     }
     e = hipFuncSetAttribute((const void*)select_reg_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
@@ -557,8 +563,8 @@ hipError_t launch_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_
     const Threshold* known = static_cast<const Threshold*>(known_thresholds);
     const int32_t n32 = (int32_t)n;
     const int ws = write_scaled ? 1 : 0;
-    if (!known && split_applicable(ctx, n, scale_blocks > 0))
-        return launch_split_select(ctx, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, write_scaled, gather);
+    if (split_applicable(ctx, n, scale_blocks > 0))
+        return launch_split_select(ctx, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, write_scaled, known_thresholds, gather);
     if (n <= 4 * kSelThreads) return launch_reg<4>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);
     if (n <= 8 * kSelThreads) return launch_reg<8>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);
     if (n <= 16 * kSelThreads) return launch_reg<16>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);

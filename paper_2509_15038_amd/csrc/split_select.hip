@@ -92,6 +92,7 @@ struct SplitArgs {
     int scale_blocks, write_scaled;                // as in launch_select
     int part;                                      // tokens per workgroup of step 2, a multiple of 512
     int hists;                                     // histograms per head
+    const Threshold* known;                        // as in launch_select, or nullptr
 };
 
 // k - s' and whether anything has to be searched (not all of the candidates are kept, nor none)
@@ -113,6 +114,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_hist_kernel(SplitArgs a) 
     const int32_t n = a.n, s = a.n_sink < n ? a.n_sink : n;
     uint32_t m;
     if (!needs_search((int32_t)(a.offsets[head + 1] - a.offsets[head]), n, s, &m)) return;
+    if (a.known && a.known[head].key31 != kNoThreshold) return;
     const int32_t part = (n + a.hists - 1) / a.hists;
     const int32_t j0 = (int32_t)blockIdx.x * part;
     const int32_t j1 = j0 + part < n ? j0 + part : n;
@@ -159,6 +161,8 @@ __device__ __forceinline__ uint32_t wave_find(const uint32_t (&c)[PER], uint32_t
     return (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
 }
 
+// KNOWN: a.known is given.
+template <bool KNOWN>
 __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) {
     __shared__ uint32_t exps[256], fine[64], found[2];
     const int head = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
@@ -168,10 +172,13 @@ __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) 
     const int32_t j1 = j0 + a.part < n ? j0 + a.part : n;
     float* sc = a.scores + (size_t)head * n;
     // all of the first loads go out together, before anything is decided
+    const uint32_t given = KNOWN ? a.known[head].key31 : kNoThreshold;
     uint32_t ce = 0;                               // thread (half, exponent): half of the histograms each
     const uint32_t* co = a.ws.coarse + (size_t)head * a.ws.hists * 256 + (tid & 255);
+    if (!KNOWN || given == kNoThreshold) {
 #pragma unroll 8
-    for (int h = tid >> 8; h < a.hists; h += 2) ce += co[h * 256];
+        for (int h = tid >> 8; h < a.hists; h += 2) ce += co[h * 256];
+    }
     constexpr int kU = 8;
     float v[kU];
     auto load = [&](int32_t b) {
@@ -187,8 +194,10 @@ __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) 
     if (!search && !write) return;
     load(j0);
     const HeadScale scale = head_scale(head_partial(a.partial + (size_t)head * kMaxBlocksPerHead, a.scale_blocks), a.scale_blocks, n);
-    uint32_t lo = 0, hi = 0;
-    if (search) {
+    uint32_t lo = given, hi = given;
+    if (KNOWN && search && given != kNoThreshold) {
+        if (blockIdx.x == 0 && tid == 0) a.ws.range[head] = uint2{lo, hi};
+    } else if (search) {
         if (tid < 64) fine[tid] = 0;
         if (tid < 256) exps[tid] = ce;
         __syncthreads();
@@ -307,8 +316,9 @@ __device__ __forceinline__ void pick_digit(uint32_t* hist, uint32_t* digit, uint
 }
 
 // ROW_U4 > 0: the workgroup also copies its share's rows of K and V (gather step of Algorithm 1);
-// share <= kSplitShare then.
-template <int ROW_U4>
+// share <= kSplitShare then.  KNOWN: budgets and thresholds come from the budget allocation, on the device: a workgroup's share is
+// the head's rows by the workgroups, listed kSplitShare at a time where it copies them.
+template <int ROW_U4, bool KNOWN>
 __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, int32_t* __restrict__ indices, int share,
                                                                    GatherArgs ga) {
     __shared__ EmitShared sm;
@@ -334,14 +344,25 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
     const HeadScale scale = head_scale(head_partial(a.partial + (size_t)head * kMaxBlocksPerHead, scale_blocks), scale_blocks, n);
     const float* sc = a.scores + (size_t)head * n;
     const int32_t k = (int32_t)(o1 - o0);
-    const int32_t r0 = (int32_t)blockIdx.x * share;
-    const int32_t r1 = r0 + share < k ? r0 + share : k;            // output rows r0 .. r1-1 are this workgroup's
+    if (KNOWN) share = (k + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int32_t begin = (int32_t)blockIdx.x * share;
+    const int32_t end = begin + share < k ? begin + share : k;     // output rows begin .. end-1 are this workgroup's
     uint32_t m;
     const bool search = needs_search(k, n, s, &m);
-    if (r0 >= r1) return;
+    if (begin >= end) return;
     int32_t* out = indices + o0;
+    // rows r0 .. r1-1 are being listed: all of them, or as many as the stage takes
+    constexpr bool kPieces = KNOWN && ROW_U4 > 0;
+    int32_t r0 = begin, r1 = kPieces && end - begin > kSplitShare ? begin + kSplitShare : end;
     auto put = [&](int32_t p, int32_t j) {                         // row p of the head is token j
         if (ROW_U4) stage[p - r0] = j; else out[p] = j;
+    };
+    auto next = [&]() {
+        if (!kPieces) return false;
+        r0 = r1;
+        r1 = end - r0 > kSplitShare ? r0 + kSplitShare : end;
+        if (r0 < end) __syncthreads();                             // the stage has been read
+        return r0 < end;
     };
     auto gather = [&]() {
         if constexpr (ROW_U4 > 0) {
@@ -374,8 +395,10 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
         }
     };
     if (!search) {                                                 // tokens 0 .. k-1: sinks only, or everything
-        for (int32_t j = r0 + tid; j < r1; j += kSplitThreads) put(j, j);
-        gather();
+        do {
+            for (int32_t j = r0 + tid; j < r1; j += kSplitThreads) put(j, j);
+            gather();
+        } while (next());
         return;
     }
     // ---- the bitmaps -------------------------------------------------------------------------------
@@ -549,6 +572,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
     }
     __syncthreads();
     // ---- this workgroup's share ----------------------------------------------------------------------------
+    do {
     for (int32_t j = r0 + tid; j < r1 && j < s; j += kSplitThreads) put(j, j);
     for (int q = tid; q < words * 4; q += kSplitThreads) {         // a thread per quarter word (16 tokens)
         const int w = q >> 2, part = q & 3;
@@ -564,6 +588,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
         }
     }
     gather();
+    } while (next());
 }
 
 // Which heads take this route.  One call, this against one workgroup per head (us): 1 head of 32768
@@ -588,8 +613,9 @@ static bool emit_gathers(const curdkv_ctx* ctx, int64_t total) { return total <=
 
 hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
                                const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
-                               int scale_blocks, bool write_scaled, SelectGather* gather) {
-    SplitArgs a{carve(ctx), scores, (int32_t)n, n_sink, d_offsets, ctx->d_partial, scale_blocks, write_scaled ? 1 : 0, 0, scale_blocks};
+                               int scale_blocks, bool write_scaled, const void* known_thresholds, SelectGather* gather) {
+    SplitArgs a{carve(ctx), scores, (int32_t)n, n_sink, d_offsets, ctx->d_partial, scale_blocks, write_scaled ? 1 : 0, 0, scale_blocks,
+                static_cast<const Threshold*>(known_thresholds)};
     if (scale_blocks == 0) {
         int64_t h = ((int64_t)ctx->num_cu * 2 + ctx->heads - 1) / ctx->heads;
         const int64_t least = (n + 8191) / 8192;
@@ -601,7 +627,9 @@ hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, 
     int64_t part = (n + parts - 1) / parts;
     if (part > 16384) part = 16384;
     a.part = (int)((part + kSplitThreads - 1) / kSplitThreads * kSplitThreads);
-    split_flag_kernel<<<dim3((unsigned)((n + a.part - 1) / a.part), (unsigned)ctx->heads), kSplitThreads, 0, stream>>>(a);
+    const dim3 parts_grid((unsigned)((n + a.part - 1) / a.part), (unsigned)ctx->heads);
+    if (a.known) split_flag_kernel<true><<<parts_grid, kSplitThreads, 0, stream>>>(a);
+    else split_flag_kernel<false><<<parts_grid, kSplitThreads, 0, stream>>>(a);
     const bool with_gather = gather && gather->total > 0 && emit_gathers(ctx, gather->total);
     // shares such that there are about two workgroups per compute unit, or one for lists alone: each resolves the
     // threshold of its head again, which two of a unit do no sooner than one after the other.  With 4096 rows each whatever their number,
@@ -615,16 +643,25 @@ hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, 
         share = (max_budget + places - 1) / places;
         if (share < 4096) share = 4096;
     }
-    const int64_t shares = (max_budget + share - 1) / share;
+    int64_t shares = (max_budget + share - 1) / share;
+    if (max_budget < 0) {                          // every workgroup takes an equal share of its head's rows
+        shares = (ctx->num_cu * (with_gather ? 2 : 1) + ctx->heads - 1) / ctx->heads;
+        share = 0;
+    }
     const dim3 grid((unsigned)(shares > 0 ? shares : 1), (unsigned)ctx->heads);
     GatherArgs ga{};
     if (with_gather) {
         ga = GatherArgs{(const u32x4*)gather->K, (const u32x4*)gather->V, (u32x4*)gather->K_out, (u32x4*)gather->V_out};
         gather->done = true;
     }
-    if (!with_gather) split_emit_kernel<0><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga);
-    else if (ctx->cfg.dtype == CURDKV_DTYPE_BF16) split_emit_kernel<16><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga);
-    else split_emit_kernel<32><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga);
+    auto emit = [&](auto known) {
+        constexpr bool KNOWN = decltype(known)::value;
+        if (!with_gather) split_emit_kernel<0, KNOWN><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga);
+        else if (ctx->cfg.dtype == CURDKV_DTYPE_BF16) split_emit_kernel<16, KNOWN><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga);
+        else split_emit_kernel<32, KNOWN><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga);
+    };
+    if (max_budget < 0) emit(std::true_type{});
+    else emit(std::false_type{});
     return hipGetLastError();
 }
 
