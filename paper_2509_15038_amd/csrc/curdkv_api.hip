@@ -351,8 +351,8 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
         return launch_fused(ctx, K, V, n, n_sink, ctx->plan.d_offsets, scores, indices, K_out, V_out, st) == hipSuccess
                    ? CURDKV_OK : CURDKV_ERR_HIP;
     const bool scores_wanted = scores != nullptr;
-    const bool with_hist = !fusable && split_applicable(ctx, n, true);
-    const bool together = !fusable && !with_hist && select_gather_applicable(ctx, n, total);
+    const bool split = !fusable && split_applicable(ctx, n, true), with_hist = split && split_counts_in_scan(ctx, n);
+    const bool together = !fusable && !split && select_gather_applicable(ctx, n, total);
     if (!scores && !together) {
         if (!ctx->d_scores_ws &&
             hipMalloc((void**)&ctx->d_scores_ws, (size_t)ctx->heads * (size_t)ctx->cfg.max_tokens * sizeof(float)) != hipSuccess) {
@@ -378,7 +378,8 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     if (together)
         return launch_select_gather(ctx, ctx->d_raw_ws, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st, bph, gather) == hipSuccess
                    ? CURDKV_OK : CURDKV_ERR_HIP;
-    if (launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st, bph, scores_wanted, nullptr, &gather) != hipSuccess)
+    if (launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st, bph, scores_wanted, nullptr, &gather,
+                      with_hist ? bph : 0) != hipSuccess)
         return CURDKV_ERR_HIP;
     if (total == 0 || gather.done) return CURDKV_OK;
     return launch_compact(ctx, K, V, n, indices, ctx->plan.d_offsets, total, K_out, V_out, st) == hipSuccess

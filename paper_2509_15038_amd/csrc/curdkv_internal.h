@@ -13,7 +13,7 @@ namespace curdkv {
 constexpr int kHeadDim = 128;          // d the kernels are written for
 constexpr int kColBlock = 32;          // sketch columns per MFMA tile (M of the 32x32 tile)
 constexpr int kMaxColBlocks = 4;       // r padded to 32, 64 or 128
-constexpr int kMaxBlocksPerHead = 64;  // partial sums kept per (layer, group)
+constexpr int kMaxBlocksPerHead = 256; // partial sums kept per (layer, group): one head can have a workgroup per compute unit
 constexpr int kTileTokens = 32;        // tokens per wave tile
 constexpr int kCompactRowsPerBlock = 128;  // output rows per entry of the gather's table of heads
 constexpr int kFusedGatherMaxPercent = 11;  // curdkv_compress: share of rows kept up to which the fused kernel also gathers
@@ -111,7 +111,7 @@ struct SelectGather {
 hipError_t launch_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
                          const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
                          int scale_blocks = 0, bool write_scaled = true,
-                         const void* known_thresholds = nullptr, SelectGather* gather = nullptr);
+                         const void* known_thresholds = nullptr, SelectGather* gather = nullptr, int hists = 0);
 // Few, short heads, one call: selection and gather in one launch.  `raw`: the un-normalised products (ctx->d_raw_ws);
 // scores: where the normalised ones go, or nullptr.  max_budget < 0: the budgets exist on the device only.
 bool select_gather_wanted(const curdkv_ctx* ctx);      // the context needs the workspace
@@ -122,7 +122,7 @@ hipError_t launch_select_gather(const curdkv_ctx* ctx, const float* raw, float* 
                                 int scale_blocks, const SelectGather& gather, const void* known_thresholds = nullptr);
 // gather given: the selection may copy the kept rows itself; gather->done says whether it has.
 // split_select.hip: the same for long heads, several workgroups per head (workspace ctx->d_split_ws).
-// scale_blocks > 0: step 1's histograms, scale_blocks of them per head, have been made by launch_scores.
+// hists > 0: step 1's histograms, so many of them per head, have been made by launch_scores; otherwise they are made here.
 bool split_wanted(const curdkv_ctx* ctx);              // some n <= max_tokens may take it: the context needs the workspace
 bool split_applicable(const curdkv_ctx* ctx, int64_t n, bool one_call);   // one_call: scores not normalised yet, histograms from launch_scores
 size_t split_workspace_bytes(const curdkv_ctx* ctx);
@@ -132,7 +132,8 @@ uint32_t* split_coarse(const curdkv_ctx* ctx);         // [heads][split_hists][2
 constexpr int kSplitMaxHeads = 128;                    // (layer, group) pairs the split is used for (its workspace takes 9 KB per histogram, 64 per pair up to 32 pairs and 32 beyond, and 32 KB of bitmaps at most: 0.62 or 0.33 MB a pair)
 hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
                                const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
-                               int scale_blocks, bool write_scaled, const void* known_thresholds, SelectGather* gather);
+                               int scale_blocks, bool write_scaled, const void* known_thresholds, SelectGather* gather, int hists);
+bool split_counts_in_scan(const curdkv_ctx* ctx, int64_t n);      // one call: the histograms are launch_scores' to make
 hipError_t launch_compact(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n,
                           const int32_t* indices, const int64_t* d_offsets, int64_t total,
                           void* K_out, void* V_out, hipStream_t stream,

@@ -259,7 +259,7 @@ __global__ __launch_bounds__(256) void fold_kernel(const float* __restrict__ sq,
 // head, writing its scores in two bursts, beats any split by 2.5-3.5 % although units stay idle
 // (192 heads: 562 us against 576 for four per head; 224: 649 against 671; 448: 1305 against
 // 1338).
-static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
+static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n, int64_t most_blocks = kMaxBlocksPerHead) {
     const int64_t tiles = (n + kTileTokens - 1) / kTileTokens;
     const bool wide = ctx->cfg.dtype == CURDKV_DTYPE_BF16 && ctx->col_blocks > 2 && !ctx->cfg.no_projection;
     const bool f32 = ctx->cfg.dtype == CURDKV_DTYPE_F32;         // one workgroup per compute unit, like the wide kernel
@@ -277,7 +277,7 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
     const bool spare = ctx->cfg.dtype == CURDKV_DTYPE_BF16 && ctx->heads * 16 <= ctx->num_cu && (int64_t)ctx->heads * tiles >= 8 * waves * slots;
     if (spare) slots -= slots / 16;
     int64_t cap = (tiles + waves - 1) / waves;                                     // at least one tile per wave
-    if (cap > kMaxBlocksPerHead) cap = kMaxBlocksPerHead;
+    if (cap > most_blocks) cap = most_blocks;
     int64_t lo = (tiles + waves * stage - 1) / (waves * stage);
     if (lo > cap) lo = cap;
     if (lo < 1) lo = 1;
@@ -286,7 +286,7 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n) {
         if (in_last * 4 >= 3 * (int64_t)ctx->num_cu) return 1;
     }
     // (up to one workgroup per place where the heads are few: 8 heads of 131072 tokens 105 us on 184 units, 99 on 256;
-    // the whole call for 1 head of 32768 tokens 52 us with 17 workgroups, 33 with 64)
+    // curdkv_scores of 1 head of 131072 tokens 34.6 us with 64 workgroups, 18.3 with 256, in fp32 77.1 and 36.8)
     const int64_t fill = (slots + ctx->heads - 1) / ctx->heads;
     const int64_t most = lo + 15 > fill ? lo + 15 : fill;
     int64_t hi = most < cap ? most : cap;
@@ -321,9 +321,9 @@ static int few_blocks_per_head(const curdkv_ctx* ctx, int64_t n, bool running) {
 // Calls of few tokens in all take scan_few.  Measured, us per curdkv_scores_append, the other kernel -> this one.
 // fp32, r = 20 / 64 / 128: 16384 tokens in 8 heads 17.9 -> 12.1 / 23.8 -> 16.4 / 34.9 -> 21.6, 32768 tokens in 8
 // heads 18.4 -> 16.1 / 24.7 -> 24.1 / 36.5 -> 36.4; in 256 heads level at 16384 tokens (13.2 -> 13.2 at
-// r = 64) and behind at 32768 (15.3 -> 23.4).  One long head has at most 64 workgroups: 4096
+// r = 64) and behind at 32768 (15.3 -> 23.4).  Many steps in a workgroup cost more than they save (one head in 64 workgroups: 4096
 // tokens, 4 steps each, 18.0 -> 11.3 / 23.8 -> 15.5 / 34.7 -> 23.2; 16384 tokens, 16 steps each,
-// 20.7 -> 22.1 / 25.3 -> 36.2 / 36.2 -> 64.6.
+// 20.7 -> 22.1 / 25.3 -> 36.2 / 36.2 -> 64.6).
 // bf16: 256 heads of one token 4.4 -> 2.8 / 4.7 -> 3.1 / 5.5 -> 3.6; 8192 tokens in 8 heads 7.9 -> 5.1 / 8.6 -> 6.2 / 10.4 -> 8.0;
 // 16384 in 8 heads 8.2 -> 5.9 / 9.0 -> 7.9 / 10.6 -> 11.4 and in 64 heads 6.6 -> 6.4 / 7.3 -> 8.1 / 9.0 -> 11.5; one head
 // of 4096 tokens 8.6 -> 5.5 / 9.3 -> 7.4 / 11.1 -> 11.1.  Wide sketches in many heads end earlier, as each row goes to more
@@ -362,7 +362,7 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
                          bool* summed, bool with_hist, int32_t n_sink) {
     if (out_stride <= 0) out_stride = n;
     const bool few = few_tokens(ctx, n, sums != nullptr) && !with_hist;
-    const int bph = few ? few_blocks_per_head(ctx, n, sums != nullptr) : pick_blocks_per_head(ctx, n);
+    const int bph = few ? few_blocks_per_head(ctx, n, sums != nullptr) : pick_blocks_per_head(ctx, n, with_hist ? split_hists(ctx) : kMaxBlocksPerHead);
     if (blocks_per_head) *blocks_per_head = bph;
     if (bph != 1) sums = nullptr;                 // several blocks per head: the caller adds the partials
     if (summed) *summed = sums != nullptr;
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(256) void accumulate_sums_kernel(const float* __res
                                                               double* __restrict__ sums, int heads, int reset) {
     const int head = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (head >= heads) return;
-    const double total = wave_total((double)head_partial(partial + (size_t)head * kMaxBlocksPerHead, blocks_per_head));
+    const double total = wave_total(head_partial(partial + (size_t)head * kMaxBlocksPerHead, blocks_per_head));
     if ((threadIdx.x & 63) == 0) sums[head] = (reset ? 0.0 : sums[head]) + total;
 }
 

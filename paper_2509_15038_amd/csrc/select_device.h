@@ -76,11 +76,18 @@ struct HeadScale {
         return !on ? v : (zero ? uniform : v * inv);
     }
 };
-// A head's partial sums, a lane each (at most 64); the load can go out long before head_scale needs it.
-__device__ __forceinline__ float head_partial(const float* __restrict__ partial, int blocks) {
-    static_assert(kMaxBlocksPerHead <= 64, "a lane per partial sum");
+// A lane's share of a head's partial sums, one each up to 64; the loads can go out long before head_scale needs them.
+__device__ __forceinline__ double head_partial(const float* __restrict__ partial, int blocks) {
     const int lane = threadIdx.x & 63;
-    return lane < blocks ? partial[lane] : 0.f;
+    double sum = lane < blocks ? (double)partial[lane] : 0.0;
+    if (blocks > 64) {
+        static_assert(kMaxBlocksPerHead == 256, "four partial sums a lane");
+        float x[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) x[i] = lane + 64 * (i + 1) < blocks ? partial[lane + 64 * (i + 1)] : 0.f;
+        sum += (double)x[0] + ((double)x[1] + (double)x[2]);
+    }
+    return sum;
 }
 // The sum of a double over the 64 lanes, in every lane: neighbours first, then pairs, and so on, by
 // lane exchanges in registers.  All 64 lanes must be there.
@@ -122,9 +129,9 @@ __device__ __forceinline__ HeadScale scale_by(double tot, int64_t n) {
     h.uniform = (float)(1.0 / (double)n);
     return h;
 }
-__device__ __forceinline__ HeadScale head_scale(float mine, int blocks, int64_t n) {
+__device__ __forceinline__ HeadScale head_scale(double mine, int blocks, int64_t n) {
     if (blocks <= 0) return HeadScale{0.f, 0.f, false, false};
-    return scale_by(wave_total((double)mine), n);
+    return scale_by(wave_total(mine), n);
 }
 
 // A threshold the caller already knows (the head-wise budget allocation finds one per layer):

@@ -349,7 +349,7 @@ __global__ __launch_bounds__(kSelThreads) void select_reg_kernel(float* __restri
     // all loads go out together, before anything is decided: offsets, partial sums and scores fetched one
     // after the other each cost a trip to memory (one call, 8 heads of 8192 tokens: 21.0 -> 19.7 us together with
     // the sum of the partials)
-    const float mine = head_partial(partial + (size_t)head * kMaxBlocksPerHead, scale_blocks);
+    const double mine = head_partial(partial + (size_t)head * kMaxBlocksPerHead, scale_blocks);
     float v[KPT];
 #pragma unroll
     for (int it = 0; it < KPT; ++it) {
@@ -396,7 +396,7 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float*
     const int head = blockIdx.y;
     const int tid = threadIdx.x;
     raw += (size_t)head * n;
-    const float mine = head_partial(partial + (size_t)head * kMaxBlocksPerHead, scale_blocks);
+    const double mine = head_partial(partial + (size_t)head * kMaxBlocksPerHead, scale_blocks);
     float v[KPT];
 #pragma unroll
     for (int it = 0; it < KPT; ++it) {
@@ -559,12 +559,12 @@ hipError_t configure_select(curdkv_ctx* ctx) {
 
 hipError_t launch_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
                          const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
-                         int scale_blocks, bool write_scaled, const void* known_thresholds, SelectGather* gather) {
+                         int scale_blocks, bool write_scaled, const void* known_thresholds, SelectGather* gather, int hists) {
     const Threshold* known = static_cast<const Threshold*>(known_thresholds);
     const int32_t n32 = (int32_t)n;
     const int ws = write_scaled ? 1 : 0;
     if (split_applicable(ctx, n, scale_blocks > 0))
-        return launch_split_select(ctx, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, write_scaled, known_thresholds, gather);
+        return launch_split_select(ctx, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, write_scaled, known_thresholds, gather, hists);
     if (n <= 4 * kSelThreads) return launch_reg<4>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);
     if (n <= 8 * kSelThreads) return launch_reg<8>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);
     if (n <= 16 * kSelThreads) return launch_reg<16>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);

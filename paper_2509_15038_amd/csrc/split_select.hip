@@ -64,7 +64,7 @@ static int words_for(int64_t max_tokens) {
 }
 
 // histograms per head: what pick_blocks_per_head (scores_kernels.hip) can ask for; fewer heads, more workgroups each
-int split_hists(const curdkv_ctx* ctx) { return ctx->heads <= 32 ? kMaxBlocksPerHead : 32; }
+int split_hists(const curdkv_ctx* ctx) { return ctx->heads <= 32 ? 64 : 32; }
 
 static SplitWorkspace carve(const curdkv_ctx* ctx) {
     SplitWorkspace w;
@@ -604,6 +604,12 @@ bool split_applicable(const curdkv_ctx* ctx, int64_t n, bool one_call) {
     return n > (one_call && ctx->heads <= 32 ? kSplitMinTokens : kSplitMinTokensElse);
 }
 
+// One or two long heads are better scored by more workgroups each than there are histograms, which are then made from
+// memory, a launch more.  One call, us, at most 64 workgroups a head that count and as many as there are units: 1 head of 32768
+// tokens 26.8 and 26.2, of 131072 50.6 and 36.8; 2 heads of 32768 26.9 and 27.6, of 65536 37.7 and 36.9, of 131072 59.8 and 53.3; 3 heads
+// put 192 workgroups on the chip as it is.
+bool split_counts_in_scan(const curdkv_ctx* ctx, int64_t n) { return ctx->heads > 2 || n <= (int64_t)ctx->heads * kSplitMinTokens; }
+
 uint32_t* split_hist(const curdkv_ctx* ctx) { return carve(ctx).hist; }
 uint32_t* split_coarse(const curdkv_ctx* ctx) { return carve(ctx).coarse; }
 
@@ -613,10 +619,10 @@ static bool emit_gathers(const curdkv_ctx* ctx, int64_t total) { return total <=
 
 hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
                                const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
-                               int scale_blocks, bool write_scaled, const void* known_thresholds, SelectGather* gather) {
-    SplitArgs a{carve(ctx), scores, (int32_t)n, n_sink, d_offsets, ctx->d_partial, scale_blocks, write_scaled ? 1 : 0, 0, scale_blocks,
+                               int scale_blocks, bool write_scaled, const void* known_thresholds, SelectGather* gather, int hists) {
+    SplitArgs a{carve(ctx), scores, (int32_t)n, n_sink, d_offsets, ctx->d_partial, scale_blocks, write_scaled ? 1 : 0, 0, hists,
                 static_cast<const Threshold*>(known_thresholds)};
-    if (scale_blocks == 0) {
+    if (hists == 0) {
         int64_t h = ((int64_t)ctx->num_cu * 2 + ctx->heads - 1) / ctx->heads;
         const int64_t least = (n + 8191) / 8192;
         if (h < least) h = least;
