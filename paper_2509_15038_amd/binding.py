@@ -1,5 +1,5 @@
-"""ctypes binding of libcurdkv.so: the same entry points as include/curdkv.h,
-argument marshalling only.  Every step of the path runs in the HIP kernels.
+"""Binding of libcurdkv.so: the same entry points as include/curdkv.h,
+argument marshalling only, by ctypes and, for the calls that a program makes over and over, the module _call.so.  Every step of the path runs in the HIP kernels.
 
 torch appears here only as the owner of device memory and streams: tensors are
 passed as raw pointers.  If the compiled library is missing the import of any
@@ -16,6 +16,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libcurdkv.so")
+CALL_PATH = os.path.join(_HERE, "_call.so")
 
 OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_HIP, ERR_OOM, ERR_TOO_LARGE = 0, -1, -2, -3, -4, -5
 DTYPE_F32, DTYPE_BF16 = 0, 1
@@ -73,6 +74,7 @@ def lib() -> C.CDLL:
     L.curdkv_strerror.restype = C.c_char_p
     for name in EXPORTS[:-1]:
         getattr(L, name).restype = C.c_int
+    _bind_calls(L)
     _lib = L
     return L
 
@@ -103,8 +105,6 @@ def curdkv_sketch_host(cfg: CurdkvConfig, layer: int, head: int) -> np.ndarray:
     return out
 
 
-# A call of one kernel on a few tokens takes the GPU 3 us, less than the marshalling took: what follows is written for
-# that (one token for 256 heads, a call among others: 7.8 us before, 5.3 now).
 def _ptr(t) -> int:
     """Device (torch) or host (numpy) buffer -> address; None -> NULL."""
     if t is None:
@@ -128,15 +128,30 @@ def _stream(stream) -> int:
     if stream is None:
         if _current_stream is None:
             import torch
-            raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-            if raw is None:                         # the same without a stream object, where torch offers it
+            raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+            if raw is None or device is None:       # the same without a stream object, where torch offers it
                 _current_stream = lambda: torch.cuda.current_stream().cuda_stream
             else:
-                _current_stream = lambda: raw(torch.cuda.current_device())
+                torch.cuda.current_device()         # (brings CUDA up; from then on the device is torch's to say at once)
+                _current_stream = lambda: raw(device())
         return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
+
+
+_call = None                                        # the module _call.so, bound to the library by lib()
+
+
+def _bind_calls(L) -> None:
+    global _call
+    if not os.path.exists(CALL_PATH):
+        raise RuntimeError(f"{CALL_PATH} is missing: build it with `python -m paper_2509_15038_amd.build`")
+    from paper_2509_15038_amd import _call as module
+    entry = [C.cast(getattr(L, "curdkv_" + name), C.c_void_p).value
+             for name in ("scores", "scores_append", "normalise", "select", "compact", "compress", "compress_adaptive")]
+    module.bind(*entry, _ptr, _stream)
+    _call = module
 
 
 class Context:
@@ -153,11 +168,13 @@ class Context:
         if rc != OK:
             self._h = None
             raise CurdkvError(rc, "curdkv_create")
+        self._address = self._h.value               # (0 once closed)
+        self._heads = self.heads
 
     def close(self):
         h = getattr(self, "_h", None)
         if h is not None and h.value:
-            self._h = None
+            self._h, self._address = None, 0
             self._destroy(h)
 
     __del__ = close
@@ -180,7 +197,7 @@ class Context:
             raise CurdkvError(rc, "curdkv_set_sketch")
 
     def scores(self, K, V, n: int, scores, stream=None):
-        rc = lib().curdkv_scores(self._h, _ptr(K), _ptr(V), int(n), _ptr(scores), _stream(stream))
+        rc = _call.scores(self._address, K, V, n, scores, stream)
         if rc != OK:
             raise CurdkvError(rc, "curdkv_scores")
 
@@ -191,27 +208,18 @@ class Context:
 
     def select(self, scores, n: int, budgets: np.ndarray, n_sink: int, offsets: np.ndarray,
                indices, stream=None):
-        assert budgets.dtype == np.int32 and offsets.dtype == np.int64
-        assert budgets.size == self.heads and offsets.size == self.heads + 1
-        rc = lib().curdkv_select(self._h, _ptr(scores), int(n), _host_ptr(budgets), int(n_sink),
-                                 _host_ptr(offsets), _ptr(indices), _stream(stream))
+        rc = _call.select(self._address, scores, n, budgets, n_sink, offsets, indices, stream, self._heads)
         if rc != OK:
             raise CurdkvError(rc, "curdkv_select")
 
     def compact(self, K, V, n: int, indices, offsets: np.ndarray, K_out, V_out, stream=None):
-        assert offsets.dtype == np.int64 and offsets.size == self.heads + 1
-        rc = lib().curdkv_compact(self._h, _ptr(K), _ptr(V), int(n), _ptr(indices),
-                                  _host_ptr(offsets), _ptr(K_out), _ptr(V_out), _stream(stream))
+        rc = _call.compact(self._address, K, V, n, indices, offsets, K_out, V_out, stream, self._heads)
         if rc != OK:
             raise CurdkvError(rc, "curdkv_compact")
 
     def compress(self, K, V, n: int, budgets: np.ndarray, n_sink: int, offsets: np.ndarray,
                  scores, indices, K_out, V_out, stream=None):
-        assert budgets.dtype == np.int32 and offsets.dtype == np.int64
-        assert budgets.size == self.heads and offsets.size == self.heads + 1
-        rc = lib().curdkv_compress(self._h, _ptr(K), _ptr(V), int(n), _host_ptr(budgets),
-                                   int(n_sink), _host_ptr(offsets), _ptr(scores), _ptr(indices),
-                                   _ptr(K_out), _ptr(V_out), _stream(stream))
+        rc = _call.compress(self._address, K, V, n, budgets, n_sink, offsets, scores, indices, K_out, V_out, stream, self._heads)
         if rc != OK:
             raise CurdkvError(rc, "curdkv_compress")
 
@@ -237,21 +245,17 @@ class Context:
 
     def compress_adaptive(self, K, V, n: int, budget: int, n_sink: int, alpha: float, scores,
                           budgets_out, offsets_out, indices, K_out, V_out, stream=None):
-        rc = lib().curdkv_compress_adaptive(self._h, _ptr(K), _ptr(V), int(n), int(budget), int(n_sink),
-                                            float(alpha), _ptr(scores), _ptr(budgets_out),
-                                            _ptr(offsets_out), _ptr(indices), _ptr(K_out), _ptr(V_out),
-                                            _stream(stream))
+        rc = _call.compress_adaptive(self._address, K, V, n, budget, n_sink, alpha, scores, budgets_out, offsets_out, indices, K_out,
+                                     V_out, stream)
         if rc != OK:
             raise CurdkvError(rc, "curdkv_compress_adaptive")
 
     def scores_append(self, K_new, V_new, m: int, n_old: int, stride: int, raw, sums, stream=None):
-        rc = lib().curdkv_scores_append(self._h, _ptr(K_new), _ptr(V_new), int(m), int(n_old),
-                                        int(stride), _ptr(raw), _ptr(sums), _stream(stream))
+        rc = _call.scores_append(self._address, K_new, V_new, m, n_old, stride, raw, sums, stream)
         if rc != OK:
             raise CurdkvError(rc, "curdkv_scores_append")
 
     def normalise(self, raw, sums, stride: int, n: int, scores, stream=None):
-        rc = lib().curdkv_normalise(self._h, _ptr(raw), _ptr(sums), int(stride), int(n),
-                                    _ptr(scores), _stream(stream))
+        rc = _call.normalise(self._address, raw, sums, stride, n, scores, stream)
         if rc != OK:
             raise CurdkvError(rc, "curdkv_normalise")

@@ -1,4 +1,5 @@
-"""Compile the HIP sources into paper_2509_15038_amd/libcurdkv.so for gfx950.
+"""Compile the HIP sources into paper_2509_15038_amd/libcurdkv.so for gfx950, and the CPython module
+_call.so beside it (argument marshalling, no device code).
 
     python -m paper_2509_15038_amd.build
 
@@ -11,10 +12,12 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libcurdkv.so")
+CALL = os.path.join(HERE, "_call.so")
 SOURCES = ["curdkv_api.hip", "scores_kernels.hip", "select_kernels.hip", "split_select.hip", "compact_kernels.hip", "fused_kernel.hip", "adaptive_kernels.hip",
            "sketch_host.cpp"]
 
@@ -28,6 +31,11 @@ def build(verbose: bool = True) -> str:
            "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc")]
     cmd += ["-x", "hip"] + [os.path.join(HERE, "csrc", s) for s in SOURCES]
     cmd += ["-o", LIB]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(ROOT, "include"), os.path.join(HERE, "csrc", "call_module.cpp"), "-o", CALL]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
