@@ -283,7 +283,7 @@ struct AdaShared {
     uint32_t total_in;                            // keys inside the cut bin, all heads
     uint32_t slow;
     unsigned long long over;                      // sum of the heads' keys above the bin beyond their safeguards
-    uint32_t hist64[64];
+    uint32_t scratch[kListScratch];
 };
 
 __global__ __launch_bounds__(kAdaThreads) void ada_allot_kernel(
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(kAdaThreads) void ada_allot_kernel(
     const uint32_t my_above = tid < H ? ws.above[(size_t)layer * H + tid] : 0u;
     const uint32_t my_in = tid < H ? ws.inbin[(size_t)layer * H + tid] : 0u;
     if (tid == 0) { sm.slow = bstar >= (uint32_t)(kBins12 - 1) ? 1u : 0u; sm.over = 0; }
-    if (tid < 64) sm.hist64[tid] = 0;
+    if (tid < kListScratch) sm.scratch[tid] = 0;
     // A head whose safeguard ends inside the bin counts from there on only.  Usually there is none: heads
     // beyond their safeguard before the bin count all of its keys, the others none of them, and the threshold is the key
     // of one rank among the former's.
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(kAdaThreads) void ada_allot_kernel(
     if (!slow && by_rank && rank >= 1 && rank <= total_in) {
         uint32_t need;
         for (int h = tid; h < H; h += kAdaThreads) dig[h] = 0;
-        fixed = threshold_on_list<kAdaThreads>(reinterpret_cast<const int32_t*>(list), total_in, bstar, (uint32_t)rank, sm.hist64, &sm.digit,
+        fixed = threshold_on_list<kAdaThreads>(reinterpret_cast<const int32_t*>(list), total_in, bstar, (uint32_t)rank, sm.scratch, &sm.digit,
                                                &sm.want, &need);
         __syncthreads();
         for (uint32_t i = tid; i < total_in; i += kAdaThreads) {

@@ -178,16 +178,25 @@ __device__ __forceinline__ void find_bin_from_top(const uint32_t* hist, uint32_t
     static_assert(kPer >= 1 && kPer * THREADS == BINS, "bins must be a multiple of the threads");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t c[kPer], tot = 0;
+    if constexpr (kPer % 4 == 0) {                 // (hist is 16-byte aligned)
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        c[i] = hist[BINS - 1 - (tid * kPer + i)];
-        tot += c[i];
+        for (int i = 0; i < kPer; i += 4) {
+            const uint4 v = reinterpret_cast<const uint4*>(hist)[(BINS - 4 - tid * kPer - i) / 4];
+            c[i] = v.w; c[i + 1] = v.z; c[i + 2] = v.y; c[i + 3] = v.x;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) c[i] = hist[BINS - 1 - (tid * kPer + i)];
     }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) tot += c[i];
     uint32_t incl = wave_inclusive(tot);
     if (lane == 63) wave_tot[wave] = incl;
     __syncthreads();
-    uint32_t before = 0;
-    for (int w = 0; w < wave; ++w) before += wave_tot[w];
+    // the waves' totals by a lane each: one trip to the LDS instead of one per wave
+    const uint32_t waves = wave_inclusive(lane < THREADS / 64 ? wave_tot[lane] : 0u);
+    const int w = __builtin_amdgcn_readfirstlane(wave);
+    const uint32_t before = w > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)waves, w - 1) : 0u;
     uint32_t run = before + incl - tot;            // keys in higher bins
     if (run < want && want <= run + tot) {
 #pragma unroll
@@ -223,7 +232,7 @@ template <int THREADS, int KPT>
 __device__ __forceinline__ void build_hist12(const uint32_t (&x)[KPT], int32_t n, int32_t s,
                                              SelectShared<THREADS, KPT>& sm) {
     const int tid = threadIdx.x;
-    for (int i = tid; i < kBins12; i += THREADS) sm.hist[i] = 0;
+    for (int i = tid; i < kBins12 / 4; i += THREADS) reinterpret_cast<uint4*>(sm.hist)[i] = uint4{0, 0, 0, 0};
     __syncthreads();
     const uint32_t span = (uint32_t)(n - s);
     const uint32_t jt = (uint32_t)(tid - s);       // token - s of row 0, wraps for sinks
@@ -347,13 +356,16 @@ __device__ __forceinline__ uint32_t threshold_by_radix(uint32_t (&x)[KPT], int32
 
 // Resolves the 18 key bits below the bin number on a list of (key, token) pairs in LDS:
 // pairs[2i] = key, pairs[2i+1] = token of the i-th of `count` candidates, all of bin `bin`
-// (< 4095).  `want` = rank of the threshold among them, from the top.  Three 6-bit digits;
-// hist64 is LDS scratch of 64 zeroed words (left zeroed), digit/want_s LDS words.  Returns
+// (< 4095).  `want` = rank of the threshold among them, from the top.  scratch: kListScratch zeroed LDS words,
+// digit/want_s LDS words.  Returns
 // the threshold as (key & 0x7FFFFFFF) and, through *need, how many keys equal to it are still
 // to be kept.  All THREADS threads call it; ends with a barrier.
+constexpr uint32_t kListPairs = 128;               // keys up to which every one is compared with every other
+constexpr int kListScratch = 64 + (int)kListPairs;
+
 template <int THREADS>
 __device__ __forceinline__ uint32_t threshold_on_list(const int32_t* pairs, uint32_t count, uint32_t bin,
-                                                      uint32_t want, uint32_t* hist64, uint32_t* digit,
+                                                      uint32_t want, uint32_t* scratch, uint32_t* digit,
                                                       uint32_t* want_s, uint32_t* need) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (count <= 32u) {
@@ -378,6 +390,33 @@ __device__ __forceinline__ uint32_t threshold_on_list(const int32_t* pairs, uint
         *need = *want_s;
         return *digit;
     }
+    if (count <= kListPairs) {
+        // all waves compare: a thread has one key and an equal part of the others, which is the same for a wave's threads.
+        // Two barriers instead of six: selection of 8 heads of 8192 tokens 7.3 -> 6.9 us, of 112 of 10007 9.5 -> 9.0, the waves'
+        // totals in one read (find_bin_from_top) included; up to 256 keys the allotment of 8 heads' budgets took 0.6 us longer than with digits
+        const uint32_t places = count <= 64u ? 64u : 128u;      // threads 0 .. places-1 have the first part
+        const uint32_t i = (uint32_t)tid & (places - 1u), parts = (uint32_t)THREADS / places;
+        const uint32_t per = (count + parts - 1u) / parts;
+        const uint32_t j0 = (uint32_t)__builtin_amdgcn_readfirstlane(tid / (int)places) * per;
+        const uint32_t j1 = j0 + per < count ? j0 + per : count;
+        const uint32_t key = i < count ? (uint32_t)pairs[2 * i] & 0x7FFFFFFFu : 0u;
+        uint32_t sums = 0;                         // keys above in the lower half, equal ones in the upper
+#pragma unroll 4
+        for (uint32_t j = j0; j < j1; ++j) {
+            const uint32_t other = (uint32_t)pairs[2 * j] & 0x7FFFFFFFu;
+            sums += other > key ? 1u : other == key ? 0x10000u : 0u;
+        }
+        if (i < count && sums) atomicAdd(&scratch[64 + i], sums);
+        __syncthreads();
+        if ((uint32_t)tid < count) {               // (equal keys all write the same)
+            const uint32_t all = scratch[64 + tid], above = all & 0xFFFFu;
+            if (above < want && want <= above + (all >> 16)) { *digit = key; *want_s = want - above; }
+        }
+        __syncthreads();
+        *need = *want_s;
+        return *digit;
+    }
+    uint32_t* hist64 = scratch;
     uint32_t fixed = bin;                          // decided high part of (key & 0x7FFFFFFF): >> rem
     for (int rem = kBinShift; rem > 0; rem -= 6) {
         const int shift = rem - 6;
@@ -462,7 +501,7 @@ __device__ __forceinline__ void select_core(uint32_t (&x)[KPT], int32_t n, int32
     if (bstar < (uint32_t)(kBins12 - 1) && (int64_t)in_bin * 2 <= (int64_t)cap) {
         const uint32_t jt = (uint32_t)(tid - s);
         for (int i = tid; i < kWords; i += THREADS) sm.emask[i] = 0ull;
-        for (int i = tid; i < 64; i += THREADS) sm.hist[i] = 0;
+        for (int i = tid; i < kListScratch; i += THREADS) sm.hist[i] = 0;
         // ---- candidates in higher bins are kept; those inside the bin go to the list ---------
 #pragma unroll
         for (int it = 0; it < KPT; ++it) {

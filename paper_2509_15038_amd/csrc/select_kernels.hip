@@ -37,7 +37,7 @@ constexpr int kStreamSuper = 8 * kStreamChunk;            // tokens per compacti
 constexpr int kStreamWords = kStreamSuper / 64;           // bitmap words per super-chunk
 
 struct StreamShared {
-    uint32_t hist[kStreamBins];
+    alignas(16) uint32_t hist[kStreamBins];
     uint32_t list[kStreamList];
     unsigned long long gmask[kStreamWords], emask[kStreamWords];   // "above T" / "equal to T" flags
     uint32_t wpos[kStreamWords];                  // output position of a word's first kept token
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kSelThreads) void select_stream_kernel(float* __res
         if (bstar < (uint32_t)(kBins12 - 1) && in_bin * 2 <= (uint32_t)kStreamList) {
             const int words = (int)(chunks * (kStreamChunk / 64));
             for (int i = tid; i < words; i += kSelThreads) sm.emask[i] = 0ull;
-            for (int i = tid; i < 64; i += kSelThreads) sm.hist[i] = 0;
+            for (int i = tid; i < kListScratch; i += kSelThreads) sm.hist[i] = 0;
             float cur[kStreamU], nxt[kStreamU];
             load_chunk(cur, 0);
             for (uint32_t c = 0; c < chunks; ++c) {

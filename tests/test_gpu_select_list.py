@@ -36,6 +36,14 @@ def test_cut_bin_of_every_size(n, inside):
         assert np.array_equal(out[offsets[h]:offsets[h + 1]], want), (n, inside, h)
 
 
+# the sizes around which threads are dealt differently to the keys and to the parts of the others that they are compared
+# with, and where the digits take over
+@pytest.mark.parametrize("n", [3000, 33000])
+@pytest.mark.parametrize("inside", [47, 48, 49, 63, 65, 127, 128, 129])
+def test_cut_bin_compared_in_parts(n, inside):
+    test_cut_bin_of_every_size(n, inside)
+
+
 @pytest.mark.parametrize("n", [1, 2, 63, 65, 255, 257, 1025, 2049, 4099])
 @pytest.mark.parametrize("heads", [1, 5])
 def test_normalised_scores_add_up(n, heads):
