@@ -351,8 +351,8 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
         return launch_fused(ctx, K, V, n, n_sink, ctx->plan.d_offsets, scores, indices, K_out, V_out, st) == hipSuccess
                    ? CURDKV_OK : CURDKV_ERR_HIP;
     const bool scores_wanted = scores != nullptr;
-    const bool split = !fusable && split_applicable(ctx, n, true), with_hist = split && split_counts_in_scan(ctx, n);
-    const bool together = !fusable && !split && select_gather_applicable(ctx, n, total);
+    const bool together = !fusable && select_gather_applicable(ctx, n, total);
+    const bool split = !fusable && !together && split_applicable(ctx, n, true), with_hist = split && split_counts_in_scan(ctx, n);
     if (!scores && !together) {
         if (!ctx->d_scores_ws &&
             hipMalloc((void**)&ctx->d_scores_ws, (size_t)ctx->heads * (size_t)ctx->cfg.max_tokens * sizeof(float)) != hipSuccess) {

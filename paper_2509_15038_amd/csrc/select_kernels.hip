@@ -477,6 +477,9 @@ static hipError_t launch_reg(const curdkv_ctx* ctx, float* scores, int32_t n, in
 // of 16384, 10 %, 72.8 -> 70.5; 64 heads of 8192, 10 %, 74.6 -> 71.3; 128 heads of 2048, 10 %, 40.6 -> 38.5.  With more rows the
 // gather kernel's many small workgroups make up for its launch: half kept of 64 heads of 8192 tokens (262144 rows)
 // 106.4 -> 105.6, of 128 heads 185.9 -> 190.6; a tenth of 64 heads of 32768 (209664) 241.8 -> 242.5: hence 512 rows a unit.
+// The split selection, which comes second, is behind up to the longest head this holds, as long as the rows are few: a tenth kept, this
+// and split, 1 head of 32768 tokens 22.6 and 26.9, 2 heads of 24600 22.2 and 27.3, 8 of 32768 44.8 and 49.6, 32 of 32768 131.3 and 132.4
+// (half kept, separate kernels and split, 194.1 and 192.5).
 // Smaller workgroups for shorter heads give nothing (256 threads: 1024 tokens 9.9, 8192 tokens 21.7).
 constexpr int64_t kGatherMaxTokens = 32 * kSelThreads;             // what a workgroup's registers and LDS hold
 constexpr int64_t kGatherRowsPerUnit = 512;
@@ -512,6 +515,30 @@ static hipError_t launch_gather(const curdkv_ctx* ctx, const float* raw, float* 
     return hipGetLastError();
 }
 
+// Keys per thread: the smallest of these that holds the head (every pass of the selection walks all of a thread's keys,
+// present or not).  With 4, 8, 16 and 32 only: curdkv_select of 112 heads of 10007 tokens 9.0 us, so 7.9; 256 heads of 1000 5.1 and 4.6, of
+// 18000 15.0 and 12.7; one call for 8 heads of 18000 31.7 and 29.1.
+constexpr int kKeyVariants[] = {1, 2, 3, 4, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32};
+template <class Go>
+static hipError_t by_keys_per_thread(int64_t n, Go go) {
+    using std::integral_constant;
+    const int64_t kpt = (n + kSelThreads - 1) / kSelThreads;
+    if (kpt <= 1) return go(integral_constant<int, 1>{});
+    if (kpt <= 2) return go(integral_constant<int, 2>{});
+    if (kpt <= 3) return go(integral_constant<int, 3>{});
+    if (kpt <= 4) return go(integral_constant<int, 4>{});
+    if (kpt <= 6) return go(integral_constant<int, 6>{});
+    if (kpt <= 8) return go(integral_constant<int, 8>{});
+    if (kpt <= 10) return go(integral_constant<int, 10>{});
+    if (kpt <= 12) return go(integral_constant<int, 12>{});
+    if (kpt <= 14) return go(integral_constant<int, 14>{});
+    if (kpt <= 16) return go(integral_constant<int, 16>{});
+    if (kpt <= 20) return go(integral_constant<int, 20>{});
+    if (kpt <= 24) return go(integral_constant<int, 24>{});
+    if (kpt <= 28) return go(integral_constant<int, 28>{});
+    return go(integral_constant<int, 32>{});
+}
+
 template <int ROW_U4>
 static hipError_t gather_by_keys(const curdkv_ctx* ctx, const float* raw, float* scores, int32_t n, int32_t n_sink,
                                  const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
@@ -519,11 +546,7 @@ static hipError_t gather_by_keys(const curdkv_ctx* ctx, const float* raw, float*
     auto go = [&](auto kpt) {
         return launch_gather<decltype(kpt)::value, ROW_U4>(ctx, raw, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g, known, dyn);
     };
-    using std::integral_constant;
-    if (n <= 4 * kSelThreads) return go(integral_constant<int, 4>{});
-    if (n <= 8 * kSelThreads) return go(integral_constant<int, 8>{});
-    if (n <= 16 * kSelThreads) return go(integral_constant<int, 16>{});
-    return go(integral_constant<int, 32>{});
+    return by_keys_per_thread(n, go);
 }
 
 hipError_t launch_select_gather(const curdkv_ctx* ctx, const float* raw, float* scores, int64_t n, int32_t n_sink,
@@ -539,21 +562,18 @@ hipError_t configure_select(curdkv_ctx* ctx) {
     const int dyn = ctx->lds_limit - kSelStaticReserve;   // what the kernels' static LDS leaves
     if (dyn <= 48 * 1024) return hipSuccess;
     hipError_t e;
-    for (int kpt : {4, 8, 16, 32}) {
+    for (int kpt : kKeyVariants) {
         const SelectGather none{};
+        const int64_t n = (int64_t)kpt * kSelThreads;
         e = ctx->cfg.dtype == CURDKV_DTYPE_BF16
-            ? gather_by_keys<16>(ctx, nullptr, nullptr, kpt * kSelThreads, 0, nullptr, 0, nullptr, nullptr, 0, none, nullptr, dyn)
-            : gather_by_keys<32>(ctx, nullptr, nullptr, kpt * kSelThreads, 0, nullptr, 0, nullptr, nullptr, 0, none, nullptr, dyn);
+            ? gather_by_keys<16>(ctx, nullptr, nullptr, (int32_t)n, 0, nullptr, 0, nullptr, nullptr, 0, none, nullptr, dyn)
+            : gather_by_keys<32>(ctx, nullptr, nullptr, (int32_t)n, 0, nullptr, 0, nullptr, nullptr, 0, none, nullptr, dyn);
+        if (e != hipSuccess) return e;
+        e = by_keys_per_thread(n, [&](auto k) {
+            return hipFuncSetAttribute((const void*)select_reg_kernel<decltype(k)::value>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
+        });
         if (e != hipSuccess) return e;
     }
-    e = hipFuncSetAttribute((const void*)select_reg_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)select_reg_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)select_reg_kernel<16>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)select_reg_kernel<32>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    if (e != hipSuccess) return e;
     return hipFuncSetAttribute((const void*)select_reg_kernel<36>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
 }
 
@@ -565,10 +585,10 @@ hipError_t launch_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_
     const int ws = write_scaled ? 1 : 0;
     if (split_applicable(ctx, n, scale_blocks > 0))
         return launch_split_select(ctx, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, write_scaled, known_thresholds, gather, hists);
-    if (n <= 4 * kSelThreads) return launch_reg<4>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);
-    if (n <= 8 * kSelThreads) return launch_reg<8>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);
-    if (n <= 16 * kSelThreads) return launch_reg<16>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);
-    if (n <= 32 * kSelThreads) return launch_reg<32>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);
+    if (n <= 32 * kSelThreads)
+        return by_keys_per_thread(n, [&](auto kpt) {
+            return launch_reg<decltype(kpt)::value>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);
+        });
     if (n <= 36 * kSelThreads) return launch_reg<36>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);
     select_stream_kernel<<<dim3((unsigned)ctx->heads), kSelThreads, 0, stream>>>(
         scores, n, n_sink, d_offsets, indices, ctx->d_partial, scale_blocks, ws);

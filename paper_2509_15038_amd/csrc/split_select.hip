@@ -591,7 +591,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
     } while (next());
 }
 
-// Which heads take this route.  One call, this against one workgroup per head (us): 1 head of 32768
+// Which heads take this route, where select_gather_kernel does not.  One call, this against one workgroup per head (us): 1 head of 32768
 // tokens 31 against 33, 8 heads 47 against 50, 32 heads 133 against 137; 8 heads of 16384 33.8 against 32, 64 heads
 // of 32768 247 against 246: hence 24576 and 32 heads.  Longer heads would otherwise be streamed twice by one
 // workgroup (8 heads of 131072 tokens: 188 -> 136, 1 head 157 -> 54, 64 heads 933 -> 902, 256 heads no
@@ -605,8 +605,8 @@ bool split_applicable(const curdkv_ctx* ctx, int64_t n, bool one_call) {
 }
 
 // One or two long heads are better scored by more workgroups each than there are histograms, which are then made from
-// memory, a launch more.  One call, us, at most 64 workgroups a head that count and as many as there are units: 1 head of 32768
-// tokens 26.8 and 26.2, of 131072 50.6 and 36.8; 2 heads of 32768 26.9 and 27.6, of 65536 37.7 and 36.9, of 131072 59.8 and 53.3; 3 heads
+// memory, a launch more.  One call, us, at most 64 workgroups a head that count and as many as there are units: 1 head of 131072
+// tokens 50.6 and 36.8; 2 heads of 32768 26.9 and 27.6, of 65536 37.7 and 36.9, of 131072 59.8 and 53.3; 3 heads
 // put 192 workgroups on the chip as it is.
 bool split_counts_in_scan(const curdkv_ctx* ctx, int64_t n) { return ctx->heads > 2 || n <= (int64_t)ctx->heads * kSplitMinTokens; }
 

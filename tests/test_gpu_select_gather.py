@@ -76,3 +76,26 @@ def test_both_sides_of_the_rule(heads, n, total):
 def test_nothing_kept():
     """All budgets zero: scores only."""
     _check(4, 2000, "bf16", [0] * 4, 4)
+
+
+# the longest head of every number of keys per thread, and one token more
+@pytest.mark.parametrize("keys", [1, 2, 3, 4, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32])
+@pytest.mark.parametrize("more", [0, 1])
+def test_keys_per_thread(keys, more):
+    import torch
+    n = 1024 * keys + more
+    rng = np.random.default_rng(n)
+    scores = np.exp(rng.standard_normal((3, n)) * 2).astype(np.float32)
+    scores[1] = np.round(rng.random(n) * 50)
+    scores[2, :-1] = 0.0
+    budgets = np.array([n // 10, n // 3, n - 5], dtype=np.int32)
+    off = wl.offsets_for(budgets)
+    with B.Context(1, 3, 4, 128, 20, "bf16", n, 1) as ctx:
+        out = gu.Guarded((int(off[-1]),), torch.int32, -7)
+        ctx.select(torch.from_numpy(scores).cuda(), n, budgets, 4, off, out.t)
+        got = out.t.cpu().numpy()
+        out.check()
+    for h in range(3):
+        assert np.array_equal(got[off[h]:off[h + 1]], orc.select(scores[h].astype(np.float64), int(budgets[h]), 4)), h
+    if keys in (1, 3, 10, 24, 32):
+        _check(2, n, "bf16", [n // 10, n // 7], 4)
