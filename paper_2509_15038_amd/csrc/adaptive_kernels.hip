@@ -13,7 +13,7 @@
 //   * the histograms, and their sums per exponent, are made by the fused kernel while it has a
 //     head's keys in registers, or by ada_hist_kernel from scores in memory, several workgroups per
 //     (layer, head) where heads are few, each a histogram of its part;
-//   * ada_cut_kernel, workgroup (part, head): every workgroup finds the bin in which the sum above reaches R (the same
+//   * ada_cut_kernel, a workgroup per head and part: every workgroup finds the bin in which the sum above reaches R (the same
 //     small computation in each of them: first over the layer's sums per exponent, then over the 32 bins of one exponent),
 //     and copies its own part's keys inside that bin (a fraction of a percent of the head) to the workspace;
 //   * ada_allot_kernel, one workgroup per layer, resolves the remaining key bits on those few keys in LDS, allots keys equal to the
@@ -77,15 +77,15 @@ static AdaWorkspace carve(void* base, size_t heads) {
     return w;
 }
 
-// Histogram of a part of a head's candidate keys (tokens sp and up) over the selection's 4096 bins: workgroup (part, head).
+// Histogram of a part of a head's candidate keys (tokens sp and up) over the selection's 4096 bins: workgroup head*parts + part.
 // scale_blocks > 0: `scores` holds un-normalised products, which are normalised on the way.
-__global__ __launch_bounds__(kAdaThreads) void ada_hist_kernel(float* __restrict__ scores, int64_t n, int32_t sp, int64_t part,
+__global__ __launch_bounds__(kAdaThreads) void ada_hist_kernel(float* __restrict__ scores, int64_t n, int32_t sp, int parts, int64_t part,
                                                                uint32_t* __restrict__ ws_hist, uint32_t* __restrict__ ws_coarse,
                                                                const float* __restrict__ partial, int scale_blocks) {
     __shared__ __align__(16) uint32_t hist[kBins12];
-    const int head = blockIdx.y, slot = head * gridDim.x + blockIdx.x;
+    const int slot = blockIdx.x, head = slot / parts;
     const int tid = threadIdx.x;
-    const int64_t j_begin = (int64_t)blockIdx.x * part;
+    const int64_t j_begin = (int64_t)(slot - head * parts) * part;
     const int64_t j_end = j_begin + part < n ? j_begin + part : n;
     float* sc = scores + (size_t)head * n;
     float cur[kAdaU], nxt[kAdaU];
@@ -124,11 +124,11 @@ constexpr int kAdaHeadsAtOnce = kAdaThreads / kExps;             // 8: a thread 
 // KPT: scores per thread loaded up front.
 template <int KPT>
 __global__ __launch_bounds__(kAdaThreads) void ada_cut_kernel(AdaWorkspace ws, const float* __restrict__ scores, int64_t n, int H,
-                                                              int32_t sp, int32_t g, long long R, int64_t part) {
+                                                              int32_t sp, int32_t g, long long R, int parts, int64_t part) {
     __shared__ uint32_t cum[kAdaHeadsAtOnce][kExps];             // keys of a head in exponents from the top to the i-th
     __shared__ uint32_t fine[kAdaHeadsAtOnce][32];               // the same over the bins of one exponent
     __shared__ uint32_t wave_tot[kAdaWaves], own[33], first[2], count;
-    const int parts = gridDim.x, q = blockIdx.x, head = blockIdx.y;
+    const int head = blockIdx.x / parts, q = blockIdx.x - head * parts;
     const int layer = head / H, my = head - layer * H;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t j_begin = (int64_t)q * part;
@@ -690,10 +690,10 @@ hipError_t launch_adaptive(const curdkv_ctx* ctx, void* workspace, float* scores
     const AdaWorkspace ws = carve(workspace, (size_t)ctx->heads);
     const int parts = hist_ready ? 1 : parts_for(ctx, n);
     const int64_t part = (n + parts - 1) / parts;
-    const dim3 grid((unsigned)parts, (unsigned)ctx->heads);
-    if (!hist_ready) ada_hist_kernel<<<grid, kAdaThreads, 0, stream>>>(scores, n, sp, part, ws.hist, ws.coarse, ctx->d_partial, scale_blocks);
+    const dim3 grid((unsigned)parts * (unsigned)ctx->heads);
+    if (!hist_ready) ada_hist_kernel<<<grid, kAdaThreads, 0, stream>>>(scores, n, sp, parts, part, ws.hist, ws.coarse, ctx->d_partial, scale_blocks);
     auto cut = [&](auto kpt) {
-        ada_cut_kernel<decltype(kpt)::value><<<grid, kAdaThreads, 0, stream>>>(ws, scores, n, H, sp, g, R, part);
+        ada_cut_kernel<decltype(kpt)::value><<<grid, kAdaThreads, 0, stream>>>(ws, scores, n, H, sp, g, R, parts, part);
     };
     if (part <= 4 * kAdaThreads) cut(std::integral_constant<int, 4>{});
     else if (part <= 16 * kAdaThreads) cut(std::integral_constant<int, 16>{});

@@ -17,8 +17,8 @@
 // bins from the top to the bin that holds T, then one more pass over the keys that
 // marks every candidate in a higher bin as kept and copies the few candidates
 // inside the bin (typically a fraction of a percent of the head) to a list in LDS.
-// The remaining 18 key bits are resolved on that list alone, three 6-bit digits,
-// and the list's members are then marked "above T" or "equal to T".  The keys in
+// The remaining 18 key bits are resolved on that list alone, by comparing its keys where they are few, else in three
+// 6-bit digits, and the list's members are then marked "above T" or "equal to T".  The keys in
 // registers are walked twice in all.
 //
 // Finding T, general case (the bin holds more keys than the list takes, e.g. a

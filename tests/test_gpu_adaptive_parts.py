@@ -120,3 +120,18 @@ def test_one_call(L, H, n, dtype, alpha):
             a, b = int(offsets[h]), int(offsets[h + 1])
             assert np.array_equal(got[a:b], orc.select(scores[h], int(budgets[h]), s)), h
             assert torch.equal(Ko.t[a:b], K[h, where[a:b]]) and torch.equal(Vo.t[a:b], V[h, where[a:b]]), h
+
+
+def test_more_heads_than_a_grid_is_high():
+    """66000 (layer, head) pairs, each its own workgroup."""
+    import torch
+    L, H, n = 16500, 4, 20
+    rng = np.random.default_rng(5)
+    sc = rng.random((L, H, n)).astype(np.float32)
+    out = torch.full((L * H,), -7, dtype=torch.int32, device="cuda")
+    with B.Context(L, H, 4, 128, 1, "bf16", n, 1) as ctx:
+        ctx.adaptive_budgets(torch.from_numpy(sc.reshape(L * H, n)).cuda(), n, 7, 2, 0.5, out)
+        got = out.cpu().numpy().reshape(L, H)
+    for layer in (0, 1, 8000, 16383, 16384, L - 1):
+        assert got[layer].tolist() == orc.adaptive_budgets(sc[layer].astype(np.float64), 7, 2, 0.5).tolist(), layer
+    assert np.all(got.sum(1) == 7 * H)
