@@ -44,7 +44,7 @@ constexpr int kAdaSeg = 1920;                     // in-bin keys a head hands to
 constexpr int kAdaList = 4096;                    // (key, head) pairs that workgroup resolves in LDS
 constexpr int kAdaDigWords = 8192;                // its per-head digit histograms: H << bits words
 constexpr int kAdaMaxHeads = 1024;                // kv_heads these kernels are laid out for
-constexpr int kAdaSlots = 256;                    // histograms there is room for, or one per head where there are more
+constexpr int kAdaSlots = 256;                    // histograms in all, or one per head where there are more
 constexpr int kAdaMaxParts = 32;                  // histograms per head
 constexpr int kAdaPartTokens = 4096;              // a part is no shorter
 constexpr int kExps = kBins12 / 32;               // sums per exponent: 32 bins each
@@ -59,17 +59,24 @@ struct AdaWorkspace {                             // device pointers into one al
     AdaLayerState* layer;                         // [layers]
 };
 
-static constexpr size_t slots_for(size_t heads) { return heads > (size_t)kAdaSlots ? heads : (size_t)kAdaSlots; }
+// Parts a head is counted in: one per compute unit at most, where heads are fewer than those.
+static int parts_for(int heads, int64_t n) {
+    int64_t parts = kAdaSlots / heads;
+    if (parts > (n + kAdaPartTokens - 1) / kAdaPartTokens) parts = (n + kAdaPartTokens - 1) / kAdaPartTokens;
+    return (int)(parts < 1 ? 1 : parts < kAdaMaxParts ? parts : kAdaMaxParts);
+}
+static size_t slots_for(const curdkv_ctx* ctx) { return (size_t)ctx->heads * parts_for(ctx->heads, ctx->cfg.max_tokens); }
 
-static constexpr size_t workspace_bytes_for(size_t heads, size_t layers) {
-    return slots_for(heads) * (size_t)(kBins12 + kExps) * 4 + heads * (size_t)kAdaSeg * 4 + heads * 16 + layers * sizeof(AdaLayerState);
+static constexpr size_t workspace_bytes_for(size_t slots, size_t heads, size_t layers) {
+    return slots * (size_t)(kBins12 + kExps) * 4 + heads * (size_t)kAdaSeg * 4 + heads * 16 + layers * sizeof(AdaLayerState);
 }
 
-static AdaWorkspace carve(void* base, size_t heads) {
+static AdaWorkspace carve(void* base, const curdkv_ctx* ctx) {
+    const size_t heads = (size_t)ctx->heads, slots = slots_for(ctx);
     AdaWorkspace w;
     w.hist = reinterpret_cast<uint32_t*>(base);
-    w.coarse = w.hist + slots_for(heads) * kBins12;
-    w.seg = w.coarse + slots_for(heads) * kExps;
+    w.coarse = w.hist + slots * kBins12;
+    w.seg = w.coarse + slots * kExps;
     w.above = w.seg + heads * kAdaSeg;
     w.inbin = w.above + heads;
     w.known = reinterpret_cast<Threshold*>(w.inbin + heads);
@@ -616,7 +623,7 @@ hipError_t configure_adaptive(curdkv_ctx* ctx) {
 }
 
 size_t adaptive_workspace_bytes(const curdkv_ctx* ctx) {
-    return workspace_bytes_for((size_t)ctx->heads, (size_t)ctx->cfg.layers);
+    return workspace_bytes_for(slots_for(ctx), (size_t)ctx->heads, (size_t)ctx->cfg.layers);
 }
 
 // ---- the same workspace as a static device array, for callers that cannot allocate ----------
@@ -627,7 +634,8 @@ size_t adaptive_workspace_bytes(const curdkv_ctx* ctx) {
 // that call returns, looked up once per device at curdkv_create.  Nothing in the array has to
 // hold a particular value when a call starts: the kernels set what they read.
 constexpr int kScratchMaxHeads = 1024;                 // layers * kv_heads the static workspace covers
-constexpr size_t kScratchBytes = workspace_bytes_for(kScratchMaxHeads, kScratchMaxHeads);   // 24 MiB + 32 KiB
+constexpr size_t kScratchBytes = workspace_bytes_for(kScratchMaxHeads, kScratchMaxHeads, kScratchMaxHeads);   // 24 MiB + 32 KiB
+static_assert(kScratchMaxHeads >= kAdaSlots, "fewer heads than histograms take no more room");
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kScratchMaxDevices = 64;
@@ -656,22 +664,15 @@ void* adaptive_static_workspace(int device) {
 }
 
 uint32_t* adaptive_hist_buffer(const curdkv_ctx* ctx, void* workspace) {
-    return carve(workspace, (size_t)ctx->heads).hist;
+    return carve(workspace, ctx).hist;
 }
 
 uint32_t* adaptive_coarse_buffer(const curdkv_ctx* ctx, void* workspace) {
-    return carve(workspace, (size_t)ctx->heads).coarse;
+    return carve(workspace, ctx).coarse;
 }
 
 const void* adaptive_thresholds(const curdkv_ctx* ctx, void* workspace) {
-    return carve(workspace, (size_t)ctx->heads).known;
-}
-
-// Parts a head is counted in: one per compute unit at most, where heads are fewer than those.
-static int parts_for(const curdkv_ctx* ctx, int64_t n) {
-    int64_t parts = kAdaSlots / ctx->heads;
-    if (parts > (n + kAdaPartTokens - 1) / kAdaPartTokens) parts = (n + kAdaPartTokens - 1) / kAdaPartTokens;
-    return (int)(parts < 1 ? 1 : parts < kAdaMaxParts ? parts : kAdaMaxParts);
+    return carve(workspace, ctx).known;
 }
 
 bool adaptive_allots(int32_t k, int32_t sp, long long R) { return k > sp && R > 0; }
@@ -687,8 +688,8 @@ hipError_t launch_adaptive(const curdkv_ctx* ctx, void* workspace, float* scores
         return hipGetLastError();
     }
     if ((size_t)ctx->lds_limit < kAdaAllotLds + 4096 || H > kAdaMaxHeads) return hipErrorInvalidConfiguration;
-    const AdaWorkspace ws = carve(workspace, (size_t)ctx->heads);
-    const int parts = hist_ready ? 1 : parts_for(ctx, n);
+    const AdaWorkspace ws = carve(workspace, ctx);
+    const int parts = hist_ready ? 1 : parts_for(ctx->heads, n);
     const int64_t part = (n + parts - 1) / parts;
     const dim3 grid((unsigned)parts * (unsigned)ctx->heads);
     if (!hist_ready) ada_hist_kernel<<<grid, kAdaThreads, 0, stream>>>(scores, n, sp, parts, part, ws.hist, ws.coarse, ctx->d_partial, scale_blocks);

@@ -35,7 +35,7 @@ struct AdaLayerState {
 struct Plan {
     int64_t* d_offsets = nullptr;      // [heads + 1]
     BlockInfo* d_block_info = nullptr; // [max_blocks]
-    char* d_buf = nullptr;             // one allocation holding both
+    char* d_buf = nullptr;             // holds both
     char* h_staging = nullptr;         // pinned, same layout
     size_t max_blocks = 0;
     std::vector<int64_t> cached;       // what d_offsets holds (after the queued copy)
@@ -53,6 +53,7 @@ struct curdkv_ctx {
     int heads = 0;                     // layers * kv_heads
     int col_blocks = 0;                // padded sketch_dim / 32 (1, 2 or 4)
     size_t g_elems_per_head = 0;       // packed operand elements per (layer, group)
+    char* d_slab = nullptr;            // the one allocation that the following lie in (d_scores_ws excepted)
     void* d_G = nullptr;               // packed sketches, storage type
     float* d_partial = nullptr;        // [heads, kMaxBlocksPerHead]
     int64_t* d_zero_offsets = nullptr; // [heads + 1] zeros: "keep nothing", for the scores-only use of the fused kernel

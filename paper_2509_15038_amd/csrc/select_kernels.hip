@@ -561,19 +561,26 @@ hipError_t launch_select_gather(const curdkv_ctx* ctx, const float* raw, float* 
 hipError_t configure_select(curdkv_ctx* ctx) {
     const int dyn = ctx->lds_limit - kSelStaticReserve;   // what the kernels' static LDS leaves
     if (dyn <= 48 * 1024) return hipSuccess;
-    hipError_t e;
+    // the limit is raised where it has to be: from 48 KB of indices on, and up to the longest head of this context
+    int64_t below = 0;                             // heads up to here take the variants before
     for (int kpt : kKeyVariants) {
-        const SelectGather none{};
         const int64_t n = (int64_t)kpt * kSelThreads;
-        e = ctx->cfg.dtype == CURDKV_DTYPE_BF16
-            ? gather_by_keys<16>(ctx, nullptr, nullptr, (int32_t)n, 0, nullptr, 0, nullptr, nullptr, 0, none, nullptr, dyn)
-            : gather_by_keys<32>(ctx, nullptr, nullptr, (int32_t)n, 0, nullptr, 0, nullptr, nullptr, 0, none, nullptr, dyn);
+        if (below >= ctx->cfg.max_tokens) return hipSuccess;
+        below = n;
+        if (n * 4 <= 48 * 1024) continue;
+        const SelectGather none{};
+        hipError_t e = hipSuccess;
+        if (ctx->d_raw_ws)
+            e = ctx->cfg.dtype == CURDKV_DTYPE_BF16
+                ? gather_by_keys<16>(ctx, nullptr, nullptr, (int32_t)n, 0, nullptr, 0, nullptr, nullptr, 0, none, nullptr, dyn)
+                : gather_by_keys<32>(ctx, nullptr, nullptr, (int32_t)n, 0, nullptr, 0, nullptr, nullptr, 0, none, nullptr, dyn);
         if (e != hipSuccess) return e;
         e = by_keys_per_thread(n, [&](auto k) {
             return hipFuncSetAttribute((const void*)select_reg_kernel<decltype(k)::value>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
         });
         if (e != hipSuccess) return e;
     }
+    if (below >= ctx->cfg.max_tokens) return hipSuccess;
     return hipFuncSetAttribute((const void*)select_reg_kernel<36>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
 }
 
