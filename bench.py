@@ -371,12 +371,12 @@ def main():
     }
 
     # An fp32 cache with a wide sketch can be bound by the matrix units rather than by HBM: 4*d*r flop per
-    # token (2*d*r for key-only / value-only) against 8*d bytes, on the fp32 units up to 32 columns, as three
-    # fp16 products each beyond.  The scoring kernel is then the dominant one and is priced against those
+    # token (2*d*r for key-only / value-only) against 8*d bytes, on the fp32 units up to 32 columns, as six
+    # bf16 products each beyond.  The scoring kernel is then the dominant one and is priced against those
     # units; the HBM view stays beside it.
     if cfg.dtype == "fp32" and not args.no_projection:
         flops = (4 if args.source == "kv" else 2) * d * cfg.r * heads * n
-        peak = FP32_MFMA_PEAK_TFLOPS if cfg.r <= 32 else BF16_MFMA_PEAK_TFLOPS / 3
+        peak = FP32_MFMA_PEAK_TFLOPS if cfg.r <= 32 else BF16_MFMA_PEAK_TFLOPS / 6
         if flops / (peak * 1e12) > ab["total"] / (HBM_PEAK_GBS * 1e9):
             sc_ms = calls["ms"]["scores"]
             tf = flops / (sc_ms * 1e-3) / 1e12

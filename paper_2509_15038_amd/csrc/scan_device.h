@@ -98,6 +98,7 @@ __device__ __forceinline__ void sum_rows(double& lk, double& lv) {
     lv = lk;
     swap(swap_halves, lk, lv);
 }
+// Returns (sum of the four lk) * (sum of the four lv) in all four lanes.
 __device__ __forceinline__ float combine_rows(float lk, float lv) {
     sum_rows(lk, lv);
     return lk * lv;
@@ -275,8 +276,9 @@ __device__ __forceinline__ float scan_tiles(const SketchRegs<CB>& G, const uint4
 // load instruction again asks for 64 contiguous bytes per row.  One MFMA takes one of the four
 // floats as the token operand; its sketch operand in lane L is
 // G[(4*s + L/16)*4 + e][16*cb + L%16] for step s = 0..7 and float e = 0..3, 32*CB floats per
-// lane in registers.  HBM is the bound here (32 columns are 16 flop/B): splitting the products, as the wider
-// sketches do, has nothing to give (256 heads of 16384 tokens, r = 20: 729 us, r = 64 split 752).
+// lane in registers.  HBM is the bound here (32 columns are 16 flop/B): splitting the products
+// over the bf16 matrix units, as the wider sketches do, measured 2 % slower (256 heads of 16384
+// tokens, r = 20: 746 us against 729).
 struct TileRegsF32 {    // one 32-token tile of K and of V as seen by a lane
     float4 k[2][8];
     float4 v[2][8];
@@ -454,133 +456,95 @@ __device__ __forceinline__ void scan_few(const typename FewOperand<F32>::Word* _
 }
 
 // ---- fp32 storage, more than 32 sketch columns -------------------------------------------
-// Lane roles as above; the products go through the fp16 matrix units.  A float is split into two fp16 numbers,
-// x = x1 + x2 (rounded to nearest each time: 11 significant bits and a sign per part hold 23 bits, and the 24th
-// in three floats of four), the sketch likewise, and x*g is taken as three products,
-//     x2*g1 + x1*g2 + x1*g1,
-// smallest first, accumulated in fp32.  x2*g2, left out, is at most 2^-22 of |x*g| and 2^-24 at root mean square, like the
-// rounding of an fp32 product; a product of fp16 numbers is exact: the matrix unit rounds once per 32 terms.
-// fp16 has five exponent bits: every row and every head's sketch is first scaled, exactly, by a power of two that
-// puts its largest element between 2^14 and 2^15, or 2^6 and 2^7, and the squared norm is scaled back.  An element at
-// least 2^-16 of its row's largest keeps all of both parts, and a smaller one errs by 2^-40 of the largest: nothing,
-// unless the sketch takes the large elements away.  A row whose squared norm is below 2^-21 of the largest product's
-// square (never with normal sketches, whose norms are near the rows') is scored again in plain fp32 by
-// rescore_row, as is one that is not finite.
+// Lane roles as above; the products go through the bf16 matrix units.  A float is split into three bf16 numbers,
+// x = x1 + x2 + x3 (rounded to nearest each time: 8 significant bits and a sign per part
+// hold 24 bits; exact from 2^-110 up, below which the third part loses bits as a subnormal), the sketch likewise,
+// and x*g is taken as the six products whose size is at least 2^-18 of it:
+//     x3*g1 + x1*g3 + x2*g2  +  x1*g2 + x2*g1  +  x1*g1,
+// smallest first, accumulated in fp32.  What is left out (x2*g3, x3*g2, x3*g3) is at most 2^-24 of |x*g|, the
+// rounding of one fp32 product (|x2| <= 2^-8 and |x3| <= 2^-17 for x in [1, 2)), and 2^-27 at root mean square; a
+// product of bf16 numbers is exact: the matrix unit rounds once per 32 terms instead of once per 4.  bf16 has the
+// exponents of a float, so rows and sketches of any range need no scaling: the parts of two fp16 numbers with a scale per row and per
+// sketch took half the matrix time, but hold 22 to 23 bits, and fewer of a sketch's smaller rows: with 40 channels 2^12 to 2^14 times
+// the others and their sketch rows as much smaller, the scores erred by up to 1.2e-5.
+// A float whose first part is infinite turns its row into NaN here; rescore_row then does such
+// a row again in plain fp32.
 //
-// Why: 4*d*r flop per 1024 bytes of a token's K and V rows made the fp32 matrix units the bound from r = 64 on; three
-// fp16 products take 3/16 of their time.  256 heads of 16384 tokens (HBM alone: 720 us): r = 64 1148 us in plain
-// fp32, 843 as six products of three bf16 parts, 752 so; r = 128 2146, 1296 and 931.  What bounds it is HBM at 64 columns and the
-// power of the matrix units at 128: a fourth product (x2*g2, or a third part of x) costs 40 and 150 us.
+// The squares are added two by two within a lane and block, and from there on in double.  Error of a score against 64 bits, normal rows,
+// root mean square (largest): r = 33 5.8e-8 (2.9e-7), r = 64 4.5e-8 (1.9e-7), r = 128 3.7e-8 (1.6e-7), and the same whatever
+// the channels' sizes are; with a chain of fp32 additions 8.2e-8 (3.7e-7), 8.0e-8 (3.7e-7), 8.7e-8 (3.5e-7).
 //
-// Error of the scores against 64 bits, relative, root mean square over the elements: six bf16 products 8.1e-8 (r = 64) and
-// 8.7e-8 (r = 128), so 7.4e-8 and 6.4e-8 for K with log-normal channels and V with heavy-tailed rows, 6.6e-8 and 5.6e-8
-// for normal rows (r = 33: 8.2e-8 and 8.2e-8).  The split by itself is coarser: it is the squares, added two by two and from
-// the lanes on in double, that lose less than a chain did.  Where one element is a thousand times the
-// others, its 24th bit shows: 0.94e-7 and 1.5e-7.
+// Why: 4*d*r flop per 1024 bytes of a token's K and V rows made the fp32 matrix units the bound
+// from r = 64 on; six bf16 products take 6/16 of their time.  256 heads of 16384
+// tokens: r = 64 1148 -> 840 us (HBM alone: 720), r = 128 2146 -> 1310 us (the bf16 units are busy
+// two thirds of the time); the sums in double are 1 % of it (833 and 1295 us with the chain).
 //
 // The token operand of MFMA step s (0..3) in lane L are the floats of stretches 2s and 2s + 1,
 // d = (2s + e/4)*16 + (L/16)*4 + e%4 for e = 0..7, the sketch operand G[d][16*cb + L%16]: two
 // neighbouring float4 of the packed sketch.  The sketch's parts live in LDS
-// ([cb][s][part][lane], 8 KB per 16 columns) and are read once per 16 tokens of K and V.
-typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
-
-constexpr int kRowTop = 14, kSketchTop = 6;         // exponents of the largest element once scaled
-constexpr int kMostExponent = 126;
-
-// The exponent that scales a number of largest magnitude m to 2^top .. 2^(top+1): m * 2^e.  At most kMostExponent, so that 2^e is
-// a float: magnitudes below 2^(top - 126) stay below 2^top.
-__device__ __forceinline__ int scale_exponent(float m, int top) {
-    const int e = top + 127 - (int)((__float_as_uint(m) & 0x7FFFFFFFu) >> 23);
-    return e < kMostExponent ? e : kMostExponent;
-}
-__device__ __forceinline__ float power_of_two(int e) {       // -126 <= e <= 127
-    return __uint_as_float((uint32_t)(e + 127) << 23);
-}
-
-struct Parts {          // eight floats as two fp16 operands, larger first
-    f16x8 p[2];
+// ([cb][s][part][lane], 12 KB per 16 columns) and are read once per 16 tokens of K and V.
+union Parts {           // eight floats as three bf16 operands, largest first
+    bf16x8 p[3];
+    uint32_t w[3][4];
 };
 
-__device__ __forceinline__ Parts split_f16(const float4& a, const float4& b, float scale) {
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+
+// two floats rounded to bf16 (nearest even), packed
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+
+__device__ __forceinline__ Parts split_bf16(const float4& a, const float4& b) {
     const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
     Parts r;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const _Float16 h = (_Float16)(x[e] * scale);
-        r.p[0][e] = h;
-        r.p[1][e] = (_Float16)fmaf(x[e], scale, -(float)h);      // the difference is exact before it is rounded
+    for (int e = 0; e < 4; ++e) {
+        float lo = x[2 * e], hi = x[2 * e + 1];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const uint32_t h = pack_bf16(lo, hi);
+            r.w[j][e] = h;
+            // exact: at most 16 bits remain after the first part, at most 8 after the second
+            lo -= __uint_as_float(h << 16);
+            hi -= __uint_as_float(h & 0xFFFF0000u);
+        }
     }
     return r;
 }
 
-__device__ __forceinline__ float largest(const float4& v, float m) {
-    return fmaxf(fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))), m);
-}
-
-template <int CB> constexpr int kSketchF32Chunks = CB * 4 * 2 * 64;     // 16-byte words in LDS
-
-struct SketchScale {
-    int exponent;
-    double least;       // squared norms below this, as scaled, are taken again (0: the sketch is zero, or too small to be scaled up)
-};
+template <int CB> constexpr int kSketchF32Chunks = CB * 4 * 3 * 64;     // 16-byte words in LDS
 
 // The whole workgroup splits the head's packed sketch ([cb][step 0..7][lane] float4) into LDS.
 template <int CB, int THREADS>
-__device__ __forceinline__ SketchScale split_sketch_to_lds(f16x8* gs, float* wave_top, const float4* __restrict__ Gh) {
-    constexpr int kPer = CB * 4 * 64 / THREADS;                         // operands per thread
-    static_assert(kPer * THREADS == CB * 4 * 64, "every thread has the same number");
-    float4 a[kPer], b[kPer];
-    float m = 0.f;
+__device__ __forceinline__ void split_sketch_to_lds(bf16x8* gs, const float4* __restrict__ Gh) {
+    for (int i = threadIdx.x; i < CB * 4 * 64; i += THREADS) {          // i = (cb*4 + s)*64 + lane
+        const int l = i & 63, cs = i >> 6;
+        const Parts p = split_bf16(Gh[cs * 128 + l], Gh[cs * 128 + 64 + l]);
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int at = i * THREADS + threadIdx.x, l = at & 63, cs = at >> 6;     // at = (cb*4 + s)*64 + lane
-        a[i] = Gh[cs * 128 + l];
-        b[i] = Gh[cs * 128 + 64 + l];
-        m = largest(a[i], largest(b[i], m));
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    if ((threadIdx.x & 63) == 0) wave_top[threadIdx.x >> 6] = m;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < THREADS / 64; ++w) m = fmaxf(m, wave_top[w]);
-    const int e = __builtin_amdgcn_readfirstlane(scale_exponent(m, kSketchTop));
-    const float scale = power_of_two(e);
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int at = i * THREADS + threadIdx.x, l = at & 63, cs = at >> 6;
-        const Parts p = split_f16(a[i], b[i], scale);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) gs[(cs * 2 + j) * 64 + l] = p.p[j];
+        for (int j = 0; j < 3; ++j) gs[(cs * 3 + j) * 64 + l] = p.p[j];
     }
     __syncthreads();
-    return SketchScale{e, e < kMostExponent ? 0x1p20 : 0.0};
 }
 
-// One row's squared projected norm in plain fp32, all lanes of a wave on the row's columns.  Gh: the head's packed sketch.
+// One row's squared projected norm in plain fp32, all lanes of a wave on the row's columns.
 template <int CB>
-__device__ float rescore_row(const float* __restrict__ Gh, const float* __restrict__ row, int lane) {
+__device__ float rescore_row(const bf16x8* gs, const float* __restrict__ row, int lane) {
     float l = 0.f;
     for (int c = lane; c < 16 * CB; c += 64) {
         float y = 0.f;
-        for (int d = 0; d < kHeadDim; ++d)
-            y = fmaf(row[d], Gh[(((c >> 4) * 8 + (d >> 4)) * 64 + ((d >> 2) & 3) * 16 + (c & 15)) * 4 + (d & 3)], y);
+        for (int d = 0; d < kHeadDim; ++d) {
+            const int at = ((c >> 4) * 4 + (d >> 5)) * 3 * 64 + ((d >> 2) & 3) * 16 + (c & 15);
+            const int e = ((d >> 4) & 1) * 4 + (d & 3);
+            const float g = ((float)gs[at + 128][e] + (float)gs[at + 64][e]) + (float)gs[at][e];   // exact
+            y = fmaf(row[d], g, y);
+        }
         l = fmaf(y, y, l);
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) l += __shfl_xor(l, off, 64);
     return l;
-}
-
-// mk, mv: magnitudes in a token's lanes t, t+16, t+32, t+48; the largest of the four, in all four.
-__device__ __forceinline__ void largest_of_rows(float& mk, float& mv) {
-    swap_halves(mk, mv);                 // as in sum_rows
-    float x = fmaxf(mk, mv);
-    float y = x;
-    swap_rows(x, y);
-    mk = fmaxf(x, y);
-    mv = mk;
-    swap_halves(mk, mv);
 }
 
 struct TileF32 {        // 16 tokens of K and of V as seen by a lane
@@ -591,12 +555,12 @@ struct TileF32 {        // 16 tokens of K and of V as seen by a lane
 // Scores tiles [t_begin, t_end) (32 tokens each, as elsewhere) of one head, 64 tokens at a time;
 // t_begin must be even, and t_end even or equal to ceil(n/32).  16 tokens are split into parts,
 // then the loads of the next 16 go out into the registers just freed and stay in flight while
-// the matrix units work on the parts: one buffer of 64 registers and 64 of parts, so that two
+// the matrix units work on the parts: one buffer of 64 registers and 96 of parts, so that two
 // waves share a SIMD and one's splitting runs beside the other's products.  (One wave of two
-// 32-token buffers per SIMD took turns at the two, 13 to 16 % slower with three bf16 parts.  Two chains
+// 32-token buffers per SIMD took turns at the two: 950 us at r = 64, 1460 at r = 128.  Two chains
 // of products per 16 columns and wave, K's and V's, are enough: four measured 3 to 5 % slower.)
 template <int CB, int SRC = kSrcKV, bool COUNT = false>
-__device__ __forceinline__ float scan_tiles_f32_split(const f16x8* gs, const SketchScale& scale, const float4* __restrict__ Gh, const float4* __restrict__ Kh,
+__device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const float4* __restrict__ Kh,
                                                 const float4* __restrict__ Vh,
                                                 int32_t n, int32_t t_begin, int32_t t_end, float* lds_rows,
                                                 int32_t row0, int lane, uint32_t phase, uint32_t* hist,
@@ -623,69 +587,44 @@ __device__ __forceinline__ float scan_tiles_f32_split(const f16x8* gs, const Ske
     };
     auto step = [&](int part, int32_t next) {                   // scores the 16 tokens in r, loads those from `next`
         Parts xk[4], xv[4];
-        float mk = 0.f, mv = 0.f;
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            if (SRC != kSrcV) mk = largest(r.k[s], mk);
-            if (SRC != kSrcK) mv = largest(r.v[s], mv);
-        }
-        largest_of_rows(mk, mv);
-        const int ek = scale_exponent(mk, kRowTop), ev = scale_exponent(mv, kRowTop);
-        const float fk = power_of_two(ek), fv = power_of_two(ev);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            if (SRC != kSrcV) xk[s] = split_f16(r.k[2 * s], r.k[2 * s + 1], fk);
-            if (SRC != kSrcK) xv[s] = split_f16(r.v[2 * s], r.v[2 * s + 1], fv);
+            if (SRC != kSrcV) xk[s] = split_bf16(r.k[2 * s], r.k[2 * s + 1]);
+            if (SRC != kSrcK) xv[s] = split_bf16(r.v[2 * s], r.v[2 * s + 1]);
         }
         __builtin_amdgcn_sched_barrier(0);
         load(next);
         __builtin_amdgcn_sched_barrier(0);
-        float sk[CB], sv[CB];                                   // squares of each block's columns
+        double lk = SRC == kSrcV ? 0.25 : 0.0, lv = SRC == kSrcK ? 0.25 : 0.0;
         // the lane's offset is made opaque, or the compiler lifts the sketch's loads out of the walk
         int gl = lane;
         asm volatile("" : "+v"(gl));
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
             f32x4 ak = f32x4{0.f, 0.f, 0.f, 0.f}, av = f32x4{0.f, 0.f, 0.f, 0.f};
-            f16x8 g[4][2];
+            bf16x8 g[4][3];
 #pragma unroll
             for (int s = 0; s < 4; ++s)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) g[s][j] = gs[((cb * 4 + s) * 2 + j) * 64 + gl];
+                for (int j = 0; j < 3; ++j) g[s][j] = gs[((cb * 4 + s) * 3 + j) * 64 + gl];
             auto mac = [&](int s, int jg, int jx) {
-                if (SRC != kSrcV) ak = __builtin_amdgcn_mfma_f32_16x16x32_f16(g[s][jg], xk[s].p[jx], ak, 0, 0, 0);
-                if (SRC != kSrcK) av = __builtin_amdgcn_mfma_f32_16x16x32_f16(g[s][jg], xv[s].p[jx], av, 0, 0, 0);
+                if (SRC != kSrcV) ak = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[s][jg], xk[s].p[jx], ak, 0, 0, 0);
+                if (SRC != kSrcK) av = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[s][jg], xv[s].p[jx], av, 0, 0, 0);
             };
 #pragma unroll
-            for (int s = 0; s < 4; ++s) { mac(s, 0, 1); mac(s, 1, 0); }
+            for (int s = 0; s < 4; ++s) { mac(s, 0, 2); mac(s, 2, 0); mac(s, 1, 1); }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) { mac(s, 1, 0); mac(s, 0, 1); }
 #pragma unroll
             for (int s = 0; s < 4; ++s) mac(s, 0, 0);
-            // two by two: a chain of 4*CB additions loses more
-            auto squares = [](const f32x4& a) { return fmaf(a[0], a[0], a[1] * a[1]) + fmaf(a[2], a[2], a[3] * a[3]); };
-            if (SRC != kSrcV) sk[cb] = squares(ak);
-            if (SRC != kSrcK) sv[cb] = squares(av);
+            // four squares two by two, and from there on in double: a chain of 4*CB additions loses more
+            auto squares = [](const f32x4& a) { return (double)(fmaf(a[0], a[0], a[1] * a[1]) + fmaf(a[2], a[2], a[3] * a[3])); };
+            if (SRC != kSrcV) lk += squares(ak);
+            if (SRC != kSrcK) lv += squares(av);
             __builtin_amdgcn_sched_barrier(0);                  // or several blocks' loads pile up in registers
         }
-#pragma unroll
-        for (int step = 1; step < CB; step *= 2)
-#pragma unroll
-            for (int cb = 0; cb < CB; cb += 2 * step) {
-                if (SRC != kSrcV) sk[cb] += sk[cb + step];
-                if (SRC != kSrcK) sv[cb] += sv[cb + step];
-            }
-        double lk = SRC == kSrcV ? 0.25 : (double)sk[0], lv = SRC == kSrcK ? 0.25 : (double)sv[0];
         sum_rows(lk, lv);
-        int e = 0;
-        bool again = false;
-        if (SRC != kSrcV) {
-            again = again || (ek < kMostExponent && lk < scale.least);
-            e -= 2 * (ek + scale.exponent);
-        }
-        if (SRC != kSrcK) {
-            again = again || (ev < kMostExponent && lv < scale.least);
-            e -= 2 * (ev + scale.exponent);
-        }
-        const float lkv = again ? __uint_as_float(0x7FC00000u) : (float)ldexp(lk * lv, e);
+        const float lkv = (float)(lk * lv);
         pend = q == part ? lkv : pend;
     };
     // the walk starts at a rotated group, as in walk_tiles (whole groups only)
@@ -715,8 +654,8 @@ __device__ __forceinline__ float scan_tiles_f32_split(const f16x8* gs, const Ske
             for (uint64_t bad = __ballot(v != v); bad; bad &= bad - 1) {
                 const int b = __ffsll((unsigned long long)bad) - 1;
                 const size_t at = (size_t)(uint32_t)(j + b) * kHeadDim;
-                const float lk = SRC == kSrcV ? 1.f : rescore_row<CB>((const float*)Gh, (const float*)Kh + at, lane);
-                const float lv = SRC == kSrcK ? 1.f : rescore_row<CB>((const float*)Gh, (const float*)Vh + at, lane);
+                const float lk = SRC == kSrcV ? 1.f : rescore_row<CB>(gs, (const float*)Kh + at, lane);
+                const float lv = SRC == kSrcK ? 1.f : rescore_row<CB>(gs, (const float*)Vh + at, lane);
                 if (lane == b) {
                     if (COUNT) raw_hist_uncount(hist, v, row >= n_sink);
                     v = lk * lv;

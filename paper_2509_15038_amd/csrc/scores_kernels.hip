@@ -96,13 +96,13 @@ __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
 // fp32 storage: the same structure (scan_device.h).  CB = 16-column blocks of the padded sketch.
 // Up to 32 columns (CB = 2, and the ablation without projection) the sketch is in registers and a
 // lane's two tile buffers take 256 more: a SIMD holds one wave and a compute unit one workgroup
-// of four.  Wider sketches split the products over the fp16 matrix units: the sketch's parts share
+// of four.  Wider sketches split the products over the bf16 matrix units: the sketch's parts share
 // the LDS with the score stages, and a workgroup has eight waves, two to a SIMD.
 // ---------------------------------------------------------------------------
 template <int CB> struct ShapeF32 {
     static constexpr bool kSplit = CB > 2;
     static constexpr int kWaves = kSplit ? 8 : 4;
-    static constexpr int kTiles = CB > 4 ? 80 : CB > 2 ? 112 : 256;    // per wave between bursts: 80, 112 or 128 KB in all
+    static constexpr int kTiles = CB > 4 ? 48 : CB > 2 ? 96 : 256;    // per wave between bursts: 48, 96 or 128 KB in all
 };
 
 template <int CB, int SRC, bool PROJ, bool COUNT>
@@ -115,8 +115,7 @@ __global__ __launch_bounds__((ShapeF32<CB>::kWaves * 64), (ShapeF32<CB>::kSplit 
     constexpr int kWaves = ShapeF32<CB>::kWaves;
     constexpr int kStageTiles = ShapeF32<CB>::kTiles;
     __shared__ float stage[kWaves][kStageTiles * kTileTokens];
-    __shared__ f16x8 gs[kSplit ? kSketchF32Chunks<CB> : 1];
-    __shared__ float wave_top[kWaves];
+    __shared__ bf16x8 gs[kSplit ? kSketchF32Chunks<CB> : 1];
     __shared__ uint32_t hist[COUNT ? kRawHistWords : 1];
     const int head = blockIdx.x / blocks_per_head;
     const int blk = blockIdx.x - head * blocks_per_head;
@@ -128,9 +127,8 @@ __global__ __launch_bounds__((ShapeF32<CB>::kWaves * 64), (ShapeF32<CB>::kSplit 
     }
     const float4* Gh = Gp + (size_t)head * (CB * 8 * 64);
     SketchF32<kSplit ? 1 : CB> G;
-    SketchScale scale{};
-    if constexpr (kSplit) {
-        scale = split_sketch_to_lds<CB, kWaves * 64>(gs, wave_top, Gh);
+    if (kSplit) {
+        split_sketch_to_lds<CB, kWaves * 64>(gs, Gh);
     } else if (PROJ) {
 #pragma unroll
         for (int cb = 0; cb < (kSplit ? 1 : CB); ++cb)
@@ -154,7 +152,7 @@ __global__ __launch_bounds__((ShapeF32<CB>::kWaves * 64), (ShapeF32<CB>::kSplit 
         const int32_t seg_end = seg + kStageTiles < t_end ? seg + kStageTiles : t_end;
         const int32_t r0 = seg * kTileTokens;
         const uint32_t phase = scan_phase(head, blk * kWaves + wave);
-        if constexpr (kSplit) acc_sum += scan_tiles_f32_split<CB, SRC, COUNT>(gs, scale, Gh, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink);
+        if constexpr (kSplit) acc_sum += scan_tiles_f32_split<CB, SRC, COUNT>(gs, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink);
         else acc_sum += scan_tiles_f32<CB, SRC, PROJ, COUNT>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink);
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
         for (int32_t r = r0 + lane; r < r1; r += 64) __builtin_nontemporal_store(mine[r - r0], &sh[r]);

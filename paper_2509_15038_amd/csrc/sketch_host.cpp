@@ -76,7 +76,7 @@ size_t packed_elems(int col_blocks) { return static_cast<size_t>(col_blocks) * 4
 //   whose A operand in lane L is G[(s*4 + L/16)*4 + e][cb*16 + L%16]  (the token
 //   operand of lane L is float e of the 16-byte chunk s*4 + L/16 of token L%16);
 //   the four values of a lane for one (cb, s) lie together, so a lane loads them
-//   as one 16-byte word.  (More than 32 columns: the kernel splits each value into two fp16 and
+//   as one 16-byte word.  (More than 32 columns: the kernel splits each value into three bf16 and
 //   two neighbouring words of a lane, steps 2t and 2t + 1, make its operand of step t.)
 void pack_sketch(const curdkv_config& cfg, int col_blocks, const float* G, void* packed) {
     const int r = cfg.sketch_dim;

@@ -1,5 +1,5 @@
-"""fp32 caches with more than 32 sketch columns: every float goes through the fp16 matrix units as
-two fp16 numbers.  Scores against the float64 oracle, and rows that are not finite.  (Calls of few tokens in all,
+"""fp32 caches with more than 32 sketch columns: every float goes through the bf16 matrix units as
+three bf16 numbers.  Scores against the float64 oracle, and rows that are not finite.  (Calls of few tokens in all,
 the smaller sizes here, take a kernel of plain fp32 products; the edges of this one's steps, groups and
 ranges beyond that limit are in test_gpu_dispatch_sides.py.)"""
 import numpy as np
@@ -12,8 +12,8 @@ from paper_2509_15038_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 # 2-norm error of a head's scores: a projected coordinate is 128 exact products, summed with one
-# rounding per 32 of them over three passes (12 roundings), the parts left out weigh 2^-22 of a product at most
-# and 2^-24 at root mean square; squared and summed over r, multiplied and normalised (about 30 roundings
+# rounding per 32 of them over six passes (24 roundings), the parts left out weigh 2^-24 of a product at most
+# and 2^-27 at root mean square; squared and summed over r, multiplied and normalised (about 30 roundings
 # of 2^-24 relative, at random)
 NORM_TOL = 1e-6
 
@@ -45,7 +45,7 @@ def test_scores_against_the_oracle(n, layers, r, source):
 
 @pytest.mark.parametrize("r", [64, 128])
 def test_rows_that_are_not_finite(r):
-    """A row with an infinity, one at the top of the fp32 range (its first part's exponent is the largest there is) and one
+    """A row with an infinity, one at the top of the fp32 range (its bf16 rounding is infinite) and one
     with a NaN score what plain fp32 arithmetic gives them; every other row is as without them."""
     cfg = wl.scaled(wl.CONFIGS["c2"], layers=1, kv_heads=1, n=300, r=r, dtype="fp32")
     K, V = wl.host_cache(cfg)
@@ -60,17 +60,18 @@ def test_rows_that_are_not_finite(r):
     assert np.array_equal(raw[0, rest], clean[0, rest])
 
 
-# The error of one score: a row is scaled by a power of two and split into two fp16 numbers of 11 bits (2^-24 of an
-# element at most, likewise of the sketch; their product left out 2^-22, at random over 128 products), squared twice:
-# 2 * 2 * 3 * 2^-22 if all of it pointed one way.
-ELEMENT_TOL = 12 * 2.0 ** -22
+# The error of one score: a projected coordinate errs by some 24 roundings of its running sum, 1.5e-7 at root mean square, a
+# norm of 33 such coordinates by 5e-8, a score by 9e-8 with its squares and the last rounding; five times that over the 30000 scores compared, and twice
+# that again for rows that lean on few coordinates.
+ELEMENT_TOL = 16 * 2.0 ** -24
 
 
 @pytest.mark.parametrize("r", [33, 64, 128])
-@pytest.mark.parametrize("rows", ["scaled", "uncovered", "zero sketch"])
+@pytest.mark.parametrize("rows", ["scaled", "uncovered", "zero sketch", "unlike 8", "unlike 12", "unlike 14", "unlike 20", "white 2", "white 3"])
 def test_rows_and_sketches_of_any_size(r, rows):
-    """Rows between 1e-8 and 1e8 (every row is scaled by itself; products of squared norms stay below 2^127); a sketch that is zero where the rows are
-    largest (such rows are scored in plain fp32); a sketch of zeros, and rows of zeros."""
+    """Rows between 1e-8 and 1e8 (products of squared norms stay below 2^127); a sketch that is zero where the rows are
+    largest; a sketch of zeros, and rows of zeros; sketches that make up for channels of unlike size: 40 channels 2^p times the
+    others, or log-normal ones, and the rows of the sketch as much smaller, so that every element matters alike."""
     import torch
     L, H, n = 2, 8, 2048 + 37                                          # beyond the calls of few tokens
     rng = np.random.default_rng([5, r])
@@ -83,8 +84,12 @@ def test_rows_and_sketches_of_any_size(r, rows):
         G[:40] = 0
         K[..., :40] *= 1e8
         V[..., 7] *= np.exp(rng.uniform(0, 30, (L, H, n))).astype(np.float32)
-    else:
+    elif rows == "zero sketch":
         G[:] = 0
+    else:
+        kind, p = rows.split()
+        size = np.where(np.arange(128) < 40, 2.0 ** int(p), 1.0) if kind == "unlike" else np.exp(rng.standard_normal(128) * int(p))
+        K, V, G = (K * size).astype(np.float32), (V * size).astype(np.float32), (G / size[:, None]).astype(np.float32)
     K[1, 3, 99:140] = 0
     K[0, 0, 130, 50], V[0, 0, 77, 100], V[0, 0, 2084, 0], K[0, 0, 64, 64] = np.inf, np.nan, -np.inf, np.finfo(np.float32).max
     with B.Context(L, H, 4, 128, r, "fp32", n, 1) as ctx:
@@ -94,12 +99,12 @@ def test_rows_and_sketches_of_any_size(r, rows):
         sums = torch.zeros((L * H,), dtype=torch.float64, device="cuda")
         ctx.scores_append(torch.from_numpy(K).cuda(), torch.from_numpy(V).cuda(), n, 0, n, raw, sums)
         raw = raw.cpu().numpy().reshape(L, H, n)
-    for i, j in ((0, 0), (1, 3), (1, 7)):
+    for i, j in np.ndindex(L, H):
         K64, V64, G64 = (x.astype(np.float64) for x in (K[i, j], V[i, j], G))
         with np.errstate(invalid="ignore"):
             want = ((K64 @ G64) ** 2).sum(1) * ((V64 @ G64) ** 2).sum(1)
         if (i, j) == (0, 0):
-            if rows == "scaled":                                        # (elsewhere infinities meet zeros of the sketch, at r = 33 of its padding)
+            if rows == "scaled":                                        # (in some others infinities meet zeros of the sketch, at r = 33 of its padding)
                 assert np.isnan(raw[0, 0, 77]) and np.all(np.isposinf(raw[0, 0, [64, 130, 2084] if r != 33 else [64]]))
             raw[0, 0, [64, 77, 130, 2084]] = want[[64, 77, 130, 2084]] = 0
         assert np.all(np.abs(raw[i, j] - want) <= ELEMENT_TOL * want), (i, j)
