@@ -470,14 +470,15 @@ __device__ __forceinline__ void scan_few(const typename FewOperand<F32>::Word* _
 // A float whose first part is infinite turns its row into NaN here; rescore_row then does such
 // a row again in plain fp32.
 //
-// The squares are added two by two within a lane and block, and from there on in double.  Error of a score against 64 bits, normal rows,
-// root mean square (largest): r = 33 5.8e-8 (2.9e-7), r = 64 4.5e-8 (1.9e-7), r = 128 3.7e-8 (1.6e-7), and the same whatever
-// the channels' sizes are; with a chain of fp32 additions 8.2e-8 (3.7e-7), 8.0e-8 (3.7e-7), 8.7e-8 (3.5e-7).
+// The squares of a lane's four columns of every block have a sum each, and these and the lanes' are added in double.  Error of a score
+// against 64 bits, normal rows, root mean square (largest): r = 33 5.6e-8 (2.5e-7), r = 64 4.5e-8 (1.9e-7), r = 128 4.0e-8 (1.6e-7), and the
+// same whatever the channels' sizes are; with one chain of fp32 additions 8.2e-8 (3.7e-7), 8.0e-8 (3.7e-7), 8.7e-8 (3.5e-7).
 //
 // Why: 4*d*r flop per 1024 bytes of a token's K and V rows made the fp32 matrix units the bound
 // from r = 64 on; six bf16 products take 6/16 of their time.  256 heads of 16384
 // tokens: r = 64 1148 -> 840 us (HBM alone: 720), r = 128 2146 -> 1310 us (the bf16 units are busy
-// two thirds of the time); the sums in double are 1 % of it (833 and 1295 us with the chain).
+// two thirds of the time).  One chain of sums is 1 % faster there, and 34.7 us against 36.9 where a wave has a group or two (3 heads of
+// 6000 tokens, r = 128).
 //
 // The token operand of MFMA step s (0..3) in lane L are the floats of stretches 2s and 2s + 1,
 // d = (2s + e/4)*16 + (L/16)*4 + e%4 for e = 0..7, the sketch operand G[d][16*cb + L%16]: two
@@ -595,7 +596,7 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
         __builtin_amdgcn_sched_barrier(0);
         load(next);
         __builtin_amdgcn_sched_barrier(0);
-        double lk = SRC == kSrcV ? 0.25 : 0.0, lv = SRC == kSrcK ? 0.25 : 0.0;
+        f32x4 qk = f32x4{0.f, 0.f, 0.f, 0.f}, qv = qk;          // squares, a sum each
         // the lane's offset is made opaque, or the compiler lifts the sketch's loads out of the walk
         int gl = lane;
         asm volatile("" : "+v"(gl));
@@ -617,12 +618,15 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
             for (int s = 0; s < 4; ++s) { mac(s, 1, 0); mac(s, 0, 1); }
 #pragma unroll
             for (int s = 0; s < 4; ++s) mac(s, 0, 0);
-            // four squares two by two, and from there on in double: a chain of 4*CB additions loses more
-            auto squares = [](const f32x4& a) { return (double)(fmaf(a[0], a[0], a[1] * a[1]) + fmaf(a[2], a[2], a[3] * a[3])); };
-            if (SRC != kSrcV) lk += squares(ak);
-            if (SRC != kSrcK) lv += squares(av);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (SRC != kSrcV) qk[e] = fmaf(ak[e], ak[e], qk[e]);
+                if (SRC != kSrcK) qv[e] = fmaf(av[e], av[e], qv[e]);
+            }
             __builtin_amdgcn_sched_barrier(0);                  // or several blocks' loads pile up in registers
         }
+        auto total = [](const f32x4& q) { return ((double)q[0] + (double)q[1]) + ((double)q[2] + (double)q[3]); };
+        double lk = SRC == kSrcV ? 0.25 : total(qk), lv = SRC == kSrcK ? 0.25 : total(qv);
         sum_rows(lk, lv);
         const float lkv = (float)(lk * lv);
         pend = q == part ? lkv : pend;
