@@ -305,7 +305,10 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n, int64_t most_b
 // As many workgroups as the chip holds at once (16 waves per compute unit), a step each at least: one more per head
 // and some wait for a place (12 heads of 576 tokens, bf16, r = 128, 22 workgroups each 11.3 us per curdkv_scores_append, 21
 // each 7.8).  Two steps stay in one workgroup in bf16, and in fp32 where a running sum is wanted, which it then adds by
-// itself: one launch instead of two.
+// itself: one launch instead of two.  More than 64 a head, whose partial sums are then several to a lane, only for one or two
+// heads, and while each has a compute unit to itself: two on a unit share its matrix units.  Replayed graph, us per
+// curdkv_scores_append, up to 64 a head, up to one a unit, up to 256 a head: fp32, r = 64, 1 head of 8192 tokens 23.0, 9.2, 9.2; 2 heads of 6000 15.7,
+// 10.7, 13.3; 3 of 3000 10.1, 10.1, 12.6; 3 of 4096 12.1, 12.6, 12.8; bf16, r = 20, 2 heads of 4096 5.4, 4.9, 5.3; 3 of 2048 4.8, 5.0, 5.2.
 static int few_blocks_per_head(const curdkv_ctx* ctx, int64_t n, bool running) {
     const int waves = (ctx->cfg.score_source == CURDKV_SCORE_KV ? 2 : 1) * 2 * ctx->col_blocks;
     const int64_t slots = (int64_t)ctx->num_cu * (16 / waves);
@@ -313,7 +316,8 @@ static int few_blocks_per_head(const curdkv_ctx* ctx, int64_t n, bool running) {
     if (steps <= 2 && (running || ctx->cfg.dtype == CURDKV_DTYPE_BF16)) return 1;
     int64_t b = slots / ctx->heads;
     b = b < 1 ? 1 : b < steps ? b : steps;
-    return (int)(b < kMaxBlocksPerHead ? b : kMaxBlocksPerHead);
+    const int64_t units = ctx->num_cu / ctx->heads, most = ctx->heads > 2 || units < 64 ? 64 : units < kMaxBlocksPerHead ? units : kMaxBlocksPerHead;
+    return (int)(b < most ? b : most);
 }
 
 // Calls of few tokens in all take scan_few.  Measured, us per curdkv_scores_append, the other kernel -> this one.
