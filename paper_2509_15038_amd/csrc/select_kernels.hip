@@ -411,8 +411,12 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float*
     const int32_t r1 = r0 + share < k ? r0 + share : k;            // output rows r0 .. r1-1 are this workgroup's
     if (r0 >= r1 && blockIdx.x > 0) return;
     uint32_t x[KPT];
+    int none;                                      // the head has no sum
+    uint32_t key0;
     {
         const HeadScale scale = head_scale(mine, scale_blocks, n);
+        none = __builtin_amdgcn_readfirstlane(scale.on && scale.zero);
+        key0 = order_key(scale.uniform) & 0x7FFFFFFFu;
 #pragma unroll
         for (int it = 0; it < KPT; ++it) {
             v[it] = scale(v[it]);
@@ -422,7 +426,11 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float*
         }
     }
     if (r0 >= r1) return;
-    select_core<kSelThreads, KPT, true>(x, n, s, k, sm, stage, n, nullptr, known ? known[head] : Threshold{kNoThreshold, 0u}, r0, r1);
+    Threshold given = known ? known[head] : Threshold{kNoThreshold, 0u};
+    // a head without a sum has one score, 1/n, and the search would need all of its passes: 8 heads of 32768 tokens that score
+    // zero, one call, 70.0 us with it, 40.7 without (the split selection 43.9), 1 of 1024 11.1 and 8.5.  (Asked here: before the loop it cost 0.1 us of every call)
+    if (__builtin_expect(none, 0)) given = Threshold{(uint32_t)__builtin_amdgcn_readfirstlane((int)key0), (uint32_t)(k - s)};
+    select_core<kSelThreads, KPT, true>(x, n, s, k, sm, stage, n, nullptr, given, r0, r1);
     const int32_t count = r1 - r0;
     for (int32_t p = tid; p < count; p += kSelThreads) indices[o0 + r0 + p] = stage[p];
     constexpr int kRows = kSelThreads / ROW_U4, kFlight = 4;           // rows per instruction, and of each tensor in flight per thread
@@ -478,8 +486,10 @@ static hipError_t launch_reg(const curdkv_ctx* ctx, float* scores, int32_t n, in
 // gather kernel's many small workgroups make up for its launch: half kept of 64 heads of 8192 tokens (262144 rows)
 // 106.4 -> 105.6, of 128 heads 185.9 -> 190.6; a tenth of 64 heads of 32768 (209664) 241.8 -> 242.5: hence 512 rows a unit.
 // The split selection, which comes second, is behind up to the longest head this holds, as long as the rows are few: a tenth kept, this
-// and split, 1 head of 32768 tokens 22.6 and 26.9, 2 heads of 24600 22.2 and 27.3, 8 of 32768 44.8 and 49.6, 32 of 32768 131.3 and 132.4
-// (half kept, separate kernels and split, 194.1 and 192.5).
+// and split, r = 20, 1 head of 24577 tokens 19.4 and 25.3, of 32768 22.0 and 26.6; 8 of 32768 40.5 and 43.5; 16 of 32768 67.5 and 71.0; 24 of 28000
+// 84.9 and 86.9.  From there to 32 heads the two are level: r = 64, 24 of 32768 102.8 and 104.2, 32 of 28000 115.0 and 116.2, of 32768 132.6 and 132.8; r = 20,
+// 24 of 32768 101.0 and 101.2, 32 of 32768 131.2 and 130.4 (this reads 2.5 % more there, every workgroup its head's products); heads of one
+// value 159.8 and 186.6.  Half kept, separate kernels and split, 194.1 and 192.5.
 // Smaller workgroups for shorter heads give nothing (256 threads: 1024 tokens 9.9, 8192 tokens 21.7).
 constexpr int64_t kGatherMaxTokens = 32 * kSelThreads;             // what a workgroup's registers and LDS hold
 constexpr int64_t kGatherRowsPerUnit = 512;

@@ -78,6 +78,28 @@ def test_nothing_kept():
     _check(4, 2000, "bf16", [0] * 4, 4)
 
 
+@pytest.mark.parametrize("n", [1, 2, 65, 1025, 24577, 32768])
+def test_heads_without_a_sum(n):
+    """A head of zeros, and one whose sum is not a number: every score is 1/n, and the first tokens are kept."""
+    import torch
+    heads = 6
+    K, V = _cache(heads, n, "bf16", 5)
+    V[0, 1], K[0, 3] = 0, 0
+    V[0, 4, n // 2] = float("nan")
+    budgets = np.minimum([n // 3 + 1, n // 10 + 5, n // 7, n - 1, n // 5 + 2, 3], n).astype(np.int32)
+    with B.Context(1, heads, 4, 128, 20, "bf16", n, 77) as ctx:
+        for b in (budgets, np.full((heads,), n, np.int32), np.full((heads,), min(4, n), np.int32)):
+            sc, idx, Ko, Vo, off = gu.run_path(ctx, K, V, n, b, 4, "bf16", one_call=True)
+            where = idx.long()
+            for h in range(heads):
+                a, z = int(off[h]), int(off[h + 1])
+                if h in (1, 3, 4):
+                    assert bool((sc[h] == np.float32(1.0 / n)).all()) and where[a:z].tolist() == list(range(z - a)), h
+                assert np.array_equal(where[a:z].cpu().numpy(), orc.select(sc[h].cpu().numpy().astype(np.float64), int(b[h]), 4)), h
+                bits = torch.int16
+                assert torch.equal(Ko[a:z].view(bits), K[0, h, where[a:z]].view(bits)) and torch.equal(Vo[a:z].view(bits), V[0, h, where[a:z]].view(bits)), h
+
+
 # the longest head of every number of keys per thread, and one token more
 @pytest.mark.parametrize("keys", [1, 2, 3, 4, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32])
 @pytest.mark.parametrize("more", [0, 1])
