@@ -199,7 +199,7 @@ int curdkv_adaptive_budgets(curdkv_ctx* ctx, const float* scores, int64_t n, int
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same arguments, same results, same kernels; the histograms, key lists and
  * per-layer state that curdkv_adaptive_budgets keeps in a buffer its context got
- * from hipMalloc live here in a static device array of the library (24 MiB +
+ * from hipMalloc live here in a static device array of the library (24.5 MiB +
  * 32 KiB per GPU, resident from the moment the library is loaded, its address
  * looked up at curdkv_create).
  * The call makes no hipMalloc, hipFree or other allocating call.

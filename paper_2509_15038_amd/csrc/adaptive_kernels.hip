@@ -40,7 +40,7 @@ constexpr int kAdaThreads = 1024;
 constexpr int kAdaWaves = kAdaThreads / 64;
 constexpr int kAdaU = 8;                          // scores per thread in flight
 constexpr int kAdaOwn = 32;                       // cut kernel: scores per thread loaded up front, at most
-constexpr int kAdaSeg = 1920;                     // in-bin keys a head hands to its layer's workgroup
+constexpr int kAdaSeg = 2048;                     // in-bin keys a head hands to its layer's workgroup
 constexpr int kAdaList = 4096;                    // (key, head) pairs that workgroup resolves in LDS
 constexpr int kAdaDigWords = 8192;                // its per-head digit histograms: H << bits words
 constexpr int kAdaMaxHeads = 1024;                // kv_heads these kernels are laid out for
@@ -634,7 +634,7 @@ size_t adaptive_workspace_bytes(const curdkv_ctx* ctx) {
 // that call returns, looked up once per device at curdkv_create.  Nothing in the array has to
 // hold a particular value when a call starts: the kernels set what they read.
 constexpr int kScratchMaxHeads = 1024;                 // layers * kv_heads the static workspace covers
-constexpr size_t kScratchBytes = workspace_bytes_for(kScratchMaxHeads, kScratchMaxHeads, kScratchMaxHeads);   // 24 MiB + 32 KiB
+constexpr size_t kScratchBytes = workspace_bytes_for(kScratchMaxHeads, kScratchMaxHeads, kScratchMaxHeads);   // 24.5 MiB + 32 KiB
 static_assert(kScratchMaxHeads >= kAdaSlots, "fewer heads than histograms take no more room");
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 

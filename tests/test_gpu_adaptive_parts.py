@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 
 PART = gu.limit("adaptive_kernels.hip", "kAdaPartTokens")
 LIST = gu.limit("adaptive_kernels.hip", "kAdaList")
+SEG = gu.limit("adaptive_kernels.hip", "kAdaSeg")                        # keys a head can have in the threshold's bin before the layer's scores are read again
 
 
 def _heads(H, n, rng):
@@ -56,8 +57,8 @@ def test_budgets(L, H, n):
                 assert out.cpu().numpy().tolist() == got.reshape(-1).tolist()
 
 
-# keys in the threshold's bin: as many as the list takes, and more; the safeguard ends above the bin, inside it, below it
-@pytest.mark.parametrize("inside", [1, 31, 33, LIST // 4 - 1, LIST // 4, LIST // 4 + 1, 1920, 1921])
+# keys in the threshold's bin: as many as the list and a head's segment take, and more; the safeguard ends above the bin, inside it, below it
+@pytest.mark.parametrize("inside", [1, 31, 33, LIST // 4 - 1, LIST // 4, LIST // 4 + 1, 1920, 1921, SEG, SEG + 1])
 def test_safeguard_inside_the_bin(inside):
     import torch
     H, n, above = 4, 20000, 100
