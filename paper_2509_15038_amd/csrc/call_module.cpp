@@ -65,17 +65,20 @@ struct Args {
         if (PyLong_CheckExact(v[i])) return reinterpret_cast<void*>(wrapped(v[i]));
         return taken(PyObject_CallOneArg(slow_stream, v[i]));
     }
-    // a host array of `count` integers of `width` bytes
+    // a host array of `count` integers of `width` bytes, one after the other (at any address: a view into a file or a
+    // record need not be aligned, which numpy's format says with a '=')
     const void* array(int i, Py_ssize_t count, int width) {
         if (!ok) return nullptr;
         Py_buffer b;
         if (PyObject_GetBuffer(v[i], &b, PyBUF_STRIDES | PyBUF_FORMAT) != 0) { ok = false; return nullptr; }
         const void* p = b.buf;
-        const bool type = b.format && (width == 4 ? !std::strcmp(b.format, "i") : !std::strcmp(b.format, "l") || !std::strcmp(b.format, "q"));
-        const bool fits = type && b.itemsize == width && b.len == count * width;
+        const char* f = b.format ? b.format : "";
+        if (*f == '=' || *f == '@') ++f;
+        const bool type = width == 4 ? !std::strcmp(f, "i") : !std::strcmp(f, "l") || !std::strcmp(f, "q");
+        const bool fits = type && b.itemsize == width && b.len == count * width && PyBuffer_IsContiguous(&b, 'C');
         PyBuffer_Release(&b);                      // (the caller's reference keeps it during the call)
         if (!fits) {
-            PyErr_Format(PyExc_AssertionError, "expected an array of %zd int%d", count, 8 * width);
+            PyErr_Format(PyExc_AssertionError, "expected a contiguous array of %zd int%d", count, 8 * width);
             ok = false;
         }
         return p;

@@ -63,11 +63,22 @@ def test_other_kinds_of_buffers_and_numbers(calls):
 @pytest.mark.parametrize("budgets,offsets", [(np.zeros(3, np.int64), np.zeros(4, np.int64)), (np.zeros(3, np.int32), np.zeros(4, np.int32)),
                                              (np.zeros(2, np.int32), np.zeros(4, np.int64)), (np.zeros(3, np.int32), np.zeros(3, np.int64)),
                                              (np.zeros(3, np.float32), np.zeros(4, np.int64)), (np.zeros(3, np.uint32), np.zeros(4, np.int64)),
-                                             (np.zeros(3, ">i4"), np.zeros(4, np.int64))])
+                                             (np.zeros(3, ">i4"), np.zeros(4, np.int64)), (np.zeros(6, np.int32)[::2], np.zeros(4, np.int64)),
+                                             (np.zeros(3, np.int32), np.zeros(4, np.int64)[::-1]), (np.zeros((3, 2), np.int32)[:, 0], np.zeros(4, np.int64))])
 def test_host_arrays_of_another_kind_are_refused(calls, budgets, offsets):
     with pytest.raises(AssertionError):
         B._call.select(5, None, 9, budgets, 4, offsets, None, None, 3)
     assert not calls
+
+
+def test_host_arrays_at_any_address(calls):
+    """Views that lie at odd addresses, of two dimensions, or of the other name that 64 bits have."""
+    budgets = np.frombuffer(b"\0" * 17, np.uint8)[1:].view(np.int32)
+    offsets = np.zeros(5, np.dtype([("kind", "i1"), ("at", "i8")]))["at"].copy()
+    odd = np.frombuffer(b"\0" * 41, np.uint8)[1:].view(np.int64)
+    for b, o in ((budgets, offsets), (budgets, odd), (np.zeros((2, 2), np.int32), np.zeros(5, np.longlong))):
+        B._call.select(5, None, 9, b, 4, o, None, None, 4)
+        assert calls[-1][1][3] == b.ctypes.data and calls[-1][1][5] == o.ctypes.data
 
 
 @pytest.mark.parametrize("args", [(5, None, None, "nine", None, 1), (5, None, None, None, None, 1), (5, object(), None, 9, None, 1), (5, None, None, 9, None),
