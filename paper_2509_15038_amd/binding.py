@@ -1,5 +1,6 @@
 """Binding of libcurdkv.so: the same entry points as include/curdkv.h,
-argument marshalling only, by ctypes and, for the calls that a program makes over and over, the module _call.so.  Every step of the path runs in the HIP kernels.
+argument marshalling only, by ctypes and, for the calls that a program makes over and over, the module _call where it has been
+built for this interpreter.  Every step of the path runs in the HIP kernels.
 
 torch appears here only as the owner of device memory and streams: tensors are
 passed as raw pointers.  If the compiled library is missing the import of any
@@ -9,14 +10,16 @@ entry point fails loudly; there is no fallback.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
+import sysconfig
 from typing import Optional
 
 import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libcurdkv.so")
-CALL_PATH = os.path.join(_HERE, "_call.so")
+CALL_PATH = os.path.join(_HERE, "_call" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 
 OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_HIP, ERR_OOM, ERR_TOO_LARGE = 0, -1, -2, -3, -4, -5
 DTYPE_F32, DTYPE_BF16 = 0, 1
@@ -140,14 +143,56 @@ def _stream(stream) -> int:
     return stream.cuda_stream
 
 
-_call = None                                        # the module _call.so, bound to the library by lib()
+class _CtypesCalls:
+    """The functions of the module _call by ctypes: the same arguments and the same checks, 1 us a call slower."""
+
+    def __init__(self, L):
+        self._lib = L
+
+    @staticmethod
+    def _array(a, count, dtype):
+        assert isinstance(a, np.ndarray) and a.dtype == dtype and a.size == count and a.flags.c_contiguous, \
+            f"expected a contiguous array of {count} {np.dtype(dtype)}"
+        return _host_ptr(a)
+
+    def scores(self, h, K, V, n, scores, stream):
+        return self._lib.curdkv_scores(h, _ptr(K), _ptr(V), int(n), _ptr(scores), _stream(stream))
+
+    def scores_append(self, h, K, V, m, n_old, stride, raw, sums, stream):
+        return self._lib.curdkv_scores_append(h, _ptr(K), _ptr(V), int(m), int(n_old), int(stride), _ptr(raw), _ptr(sums), _stream(stream))
+
+    def normalise(self, h, raw, sums, stride, n, scores, stream):
+        return self._lib.curdkv_normalise(h, _ptr(raw), _ptr(sums), int(stride), int(n), _ptr(scores), _stream(stream))
+
+    def select(self, h, scores, n, budgets, n_sink, offsets, indices, stream, heads):
+        return self._lib.curdkv_select(h, _ptr(scores), int(n), self._array(budgets, heads, np.int32), int(n_sink),
+                                       self._array(offsets, heads + 1, np.int64), _ptr(indices), _stream(stream))
+
+    def compact(self, h, K, V, n, indices, offsets, K_out, V_out, stream, heads):
+        return self._lib.curdkv_compact(h, _ptr(K), _ptr(V), int(n), _ptr(indices), self._array(offsets, heads + 1, np.int64), _ptr(K_out),
+                                        _ptr(V_out), _stream(stream))
+
+    def compress(self, h, K, V, n, budgets, n_sink, offsets, scores, indices, K_out, V_out, stream, heads):
+        return self._lib.curdkv_compress(h, _ptr(K), _ptr(V), int(n), self._array(budgets, heads, np.int32), int(n_sink),
+                                         self._array(offsets, heads + 1, np.int64), _ptr(scores), _ptr(indices), _ptr(K_out), _ptr(V_out),
+                                         _stream(stream))
+
+    def compress_adaptive(self, h, K, V, n, budget, n_sink, alpha, scores, budgets_out, offsets_out, indices, K_out, V_out, stream):
+        return self._lib.curdkv_compress_adaptive(h, _ptr(K), _ptr(V), int(n), int(budget), int(n_sink), float(alpha), _ptr(scores),
+                                                  _ptr(budgets_out), _ptr(offsets_out), _ptr(indices), _ptr(K_out), _ptr(V_out), _stream(stream))
+
+
+_call = None                                        # the module _call bound to the library, or _CtypesCalls; set by lib()
 
 
 def _bind_calls(L) -> None:
     global _call
-    if not os.path.exists(CALL_PATH):
-        raise RuntimeError(f"{CALL_PATH} is missing: build it with `python -m paper_2509_15038_amd.build`")
-    from paper_2509_15038_amd import _call as module
+    if not os.path.exists(CALL_PATH):               # (not built for this interpreter)
+        _call = _CtypesCalls(L)
+        return
+    spec = importlib.util.spec_from_file_location("paper_2509_15038_amd._call", CALL_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
     entry = [C.cast(getattr(L, "curdkv_" + name), C.c_void_p).value
              for name in ("scores", "scores_append", "normalise", "select", "compact", "compress", "compress_adaptive")]
     module.bind(*entry, _ptr, _stream)

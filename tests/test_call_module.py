@@ -1,6 +1,8 @@
-"""The argument marshalling of _call.so, without a GPU: entry points written in Python are bound in the library's place
-and record what they are given."""
+"""The argument marshalling of the module _call, and of ctypes where that has not been built, without a GPU: entry points written in
+Python are bound in the library's place and record what they are given."""
 import ctypes as C
+import os
+import types
 
 import numpy as np
 import pytest
@@ -14,21 +16,50 @@ SIGNATURES = {"scores": [VP, VP, VP, I64, VP, VP], "scores_append": [VP, VP, VP,
               "compress": [VP, VP, VP, I64, VP, I32, VP, VP, VP, VP, VP, VP], "compress_adaptive": [VP, VP, VP, I64, I32, I32, F64, VP, VP, VP, VP, VP, VP, VP]}
 
 
-@pytest.fixture
-def calls():
-    B.lib()
-    seen, kept = [], []
+@pytest.fixture(params=["module", "ctypes"])
+def calls(request, monkeypatch):
+    L = B.lib()
+    seen, kept = [], {}
 
     def entry(name, types):
         def f(*a):
             seen.append((name, [x or 0 if t is VP else x for x, t in zip(a, types)]))
             return -1 if name == "normalise" else 0
-        kept.append(C.CFUNCTYPE(C.c_int, *types)(f))
-        return C.cast(kept[-1], VP).value
+        kept[name] = C.CFUNCTYPE(C.c_int, *types)(f)
+        return C.cast(kept[name], VP).value
 
-    B._call.bind(*[entry(n, t) for n, t in SIGNATURES.items()], B._ptr, lambda s: 77 if s is None else B._stream(s))
+    addresses = [entry(n, t) for n, t in SIGNATURES.items()]
+    by_default = lambda s, usual=B._stream: 77 if s is None else usual(s)
+    monkeypatch.setattr(B, "_stream", by_default)
+    if request.param == "module":
+        if not os.path.exists(B.CALL_PATH):
+            pytest.skip("not built for this interpreter")
+        B._call.bind(*addresses, B._ptr, by_default)
+    else:
+        monkeypatch.setattr(B, "_call", B._CtypesCalls(types.SimpleNamespace(**{"curdkv_" + n: f for n, f in kept.items()})))
     yield seen
-    B._bind_calls(B.lib())
+    monkeypatch.undo()
+    B._bind_calls(L)
+
+
+def test_without_the_module(monkeypatch, tmp_path):
+    """A build without Python.h, or for another interpreter: the library loads and is called through ctypes."""
+    monkeypatch.setattr(B, "CALL_PATH", str(tmp_path / "_call.none.so"))
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_call", None)
+    B.lib()
+    assert isinstance(B._call, B._CtypesCalls)
+    assert B._call.scores(0, None, None, 1, None, 0) == B.ERR_INVALID_ARG      # (no context: refused before anything is launched)
+    assert B.curdkv_sketch_host(B.make_config(1, 1, 1, 128, 4, "fp32", 1, 1), 0, 0).shape == (128, 4)
+
+
+def test_a_build_without_headers(monkeypatch, tmp_path, capsys):
+    from paper_2509_15038_amd import build
+    monkeypatch.setattr(build, "CALL", str(tmp_path / "_call.so"))
+    (tmp_path / "_call.so").write_bytes(b"of an older source")
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    build._build_call_module("hipcc", False)
+    assert not (tmp_path / "_call.so").exists() and "ctypes" in capsys.readouterr().out
 
 
 def test_every_argument_arrives(calls):
