@@ -102,6 +102,7 @@ int sync_offsets(curdkv_ctx* ctx, const int64_t* offsets, const int32_t* budgets
 void release(curdkv_ctx* ctx) {
     if (!ctx) return;
     if (ctx->d_slab) (void)hipFree(ctx->d_slab);
+    if (ctx->d_zero_offsets) (void)hipFree(ctx->d_zero_offsets);
     if (ctx->d_scores_ws) (void)hipFree(ctx->d_scores_ws);
     if (ctx->plan.h_staging) (void)hipHostFree(ctx->plan.h_staging);
     if (ctx->plan.copied) (void)hipEventDestroy(ctx->plan.copied);
@@ -174,23 +175,23 @@ int curdkv_create(curdkv_ctx** out, const curdkv_config* cfg) {
     ctx->plan.max_blocks = ((size_t)ctx->heads * (size_t)cfg->max_tokens + kCompactRowsPerBlock - 1) /
                                kCompactRowsPerBlock + 1;
     const size_t plan_bytes = off_bytes + ctx->plan.max_blocks * sizeof(BlockInfo);
-    // Everything the context keeps on the device in one allocation (an allocation takes the driver 50 us and more): the
+    // What the context keeps on the device in one allocation: the
     // sketches, the partial sums, the offsets with their gather table, the workspace of the head-wise budget allocation and its
     // device-built table (a few tens of KB per head; here, so that the adaptive calls are kernel launches
     // only), and where a call can be long or short enough for them those of the split selection and of the one that gathers.
+    // The zeroed offsets have one of their own: hipMemset of a part of the large one takes 12 to 17 us, of a small one 3.
     struct { void** at; size_t bytes; } part[] = {
         {&ctx->d_G, g_bytes},
         {(void**)&ctx->d_partial, (size_t)ctx->heads * kMaxBlocksPerHead * sizeof(float)},
         {(void**)&ctx->plan.d_buf, plan_bytes},
         {&ctx->d_adaptive_ws, adaptive_workspace_bytes(ctx)},
         {(void**)&ctx->d_adaptive_blocks, ctx->plan.max_blocks * sizeof(BlockInfo)},
-        {(void**)&ctx->d_zero_offsets, off_bytes},
         {&ctx->d_split_ws, split_wanted(ctx) ? split_workspace_bytes(ctx) : 0},
         {(void**)&ctx->d_raw_ws, select_gather_wanted(ctx) ? select_gather_workspace_bytes(ctx) : 0},
     };
     size_t slab = 0;
     for (const auto& x : part) slab += (x.bytes + 255) & ~(size_t)255;
-    if (hipMalloc((void**)&ctx->d_slab, slab) != hipSuccess ||
+    if (hipMalloc((void**)&ctx->d_slab, slab) != hipSuccess || hipMalloc((void**)&ctx->d_zero_offsets, off_bytes) != hipSuccess ||
         hipHostMalloc((void**)&ctx->plan.h_staging, plan_bytes, hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         release(ctx);

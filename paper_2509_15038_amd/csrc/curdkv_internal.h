@@ -53,7 +53,7 @@ struct curdkv_ctx {
     int heads = 0;                     // layers * kv_heads
     int col_blocks = 0;                // padded sketch_dim / 32 (1, 2 or 4)
     size_t g_elems_per_head = 0;       // packed operand elements per (layer, group)
-    char* d_slab = nullptr;            // the one allocation that the following lie in (d_scores_ws excepted)
+    char* d_slab = nullptr;            // the one allocation that the following lie in (d_zero_offsets and d_scores_ws excepted)
     void* d_G = nullptr;               // packed sketches, storage type
     float* d_partial = nullptr;        // [heads, kMaxBlocksPerHead]
     int64_t* d_zero_offsets = nullptr; // [heads + 1] zeros: "keep nothing", for the scores-only use of the fused kernel
@@ -103,6 +103,8 @@ hipError_t launch_fold(const curdkv_ctx* ctx, const float* scores_q, int64_t n, 
 // max_budget: the largest of the heads' budgets; negative: they exist on the device only.
 // known_thresholds (device, one {key, need} pair per head as the budget allocation leaves them,
 // adaptive_thresholds): heads whose entry is valid skip the search for their threshold.
+// gather given: the selection may copy the kept rows itself; gather->done says whether it has.
+// hists > 0: so many histograms per head, of the un-normalised scores, have been made by launch_scores for the split selection.
 struct SelectGather {
     const void *K, *V;
     void *K_out, *V_out;
@@ -121,7 +123,6 @@ bool select_gather_applicable(const curdkv_ctx* ctx, int64_t n, int64_t total);
 hipError_t launch_select_gather(const curdkv_ctx* ctx, const float* raw, float* scores, int64_t n, int32_t n_sink,
                                 const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
                                 int scale_blocks, const SelectGather& gather, const void* known_thresholds = nullptr);
-// gather given: the selection may copy the kept rows itself; gather->done says whether it has.
 // split_select.hip: the same for long heads, several workgroups per head (workspace ctx->d_split_ws).
 // hists > 0: step 1's histograms, so many of them per head, have been made by launch_scores; otherwise they are made here.
 bool split_wanted(const curdkv_ctx* ctx);              // some n <= max_tokens may take it: the context needs the workspace
