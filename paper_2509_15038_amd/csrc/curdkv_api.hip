@@ -229,8 +229,7 @@ int curdkv_create(curdkv_ctx** out, const curdkv_config* cfg) {
             err = upload_sketch(ctx, l * cfg->kv_heads + h, G);
         }
     std::free(G);
-    if (err == CURDKV_OK && (configure_kernels(ctx) != hipSuccess || configure_select(ctx) != hipSuccess ||
-                              configure_fused(ctx) != hipSuccess || configure_adaptive(ctx) != hipSuccess))
+    if (err == CURDKV_OK && (configure_kernels(ctx) != hipSuccess || configure_fused(ctx) != hipSuccess || configure_adaptive(ctx) != hipSuccess))
         err = CURDKV_ERR_HIP;
     if (err != CURDKV_OK) { release(ctx); return err; }
     *out = ctx;

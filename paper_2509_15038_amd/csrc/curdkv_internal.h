@@ -141,7 +141,6 @@ hipError_t launch_compact(const curdkv_ctx* ctx, const void* K, const void* V, i
                           void* K_out, void* V_out, hipStream_t stream,
                           const BlockInfo* block_info = nullptr);   // default: the table of the host-side plan
 hipError_t configure_kernels(curdkv_ctx* ctx);
-hipError_t configure_select(curdkv_ctx* ctx);
 hipError_t configure_fused(curdkv_ctx* ctx);
 hipError_t configure_adaptive(curdkv_ctx* ctx);
 size_t adaptive_workspace_bytes(const curdkv_ctx* ctx);

@@ -463,18 +463,26 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float*
     }
 }
 
+// Raises the kernel's limit of dynamic LDS to what its static part leaves, where `bytes` of indices need it.  At the launch (0.1 us):
+// all variants a long context could launch, 17 of them, made the first curdkv_create of a process 2.4 ms longer.
+static hipError_t allow_indices(const curdkv_ctx* ctx, const void* kernel, size_t bytes) {
+    return bytes <= 48 * 1024 ? hipSuccess : hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, ctx->lds_limit - kSelStaticReserve);
+}
+
 template <int KPT>
 static hipError_t launch_reg(const curdkv_ctx* ctx, float* scores, int32_t n, int32_t n_sink,
                              const int64_t* d_offsets, int32_t* indices, hipStream_t stream,
                              int scale_blocks, int write_scaled, const Threshold* known) {
-    // the staging area takes what the kernel's static LDS leaves, within the dynamic size the
-    // kernel was configured for (configure_select); indices beyond it go straight to memory
+    // the staging area takes what the kernel's static LDS leaves, within the limit that allow_indices
+    // sets; indices beyond it go straight to memory
     const size_t fixed = sizeof(SelectShared<kSelThreads, KPT>) + 256;
     int64_t cap = ((int64_t)ctx->lds_limit - (int64_t)fixed) / 4;
     const int64_t configured = ((int64_t)ctx->lds_limit - kSelStaticReserve) / 4;
     if (cap > configured) cap = configured;
     if (cap > n) cap = n;
     if (cap < 0) cap = 0;
+    const hipError_t e = allow_indices(ctx, (const void*)select_reg_kernel<KPT>, (size_t)cap * 4);
+    if (e != hipSuccess) return e;
     select_reg_kernel<KPT><<<dim3((unsigned)ctx->heads), kSelThreads, (size_t)cap * 4, stream>>>(
         scores, n, n_sink, d_offsets, indices, (int32_t)cap, ctx->d_partial, scale_blocks, write_scaled, known);
     return hipGetLastError();
@@ -509,9 +517,9 @@ bool select_gather_applicable(const curdkv_ctx* ctx, int64_t n, int64_t total) {
 template <int KPT, int ROW_U4>
 static hipError_t launch_gather(const curdkv_ctx* ctx, const float* raw, float* scores, int32_t n, int32_t n_sink,
                                 const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
-                                int scale_blocks, const SelectGather& g, const Threshold* known, int dyn) {
-    if (dyn > 0)
-        return hipFuncSetAttribute((const void*)select_gather_kernel<KPT, ROW_U4>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
+                                int scale_blocks, const SelectGather& g, const Threshold* known) {
+    const hipError_t e = allow_indices(ctx, (const void*)select_gather_kernel<KPT, ROW_U4>, (size_t)n * 4);
+    if (e != hipSuccess) return e;
     // max_budget < 0: the budgets are on the device, and every workgroup takes an equal share of its head's rows
     const int64_t places = ctx->num_cu / ctx->heads;
     int64_t share = (max_budget + places - 1) / places;
@@ -528,7 +536,6 @@ static hipError_t launch_gather(const curdkv_ctx* ctx, const float* raw, float* 
 // Keys per thread: the smallest of these that holds the head (every pass of the selection walks all of a thread's keys,
 // present or not).  With 4, 8, 16 and 32 only: curdkv_select of 112 heads of 10007 tokens 9.0 us, so 7.9; 256 heads of 1000 5.1 and 4.6, of
 // 18000 15.0 and 12.7; one call for 8 heads of 18000 31.7 and 29.1.
-constexpr int kKeyVariants[] = {1, 2, 3, 4, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32};
 template <class Go>
 static hipError_t by_keys_per_thread(int64_t n, Go go) {
     using std::integral_constant;
@@ -552,9 +559,9 @@ static hipError_t by_keys_per_thread(int64_t n, Go go) {
 template <int ROW_U4>
 static hipError_t gather_by_keys(const curdkv_ctx* ctx, const float* raw, float* scores, int32_t n, int32_t n_sink,
                                  const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
-                                 int scale_blocks, const SelectGather& g, const Threshold* known, int dyn = 0) {
+                                 int scale_blocks, const SelectGather& g, const Threshold* known) {
     auto go = [&](auto kpt) {
-        return launch_gather<decltype(kpt)::value, ROW_U4>(ctx, raw, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g, known, dyn);
+        return launch_gather<decltype(kpt)::value, ROW_U4>(ctx, raw, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g, known);
     };
     return by_keys_per_thread(n, go);
 }
@@ -566,32 +573,6 @@ hipError_t launch_select_gather(const curdkv_ctx* ctx, const float* raw, float* 
     return ctx->cfg.dtype == CURDKV_DTYPE_BF16
         ? gather_by_keys<16>(ctx, raw, scores, (int32_t)n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g, known)
         : gather_by_keys<32>(ctx, raw, scores, (int32_t)n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, g, known);
-}
-
-hipError_t configure_select(curdkv_ctx* ctx) {
-    const int dyn = ctx->lds_limit - kSelStaticReserve;   // what the kernels' static LDS leaves
-    if (dyn <= 48 * 1024) return hipSuccess;
-    // the limit is raised where it has to be: from 48 KB of indices on, and up to the longest head of this context
-    int64_t below = 0;                             // heads up to here take the variants before
-    for (int kpt : kKeyVariants) {
-        const int64_t n = (int64_t)kpt * kSelThreads;
-        if (below >= ctx->cfg.max_tokens) return hipSuccess;
-        below = n;
-        if (n * 4 <= 48 * 1024) continue;
-        const SelectGather none{};
-        hipError_t e = hipSuccess;
-        if (ctx->d_raw_ws)
-            e = ctx->cfg.dtype == CURDKV_DTYPE_BF16
-                ? gather_by_keys<16>(ctx, nullptr, nullptr, (int32_t)n, 0, nullptr, 0, nullptr, nullptr, 0, none, nullptr, dyn)
-                : gather_by_keys<32>(ctx, nullptr, nullptr, (int32_t)n, 0, nullptr, 0, nullptr, nullptr, 0, none, nullptr, dyn);
-        if (e != hipSuccess) return e;
-        e = by_keys_per_thread(n, [&](auto k) {
-            return hipFuncSetAttribute((const void*)select_reg_kernel<decltype(k)::value>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-        });
-        if (e != hipSuccess) return e;
-    }
-    if (below >= ctx->cfg.max_tokens) return hipSuccess;
-    return hipFuncSetAttribute((const void*)select_reg_kernel<36>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
 }
 
 hipError_t launch_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
