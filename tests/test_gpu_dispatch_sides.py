@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 SEED = 0xC0DE0013
 FEW_F32 = gu.limit("scores_kernels.hip", "kFewF32Tokens")
 SPLIT_HEADS = gu.limit("curdkv_internal.h", "kSplitMaxHeads")
-SPLIT_FROM, SPLIT_FROM_ELSE = gu.limit("split_select.hip", "kSplitMinTokens"), gu.limit("split_select.hip", "kSplitMinTokensElse")
+SPLIT_FROM_ELSE = gu.limit("split_select.hip", "kSplitMinTokensElse")
+GATHER_LONGEST = 32 * gu.limit("select_kernels.hip", "kSelThreads")     # up to here few heads take the selection that gathers
 
 # A projected coordinate takes 32 roundings of a sum of 128 products (one per 4 products in fp32; one per 32 over six
 # passes of split products, and 2^-24 per product at most left out), at random; squared and summed over r,
@@ -112,7 +113,7 @@ def test_streaming_selection_in_many_heads(n, in_bin):
                                                        ("bf16", 64, "k", False), ("fp32", 20, "kv", True), ("fp32", 32, "v", True), ("fp32", 64, "k", True),
                                                        ("fp32", 128, "kv", True), ("fp32", 64, "kv", False), ("fp32", 64, "v", False)])
 def test_one_call_of_long_heads(dtype, r, source, projection):
-    n = SPLIT_FROM + 1213
+    n = GATHER_LONGEST + 1213
     cfg = wl.scaled(wl.CONFIGS["c2"], kv_heads=3, n=n, r=r, dtype=dtype)
     budgets = np.array([n // 10, n // 2, 67], dtype=np.int32)
     gu.run_and_check(cfg, budgets, one_call=True, source=source, projection=projection, fused=False)

@@ -11,7 +11,7 @@ from tests import gpu_util as gu
 pytestmark = pytest.mark.gpu
 
 ROWS = gu.limit("select_kernels.hip", "kGatherRowsPerUnit") * 256       # rows kept, all heads, up to which this route is taken
-LONGEST = gu.limit("split_select.hip", "kSplitMinTokens")               # up to 32 heads; beyond, what the registers hold
+LONGEST = 32 * gu.limit("select_kernels.hip", "kSelThreads")            # the longest head that a workgroup's registers hold
 
 
 def _cache(heads, n, dtype, seed):
@@ -67,8 +67,10 @@ def test_other_scores(source, projection):
     _check(6, 1500, "bf16", [300] * 6, 4, source=source, projection=projection)
 
 
-# 33 heads: more than the split selection takes below 36864 tokens; budgets on both sides of the limit of rows
-@pytest.mark.parametrize("heads,n,total", [(33, 32768, 33 * 200), (64, 8192, ROWS), (64, 8192, ROWS + 64), (128, 2048, ROWS)])
+# budgets on both sides of the limit of rows, heads on both sides of the limit of tokens (33: more than the split selection takes
+# below 36864 tokens)
+@pytest.mark.parametrize("heads,n,total", [(33, LONGEST, 33 * 200), (33, LONGEST + 1, 33 * 200), (32, LONGEST, 32 * 200), (3, LONGEST + 1, 3 * 2000), (64, 8192, ROWS),
+                                           (64, 8192, ROWS + 64), (128, 2048, ROWS)])
 def test_both_sides_of_the_rule(heads, n, total):
     _check(heads, n, "bf16", [total // heads] * heads, 4)
 

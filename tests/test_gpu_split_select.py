@@ -109,8 +109,10 @@ def _one_call(K, V, dtype, r, budgets, s, with_scores=True, sketch=None):
         return sc.t.cpu().numpy(), idx, off
 
 
-# 1 to 33 heads on both sides of the lengths at which the route changes; 128 columns and fp32 have other scoring kernels
+# 1 to 33 heads on both sides of the lengths at which the route changes (up to 32768 tokens, with few rows, it is the selection that gathers
+# as well); 128 columns and fp32 have other scoring kernels
 @pytest.mark.parametrize("heads,n,r,dtype", [(1, 24576, 20, "bf16"), (1, 24577, 20, "bf16"), (3, 30001, 64, "bf16"), (33, 36865, 20, "bf16"),
+                                             (1, 32768, 20, "bf16"), (1, 32769, 20, "bf16"), (3, 33001, 64, "bf16"), (8, 32767, 20, "bf16"),
                                              (2, 131072, 128, "bf16"), (1, 50000, 20, "fp32"), (2, 33333, 64, "fp32"), (1, 40000, 128, "fp32")])
 def test_one_call(heads, n, r, dtype):
     cfg = wl.scaled(wl.CONFIGS["c2"], kv_heads=heads, n=n, r=r, dtype=dtype)
@@ -128,11 +130,12 @@ def test_one_call(heads, n, r, dtype):
     assert np.array_equal(idx, idx2)
 
 
-@pytest.mark.parametrize("r", [64, 128])
-def test_rows_scored_again(r):
+# (counted in the scan: more than two heads, and longer ones than the selection that gathers takes)
+@pytest.mark.parametrize("r,n", [(64, 33002), (128, 33002), (64, 30002)])
+def test_rows_scored_again(r, n):
     """fp32 rows whose split into bf16 parts overflows (a float above the largest bf16, in a dimension that
     the sketch leaves out) but whose score is finite: counted once, in the bin of that score."""
-    n, s = 30002, 4
+    s = 4
     cfg = wl.scaled(wl.CONFIGS["c2"], kv_heads=6, n=n, r=r, dtype="fp32")
     K, V = wl.host_cache(cfg)
     rng = np.random.default_rng(r)
@@ -174,8 +177,8 @@ def test_scores_out_of_the_ordinary():
         assert got.min() == 0 and got.max() < n and np.all(np.diff(got.reshape(6, k)) > 0)
 
 
-# several workgroups per head, one, a head in parts, the fused kernel; and the two separate normalisations
-@pytest.mark.parametrize("heads,n,dtype", [(2, 30001, "fp32"), (33, 30001, "bf16"), (129, 37001, "bf16"), (256, 700, "bf16"), (2, 300, "fp32")])
+# the selection that gathers, the split one, one workgroup per head, a head in parts, the fused kernel; and the two separate normalisations
+@pytest.mark.parametrize("heads,n,dtype", [(2, 30001, "fp32"), (2, 33001, "fp32"), (33, 30001, "bf16"), (33, 34001, "bf16"), (129, 37001, "bf16"), (256, 700, "bf16"), (2, 300, "fp32")])
 def test_sum_too_small_to_divide_by(heads, n, dtype):
     """A head whose scores add up to less than the smallest number with a finite reciprocal (2.9e-39) keeps
     finite scores, in their order."""
