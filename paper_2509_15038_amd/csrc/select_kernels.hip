@@ -464,7 +464,7 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float*
 }
 
 // Raises the kernel's limit of dynamic LDS to what its static part leaves, where `bytes` of indices need it.  At the launch (0.1 us):
-// all variants a long context could launch, 17 of them, made the first curdkv_create of a process 2.4 ms longer.
+// all variants a long context could launch, 17 of them, made the first curdkv_create of a process 2.2 ms longer.
 static hipError_t allow_indices(const curdkv_ctx* ctx, const void* kernel, size_t bytes) {
     return bytes <= 48 * 1024 ? hipSuccess : hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, ctx->lds_limit - kSelStaticReserve);
 }
