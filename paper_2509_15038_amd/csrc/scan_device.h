@@ -71,37 +71,17 @@ __device__ __forceinline__ void swap_rows(float& a, float& b) {
     b = __uint_as_float(r[1]);
 }
 
-// lk, lv: per-lane partial sums of a token held by lanes t, t+16, t+32, t+48; become the sums of the four, in
-// all four lanes.
-__device__ __forceinline__ void sum_rows(float& lk, float& lv) {
+// lk, lv: per-lane partial sums of a token held by lanes t, t+16, t+32, t+48.
+// Returns (sum of the four lk) * (sum of the four lv) in all four lanes.
+__device__ __forceinline__ float combine_rows(float lk, float lv) {
     swap_halves(lk, lv);                 // lk = [lk rows 0,1 | lv rows 0,1], lv = [lk rows 2,3 | lv rows 2,3]
     float x = lk + lv;                   // rows: lk0+lk2, lk1+lk3, lv0+lv2, lv1+lv3
     float y = x;
     swap_rows(x, y);                     // x = rows 0,0,2,2 ; y = rows 1,1,3,3
-    lk = x + y;                          // rows: LK, LK, LV, LV
-    lv = lk;
-    swap_halves(lk, lv);                 // lk = LK everywhere, lv = LV everywhere
-}
-__device__ __forceinline__ void sum_rows(double& lk, double& lv) {
-    auto swap = [](auto swap_word, double& a, double& b) {
-        float al = __int_as_float(__double2loint(a)), ah = __int_as_float(__double2hiint(a));
-        float bl = __int_as_float(__double2loint(b)), bh = __int_as_float(__double2hiint(b));
-        swap_word(al, bl);
-        swap_word(ah, bh);
-        a = __hiloint2double(__float_as_int(ah), __float_as_int(al));
-        b = __hiloint2double(__float_as_int(bh), __float_as_int(bl));
-    };
-    swap(swap_halves, lk, lv);
-    double x = lk + lv, y = x;
-    swap(swap_rows, x, y);
-    lk = x + y;
-    lv = lk;
-    swap(swap_halves, lk, lv);
-}
-// Returns (sum of the four lk) * (sum of the four lv) in all four lanes.
-__device__ __forceinline__ float combine_rows(float lk, float lv) {
-    sum_rows(lk, lv);
-    return lk * lv;
+    float z = x + y;                     // rows: LK, LK, LV, LV
+    float w = z;
+    swap_halves(z, w);                   // z = LK everywhere, w = LV everywhere
+    return z * w;
 }
 
 // Scores tiles [t_begin, t_end) of one head; the score of token `row` is written
@@ -470,15 +450,15 @@ __device__ __forceinline__ void scan_few(const typename FewOperand<F32>::Word* _
 // A float whose first part is infinite turns its row into NaN here; rescore_row then does such
 // a row again in plain fp32.
 //
-// The squares of a lane's four columns of every block have a sum each, and these and the lanes' are added in double.  Error of a score
-// against 64 bits, normal rows, root mean square (largest): r = 33 5.6e-8 (2.5e-7), r = 64 4.5e-8 (1.9e-7), r = 128 4.0e-8 (1.6e-7), and the
-// same whatever the channels' sizes are; with one chain of fp32 additions 8.2e-8 (3.7e-7), 8.0e-8 (3.7e-7), 8.7e-8 (3.5e-7).
+// The squares of a lane's four columns of every block have a sum each; these are added in double, and the lanes' once for the 64 tokens
+// of a group.  Error of a score against 64 bits, normal rows, root mean square (largest): r = 33 5.6e-8 (2.5e-7), r = 64 4.5e-8
+// (1.9e-7), r = 128 4.0e-8 (1.6e-7), and the same whatever the channels' sizes are; with one chain of fp32 additions 8.2e-8 (3.7e-7), 8.0e-8 (3.7e-7), 8.7e-8 (3.5e-7).
 //
 // Why: 4*d*r flop per 1024 bytes of a token's K and V rows made the fp32 matrix units the bound
 // from r = 64 on; six bf16 products take 6/16 of their time.  256 heads of 16384
 // tokens: r = 64 1148 -> 840 us (HBM alone: 720), r = 128 2146 -> 1310 us (the bf16 units are busy
-// two thirds of the time).  One chain of sums is 1 % faster there, and 34.7 us against 36.9 where a wave has a group or two (3 heads of
-// 6000 tokens, r = 128).
+// two thirds of the time).  The sums in double cost nothing once per group; once per 16 tokens, 0.5 us each (3 heads of 6000 tokens, r = 128, 36.9 us
+// against 34.9).
 //
 // The token operand of MFMA step s (0..3) in lane L are the floats of stretches 2s and 2s + 1,
 // d = (2s + e/4)*16 + (L/16)*4 + e%4 for e = 0..7, the sketch operand G[d][16*cb + L%16]: two
@@ -548,6 +528,26 @@ __device__ float rescore_row(const bf16x8* gs, const float* __restrict__ row, in
     return l;
 }
 
+// x[q]: a lane's share of the sum of token q*16 + t, t = lane % 16, whose other shares are in lanes t, t+16, t+32, t+48.  Returns
+// in lane q*16 + t the sum of that token.
+__device__ __forceinline__ double sum_group(const double (&x)[4]) {
+    auto swap = [](auto swap_word, double& a, double& b) {
+        float al = __int_as_float(__double2loint(a)), ah = __int_as_float(__double2hiint(a));
+        float bl = __int_as_float(__double2loint(b)), bh = __int_as_float(__double2hiint(b));
+        swap_word(al, bl);
+        swap_word(ah, bh);
+        a = __hiloint2double(__float_as_int(ah), __float_as_int(al));
+        b = __hiloint2double(__float_as_int(bh), __float_as_int(bl));
+    };
+    double a = x[0], b = x[1], c = x[2], d = x[3];
+    swap(swap_halves, a, c);             // a = [x0 rows 0,1 | x2 rows 0,1], c = [x0 rows 2,3 | x2 rows 2,3]
+    swap(swap_halves, b, d);             // x1, x3 likewise
+    a += c;                              // rows: x0's 0+2, x0's 1+3, x2's 0+2, x2's 1+3
+    b += d;
+    swap(swap_rows, a, b);               // a = rows x0's, x1's, x2's, x3's 0+2 ; b = their 1+3
+    return a + b;
+}
+
 struct TileF32 {        // 16 tokens of K and of V as seen by a lane
     float4 k[8];
     float4 v[8];
@@ -570,7 +570,6 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
     const int32_t groups = (t_end - t_begin + 1) >> 1;          // of 64 tokens
     if (groups <= 0) return 0.f;
     float acc_sum = 0.f;
-    float pend = 0.f;                                           // this lane's score of the current group
     TileF32 r;
     // rows past the end reload the last one; their scores are dropped
     auto load = [&](int32_t first) {
@@ -586,6 +585,7 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
             for (int s = 0; s < 8; ++s) r.v[s] = Vh[off + s * 4];
         }
     };
+    double tk[4] = {}, tv[4] = {};                             // a lane's share of the norms of the group's tokens, 16 each
     auto step = [&](int part, int32_t next) {                   // scores the 16 tokens in r, loads those from `next`
         Parts xk[4], xv[4];
 #pragma unroll
@@ -626,10 +626,8 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
             __builtin_amdgcn_sched_barrier(0);                  // or several blocks' loads pile up in registers
         }
         auto total = [](const f32x4& q) { return ((double)q[0] + (double)q[1]) + ((double)q[2] + (double)q[3]); };
-        double lk = SRC == kSrcV ? 0.25 : total(qk), lv = SRC == kSrcK ? 0.25 : total(qv);
-        sum_rows(lk, lv);
-        const float lkv = (float)(lk * lv);
-        pend = q == part ? lkv : pend;
+        if (SRC != kSrcV) tk[part] = total(qk);
+        if (SRC != kSrcK) tv[part] = total(qv);
     };
     // the walk starts at a rotated group, as in walk_tiles (whole groups only)
     const int32_t rot = (t_begin + 2 * groups) * kTileTokens <= n && groups >= 4 ? (int32_t)(phase % (uint32_t)groups) : 0;
@@ -643,6 +641,8 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
         step(1, first + 32);
         step(2, first + 48);
         step(3, i + 1 < groups ? base + g * 64 : first + 48);   // (at the end these rows once more, from the L2, unused)
+        const double lk = SRC == kSrcV ? 1.0 : sum_group(tk), lv = SRC == kSrcK ? 1.0 : sum_group(tv);
+        const float pend = (float)(lk * lv);
         const int32_t row = first + lane;
         if (row < n) {
             lds_rows[row - row0] = pend;
