@@ -123,3 +123,42 @@ def test_keys_per_thread(keys, more):
         assert np.array_equal(got[off[h]:off[h + 1]], orc.select(scores[h].astype(np.float64), int(budgets[h]), 4)), h
     if keys in (1, 3, 10, 24, 32):
         _check(2, n, "bf16", [n // 10, n // 7], 4)
+
+
+# (33000: one workgroup's indices, 4 bytes a token, need more LDS than a launch gets by itself, as 14000's and 20000's do; 9000's do not)
+@pytest.mark.parametrize("heads,n", [(3, 9000), (3, 14000), (3, 20000), (40, 33000)])
+def test_captured(heads, n):
+    """One call and the selection in a graph, replayed on other caches, against the same calls without one."""
+    import torch
+    budgets = np.full((heads,), n // 10, np.int32)
+    off = wl.offsets_for(budgets)
+    total = int(off[-1])
+    K, V = (x.clone() for x in _cache(heads, n, "bf16", 1))
+    with B.Context(1, heads, 4, 128, 20, "bf16", n, 77) as ctx:
+        def buffers():
+            return [torch.empty((heads, n), device="cuda"), torch.empty((total,), dtype=torch.int32, device="cuda"),
+                    torch.empty((total, 128), dtype=K.dtype, device="cuda"), torch.empty((total, 128), dtype=K.dtype, device="cuda"),
+                    torch.empty((total,), dtype=torch.int32, device="cuda")]
+
+        def calls(sc, ix, Ko, Vo, again):
+            ctx.compress(K, V, n, budgets, 4, off, sc, ix, Ko, Vo)
+            ctx.select(sc, n, budgets, 4, off, again)
+
+        kept, eager = buffers(), buffers()
+        calls(*kept)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            calls(*kept)
+        for seed in (2, 3, 4):
+            for mine, new in zip((K, V), _cache(heads, n, "bf16", seed)):
+                mine.copy_(new)
+            for x in kept:
+                x.fill_(-1)
+            graph.replay()
+            torch.cuda.synchronize()
+            calls(*eager)
+            torch.cuda.synchronize()
+            for a, b in zip(kept, eager):
+                assert torch.equal(a, b), seed
+            assert torch.equal(kept[1], kept[4]), seed
