@@ -51,7 +51,9 @@ __global__ __launch_bounds__(kFusedThreads, 2) void fused_kernel(
         per_wave += per_wave & 1;                  // whole pairs
         const int32_t t_begin = wave * per_wave;
         const int32_t t_end = t_begin + per_wave < tiles ? t_begin + per_wave : tiles;
-        acc = scan_tiles<CB, SRC, PROJ>(G, Kh, Vh, n, t_begin, t_end, sc, 0, lane, scan_phase(head, wave));
+        // more than 2048 tokens a head are more rows than the caches hold (fetch in scan_device.h): 256 heads of 2048 tokens (268 MB), a tenth
+        // kept, 63.2 us either way, of 4096, a fifth, 134.6 and streamed 126.5, of 32768, a tenth, 863 and 781; of 1024 33.8 and 35.0
+        acc = scan_tiles<CB, SRC, PROJ, false, (KPT > 4)>(G, Kh, Vh, n, t_begin, t_end, sc, 0, lane, scan_phase(head, wave));
     }
     // ---- 2. sum over the head ----------------------------------------------------------
     acc = wave_sum(acc);

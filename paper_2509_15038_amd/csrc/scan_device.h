@@ -30,11 +30,42 @@ namespace curdkv {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+typedef __attribute__((ext_vector_type(4))) unsigned int words4;
 
 union Chunk {           // 16 bytes of a token row: 8 bf16
     uint4 u;
     bf16x8 v;
 };
+
+// How rows are fetched.  STREAM = false: a load instruction asks for 64 bytes of each of 16 rows, in operand layout, and leaves the rows
+// in the caches, for a call that reads them again (a gather) or was called right after they were written.  STREAM = true, for calls
+// that read more than the caches hold (stream_rows in scores_kernels.hip): whole 128-byte lines, 8 rows an instruction, marked
+// non-temporal, which spares the Infinity Cache the filling.  Non-temporal loads of half lines fetch lines twice.  Plain reads of 512 MB and
+// 2 GB by 1024 such waves, us: half lines 95.6 and 357, non-temporal 94.8 and 362; whole lines 95.1 and 357, non-temporal 81.8 and 312 (6.9 TB/s).
+// The loads of 16 rows come in pairs (a, b) of 128 bytes a row: for a, lanes (tok, q) take 16-byte piece q of row tok (tok < 8) or q + 4 of row tok - 8,
+// for b the same of rows 8..15; settle_pair then exchanges between the halves of every 16 lanes, three register moves a word.
+template <bool STREAM>
+__device__ __forceinline__ int load_row(int tok, int which) { return STREAM ? (tok & 7) + 8 * which : tok; }
+template <bool STREAM>
+__device__ __forceinline__ int load_piece(int tok, int q, int which) { return STREAM ? q + ((tok >> 3) << 2) : q + 4 * which; }
+template <bool STREAM, class W>
+__device__ __forceinline__ W fetch(const W* p) {
+    if constexpr (STREAM) return __builtin_bit_cast(W, __builtin_nontemporal_load(reinterpret_cast<const words4*>(p)));
+    else return *p;
+}
+// After it lane (tok, q) has pieces q (in a) and q + 4 (in b) of row tok, as without STREAM.
+template <class W>
+__device__ __forceinline__ void settle_pair(W& a, W& b) {
+    words4 x = __builtin_bit_cast(words4, a), y = __builtin_bit_cast(words4, b);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int lo = (int)x[i], hi = (int)y[i];
+        x[i] = (unsigned)__builtin_amdgcn_update_dpp(lo, hi, 0x128, 0xF, 0xC, false);   // row_ror:8 into lanes 8..15 of each 16,
+        y[i] = (unsigned)__builtin_amdgcn_update_dpp(hi, lo, 0x128, 0xF, 0x3, false);   // and into lanes 0..7
+    }
+    a = __builtin_bit_cast(W, x);
+    b = __builtin_bit_cast(W, y);
+}
 
 struct TileRegs {       // one 32-token tile of K and of V as seen by a lane
     Chunk k[2][4];
@@ -123,7 +154,7 @@ __device__ __forceinline__ uint32_t scan_phase(int head, int wave_of_head) {
 //                                   predicate, hence no branch, which keeps the steady-state
 //                                   loop one basic block so that the compiler's wait counts let
 //                                   loads stay in flight;
-//   compute_tile(const Tile&, slot) scores the tile as first (0) or second (1) of its pair;
+//   compute_tile(Tile&, slot)       scores the tile, once per load of it, as first (0) or second (1) of its pair;
 //   store_pair(tile, check)         puts the pair's 64 scores away (tile = its first tile).
 // t_begin must be even, and t_end even or equal to ceil(n/32): a missing second tile is taken
 // to lie beyond n.
@@ -175,7 +206,7 @@ __device__ __forceinline__ void walk_tiles(int32_t n, int32_t t_begin, int32_t t
 // COUNT: every score is also counted in `hist` (raw_hist_count), those of the first n_sink rows as nothing:
 // one LDS atomic per 64 tokens, and the histogram written at the end (scan of 32 heads of 32768 tokens 95.4 us without,
 // 99.7 with it, which saves a pass over the scores).
-template <int CB, int SRC = kSrcKV, bool PROJ = true, bool COUNT = false>
+template <int CB, int SRC = kSrcKV, bool PROJ = true, bool COUNT = false, bool STREAM = false>
 __device__ __forceinline__ float scan_tiles(const SketchRegs<CB>& G, const uint4* __restrict__ Kh,
                                             const uint4* __restrict__ Vh, int32_t n, int32_t t_begin,
                                             int32_t t_end, float* lds_rows, int32_t row0, int lane,
@@ -187,24 +218,33 @@ __device__ __forceinline__ float scan_tiles(const SketchRegs<CB>& G, const uint4
     auto load_tile = [&](TileRegs& r, int32_t tile, auto check) {
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2) {
-            int32_t row = tile * kTileTokens + t2 * 16 + tok;
-            if (decltype(check)::value) row = row < n ? row : n - 1;   // ragged tail: reload the last row
-            const size_t off = (size_t)(uint32_t)row * 16 + q;
-            const uint4* kp = Kh + off;
-            const uint4* vp = Vh + off;
+            size_t off[2];
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+                int32_t row = tile * kTileTokens + t2 * 16 + load_row<STREAM>(tok, w);
+                if (decltype(check)::value) row = row < n ? row : n - 1;   // ragged tail: reload the last row
+                off[w] = (size_t)(uint32_t)row * 16 + load_piece<STREAM>(tok, q, w);
+            }
             if (SRC != kSrcV) {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) r.k[t2][s].u = kp[s * 4];
+                for (int s = 0; s < 4; ++s) r.k[t2][s].u = fetch<STREAM>(Kh + off[s & 1] + (s >> 1) * 8);
             }
             if (SRC != kSrcK) {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) r.v[t2][s].u = vp[s * 4];
+                for (int s = 0; s < 4; ++s) r.v[t2][s].u = fetch<STREAM>(Vh + off[s & 1] + (s >> 1) * 8);
             }
         }
     };
-    auto compute_tile = [&](const TileRegs& r, int slot) {      // slot: 0 = first tile of the pair
+    auto compute_tile = [&](TileRegs& r, int slot) {      // slot: 0 = first tile of the pair
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2) {
+            if constexpr (STREAM) {
+#pragma unroll
+                for (int s = 0; s < 4; s += 2) {
+                    if (SRC != kSrcV) settle_pair(r.k[t2][s], r.k[t2][s + 1]);
+                    if (SRC != kSrcK) settle_pair(r.v[t2][s], r.v[t2][s + 1]);
+                }
+            }
             // a tensor that is not scored contributes 1/4 per lane: four lanes make exactly 1
             float lk = SRC == kSrcV ? 0.25f : 0.f, lv = SRC == kSrcK ? 0.25f : 0.f;
             if (PROJ) {

@@ -47,7 +47,8 @@ template <int CB> struct Stage {    // tiles (of 32 tokens) a wave collects betw
 };
 
 // COUNT: the workgroup also leaves its histogram of scores for the split selection (split_select.hip).
-template <int CB, int SRC, bool PROJ, bool COUNT>
+// STREAM: rows past the caches (scan_device.h).
+template <int CB, int SRC, bool PROJ, bool COUNT, bool STREAM>
 __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
     const uint4* __restrict__ K, const uint4* __restrict__ V, const uint4* __restrict__ Gp,
     float* __restrict__ scores, float* __restrict__ partial, int64_t n, int blocks_per_head,
@@ -82,7 +83,7 @@ __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
     for (int32_t seg = t_begin; seg < t_end; seg += kStageTiles) {
         const int32_t seg_end = seg + kStageTiles < t_end ? seg + kStageTiles : t_end;
         const int32_t r0 = seg * kTileTokens;
-        acc_sum += scan_tiles<CB, SRC, PROJ, COUNT>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane,
+        acc_sum += scan_tiles<CB, SRC, PROJ, COUNT, STREAM>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane,
                                                    scan_phase(head, blk * 4 + wave), hist, n_sink);
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
         for (int32_t r = r0 + lane; r < r1; r += 64) __builtin_nontemporal_store(mine[r - r0], &sh[r]);
@@ -353,6 +354,18 @@ static bool few_tokens(const curdkv_ctx* ctx, int64_t n, bool running) {
     return steps <= (f32 ? kFewF32Steps : kFewBf16Steps) * few_blocks_per_head(ctx, n, running);
 }
 
+// Whether rows are fetched past the caches (fetch in scan_device.h).  What fits the 256 MB Infinity Cache is often there already, and a gather
+// of the same call finds its rows there.  us, kept in the caches and streamed, three caches in turn, r = 64: curdkv_scores of 8 heads of
+// 24576 tokens (101 MB) 22.2 and 23.2, of 32768 (134) 31.2 and 29.0, of 65536 53.8 and 47.8; appends of 768 tokens to 256 heads (101) 19.8 and
+// 20.6, of 1024 28.7 and 26.9; one call, a tenth kept, 8 heads of 8192 17.3 and 19.2, of 32768 (134) 44.8 and 45.4, of 40960 (168) 57.7 and 54.7, half
+// kept (168) 73.8 and 74.7, of 49152 (201) 88.6 and 85.7.  Large: 256 heads of 32768 703 and 624, of 131072, r = 128, 2858 and 2578.
+constexpr int64_t kStreamBytes = 120000000, kStreamBytesReread = 160000000;
+
+static bool stream_rows(const curdkv_ctx* ctx, int64_t n, bool reread) {
+    const int64_t row = kHeadDim * (ctx->cfg.dtype == CURDKV_DTYPE_BF16 ? 2 : 4) * (ctx->cfg.score_source == CURDKV_SCORE_KV ? 2 : 1);
+    return ctx->cfg.dtype == CURDKV_DTYPE_BF16 && ctx->heads * n * row > (reread ? kStreamBytesReread : kStreamBytes);
+}
+
 hipError_t configure_kernels(curdkv_ctx* ctx) {
     (void)ctx;                     // every scoring kernel uses static LDS only
     return hipSuccess;
@@ -361,7 +374,7 @@ hipError_t configure_kernels(curdkv_ctx* ctx) {
 hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n,
                          float* scores, hipStream_t stream, bool normalise, int* blocks_per_head,
                          int64_t out_stride, int64_t out_offset, double* sums, bool restart,
-                         bool* summed, bool with_hist, int32_t n_sink) {
+                         bool* summed, bool with_hist, int32_t n_sink, bool reread) {
     if (out_stride <= 0) out_stride = n;
     const bool few = few_tokens(ctx, n, sums != nullptr) && !with_hist;
     const int bph = few ? few_blocks_per_head(ctx, n, sums != nullptr) : pick_blocks_per_head(ctx, n, with_hist ? split_hists(ctx) : kMaxBlocksPerHead);
@@ -377,6 +390,7 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
     }
     uint32_t* hist = with_hist ? split_hist(ctx) : nullptr;
     uint32_t* coarse = with_hist ? split_coarse(ctx) : nullptr;
+    const bool stream_past = stream_rows(ctx, n, reread);
     const dim3 grid((unsigned)(ctx->heads * bph));
     float* part = ctx->d_partial;
     auto launch = [&](auto cb, auto src, auto proj, auto count) {
@@ -393,11 +407,15 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
             };
             if (bf16) launch_few(std::false_type{});
             else launch_few(std::true_type{});
-        } else if (bf16)
-            scores_bf16_kernel<CB, SRC, PROJ, COUNT><<<grid, 256, 0, stream>>>(
-                (const uint4*)K, (const uint4*)V, (const uint4*)ctx->d_G, scores, part, n, bph, out_stride, out_offset, sums, rs,
-                hist, coarse, hists, n_sink);
-        else
+        } else if (bf16) {
+            auto launch_bf16 = [&](auto past) {
+                scores_bf16_kernel<CB, SRC, PROJ, COUNT, decltype(past)::value><<<grid, 256, 0, stream>>>(
+                    (const uint4*)K, (const uint4*)V, (const uint4*)ctx->d_G, scores, part, n, bph, out_stride, out_offset, sums, rs,
+                    hist, coarse, hists, n_sink);
+            };
+            if (stream_past) launch_bf16(std::true_type{});
+            else launch_bf16(std::false_type{});
+        } else
             scores_f32_kernel<CB, SRC, PROJ, COUNT><<<grid, ShapeF32<CB>::kWaves * 64, 0, stream>>>(
                 (const float4*)K, (const float4*)V, (const float4*)ctx->d_G, scores, part, n, bph, out_stride, out_offset, sums, rs,
                 hist, coarse, hists, n_sink);

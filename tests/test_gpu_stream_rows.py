@@ -1,0 +1,79 @@
+"""Scoring of more rows than the caches hold, which are fetched by whole lines past them: at sizes taken from that limit,
+at the edges of the 16-token steps, the 32-token tiles and a wave's range.  Against the float64 oracle."""
+import numpy as np
+import pytest
+
+from oracle import curdkv_oracle as orc
+from paper_2509_15038_amd import binding as B
+from paper_2509_15038_amd import workloads as wl
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+SEED = 0xC0DE0014
+LIMIT = gu.limit("scores_kernels.hip", "kStreamBytes")
+LIMIT_REREAD = gu.limit("scores_kernels.hip", "kStreamBytesReread")
+
+# A projected coordinate is an fp32 sum of 128 exact products, rounded once per 32 terms, its square and their sum over r columns as many
+# roundings again, then a product and the division: some 30 roundings of 2^-24 at random, relative to the score
+NORM_TOL = 1e-6
+
+
+def _heads(limit, n, dtype, source):
+    return limit // (n * 128 * (2 if dtype == "bf16" else 4) * (2 if source == "kv" else 1)) + 1
+
+
+def _cache(heads, n, dtype, seed):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    K = torch.randn((heads, n, 128), generator=g, device="cuda") * torch.exp(torch.randn((heads, 1, 128), generator=g, device="cuda"))
+    V = torch.randn((heads, n, 128), generator=g, device="cuda") * torch.exp(torch.randn((heads, n, 1), generator=g, device="cuda"))
+    return K.to(dt), V.to(dt)
+
+
+def _want(K, V, i, r, dtype, source, projection):
+    G = orc.sketch(SEED, i, 0, 1, 128, r, dtype)
+    return orc.scores(K[i].double().cpu().numpy(), V[i].double().cpu().numpy(), G, source, projection)
+
+
+@pytest.mark.parametrize("n", [257, 300, 1009, 1024, 4133, 70001])
+@pytest.mark.parametrize("dtype,r,source,projection", [("bf16", 20, "kv", True), ("bf16", 33, "k", True), ("bf16", 64, "v", True), ("bf16", 64, "kv", True),
+                                                       ("bf16", 128, "kv", True), ("bf16", 64, "kv", False)])
+def test_scores(n, dtype, r, source, projection):
+    import torch
+    heads = _heads(LIMIT, n, dtype, source)
+    K, V = _cache(heads, n, dtype, n * 512 + r)
+    with B.Context(heads, 1, 4, 128, r, dtype, n, SEED, source, projection) as ctx:
+        out = gu.Guarded((heads, n), torch.float32, float("nan"))
+        ctx.scores(K, V, n, out.t)
+        raw, sums = torch.full((heads, n), float("nan"), device="cuda"), torch.zeros((heads,), dtype=torch.float64, device="cuda")
+        ctx.scores_append(K, V, n, 0, n, raw, sums)
+        out.check("scores")
+        out, raw, sums = out.t.cpu().numpy(), raw.cpu().numpy().astype(np.float64), sums.cpu().numpy()
+    assert np.allclose(sums, raw.sum(1), rtol=1e-6)
+    for i in (0, heads // 2, heads - 1):
+        want = _want(K, V, i, r, dtype, source, projection)
+        for x in (out[i], raw[i] / raw[i].sum()):
+            assert np.linalg.norm(x - want) <= NORM_TOL * np.linalg.norm(want), (n, r, source, i)
+
+
+# one call on either side of its limit: the kernel that does everything (few rows kept of as many heads as units), the selection
+# that gathers, the split selection with histograms from the scoring, and separate kernels; the rows kept are found again
+@pytest.mark.parametrize("heads,n,r,keep", [(256, 2049, 64, 0.1), (256, 2500, 20, 0.05), (20, 16411, 64, 0.1), (128, 2600, 20, 0.4), (5, 70001, 20, 0.1), (40, 40001, 128, 0.05)])
+def test_one_call(heads, n, r, keep):
+    import torch
+    if heads == 256:
+        heads = torch.cuda.get_device_properties(0).multi_processor_count
+    assert heads * n * 512 > LIMIT_REREAD
+    K, V = _cache(heads, n, "bf16", n + r)
+    budgets = np.full((heads,), int(keep * n), np.int32)
+    with B.Context(heads, 1, 4, 128, r, "bf16", n, SEED) as ctx:
+        sc, ix, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, 4, "bf16", one_call=True)
+    for i in (0, heads // 2, heads - 1):
+        rows = ix[off[i]:off[i + 1]]
+        lt = _want(K, V, i, r, "bf16", "kv", True)
+        gu.check_scores(sc[i].cpu().numpy(), lt, str(i))
+        gu.check_selection(rows.cpu().numpy().astype(np.int64), lt, int(budgets[i]), 4, str(i))
+        assert torch.equal(Ko[off[i]:off[i + 1]], K[i][rows.long()]) and torch.equal(Vo[off[i]:off[i + 1]], V[i][rows.long()])
