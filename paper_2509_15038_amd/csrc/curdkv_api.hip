@@ -355,7 +355,7 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
         scores = ctx->d_scores_ws;
     }
     if (fusable) {      // scores from the fused kernel's first phases, then select and gather kernels
-        if (launch_fused(ctx, K, V, n, 0, ctx->d_zero_offsets, scores, nullptr, nullptr, nullptr, st) != hipSuccess ||
+        if (launch_fused(ctx, K, V, n, 0, ctx->d_zero_offsets, scores, nullptr, nullptr, nullptr, st, nullptr, nullptr, stay_share(ctx, n, total)) != hipSuccess ||
             launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st) != hipSuccess ||
             launch_compact(ctx, K, V, n, indices, ctx->plan.d_offsets, total, K_out, V_out, st) != hipSuccess)
             return CURDKV_ERR_HIP;
@@ -365,7 +365,7 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     // back), which saves the separate pass over the scores
     int bph = 0;
     if (launch_scores(ctx, K, V, n, together ? ctx->d_raw_ws : scores, st, /*normalise=*/false, &bph, 0, 0, nullptr, false, nullptr,
-                      with_hist, n_sink, /*reread=*/true) != hipSuccess) return CURDKV_ERR_HIP;
+                      with_hist, n_sink, /*kept=*/total) != hipSuccess) return CURDKV_ERR_HIP;
     SelectGather gather{K, V, K_out, V_out, total, false};
     if (together)
         return launch_select_gather(ctx, ctx->d_raw_ws, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st, bph, gather) == hipSuccess
@@ -449,8 +449,8 @@ int curdkv_compress_adaptive(curdkv_ctx* ctx, const void* K, const void* V, int6
     int bph = 0;
     const hipError_t e = fused
         ? launch_fused(ctx, K, V, n, n_sink, ctx->d_zero_offsets, scores, nullptr, nullptr, nullptr, st,
-                       adaptive_hist_buffer(ctx, ctx->d_adaptive_ws), adaptive_coarse_buffer(ctx, ctx->d_adaptive_ws))
-        : launch_scores(ctx, K, V, n, scores, st, /*normalise=*/!allots, &bph, 0, 0, nullptr, false, nullptr, false, 0, /*reread=*/true);
+                       adaptive_hist_buffer(ctx, ctx->d_adaptive_ws), adaptive_coarse_buffer(ctx, ctx->d_adaptive_ws), stay_share(ctx, n, total))
+        : launch_scores(ctx, K, V, n, scores, st, /*normalise=*/!allots, &bph, 0, 0, nullptr, false, nullptr, false, 0, /*kept=*/total);
     if (e != hipSuccess) return CURDKV_ERR_HIP;
     bool planned = false;
     if (launch_adaptive(ctx, ctx->d_adaptive_ws, scores, n, budget, (int32_t)sp, (int32_t)g, R, budgets_out, st,

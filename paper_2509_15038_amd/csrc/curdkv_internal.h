@@ -83,13 +83,15 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
                          float* scores, hipStream_t stream, bool normalise = true,
                          int* blocks_per_head = nullptr, int64_t out_stride = 0, int64_t out_offset = 0,
                          double* sums = nullptr, bool restart = false, bool* summed = nullptr,
-                         bool with_hist = false, int32_t n_sink = 0, bool reread = false);
+                         bool with_hist = false, int32_t n_sink = 0, int64_t kept = 0);
 // with_hist: every workgroup also leaves its counts of the products of tokens n_sink and up for the
 // split selection (split_select.hip), which must apply to n.
-// reread: the call reads the rows it keeps again.
+// kept: rows that the call reads again to gather them.
 // sums (device, [heads]) given: where one block scores a whole head, the kernel itself adds the
 // head's total to sums[head] (after zeroing it if `restart`) and *summed is set; otherwise the
 // caller adds the partial sums (launch_accumulate).
+// In 256ths: how much of a scan, its end, should leave its rows in the caches for a gather of `kept` rows that follows.
+int stay_share(const curdkv_ctx* ctx, int64_t n, int64_t kept);
 hipError_t launch_accumulate(const curdkv_ctx* ctx, int blocks_per_head, double* sums, bool reset,
                              hipStream_t stream);
 hipError_t launch_normalise_sums(const curdkv_ctx* ctx, const float* raw, const double* sums,
@@ -181,6 +183,6 @@ bool fused_applicable(const curdkv_ctx* ctx, int64_t n);
 hipError_t launch_fused(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n, int32_t n_sink,
                         const int64_t* d_offsets, float* scores, int32_t* indices, void* K_out,
                         void* V_out, hipStream_t stream, uint32_t* hist_out = nullptr,
-                        uint32_t* coarse_out = nullptr);
+                        uint32_t* coarse_out = nullptr, int stay = 0);
 
 }  // namespace curdkv

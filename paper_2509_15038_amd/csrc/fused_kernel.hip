@@ -31,7 +31,7 @@ __global__ __launch_bounds__(kFusedThreads, 2) void fused_kernel(
     const uint4* __restrict__ K, const uint4* __restrict__ V, const uint4* __restrict__ Gp,
     int32_t n, int32_t n_sink, const int64_t* __restrict__ offsets, float* __restrict__ scores_out,
     int32_t* __restrict__ indices, u32x4* __restrict__ K_out, u32x4* __restrict__ V_out,
-    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out) {
+    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, int stay) {
     extern __shared__ float sc[];                  // [n rounded up to 64]; later int32 stage[n]
     __shared__ SelectShared<kFusedThreads, KPT> sm;
     __shared__ float wsum[kFusedWaves];
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kFusedThreads, 2) void fused_kernel(
         const int32_t t_end = t_begin + per_wave < tiles ? t_begin + per_wave : tiles;
         // more than 2048 tokens a head are more rows than the caches hold (fetch in scan_device.h): 256 heads of 2048 tokens (268 MB), a tenth
         // kept, 63.2 us either way, of 4096, a fifth, 134.6 and streamed 126.5, of 32768, a tenth, 863 and 781; of 1024 33.8 and 35.0
-        acc = scan_tiles<CB, SRC, PROJ, false, (KPT > 4)>(G, Kh, Vh, n, t_begin, t_end, sc, 0, lane, scan_phase(head, wave));
+        acc = scan_tiles<CB, SRC, PROJ, false, (KPT > 4 ? kStreamStay : kStreamNone)>(G, Kh, Vh, n, t_begin, t_end, sc, 0, lane, scan_phase(head, wave), nullptr, 0, stay_tile(t_begin, t_end, stay));
     }
     // ---- 2. sum over the head ----------------------------------------------------------
     acc = wave_sum(acc);
@@ -139,6 +139,7 @@ struct FusedArgs {
     uint32_t* hist_out;
     uint32_t* coarse_out;
     hipStream_t stream;
+    int stay;                // stay_share
     int dyn;                 // >= 0: only raise the kernel's dynamic LDS limit to this, no launch
 };
 
@@ -150,7 +151,7 @@ static hipError_t one(const FusedArgs& a) {
     const size_t lds = (((size_t)a.n + 63) & ~(size_t)63) * 4;
     fused_kernel<CB, KPT, SRC, PROJ><<<dim3((unsigned)a.ctx->heads), kFusedThreads, lds, a.stream>>>(
         (const uint4*)a.K, (const uint4*)a.V, (const uint4*)a.ctx->d_G, a.n, a.n_sink, a.d_offsets,
-        a.scores, a.indices, (u32x4*)a.K_out, (u32x4*)a.V_out, a.hist_out, a.coarse_out);
+        a.scores, a.indices, (u32x4*)a.K_out, (u32x4*)a.V_out, a.hist_out, a.coarse_out, a.stay);
     return hipGetLastError();
 }
 
@@ -221,9 +222,9 @@ bool fused_applicable(const curdkv_ctx* ctx, int64_t n) {
 
 hipError_t launch_fused(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n, int32_t n_sink,
                         const int64_t* d_offsets, float* scores, int32_t* indices, void* K_out,
-                        void* V_out, hipStream_t stream, uint32_t* hist_out, uint32_t* coarse_out) {
+                        void* V_out, hipStream_t stream, uint32_t* hist_out, uint32_t* coarse_out, int stay) {
     if (!coarse_out) hist_out = nullptr;           // the two go together
-    FusedArgs a{ctx, K, V, (int32_t)n, n_sink, d_offsets, scores, indices, K_out, V_out, hist_out, coarse_out, stream, -1};
+    FusedArgs a{ctx, K, V, (int32_t)n, n_sink, d_offsets, scores, indices, K_out, V_out, hist_out, coarse_out, stream, stay, -1};
     return dispatch(a, ctx->col_blocks, keys_per_thread(n), ctx->cfg.score_source, !ctx->cfg.no_projection);
 }
 

@@ -44,6 +44,9 @@ union Chunk {           // 16 bytes of a token row: 8 bf16
 // 2 GB by 1024 such waves, us: half lines 95.6 and 357, non-temporal 94.8 and 362; whole lines 95.1 and 357, non-temporal 81.8 and 312 (6.9 TB/s).
 // The loads of 16 rows come in pairs (a, b) of 128 bytes a row: for a, lanes (tok, q) take 16-byte piece q of row tok (tok < 8) or q + 4 of row tok - 8,
 // for b the same of rows 8..15; settle_pair then exchanges between the halves of every 16 lanes, three register moves a word.
+// A scan that gathers many rows afterwards leaves those of its end in the caches: kStreamStay.
+constexpr int kStreamNone = 0, kStreamAll = 1, kStreamStay = 2;
+
 template <bool STREAM>
 __device__ __forceinline__ int load_row(int tok, int which) { return STREAM ? (tok & 7) + 8 * which : tok; }
 template <bool STREAM>
@@ -148,21 +151,22 @@ __device__ __forceinline__ uint32_t scan_phase(int head, int wave_of_head) {
 
 // The walk over tiles [t_begin, t_end) of one wave, shared by the storage types: two tile
 // buffers, tiles taken in pairs.
-//   load_tile(Tile&, tile, check)   issues the loads of one tile; check = std::true_type clamps
+//   load_tile(Tile&, tile, check, how)  issues the loads of one tile; check = std::true_type clamps
 //                                   rows to n - 1 (a ragged last tile), std::false_type is for
 //                                   tiles known to lie entirely below n: no clamping, no
 //                                   predicate, hence no branch, which keeps the steady-state
 //                                   loop one basic block so that the compiler's wait counts let
-//                                   loads stay in flight;
+//                                   loads stay in flight; how = std::false_type (kStreamStay, from
+//                                   tile stay_from of the walk on): rows that are to stay in the caches;
 //   compute_tile(Tile&, slot)       scores the tile, once per load of it, as first (0) or second (1) of its pair;
 //   store_pair(tile, check)         puts the pair's 64 scores away (tile = its first tile).
 // t_begin must be even, and t_end even or equal to ceil(n/32): a missing second tile is taken
 // to lie beyond n.
-template <class Tile, class Load, class Compute, class Store>
-__device__ __forceinline__ void walk_tiles(int32_t n, int32_t t_begin, int32_t t_end, uint32_t phase,
+template <int MODE, class Tile, class Load, class Compute, class Store>
+__device__ __forceinline__ void walk_tiles(int32_t n, int32_t t_begin, int32_t t_end, uint32_t phase, int32_t stay_from,
                                            Load load_tile, Compute compute_tile, Store store_pair) {
-    const std::true_type checked;
-    const std::false_type unchecked;
+    const std::true_type checked, past;
+    const std::false_type unchecked, stay;
     if (t_begin < t_end) {
         Tile ra, rb;
         const int32_t full = n / kTileTokens;                   // tiles with all 32 rows below n
@@ -177,45 +181,66 @@ __device__ __forceinline__ void walk_tiles(int32_t n, int32_t t_begin, int32_t t
         int32_t t = t_begin;
         // both buffers are always filled (a lone tile is simply loaded twice): a
         // conditional load here would make every wait in the loop below pessimistic
-        load_tile(ra, at(t), checked);
-        load_tile(rb, t + 1 < t_end ? at(t + 1) : at(t), checked);
+        load_tile(ra, at(t), checked, past);
+        load_tile(rb, t + 1 < t_end ? at(t + 1) : at(t), checked, past);
         const int32_t t_steady = t_end < full ? t_end : full;
-        for (; t + 4 <= t_steady; t += 2) {                     // tiles t .. t+3 of the walk are whole
-            compute_tile(ra, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            load_tile(ra, at(t + 2), unchecked);
-            __builtin_amdgcn_sched_barrier(0);
-            compute_tile(rb, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            load_tile(rb, at(t + 3), unchecked);
-            store_pair(at(t), unchecked);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        for (; t < t_end; t += 2) {                             // last one or two pairs
-            compute_tile(ra, 0);
-            if (t + 2 < t_end) load_tile(ra, at(t + 2), checked);
-            if (t + 1 < t_end) {
+        auto steady = [&](int32_t until, auto how) {            // until: tiles t .. t+3 of the walk are whole
+            for (; t + 4 <= until; t += 2) {
+                compute_tile(ra, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                load_tile(ra, at(t + 2), unchecked, how);
+                __builtin_amdgcn_sched_barrier(0);
                 compute_tile(rb, 1);
-                if (t + 3 < t_end) load_tile(rb, at(t + 3), checked);
+                __builtin_amdgcn_sched_barrier(0);
+                load_tile(rb, at(t + 3), unchecked, how);
+                store_pair(at(t), unchecked);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            store_pair(at(t), checked);                         // an absent second tile lies beyond n
+        };
+        auto finish = [&](auto how) {                           // last one or two pairs
+            for (; t < t_end; t += 2) {
+                compute_tile(ra, 0);
+                if (t + 2 < t_end) load_tile(ra, at(t + 2), checked, how);
+                if (t + 1 < t_end) {
+                    compute_tile(rb, 1);
+                    if (t + 3 < t_end) load_tile(rb, at(t + 3), checked, how);
+                }
+                store_pair(at(t), checked);                     // an absent second tile lies beyond n
+            }
+        };
+        if constexpr (MODE == kStreamStay) {                    // (a kernel of its own: the code of both ways costs short scans 3 %)
+            steady(stay_from < t_steady ? stay_from : t_steady, past);
+            if (stay_from < t_end) {
+                steady(t_steady, stay);
+                finish(stay);
+            } else finish(past);
+        } else {
+            steady(t_steady, past);
+            finish(past);
         }
     }
+}
+
+// The first tile, in the order of the walk, whose rows stay in the caches where a wave streams tiles [begin, end): the last share / 256 of them.
+__device__ __forceinline__ int32_t stay_tile(int32_t begin, int32_t end, int share) {
+    return begin < end ? end - (int32_t)(((int64_t)(end - begin) * share) >> 8) : end;
 }
 
 // COUNT: every score is also counted in `hist` (raw_hist_count), those of the first n_sink rows as nothing:
 // one LDS atomic per 64 tokens, and the histogram written at the end (scan of 32 heads of 32768 tokens 95.4 us without,
 // 99.7 with it, which saves a pass over the scores).
-template <int CB, int SRC = kSrcKV, bool PROJ = true, bool COUNT = false, bool STREAM = false>
+template <int CB, int SRC = kSrcKV, bool PROJ = true, bool COUNT = false, int MODE = kStreamNone>
 __device__ __forceinline__ float scan_tiles(const SketchRegs<CB>& G, const uint4* __restrict__ Kh,
                                             const uint4* __restrict__ Vh, int32_t n, int32_t t_begin,
                                             int32_t t_end, float* lds_rows, int32_t row0, int lane,
-                                            uint32_t phase = 0, uint32_t* hist = nullptr, int32_t n_sink = 0) {
+                                            uint32_t phase, uint32_t* hist, int32_t n_sink, int32_t stay_from) {
+    constexpr bool STREAM = MODE != kStreamNone;
     const int tok = lane & 15, q = lane >> 4;
     float acc_sum = 0.f;
     float pend = 0.f;                                           // this lane's score of the current pair
 
-    auto load_tile = [&](TileRegs& r, int32_t tile, auto check) {
+    auto load_tile = [&](TileRegs& r, int32_t tile, auto check, auto how) {
+        constexpr bool kPast = STREAM && decltype(how)::value;
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2) {
             size_t off[2];
@@ -227,11 +252,11 @@ __device__ __forceinline__ float scan_tiles(const SketchRegs<CB>& G, const uint4
             }
             if (SRC != kSrcV) {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) r.k[t2][s].u = fetch<STREAM>(Kh + off[s & 1] + (s >> 1) * 8);
+                for (int s = 0; s < 4; ++s) r.k[t2][s].u = fetch<kPast>(Kh + off[s & 1] + (s >> 1) * 8);
             }
             if (SRC != kSrcK) {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) r.v[t2][s].u = fetch<STREAM>(Vh + off[s & 1] + (s >> 1) * 8);
+                for (int s = 0; s < 4; ++s) r.v[t2][s].u = fetch<kPast>(Vh + off[s & 1] + (s >> 1) * 8);
             }
         }
     };
@@ -286,11 +311,11 @@ __device__ __forceinline__ float scan_tiles(const SketchRegs<CB>& G, const uint4
             acc_sum += pend;
         }
     };
-    walk_tiles<TileRegs>(n, t_begin, t_end, phase, load_tile, compute_tile, store_pair);
+    walk_tiles<MODE, TileRegs>(n, t_begin, t_end, phase, stay_from, load_tile, compute_tile, store_pair);
     return acc_sum;
 }
 
-// ---- fp32 storage, at most 32 sketch columns ---------------------------------------------
+// ---- fp32 storage, at most 32 sketch columns, few tokens ---------------------------------------------
 // The same walk and the same lane roles as above with mfma_f32_16x16x4f32: lane L holds token
 // L%16 and, of every 64-byte stretch of its row, the 16 bytes (four floats) number L/16, so a
 // load instruction again asks for 64 contiguous bytes per row.  One MFMA takes one of the four
@@ -317,7 +342,7 @@ __device__ __forceinline__ float scan_tiles_f32(const SketchF32<CB>& G, const fl
     const int tok = lane & 15, q = lane >> 4;
     float acc_sum = 0.f;
     float pend = 0.f;
-    auto load_tile = [&](TileRegsF32& r, int32_t tile, auto check) {
+    auto load_tile = [&](TileRegsF32& r, int32_t tile, auto check, auto) {
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2) {
             int32_t row = tile * kTileTokens + t2 * 16 + tok;
@@ -391,7 +416,7 @@ __device__ __forceinline__ float scan_tiles_f32(const SketchF32<CB>& G, const fl
             acc_sum += pend;
         }
     };
-    walk_tiles<TileRegsF32>(n, t_begin, t_end, phase, load_tile, compute_tile, store_pair);
+    walk_tiles<kStreamNone, TileRegsF32>(n, t_begin, t_end, phase, t_end, load_tile, compute_tile, store_pair);
     return acc_sum;
 }
 
@@ -475,7 +500,7 @@ __device__ __forceinline__ void scan_few(const typename FewOperand<F32>::Word* _
     }
 }
 
-// ---- fp32 storage, more than 32 sketch columns -------------------------------------------
+// ---- fp32 storage, many tokens or more than 32 sketch columns -------------------------------------------
 // Lane roles as above; the products go through the bf16 matrix units.  A float is split into three bf16 numbers,
 // x = x1 + x2 + x3 (rounded to nearest each time: 8 significant bits and a sign per part
 // hold 24 bits; exact from 2^-110 up, below which the third part loses bits as a subnormal), the sketch likewise,
@@ -600,41 +625,50 @@ struct TileF32 {        // 16 tokens of K and of V as seen by a lane
 // waves share a SIMD and one's splitting runs beside the other's products.  (One wave of two
 // 32-token buffers per SIMD took turns at the two: 950 us at r = 64, 1460 at r = 128.  Two chains
 // of products per 16 columns and wave, K's and V's, are enough: four measured 3 to 5 % slower.)
-template <int CB, int SRC = kSrcKV, bool COUNT = false>
+template <int CB, int SRC = kSrcKV, bool COUNT = false, bool STREAM = false>
 __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const float4* __restrict__ Kh,
                                                 const float4* __restrict__ Vh,
                                                 int32_t n, int32_t t_begin, int32_t t_end, float* lds_rows,
                                                 int32_t row0, int lane, uint32_t phase, uint32_t* hist,
-                                                int32_t n_sink) {
+                                                int32_t n_sink, int32_t stay_from) {
     const int tok = lane & 15, q = lane >> 4;
     const int32_t groups = (t_end - t_begin + 1) >> 1;          // of 64 tokens
     if (groups <= 0) return 0.f;
     float acc_sum = 0.f;
     TileF32 r;
     // rows past the end reload the last one; their scores are dropped
-    auto load = [&](int32_t first) {
-        int32_t row = first + tok;
-        row = row < n ? row : n - 1;
-        const size_t off = (size_t)(uint32_t)row * 32 + q;      // 32 float4 per row
+    auto load = [&](int32_t first, auto how) {
+        constexpr bool kPast = STREAM && decltype(how)::value;
+        size_t off[2];
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            int32_t row = first + load_row<STREAM>(tok, w);
+            row = row < n ? row : n - 1;
+            off[w] = (size_t)(uint32_t)row * 32 + load_piece<STREAM>(tok, q, w);     // 32 float4 per row
+        }
         if (SRC != kSrcV) {
 #pragma unroll
-            for (int s = 0; s < 8; ++s) r.k[s] = Kh[off + s * 4];
+            for (int s = 0; s < 8; ++s) r.k[s] = fetch<kPast>(Kh + off[s & 1] + (s >> 1) * 8);
         }
         if (SRC != kSrcK) {
 #pragma unroll
-            for (int s = 0; s < 8; ++s) r.v[s] = Vh[off + s * 4];
+            for (int s = 0; s < 8; ++s) r.v[s] = fetch<kPast>(Vh + off[s & 1] + (s >> 1) * 8);
         }
     };
     double tk[4] = {}, tv[4] = {};                             // a lane's share of the norms of the group's tokens, 16 each
-    auto step = [&](int part, int32_t next) {                   // scores the 16 tokens in r, loads those from `next`
+    auto step = [&](int part, int32_t next, auto how) {                   // scores the 16 tokens in r, loads those from `next`
         Parts xk[4], xv[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
+            if constexpr (STREAM) {
+                if (SRC != kSrcV) settle_pair(r.k[2 * s], r.k[2 * s + 1]);
+                if (SRC != kSrcK) settle_pair(r.v[2 * s], r.v[2 * s + 1]);
+            }
             if (SRC != kSrcV) xk[s] = split_bf16(r.k[2 * s], r.k[2 * s + 1]);
             if (SRC != kSrcK) xv[s] = split_bf16(r.v[2 * s], r.v[2 * s + 1]);
         }
         __builtin_amdgcn_sched_barrier(0);
-        load(next);
+        load(next, how);
         __builtin_amdgcn_sched_barrier(0);
         f32x4 qk = f32x4{0.f, 0.f, 0.f, 0.f}, qv = qk;          // squares, a sum each
         // the lane's offset is made opaque, or the compiler lifts the sketch's loads out of the walk
@@ -673,23 +707,32 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
     const int32_t rot = (t_begin + 2 * groups) * kTileTokens <= n && groups >= 4 ? (int32_t)(phase % (uint32_t)groups) : 0;
     const int32_t base = t_begin * kTileTokens;
     int32_t g = rot;
-    load(base + g * 64);
-    for (int32_t i = 0; i < groups; ++i) {
-        const int32_t first = base + g * 64;
-        g = g + 1 == groups ? 0 : g + 1;
-        step(0, first + 16);
-        step(1, first + 32);
-        step(2, first + 48);
-        step(3, i + 1 < groups ? base + g * 64 : first + 48);   // (at the end these rows once more, from the L2, unused)
-        const double lk = SRC == kSrcV ? 1.0 : sum_group(tk), lv = SRC == kSrcK ? 1.0 : sum_group(tv);
-        const float pend = (float)(lk * lv);
-        const int32_t row = first + lane;
-        if (row < n) {
-            lds_rows[row - row0] = pend;
-            if (COUNT) raw_hist_count(hist, pend, row >= n_sink);
-            acc_sum += pend;
+    load(base + g * 64, std::bool_constant<STREAM>{});
+    auto walk = [&](int32_t from, int32_t to, auto how) {       // groups from .. to-1 of the walk
+        for (int32_t i = from; i < to; ++i) {
+            const int32_t first = base + g * 64;
+            g = g + 1 == groups ? 0 : g + 1;
+            step(0, first + 16, how);
+            step(1, first + 32, how);
+            step(2, first + 48, how);
+            step(3, i + 1 < groups ? base + g * 64 : first + 48, how);   // (at the end these rows once more, from the L2, unused)
+            const double lk = SRC == kSrcV ? 1.0 : sum_group(tk), lv = SRC == kSrcK ? 1.0 : sum_group(tv);
+            const float pend = (float)(lk * lv);
+            const int32_t row = first + lane;
+            if (row < n) {
+                lds_rows[row - row0] = pend;
+                if (COUNT) raw_hist_count(hist, pend, row >= n_sink);
+                acc_sum += pend;
+            }
         }
+    };
+    int32_t past = 0;                                           // groups whose rows do not stay in the caches
+    if constexpr (STREAM) {
+        past = (stay_from - t_begin) >> 1;
+        past = past < 0 ? 0 : past < groups ? past : groups;
+        walk(0, past, std::true_type{});
     }
+    walk(past, groups, std::false_type{});
     if (__any(acc_sum != acc_sum)) {                            // some row is not a number: do those again
         acc_sum = 0.f;
         for (int32_t j = base; j < base + groups * 64; j += 64) {

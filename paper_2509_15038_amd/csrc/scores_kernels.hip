@@ -47,13 +47,13 @@ template <int CB> struct Stage {    // tiles (of 32 tokens) a wave collects betw
 };
 
 // COUNT: the workgroup also leaves its histogram of scores for the split selection (split_select.hip).
-// STREAM: rows past the caches (scan_device.h).
-template <int CB, int SRC, bool PROJ, bool COUNT, bool STREAM>
+// MODE: rows past the caches or not (kStream* in scan_device.h).
+template <int CB, int SRC, bool PROJ, bool COUNT, int MODE>
 __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
     const uint4* __restrict__ K, const uint4* __restrict__ V, const uint4* __restrict__ Gp,
     float* __restrict__ scores, float* __restrict__ partial, int64_t n, int blocks_per_head,
     int64_t out_stride, int64_t out_offset, double* __restrict__ sums, int restart,
-    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, int hists, int32_t n_sink) {
+    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, int hists, int32_t n_sink, int stay) {
     constexpr int kStageTiles = Stage<CB>::kTiles;
     __shared__ float stage[4][kStageTiles * kTileTokens];
     __shared__ uint32_t hist[COUNT ? kRawHistWords : 1];
@@ -80,11 +80,12 @@ __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
     float* sh = scores + (size_t)head * out_stride + out_offset;   // score of row j goes to sh[j]
     float* mine = stage[wave];
     float acc_sum = 0.f;
+    const int32_t stay_from = stay_tile(t_begin, t_end, stay);
     for (int32_t seg = t_begin; seg < t_end; seg += kStageTiles) {
         const int32_t seg_end = seg + kStageTiles < t_end ? seg + kStageTiles : t_end;
         const int32_t r0 = seg * kTileTokens;
-        acc_sum += scan_tiles<CB, SRC, PROJ, COUNT, STREAM>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane,
-                                                   scan_phase(head, blk * 4 + wave), hist, n_sink);
+        acc_sum += scan_tiles<CB, SRC, PROJ, COUNT, MODE>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane,
+                                                   scan_phase(head, blk * 4 + wave), hist, n_sink, stay_from);
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
         for (int32_t r = r0 + lane; r < r1; r += 64) __builtin_nontemporal_store(mine[r - r0], &sh[r]);
     }
@@ -95,28 +96,26 @@ __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
 
 // ---------------------------------------------------------------------------
 // fp32 storage: the same structure (scan_device.h).  CB = 16-column blocks of the padded sketch.
-// Up to 32 columns (CB = 2, and the ablation without projection) the sketch is in registers and a
-// lane's two tile buffers take 256 more: a SIMD holds one wave and a compute unit one workgroup
-// of four.  Wider sketches split the products over the bf16 matrix units: the sketch's parts share
-// the LDS with the score stages, and a workgroup has eight waves, two to a SIMD.
+// SPLIT: the products go over the bf16 matrix units; the sketch's parts share the LDS with the score stages, and a workgroup has eight waves,
+// two to a SIMD.  Otherwise (CB = 2: up to 32 columns, and the ablation without projection) the sketch is in registers and a
+// lane's two tile buffers take 256 more: a SIMD holds one wave and a compute unit one workgroup of four.
+// STREAM: rows past the caches, as above.
 // ---------------------------------------------------------------------------
-template <int CB> struct ShapeF32 {
-    static constexpr bool kSplit = CB > 2;
-    static constexpr int kWaves = kSplit ? 8 : 4;
-    static constexpr int kTiles = CB > 4 ? 48 : CB > 2 ? 96 : 256;    // per wave between bursts: 48, 96 or 128 KB in all
+template <int CB, bool SPLIT> struct ShapeF32 {
+    static constexpr int kWaves = SPLIT ? 8 : 4;
+    static constexpr int kTiles = CB > 4 ? 48 : CB > 2 ? 96 : SPLIT ? 112 : 256;    // per wave between bursts: 48, 96, 112 or 128 KB in all
 };
 
-template <int CB, int SRC, bool PROJ, bool COUNT>
-__global__ __launch_bounds__((ShapeF32<CB>::kWaves * 64), (ShapeF32<CB>::kSplit ? 2 : 1)) void scores_f32_kernel(
+template <int CB, int SRC, bool PROJ, bool COUNT, bool SPLIT, bool STREAM>
+__global__ __launch_bounds__((ShapeF32<CB, SPLIT>::kWaves * 64), (SPLIT ? 2 : 1)) void scores_f32_kernel(
     const float4* __restrict__ K, const float4* __restrict__ V, const float4* __restrict__ Gp,
     float* __restrict__ scores, float* __restrict__ partial, int64_t n, int blocks_per_head,
     int64_t out_stride, int64_t out_offset, double* __restrict__ sums, int restart,
-    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, int hists, int32_t n_sink) {
-    constexpr bool kSplit = ShapeF32<CB>::kSplit;  // (PROJ = false comes with CB = 2 and never touches the sketch)
-    constexpr int kWaves = ShapeF32<CB>::kWaves;
-    constexpr int kStageTiles = ShapeF32<CB>::kTiles;
+    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, int hists, int32_t n_sink, int stay) {
+    constexpr int kWaves = ShapeF32<CB, SPLIT>::kWaves;
+    constexpr int kStageTiles = ShapeF32<CB, SPLIT>::kTiles;
     __shared__ float stage[kWaves][kStageTiles * kTileTokens];
-    __shared__ bf16x8 gs[kSplit ? kSketchF32Chunks<CB> : 1];
+    __shared__ bf16x8 gs[SPLIT ? kSketchF32Chunks<CB> : 1];
     __shared__ uint32_t hist[COUNT ? kRawHistWords : 1];
     const int head = blockIdx.x / blocks_per_head;
     const int blk = blockIdx.x - head * blocks_per_head;
@@ -127,12 +126,12 @@ __global__ __launch_bounds__((ShapeF32<CB>::kWaves * 64), (ShapeF32<CB>::kSplit 
         __syncthreads();
     }
     const float4* Gh = Gp + (size_t)head * (CB * 8 * 64);
-    SketchF32<kSplit ? 1 : CB> G;
-    if (kSplit) {
+    SketchF32<SPLIT ? 1 : CB> G;
+    if constexpr (SPLIT) {
         split_sketch_to_lds<CB, kWaves * 64>(gs, Gh);
-    } else if (PROJ) {
+    } else if constexpr (PROJ) {
 #pragma unroll
-        for (int cb = 0; cb < (kSplit ? 1 : CB); ++cb)
+        for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
             for (int s = 0; s < 8; ++s) G.g[cb][s] = Gh[(cb * 8 + s) * 64 + lane];
     }
@@ -140,20 +139,33 @@ __global__ __launch_bounds__((ShapeF32<CB>::kWaves * 64), (ShapeF32<CB>::kSplit 
     const int32_t n32 = (int32_t)n;
     const int32_t tiles = (n32 + kTileTokens - 1) / kTileTokens;
     const int32_t waves_per_head = blocks_per_head * kWaves;
-    int32_t per_wave = (tiles + waves_per_head - 1) / waves_per_head;
-    per_wave += per_wave & 1;                                   // whole pairs
-    const int32_t t_begin = (blk * kWaves + wave) * per_wave;
-    const int32_t t_end = t_begin + per_wave < tiles ? t_begin + per_wave : tiles;
+    int32_t t_begin, t_end;
+    if constexpr (SPLIT) {
+        // groups of 64 tokens as evenly as they go, one more to some waves spread over the head: 8 heads of 20000 tokens, r = 20, 42.7 us with the
+        // same number to every wave as long as there are any, 41.5 so.  (The bf16 kernel is 1 to 3 % slower that way.)
+        const uint32_t groups = ((uint32_t)tiles + 1) >> 1, waves = (uint32_t)waves_per_head;
+        const uint32_t each = groups / waves, more = groups - each * waves;
+        auto first = [&](uint32_t w) { return (int32_t)(2 * (w * each + w * more / waves)); };
+        t_begin = first((uint32_t)(blk * kWaves + wave));
+        t_end = first((uint32_t)(blk * kWaves + wave + 1));
+        t_end = t_end < tiles ? t_end : tiles;
+    } else {
+        int32_t per_wave = (tiles + waves_per_head - 1) / waves_per_head;
+        per_wave += per_wave & 1;                               // whole pairs
+        t_begin = (blk * kWaves + wave) * per_wave;
+        t_end = t_begin + per_wave < tiles ? t_begin + per_wave : tiles;
+    }
     const float4* Kh = K + (size_t)head * n * 32;               // 32 chunks of 16 bytes per row
     const float4* Vh = V + (size_t)head * n * 32;
     float* sh = scores + (size_t)head * out_stride + out_offset;
     float* mine = stage[wave];
     float acc_sum = 0.f;
+    const int32_t stay_from = stay_tile(t_begin, t_end, stay);
     for (int32_t seg = t_begin; seg < t_end; seg += kStageTiles) {
         const int32_t seg_end = seg + kStageTiles < t_end ? seg + kStageTiles : t_end;
         const int32_t r0 = seg * kTileTokens;
         const uint32_t phase = scan_phase(head, blk * kWaves + wave);
-        if constexpr (kSplit) acc_sum += scan_tiles_f32_split<CB, SRC, COUNT>(gs, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink);
+        if constexpr (SPLIT) acc_sum += scan_tiles_f32_split<CB, SRC, COUNT, STREAM>(gs, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink, stay_from);
         else acc_sum += scan_tiles_f32<CB, SRC, PROJ, COUNT>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink);
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
         for (int32_t r = r0 + lane; r < r1; r += 64) __builtin_nontemporal_store(mine[r - r0], &sh[r]);
@@ -243,6 +255,21 @@ __global__ __launch_bounds__(256) void fold_kernel(const float* __restrict__ sq,
     }
 }
 
+// Products of up to 32 columns of an fp32 cache: over the bf16 units, rows past the caches, where every wave of the chip has 64 tokens or more
+// (eight waves a compute unit) and the waves' shares, whole groups of 64, differ little, else in fp32.  There HBM waits for neither the matrix units nor the splitting, while the fp32 units are busy 55 %
+// of the time and one wave a SIMD does not hide the rest.  curdkv_scores, r = 20, us, fp32 units and split: 8 heads of 4096 tokens 19.0 and 25.0, of 8192 22.7 and
+// 25.5, of 16384 (64 tokens a wave) 35.6 and 31.9, of 20000 (64 or 128) 41.1 and 41.5, of 24000 45.7 and 43.5, of 32768 60.5 and 59.2, of 65536 106.4 and 95.5; 64 of 16384 198.9 and 178.1; 112 of
+// 10007 211.2 and 197.2; 256 of 512 35.5 and 31.8, of 16384 727 and 685.  Wider sketches are bound by the matrix units' power: streaming gives them
+// nothing (64 heads of 16384, r = 64, 222.4 and 221.1).
+static bool f32_split(const curdkv_ctx* ctx, int64_t n) {
+    if (ctx->cfg.dtype != CURDKV_DTYPE_F32 || ctx->cfg.no_projection) return false;
+    if (ctx->col_blocks > 1) return true;
+    const int64_t waves = (int64_t)ctx->num_cu * ShapeF32<2, true>::kWaves;
+    if (ctx->heads * n < waves * 64) return false;
+    const int64_t groups = (n + 63) / 64, places = waves / ctx->heads > 1 ? waves / ctx->heads : 1;
+    return groups * 10 >= (groups + places - 1) / places * places * 7;
+}
+
 // Workgroups per head.  A workgroup should be long-lived (its start-up and the pipeline fill
 // are paid per workgroup) and write its scores once, at its end, so the lower bound is what
 // makes a wave's share fit its LDS stage.  Above that, the smallest count is taken that fills
@@ -263,8 +290,9 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n, int64_t most_b
     const bool wide = ctx->cfg.dtype == CURDKV_DTYPE_BF16 && ctx->col_blocks > 2 && !ctx->cfg.no_projection;
     const bool f32 = ctx->cfg.dtype == CURDKV_DTYPE_F32;         // one workgroup per compute unit, like the wide kernel
     const int cb = ctx->cfg.no_projection ? 1 : ctx->col_blocks;
-    const int waves = f32 && cb > 1 ? ShapeF32<4>::kWaves : 4;       // per workgroup
-    const int64_t stage = f32 ? (cb == 1 ? ShapeF32<2>::kTiles : cb == 2 ? ShapeF32<4>::kTiles : ShapeF32<8>::kTiles)
+    const bool split = f32_split(ctx, n);
+    const int waves = split ? ShapeF32<4, true>::kWaves : 4;         // per workgroup
+    const int64_t stage = f32 ? (cb == 1 ? (split ? ShapeF32<2, true>::kTiles : ShapeF32<2, false>::kTiles) : cb == 2 ? ShapeF32<4, true>::kTiles : ShapeF32<8, true>::kTiles)
                               : (wide ? Stage<8>::kTiles : Stage<4>::kTiles);
     int64_t slots = (int64_t)ctx->num_cu * ((wide || f32 || ctx->heads <= ctx->num_cu) ? 1 : 2);
     // Few, long heads: a sixteenth of the units is left idle, and the ranges of the waves, which otherwise lie
@@ -358,12 +386,30 @@ static bool few_tokens(const curdkv_ctx* ctx, int64_t n, bool running) {
 // of the same call finds its rows there.  us, kept in the caches and streamed, three caches in turn, r = 64: curdkv_scores of 8 heads of
 // 24576 tokens (101 MB) 22.2 and 23.2, of 32768 (134) 31.2 and 29.0, of 65536 53.8 and 47.8; appends of 768 tokens to 256 heads (101) 19.8 and
 // 20.6, of 1024 28.7 and 26.9; one call, a tenth kept, 8 heads of 8192 17.3 and 19.2, of 32768 (134) 44.8 and 45.4, of 40960 (168) 57.7 and 54.7, half
-// kept (168) 73.8 and 74.7, of 49152 (201) 88.6 and 85.7.  Large: 256 heads of 32768 703 and 624, of 131072, r = 128, 2858 and 2578.
-constexpr int64_t kStreamBytes = 120000000, kStreamBytesReread = 160000000;
+// kept (168, the end of the scan left in the caches) 75.9 and 78.6, 32 heads of 12288 (201) 81.6 and 79.1.  Large: 256 heads of 32768 703 and 624, of 131072, r = 128,
+// 2858 and 2578.
+constexpr int64_t kStreamBytes = 120000000, kStreamBytesReread = 160000000, kStreamBytesRereadMany = 200000000;
+// Where a quarter of the rows or more are gathered afterwards, the end of the scan still goes through the caches: so much of it as
+// the gather then finds there.  One call, half kept, nothing left, 128, 192 and 256 MB, us: 32 heads of 16384, r = 64, 103.9, 100.4, 109.0 and 110.7 (all
+// kept in the caches 105.7); 256 of 32768 1326, 1304, 1309, 1311; fp32, r = 32, 8 heads of 32768 120.3, 109.7, 110.5, 113.0 (all 111.8), three tenths kept 101.2,
+// 93.5, 94.4, 95.8 (95.3); in bf16 three tenths are level (32 of 16384 87.5 and 87.4).
+constexpr int64_t kStayBytes = 128000000;
 
-static bool stream_rows(const curdkv_ctx* ctx, int64_t n, bool reread) {
-    const int64_t row = kHeadDim * (ctx->cfg.dtype == CURDKV_DTYPE_BF16 ? 2 : 4) * (ctx->cfg.score_source == CURDKV_SCORE_KV ? 2 : 1);
-    return ctx->cfg.dtype == CURDKV_DTYPE_BF16 && ctx->heads * n * row > (reread ? kStreamBytesReread : kStreamBytes);
+static int64_t scan_bytes(const curdkv_ctx* ctx, int64_t n) {
+    return ctx->heads * n * kHeadDim * (ctx->cfg.dtype == CURDKV_DTYPE_BF16 ? 2 : 4) * (ctx->cfg.score_source == CURDKV_SCORE_KV ? 2 : 1);
+}
+
+static bool many_kept(const curdkv_ctx* ctx, int64_t n, int64_t kept) { return kept * 4 >= ctx->heads * n; }
+
+static bool stream_rows(const curdkv_ctx* ctx, int64_t n, int64_t kept) {
+    return ctx->cfg.dtype == CURDKV_DTYPE_BF16 &&
+           scan_bytes(ctx, n) > (many_kept(ctx, n, kept) ? kStreamBytesRereadMany : kept > 0 ? kStreamBytesReread : kStreamBytes);
+}
+
+int stay_share(const curdkv_ctx* ctx, int64_t n, int64_t kept) {
+    if (!many_kept(ctx, n, kept)) return 0;
+    const int64_t share = kStayBytes * 256 / scan_bytes(ctx, n);
+    return (int)(share < 256 ? share : 256);
 }
 
 hipError_t configure_kernels(curdkv_ctx* ctx) {
@@ -374,7 +420,7 @@ hipError_t configure_kernels(curdkv_ctx* ctx) {
 hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n,
                          float* scores, hipStream_t stream, bool normalise, int* blocks_per_head,
                          int64_t out_stride, int64_t out_offset, double* sums, bool restart,
-                         bool* summed, bool with_hist, int32_t n_sink, bool reread) {
+                         bool* summed, bool with_hist, int32_t n_sink, int64_t kept) {
     if (out_stride <= 0) out_stride = n;
     const bool few = few_tokens(ctx, n, sums != nullptr) && !with_hist;
     const int bph = few ? few_blocks_per_head(ctx, n, sums != nullptr) : pick_blocks_per_head(ctx, n, with_hist ? split_hists(ctx) : kMaxBlocksPerHead);
@@ -390,7 +436,8 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
     }
     uint32_t* hist = with_hist ? split_hist(ctx) : nullptr;
     uint32_t* coarse = with_hist ? split_coarse(ctx) : nullptr;
-    const bool stream_past = stream_rows(ctx, n, reread);
+    const bool stream_past = stream_rows(ctx, n, kept);
+    const int stay = stay_share(ctx, n, kept);
     const dim3 grid((unsigned)(ctx->heads * bph));
     float* part = ctx->d_partial;
     auto launch = [&](auto cb, auto src, auto proj, auto count) {
@@ -411,14 +458,24 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
             auto launch_bf16 = [&](auto past) {
                 scores_bf16_kernel<CB, SRC, PROJ, COUNT, decltype(past)::value><<<grid, 256, 0, stream>>>(
                     (const uint4*)K, (const uint4*)V, (const uint4*)ctx->d_G, scores, part, n, bph, out_stride, out_offset, sums, rs,
-                    hist, coarse, hists, n_sink);
+                    hist, coarse, hists, n_sink, stay);
             };
-            if (stream_past) launch_bf16(std::true_type{});
-            else launch_bf16(std::false_type{});
-        } else
-            scores_f32_kernel<CB, SRC, PROJ, COUNT><<<grid, ShapeF32<CB>::kWaves * 64, 0, stream>>>(
-                (const float4*)K, (const float4*)V, (const float4*)ctx->d_G, scores, part, n, bph, out_stride, out_offset, sums, rs,
-                hist, coarse, hists, n_sink);
+            if (!stream_past) launch_bf16(std::integral_constant<int, kStreamNone>{});
+            else if (stay == 0) launch_bf16(std::integral_constant<int, kStreamAll>{});
+            else launch_bf16(std::integral_constant<int, kStreamStay>{});
+        } else {
+            auto launch_f32 = [&](auto split, auto past) {
+                constexpr bool SPLIT = decltype(split)::value;
+                scores_f32_kernel<CB, SRC, PROJ, COUNT, SPLIT, decltype(past)::value><<<grid, ShapeF32<CB, SPLIT>::kWaves * 64, 0, stream>>>(
+                    (const float4*)K, (const float4*)V, (const float4*)ctx->d_G, scores, part, n, bph, out_stride, out_offset, sums, rs,
+                    hist, coarse, hists, n_sink, stay);
+            };
+            if constexpr (CB > 2) launch_f32(std::true_type{}, std::false_type{});
+            else if constexpr (PROJ) {
+                if (f32_split(ctx, n)) launch_f32(std::true_type{}, std::true_type{});
+                else launch_f32(std::false_type{}, std::false_type{});
+            } else launch_f32(std::false_type{}, std::false_type{});
+        }
     };
     auto by_count = [&](auto cb, auto src, auto proj) {
         if (with_hist) launch(cb, src, proj, std::true_type{});

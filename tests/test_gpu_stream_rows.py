@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 SEED = 0xC0DE0014
 LIMIT = gu.limit("scores_kernels.hip", "kStreamBytes")
-LIMIT_REREAD = gu.limit("scores_kernels.hip", "kStreamBytesReread")
+LIMIT_REREAD = gu.limit("scores_kernels.hip", "kStreamBytesRereadMany")
 
 # A projected coordinate is an fp32 sum of 128 exact products, rounded once per 32 terms, its square and their sum over r columns as many
 # roundings again, then a product and the division: some 30 roundings of 2^-24 at random, relative to the score
@@ -42,8 +42,18 @@ def _want(K, V, i, r, dtype, source, projection):
 @pytest.mark.parametrize("dtype,r,source,projection", [("bf16", 20, "kv", True), ("bf16", 33, "k", True), ("bf16", 64, "v", True), ("bf16", 64, "kv", True),
                                                        ("bf16", 128, "kv", True), ("bf16", 64, "kv", False)])
 def test_scores(n, dtype, r, source, projection):
+    _check_scores(_heads(LIMIT, n, dtype, source), n, dtype, r, source, projection)
+
+
+# up to 32 columns of an fp32 cache over the bf16 units: a group of 64 tokens a wave and more, whole groups and parts
+@pytest.mark.parametrize("heads,n", [(2100, 63), (128, 1024), (1024, 300), (256, 1009), (100, 4133), (4, 70001)])
+@pytest.mark.parametrize("r,source", [(20, "kv"), (32, "k"), (8, "v")])
+def test_scores_of_narrow_sketches_in_fp32(heads, n, r, source):
+    _check_scores(heads, n, "fp32", r, source, True)
+
+
+def _check_scores(heads, n, dtype, r, source, projection):
     import torch
-    heads = _heads(LIMIT, n, dtype, source)
     K, V = _cache(heads, n, dtype, n * 512 + r)
     with B.Context(heads, 1, 4, 128, r, dtype, n, SEED, source, projection) as ctx:
         out = gu.Guarded((heads, n), torch.float32, float("nan"))
@@ -59,21 +69,25 @@ def test_scores(n, dtype, r, source, projection):
             assert np.linalg.norm(x - want) <= NORM_TOL * np.linalg.norm(want), (n, r, source, i)
 
 
-# one call on either side of its limit: the kernel that does everything (few rows kept of as many heads as units), the selection
-# that gathers, the split selection with histograms from the scoring, and separate kernels; the rows kept are found again
-@pytest.mark.parametrize("heads,n,r,keep", [(256, 2049, 64, 0.1), (256, 2500, 20, 0.05), (20, 16411, 64, 0.1), (128, 2600, 20, 0.4), (5, 70001, 20, 0.1), (40, 40001, 128, 0.05)])
-def test_one_call(heads, n, r, keep):
+# one call: the kernel that does everything (few rows kept of as many heads as units), scores by it and separate kernels, the selection
+# that gathers, the split selection with histograms from the scoring; a quarter and more kept, where the end of the scan goes through the caches,
+# is a walk in two parts.  The rows kept are found again
+@pytest.mark.parametrize("heads,n,r,keep,dtype", [(256, 2049, 64, 0.1, "bf16"), (256, 2500, 20, 0.05, "bf16"), (256, 2111, 64, 0.5, "bf16"), (25, 16411, 64, 0.1, "bf16"),
+                                                  (25, 16411, 20, 0.3, "bf16"), (160, 2600, 20, 0.4, "bf16"), (6, 70001, 20, 0.1, "bf16"), (6, 70001, 64, 0.5, "bf16"),
+                                                  (40, 40001, 128, 0.05, "bf16"), (8, 49217, 128, 0.6, "bf16"), (100, 4133, 20, 0.1, "fp32"), (4, 70001, 32, 0.4, "fp32"),
+                                                  (256, 1009, 20, 0.5, "fp32")])
+def test_one_call(heads, n, r, keep, dtype):
     import torch
     if heads == 256:
         heads = torch.cuda.get_device_properties(0).multi_processor_count
-    assert heads * n * 512 > LIMIT_REREAD
-    K, V = _cache(heads, n, "bf16", n + r)
+    assert heads * n * 512 > LIMIT_REREAD or dtype == "fp32"
+    K, V = _cache(heads, n, dtype, n + r)
     budgets = np.full((heads,), int(keep * n), np.int32)
-    with B.Context(heads, 1, 4, 128, r, "bf16", n, SEED) as ctx:
-        sc, ix, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, 4, "bf16", one_call=True)
+    with B.Context(heads, 1, 4, 128, r, dtype, n, SEED) as ctx:
+        sc, ix, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, 4, dtype, one_call=True)
     for i in (0, heads // 2, heads - 1):
         rows = ix[off[i]:off[i + 1]]
-        lt = _want(K, V, i, r, "bf16", "kv", True)
+        lt = _want(K, V, i, r, dtype, "kv", True)
         gu.check_scores(sc[i].cpu().numpy(), lt, str(i))
         gu.check_selection(rows.cpu().numpy().astype(np.int64), lt, int(budgets[i]), 4, str(i))
         assert torch.equal(Ko[off[i]:off[i + 1]], K[i][rows.long()]) and torch.equal(Vo[off[i]:off[i + 1]], V[i][rows.long()])
