@@ -61,12 +61,12 @@ __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
     const int blk = blockIdx.x - head * blocks_per_head;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
-    SketchRegs<CB> G;
-    if (PROJ) load_sketch<CB>(G, Gp + (size_t)head * (CB * 4 * 64), lane);
-    if (COUNT) {
+    if (COUNT) {                                   // (before any load goes out: the barrier would wait for it)
         for (int i = threadIdx.x; i < kRawHistWords; i += 256) hist[i] = 0;
         __syncthreads();
     }
+    SketchRegs<CB> G;
+    if (PROJ) load_sketch<CB>(G, Gp + (size_t)head * (CB * 4 * 64), lane);
 
     const int32_t n32 = (int32_t)n;
     const int32_t tiles = (n32 + kTileTokens - 1) / kTileTokens;
@@ -85,7 +85,9 @@ __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
         const int32_t seg_end = seg + kStageTiles < t_end ? seg + kStageTiles : t_end;
         const int32_t r0 = seg * kTileTokens;
         acc_sum += scan_tiles<CB, SRC, PROJ, COUNT, MODE>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane,
-                                                   scan_phase(head, blk * 4 + wave), hist, n_sink, stay_from);
+                                                   // (streamed rows gain nothing from different starts here: 32 heads of 32768 tokens 89.7 us with, 89.0 without, appends of
+                                                   // 1024 tokens to 256 heads 24.5 and 23.5; the kernel of one workgroup a head does, 256 of 32768 623 and 630)
+                                                   MODE == kStreamNone ? scan_phase(head, blk * 4 + wave) : 0u, hist, n_sink, stay_from);
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
         for (int32_t r = r0 + lane; r < r1; r += 64) __builtin_nontemporal_store(mine[r - r0], &sh[r]);
     }
@@ -285,7 +287,7 @@ static bool f32_split(const curdkv_ctx* ctx, int64_t n) {
 // head, writing its scores in two bursts, beats any split by 2.5-3.5 % although units stay idle
 // (192 heads: 562 us against 576 for four per head; 224: 649 against 671; 448: 1305 against
 // 1338).
-static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n, int64_t most_blocks = kMaxBlocksPerHead) {
+static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n, bool streams, int64_t most_blocks = kMaxBlocksPerHead) {
     const int64_t tiles = (n + kTileTokens - 1) / kTileTokens;
     const bool wide = ctx->cfg.dtype == CURDKV_DTYPE_BF16 && ctx->col_blocks > 2 && !ctx->cfg.no_projection;
     const bool f32 = ctx->cfg.dtype == CURDKV_DTYPE_F32;         // one workgroup per compute unit, like the wide kernel
@@ -301,7 +303,10 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n, int64_t most_b
     // of 131072 51.4 and 49.3; 16 of 32768 52.0 and 49.6; 32 of 32768 96.4 and 95.6, not worth a rule; 128 columns, 8 heads
     // of 131072 104.3 and 97.5.  Below eight tiles a wave the rounding to whole pairs costs more (8 heads of 8192:
     // 11.2 and 13.1).
-    const bool spare = ctx->cfg.dtype == CURDKV_DTYPE_BF16 && ctx->heads * 16 <= ctx->num_cu && (int64_t)ctx->heads * tiles >= 8 * waves * slots;
+    // Rows streamed past the caches (fetch in scan_device.h): 32 heads of 32768 tokens 89.1 and 86.8 as well, r = 20, 8 of 131072 85.7 and 83.5; but not with 128
+    // columns, where every unit's matrix time counts (8 of 131072 91.0 and 93.8).
+    const bool spare = ctx->cfg.dtype == CURDKV_DTYPE_BF16 && (streams ? !wide && ctx->heads * 8 <= ctx->num_cu : ctx->heads * 16 <= ctx->num_cu) &&
+                       (int64_t)ctx->heads * tiles >= 8 * waves * slots;
     if (spare) slots -= slots / 16;
     int64_t cap = (tiles + waves - 1) / waves;                                     // at least one tile per wave
     if (cap > most_blocks) cap = most_blocks;
@@ -377,7 +382,7 @@ static bool few_tokens(const curdkv_ctx* ctx, int64_t n, bool running) {
     // 8.2 / 5.2 -> 8.4 / 6.1 -> 7.8 launched call by call, 8 heads of 256 6.6 -> 4.6 / 7.3 -> 5.1 / 8.9 -> 6.2 and
     // 6.7 -> 8.2 / 7.4 -> 8.5 / 9.0 -> 7.9: with 128 columns beyond 192 tokens the split wins either way (48 heads of 130
     // tokens 7.3 -> 7.9 and 7.7 -> 8.1).
-    if (!f32 && running && n > 32 && !(ctx->col_blocks > 2 && n > 192) && pick_blocks_per_head(ctx, n) == 1) return false;
+    if (!f32 && running && n > 32 && !(ctx->col_blocks > 2 && n > 192) && pick_blocks_per_head(ctx, n, false) == 1) return false;
     const int64_t steps = (n + 15) / 16;
     return steps <= (f32 ? kFewF32Steps : kFewBf16Steps) * few_blocks_per_head(ctx, n, running);
 }
@@ -423,7 +428,8 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
                          bool* summed, bool with_hist, int32_t n_sink, int64_t kept) {
     if (out_stride <= 0) out_stride = n;
     const bool few = few_tokens(ctx, n, sums != nullptr) && !with_hist;
-    const int bph = few ? few_blocks_per_head(ctx, n, sums != nullptr) : pick_blocks_per_head(ctx, n, with_hist ? split_hists(ctx) : kMaxBlocksPerHead);
+    const bool stream_past = stream_rows(ctx, n, kept);
+    const int bph = few ? few_blocks_per_head(ctx, n, sums != nullptr) : pick_blocks_per_head(ctx, n, stream_past, with_hist ? split_hists(ctx) : kMaxBlocksPerHead);
     if (blocks_per_head) *blocks_per_head = bph;
     if (bph != 1) sums = nullptr;                 // several blocks per head: the caller adds the partials
     if (summed) *summed = sums != nullptr;
@@ -436,7 +442,6 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
     }
     uint32_t* hist = with_hist ? split_hist(ctx) : nullptr;
     uint32_t* coarse = with_hist ? split_coarse(ctx) : nullptr;
-    const bool stream_past = stream_rows(ctx, n, kept);
     const int stay = stay_share(ctx, n, kept);
     const dim3 grid((unsigned)(ctx->heads * bph));
     float* part = ctx->d_partial;
