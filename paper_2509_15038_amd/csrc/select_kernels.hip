@@ -393,7 +393,8 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float*
                                                                 const Threshold* __restrict__ known) {
     extern __shared__ int32_t stage[];             // [n]
     __shared__ SelectShared<kSelThreads, KPT> sm;
-    const int head = blockIdx.y;
+    int head, x0;
+    xcd_place(&x0, &head);
     const int tid = threadIdx.x;
     raw += (size_t)head * n;
     const double mine = head_partial(partial + (size_t)head * kMaxBlocksPerHead, scale_blocks);
@@ -407,9 +408,9 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float*
     const int32_t k = (int32_t)(offsets[head + 1] - o0);
     const int32_t s = n_sink < n ? n_sink : n;
     if (share == 0) share = (k + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int32_t r0 = (int32_t)blockIdx.x * share;
+    const int32_t r0 = (int32_t)x0 * share;
     const int32_t r1 = r0 + share < k ? r0 + share : k;            // output rows r0 .. r1-1 are this workgroup's
-    if (r0 >= r1 && blockIdx.x > 0) return;
+    if (r0 >= r1 && x0 > 0) return;
     uint32_t x[KPT];
     int none;                                      // the head has no sum
     uint32_t key0;
@@ -421,7 +422,7 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float*
         for (int it = 0; it < KPT; ++it) {
             v[it] = scale(v[it]);
             const int32_t j = it * kSelThreads + tid;
-            if (blockIdx.x == 0 && scores && j < n) scores[(size_t)head * n + j] = v[it];
+            if (x0 == 0 && scores && j < n) scores[(size_t)head * n + j] = v[it];
             x[it] = order_key(v[it]);
         }
     }

@@ -165,10 +165,12 @@ __device__ __forceinline__ uint32_t wave_find(const uint32_t (&c)[PER], uint32_t
 template <bool KNOWN>
 __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) {
     __shared__ uint32_t exps[256], fine[64], found[2];
-    const int head = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    int head, x0;
+    xcd_place(&x0, &head);
+    const int tid = threadIdx.x, lane = tid & 63;
     const int32_t n = a.n, s = a.n_sink < n ? a.n_sink : n;
     const int64_t o0 = a.offsets[head], o1 = a.offsets[head + 1];
-    const int32_t j0 = (int32_t)blockIdx.x * a.part;
+    const int32_t j0 = (int32_t)x0 * a.part;
     const int32_t j1 = j0 + a.part < n ? j0 + a.part : n;
     float* sc = a.scores + (size_t)head * n;
     // all of the first loads go out together, before anything is decided
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) 
     const HeadScale scale = head_scale(head_partial(a.partial + (size_t)head * kMaxBlocksPerHead, a.scale_blocks), a.scale_blocks, n);
     uint32_t lo = given, hi = given;
     if (KNOWN && search && given != kNoThreshold) {
-        if (blockIdx.x == 0 && tid == 0) a.ws.range[head] = uint2{lo, hi};
+        if (x0 == 0 && tid == 0) a.ws.range[head] = uint2{lo, hi};
     } else if (search) {
         if (tid < 64) fine[tid] = 0;
         if (tid < 256) exps[tid] = ce;
@@ -226,7 +228,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) 
         hi = key31(scale(__uint_as_float((bin << kRawShift) | ((1u << kRawShift) - 1u))));
         if (ex >= 255u) { lo = 0u; hi = 0x7FFFFFFFu; }                      // beyond the finite range: everything
         if (scale.on && scale.zero) lo = hi = key31(scale.uniform);         // all scores are this one
-        if (blockIdx.x == 0 && tid == 0) a.ws.range[head] = uint2{lo, hi};
+        if (x0 == 0 && tid == 0) a.ws.range[head] = uint2{lo, hi};
     }
     unsigned long long* g = a.ws.gmask + (size_t)head * a.ws.words;
     unsigned long long* e = a.ws.emask + (size_t)head * a.ws.words;
@@ -323,7 +325,9 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
                                                                    GatherArgs ga) {
     __shared__ EmitShared sm;
     __shared__ int32_t stage[ROW_U4 ? kSplitShare : 1];
-    const int head = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int head, x0;
+    xcd_place(&x0, &head);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int32_t n = a.n, s = a.n_sink < n ? a.n_sink : n;
     const int64_t o0 = a.offsets[head], o1 = a.offsets[head + 1];
     // all of the first loads go out together, before anything is decided
@@ -345,7 +349,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
     const float* sc = a.scores + (size_t)head * n;
     const int32_t k = (int32_t)(o1 - o0);
     if (KNOWN) share = (k + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int32_t begin = (int32_t)blockIdx.x * share;
+    const int32_t begin = (int32_t)x0 * share;
     const int32_t end = begin + share < k ? begin + share : k;     // output rows begin .. end-1 are this workgroup's
     uint32_t m;
     const bool search = needs_search(k, n, s, &m);
