@@ -38,9 +38,9 @@ __device__ __forceinline__ void block_partial_store(float wave_total, float* dst
 // burst per stage: no global store sits inside the streaming loop.  Score
 // writes that mingle with the read streams of other waves are dear on this
 // memory system (1 % of the bytes cost 7 % of the time with 8 KB stages), so the
-// stages are as large as LDS allows, normally a wave's whole range, and the
-// stores are non-temporal: the workgroups of one round then end, and write,
-// at about the same time.
+// stages are as large as LDS allows, normally a wave's whole range: the workgroups of one round then
+// end, and write, at about the same time.  The stores are ordinary ones, which leave the scores in the caches for the kernel
+// that normalises or selects (non-temporal: curdkv_scores of 112 heads of 10007 tokens 94.3 us, so 92.5; one call for 32 of 32768 118.6 and 117.0).
 // ---------------------------------------------------------------------------
 template <int CB> struct Stage {    // tiles (of 32 tokens) a wave collects between bursts
     static constexpr int kTiles = CB > 4 ? 256 : 128;     // one workgroup per CU: 128 KB; two: 64 KB each
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
                                                    // 1024 tokens to 256 heads 24.5 and 23.5; the kernel of one workgroup a head does, 256 of 32768 623 and 630)
                                                    MODE == kStreamNone ? scan_phase(head, blk * 4 + wave) : 0u, hist, n_sink, stay_from);
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
-        for (int32_t r = r0 + lane; r < r1; r += 64) __builtin_nontemporal_store(mine[r - r0], &sh[r]);
+        for (int32_t r = r0 + lane; r < r1; r += 64) sh[r] = mine[r - r0];
     }
     block_partial_store<4>(wave_sum(acc_sum), partial + (size_t)head * kMaxBlocksPerHead + blk,
                            sums ? sums + head : nullptr, restart);
@@ -170,7 +170,7 @@ __global__ __launch_bounds__((ShapeF32<CB, SPLIT>::kWaves * 64), (SPLIT ? 2 : 1)
         if constexpr (SPLIT) acc_sum += scan_tiles_f32_split<CB, SRC, COUNT, STREAM>(gs, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink, stay_from);
         else acc_sum += scan_tiles_f32<CB, SRC, PROJ, COUNT>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink);
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
-        for (int32_t r = r0 + lane; r < r1; r += 64) __builtin_nontemporal_store(mine[r - r0], &sh[r]);
+        for (int32_t r = r0 + lane; r < r1; r += 64) sh[r] = mine[r - r0];
     }
     block_partial_store<kWaves>(wave_sum(acc_sum), partial + (size_t)head * kMaxBlocksPerHead + blk,
                                 sums ? sums + head : nullptr, restart);
