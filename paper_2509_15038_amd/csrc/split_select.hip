@@ -178,8 +178,15 @@ __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) 
     uint32_t ce = 0;                               // thread (half, exponent): half of the histograms each
     const uint32_t* co = a.ws.coarse + (size_t)head * a.ws.hists * 256 + (tid & 255);
     if (!KNOWN || given == kNoThreshold) {
-#pragma unroll 8
-        for (int h = tid >> 8; h < a.hists; h += 2) ce += co[h * 256];
+        // (sixteen loads at a time, clamped instead of branched around)
+        for (int h0 = tid >> 8; h0 < a.hists; h0 += 32) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const int h = h0 + 2 * u;
+                const uint32_t c = co[(h < a.hists ? h : h0) * 256];
+                ce += h < a.hists ? c : 0u;
+            }
+        }
     }
     constexpr int kU = 8;
     float v[kU];
@@ -250,17 +257,19 @@ __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) 
     }
 }
 
+constexpr int kWideBits = 10, kWideDigits = 1 << kWideBits;   // digits of a list in LDS
+
 struct EmitShared {
     unsigned long long gmask[kSplitMaxWords];      // kept tokens
     unsigned long long emask[kSplitMaxWords];      // candidates in the range, then those equal to the threshold
     union {
         struct {
             uint32_t pairs[2 * kSplitPairs];       // (key - lo, token) of the candidates in the range,
-            uint32_t wpos[kSplitMaxWords];         // later: output position of a word's first kept token
+            alignas(16) uint32_t wpos[kSplitMaxWords];     // counts of their digits; later: output position of a word's first kept token
         };
         uint16_t list[kSplitList];                 // or the candidates' tokens, ascending, without bit 16
     };
-    uint32_t hist[256];
+    alignas(16) uint32_t hist[256];
     uint32_t wave_tot[2][kSplitWaves];
     uint32_t digit, want, count;
     uint32_t low;                                  // place in the list of the first token from 65536 on
@@ -295,21 +304,29 @@ __device__ __forceinline__ void count_digit(uint32_t* hist, uint32_t digit, bool
     else if (counts && digit != first) atomicAdd(&hist[digit], 1u);
 }
 
-// One digit of the search for the threshold: hist[0..255] counts the digit's values (zeroed
+// One digit of the search for the threshold: hist[0..VALUES-1] counts the digit's values (zeroed
 // again), *want becomes the rank inside the chosen value, *count that value's count.  Ends with a barrier.
+template <int VALUES = 256>
 __device__ __forceinline__ void pick_digit(uint32_t* hist, uint32_t* digit, uint32_t* want, uint32_t* count) {
-    if (threadIdx.x < 64) {                        // lane L looks at values 255-4L .. 252-4L
+    constexpr int kPer = VALUES / 64;
+    if (threadIdx.x < 64) {                        // lane L looks at values VALUES-1-kPer*L and down
         const int lane = threadIdx.x;
-        uint32_t c[4], tot = 0;
+        uint32_t c[kPer], tot = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { c[i] = hist[255 - 4 * lane - i]; tot += c[i]; hist[255 - 4 * lane - i] = 0; }
+        for (int i = 0; i < kPer; i += 4) {
+            uint4& four = reinterpret_cast<uint4*>(hist)[(VALUES - 4 - kPer * lane - i) / 4];
+            const uint4 v = four;
+            four = uint4{0, 0, 0, 0};
+            c[i] = v.w; c[i + 1] = v.z; c[i + 2] = v.y; c[i + 3] = v.x;
+            tot += (v.x + v.y) + (v.z + v.w);
+        }
         uint32_t incl = wave_inclusive(tot);
         uint32_t run = incl - tot;
         const uint32_t w = *want;
         if (run < w && w <= incl) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (w <= run + c[i]) { *digit = 255 - 4 * lane - i; *want = w - run; *count = c[i]; break; }
+            for (int i = 0; i < kPer; ++i) {
+                if (w <= run + c[i]) { *digit = VALUES - 1 - kPer * lane - i; *want = w - run; *count = c[i]; break; }
                 run += c[i];
             }
         }
@@ -415,8 +432,22 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
         sm.emask[w0 + i] = e[i];
     }
     for (int i = tid; i < 256; i += kSplitThreads) sm.hist[i] = 0;
-    block_exclusive(ng, sm.wave_tot[0], &total_g);
-    uint32_t slot = block_exclusive(ne, sm.wave_tot[1], &total_e);
+    for (int i = tid; i < kWideDigits; i += kSplitThreads) sm.wpos[i] = 0;
+    uint32_t slot;
+    {   // both sums behind one barrier
+        const uint32_t ig = wave_inclusive(ng), ie = wave_inclusive(ne);
+        if (lane == 63) { sm.wave_tot[0][wave] = ig; sm.wave_tot[1][wave] = ie; }
+        __syncthreads();
+        uint32_t before = 0;
+        total_g = total_e = 0;
+#pragma unroll
+        for (int w = 0; w < kSplitWaves; ++w) {
+            before += w < wave ? sm.wave_tot[1][w] : 0u;
+            total_g += sm.wave_tot[0][w];
+            total_e += sm.wave_tot[1][w];
+        }
+        slot = before + ie - ne;
+    }
     uint32_t need = m - total_g;                                   // how many of the range are kept (>= 1)
     // ---- the threshold among the keys in the range ---------------------------------------------------
     const uint32_t width = range.y - range.x;
@@ -476,14 +507,14 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
             __syncthreads();
             for (uint32_t i = tid; i < total_e; i += kSplitThreads) sm.pairs[2 * i] = key31(scale(sc[sm.pairs[2 * i + 1]])) - range.x;
             __syncthreads();
-            while (rem > 0) {
-                const int w = rem < 8 ? rem : 8, shift = rem - w;
+            while (rem > 0) {                                      // ten bits at a time: two digits of a range of a sixteenth of a binade
+                const int w = rem < kWideBits ? rem : kWideBits, shift = rem - w;
                 for (uint32_t i = tid; i < total_e; i += kSplitThreads) {
                     const uint32_t key = sm.pairs[2 * i];
-                    if ((key >> rem) == fixed) atomicAdd(&sm.hist[(key >> shift) & ((1u << w) - 1u)], 1u);
+                    if ((key >> rem) == fixed) atomicAdd(&sm.wpos[(key >> shift) & ((1u << w) - 1u)], 1u);
                 }
                 __syncthreads();
-                pick_digit(sm.hist, &sm.digit, &sm.want, &sm.count);
+                pick_digit<kWideDigits>(sm.wpos, &sm.digit, &sm.want, &sm.count);
                 fixed = (fixed << w) | sm.digit;
                 rem = shift;
             }
@@ -578,7 +609,14 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
     // ---- this workgroup's share ----------------------------------------------------------------------------
     do {
     for (int32_t j = r0 + tid; j < r1 && j < s; j += kSplitThreads) put(j, j);
-    for (int q = tid; q < words * 4; q += kSplitThreads) {         // a thread per quarter word (16 tokens)
+    // only the words that hold rows r0 .. r1-1: positions ascend, so a search finds the first one, and the pass ends behind the last.  (All
+    // words, digits of 8 bits, a barrier per sum and 8 of a histogram's counts in flight in split_flag_kernel: one call for 8 heads of 131072 tokens
+    // 119.2 us, so 116.4, 1 head 36.2 and 34.4, 8 of 60000 66.8 and 64.7; curdkv_select of 8 of 131072 21.0 and 20.0.)
+    int lo = 0;
+    for (int step = kSplitMaxWords / 2; step > 0; step >>= 1)
+        if (lo + step < words && (int32_t)sm.wpos[lo + step] <= r0) lo += step;
+    for (int q = lo * 4 + tid; q < words * 4; q += kSplitThreads) {        // a thread per quarter word (16 tokens)
+        if ((int32_t)sm.wpos[q >> 2] >= r1) break;
         const int w = q >> 2, part = q & 3;
         const unsigned long long word = sm.gmask[w];
         uint32_t mm = (uint32_t)(word >> (16 * part)) & 0xFFFFu;
