@@ -141,22 +141,10 @@ __global__ __launch_bounds__((ShapeF32<CB, SPLIT>::kWaves * 64), (SPLIT ? 2 : 1)
     const int32_t n32 = (int32_t)n;
     const int32_t tiles = (n32 + kTileTokens - 1) / kTileTokens;
     const int32_t waves_per_head = blocks_per_head * kWaves;
-    int32_t t_begin, t_end;
-    if constexpr (SPLIT) {
-        // groups of 64 tokens as evenly as they go, one more to some waves spread over the head: 8 heads of 20000 tokens, r = 20, 42.7 us with the
-        // same number to every wave as long as there are any, 41.5 so.  (The bf16 kernel is 1 to 3 % slower that way.)
-        const uint32_t groups = ((uint32_t)tiles + 1) >> 1, waves = (uint32_t)waves_per_head;
-        const uint32_t each = groups / waves, more = groups - each * waves;
-        auto first = [&](uint32_t w) { return (int32_t)(2 * (w * each + w * more / waves)); };
-        t_begin = first((uint32_t)(blk * kWaves + wave));
-        t_end = first((uint32_t)(blk * kWaves + wave + 1));
-        t_end = t_end < tiles ? t_end : tiles;
-    } else {
-        int32_t per_wave = (tiles + waves_per_head - 1) / waves_per_head;
-        per_wave += per_wave & 1;                               // whole pairs
-        t_begin = (blk * kWaves + wave) * per_wave;
-        t_end = t_begin + per_wave < tiles ? t_begin + per_wave : tiles;
-    }
+    int32_t per_wave = (tiles + waves_per_head - 1) / waves_per_head;
+    per_wave += per_wave & 1;                                   // whole pairs
+    const int32_t t_begin = (blk * kWaves + wave) * per_wave;
+    const int32_t t_end = t_begin + per_wave < tiles ? t_begin + per_wave : tiles;
     const float4* Kh = K + (size_t)head * n * 32;               // 32 chunks of 16 bytes per row
     const float4* Vh = V + (size_t)head * n * 32;
     float* sh = scores + (size_t)head * out_stride + out_offset;

@@ -52,19 +52,6 @@ struct GatherArgs {
     u32x4 *K_out, *V_out;
 };
 
-// Head and share of a workgroup in a grid of (shares, heads) whose workgroups of one head read the same data.  Workgroups are dealt to the
-// eight XCDs, each with an L2 of its own, one by one: numbered afresh, an XCD gets a stretch of neighbours, so that a head's data go
-// to one or two L2s and not to all.  One call, us, before and after: 32 heads of 32768 tokens 121.6 and 119.0, 16 of 20000 46.1 and 44.7, 100 of 5000 62.2 and 61.6, 8 of
-// 8192 17.8 and 17.7; curdkv_select of 8 heads of 131072 21.7 and 21.1, of 100 of 50000 31.8 and 30.8.
-__device__ __forceinline__ void xcd_place(int* share, int* head) {
-    constexpr uint32_t kXcds = 8;
-    const uint32_t at = blockIdx.y * gridDim.x + blockIdx.x, total = gridDim.x * gridDim.y;
-    const uint32_t xcd = at % kXcds, each = total / kXcds, more = total % kXcds;
-    const uint32_t g = xcd * each + (xcd < more ? xcd : more) + at / kXcds;
-    *head = (int)(g / gridDim.x);
-    *share = (int)(g % gridDim.x);
-}
-
 __device__ __forceinline__ uint32_t order_key(float x) {
     x = x + 0.0f;                                 // -0 -> +0
     const uint32_t b = __float_as_uint(x);

@@ -5,12 +5,12 @@
 //   1. histograms of the scores over 4096 bins (exponent and top four mantissa bits), one per
 //      workgroup that makes them: the scoring kernel, on the one-call path, while it has the
 //      (un-normalised) scores in LDS, or split_hist_kernel from scores in memory;
-//   2. split_flag_kernel, workgroup (part, head): every workgroup finds the bin that holds the
+//   2. split_flag_kernel, workgroup (head, part): every workgroup finds the bin that holds the
 //      cut (the same small sums in each: exponents first, then the sixteen bins of one
 //      exponent), turns it into a range [lo, hi] of normalised scores and writes one bit per
 //      token of its part to two bitmaps, "above hi" and "in the range".  On the one-call
 //      path it also normalises the scores;
-//   3. split_emit_kernel, workgroup (share, head): reads the head's bitmaps (n/4 bytes), resolves
+//   3. split_emit_kernel, workgroup (head, share): reads the head's bitmaps (n/4 bytes), resolves
 //      the threshold on the few keys in the range, scans the popcounts into output positions
 //      and lists its share of the output rows.  Resolving and scanning are repeated
 //      by every workgroup of a head: they are small, and it saves a launch and a trip through
@@ -165,8 +165,7 @@ __device__ __forceinline__ uint32_t wave_find(const uint32_t (&c)[PER], uint32_t
 template <bool KNOWN>
 __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) {
     __shared__ uint32_t exps[256], fine[64], found[2];
-    int head, x0;
-    xcd_place(&x0, &head);
+    const int head = blockIdx.x, x0 = blockIdx.y;  // (a head's workgroups, which read the same data, in one L2: select_gather_kernel)
     const int tid = threadIdx.x, lane = tid & 63;
     const int32_t n = a.n, s = a.n_sink < n ? a.n_sink : n;
     const int64_t o0 = a.offsets[head], o1 = a.offsets[head + 1];
@@ -342,8 +341,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
                                                                    GatherArgs ga) {
     __shared__ EmitShared sm;
     __shared__ int32_t stage[ROW_U4 ? kSplitShare : 1];
-    int head, x0;
-    xcd_place(&x0, &head);
+    const int head = blockIdx.x, x0 = blockIdx.y;  // (a head's workgroups, which read the same data, in one L2: select_gather_kernel)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int32_t n = a.n, s = a.n_sink < n ? a.n_sink : n;
     const int64_t o0 = a.offsets[head], o1 = a.offsets[head + 1];
@@ -365,7 +363,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
     const HeadScale scale = head_scale(head_partial(a.partial + (size_t)head * kMaxBlocksPerHead, scale_blocks), scale_blocks, n);
     const float* sc = a.scores + (size_t)head * n;
     const int32_t k = (int32_t)(o1 - o0);
-    if (KNOWN) share = (k + (int)gridDim.x - 1) / (int)gridDim.x;
+    if (KNOWN) share = (k + (int)gridDim.y - 1) / (int)gridDim.y;
     const int32_t begin = (int32_t)x0 * share;
     const int32_t end = begin + share < k ? begin + share : k;     // output rows begin .. end-1 are this workgroup's
     uint32_t m;
@@ -675,7 +673,7 @@ hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, 
     int64_t part = (n + parts - 1) / parts;
     if (part > 16384) part = 16384;
     a.part = (int)((part + kSplitThreads - 1) / kSplitThreads * kSplitThreads);
-    const dim3 parts_grid((unsigned)((n + a.part - 1) / a.part), (unsigned)ctx->heads);
+    const dim3 parts_grid((unsigned)ctx->heads, (unsigned)((n + a.part - 1) / a.part));
     if (a.known) split_flag_kernel<true><<<parts_grid, kSplitThreads, 0, stream>>>(a);
     else split_flag_kernel<false><<<parts_grid, kSplitThreads, 0, stream>>>(a);
     const bool with_gather = gather && gather->total > 0 && emit_gathers(ctx, gather->total);
@@ -696,7 +694,7 @@ hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, 
         shares = (ctx->num_cu * (with_gather ? 2 : 1) + ctx->heads - 1) / ctx->heads;
         share = 0;
     }
-    const dim3 grid((unsigned)(shares > 0 ? shares : 1), (unsigned)ctx->heads);
+    const dim3 grid((unsigned)ctx->heads, (unsigned)(shares > 0 ? shares : 1));
     GatherArgs ga{};
     if (with_gather) {
         ga = GatherArgs{(const u32x4*)gather->K, (const u32x4*)gather->V, (u32x4*)gather->K_out, (u32x4*)gather->V_out};
