@@ -354,12 +354,30 @@ static int few_blocks_per_head(const curdkv_ctx* ctx, int64_t n, bool running) {
 // waves: curdkv_scores, r = 64, 100 heads of 64 tokens 6.3 -> 6.7, 128 columns, 256 heads of 16 4.6 -> 4.8.
 constexpr int64_t kFewF32Tokens = 16384, kFewF32Steps = 6, kFewBf16Tokens = 8192, kFewBf16Steps = 4;
 
+// More tokens take it as long as the steps of a workgroup times the workgroups of a compute unit, which work one after the other, are few,
+// by storage and sketch width, and the heads not so many that the other kernel fills the chip with one workgroup each.  One call, a fifth kept, us, the other
+// kernel and this one (load): bf16, r = 20, 16 heads of 1024 tokens 13.6 and 11.6 (4), 8 of 3000 14.7 and 13.3 (6), 4 of 6000 15.6 and 14.9 (6), 3 of 8000 15.9 and
+// 16.2 (8), 100 of 240 12.7 and 13.0 (8), 128 of 128 10.6 and 11.0 (4); r = 64, 8 of 2048 14.4 and 13.6 (4), 12 of 1300 14.3 and 13.6 (4), 24 of 680 14.0 and
+// 15.0 (6), 48 of 200 12.3 and 13.0 (4); r = 128, 8 of 1200 15.2 and 14.8 (3), of 1600 15.6 and 16.9 (4).  fp32, r = 20, 8 of 4096 24.3 and 19.0 (8), 4 of 9000
+// 26.4 and 23.0 (9), 256 of 128 23.2 and 21.4 (8), 16 of 3000 25.0 and 24.5 (12).  curdkv_scores_append: bf16, r = 20, 8 of 2048 8.5 and 7.1, r = 64 9.0 and
+// 8.1; fp32, r = 20, 8 of 2500 18.3 and 11.0.  Wider fp32 sketches would gain as much (r = 64, 8 of 2500 30.2 and 23.4), but the split products of the other kernel err
+// less than the plain ones here.
+struct FewLoad { int heads, load; };
+constexpr FewLoad kFewLoadBf16[3] = {{64, 6}, {32, 4}, {32, 3}};   // up to 32, 64 and 128 columns
+constexpr FewLoad kFewLoadF32 = {256, 10};                         // up to 32 columns
+
 // running: a running sum is wanted (curdkv_scores_append).
 static bool few_tokens(const curdkv_ctx* ctx, int64_t n, bool running) {
     if (ctx->cfg.no_projection) return false;
     const bool f32 = ctx->cfg.dtype == CURDKV_DTYPE_F32;
     const int64_t most = f32 ? kFewF32Tokens : kFewBf16Tokens / (ctx->heads > ctx->num_cu / 4 ? ctx->col_blocks : 1);
-    if (n * ctx->heads > most) return false;
+    const int64_t steps = (n + 15) / 16, blocks = few_blocks_per_head(ctx, n, running);
+    if (n * ctx->heads > most || steps > (f32 ? kFewF32Steps : kFewBf16Steps) * blocks) {
+        if (f32 && ctx->col_blocks > 1) return false;
+        const FewLoad limit = f32 ? kFewLoadF32 : kFewLoadBf16[ctx->col_blocks == 1 ? 0 : ctx->col_blocks == 2 ? 1 : 2];
+        const int64_t load = (steps + blocks - 1) / blocks * ((blocks * ctx->heads + ctx->num_cu - 1) / ctx->num_cu);
+        if (ctx->heads > limit.heads || load > limit.load) return false;
+    }
     // bf16, two steps of a wide sketch: the other kernel's waves hold all of it and take 32 tokens at once.  8 heads, r = 20 /
     // 64 / 128, replayed graph: 32 tokens 3.6 -> 3.4 / 3.9 -> 4.3 / 4.7 -> 6.3, 16 tokens 3.5 -> 3.0 / 3.8 -> 3.5 / 4.5 -> 4.6, 8
     // tokens 4.4 -> 3.9 at r = 128; curdkv_scores of 224 heads of 19 tokens, r = 64, in two workgroups 6.2 -> 6.8.
@@ -371,8 +389,7 @@ static bool few_tokens(const curdkv_ctx* ctx, int64_t n, bool running) {
     // 6.7 -> 8.2 / 7.4 -> 8.5 / 9.0 -> 7.9: with 128 columns beyond 192 tokens the split wins either way (48 heads of 130
     // tokens 7.3 -> 7.9 and 7.7 -> 8.1).
     if (!f32 && running && n > 32 && !(ctx->col_blocks > 2 && n > 192) && pick_blocks_per_head(ctx, n, false) == 1) return false;
-    const int64_t steps = (n + 15) / 16;
-    return steps <= (f32 ? kFewF32Steps : kFewBf16Steps) * few_blocks_per_head(ctx, n, running);
+    return true;
 }
 
 // Whether rows are fetched past the caches (fetch in scan_device.h).  What fits the 256 MB Infinity Cache is often there already, and a gather
