@@ -330,15 +330,17 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     const int rc = sync_offsets(ctx, offsets, budgets, n, st, &total, &max_budget);
     if (rc != CURDKV_OK) return rc;
     if (total > 0 && (!indices || !K_out || !V_out)) return CURDKV_ERR_INVALID_ARG;
-    // One kernel for everything when it applies and about a tenth of the rows or fewer are kept.
+    // One kernel for everything when it applies and not too many rows are kept.
     // Beyond, the stand-alone gather kernel (many small workgroups, 32 waves per compute unit)
     // moves rows enough faster than the fused kernel's last phase (one long-lived workgroup of 8
-    // waves per unit) to pay for two more launches.  Measured at 256 heads of 32768 tokens, one
-    // call at keep 5 / 8 / 10 / 12 / 20 / 30 %: fused 783 / 832 / 863 / 897 / 1029 / 1195 us,
-    // scoring phases + selection kernel + gather kernel 792 / 832 / 859 / 887 / 993 / 1125 us:
-    // level at a tenth (the paper's strongest compression), 4 to 6 % apart from a fifth on.
+    // waves per unit), and finds those of the scan's end in the Infinity Cache, to pay for two more launches and a
+    // selection from memory.  One call for 256 heads, us, fused and as separate kernels: 32768 tokens at keep 5 / 10 / 12 / 15 / 20 / 30 % 700 / 779 / 813 / 865 / 944 / 1114 and
+    // 717 / 785 / 813 / 855 / 924 / 1050; 16384 at 12 / 15 % 411 / 438 and 420 / 441; 12000 at 10 / 16 / 20 % 295 / 326 / 356 and 300 / 329 / 351; 8000 at
+    // 15 / 25 % 216 / 252 and 221 / 253; 4096 at 20 / 30 / 40 % 122 / 142 / 161 and 126 / 142 / 157; 2048 at 20 / 50 / 80 % 71 / 94 / 118 and 79 / 103 / 126; 1000 at
+    // 20 / 90 % 34 / 58 and 39 / 64; 300 at 50 % 18 and 23.
     const bool fusable = fused_applicable(ctx, n);
-    const bool big_gather = total * 100 > (int64_t)ctx->heads * n * kFusedGatherMaxPercent;
+    const int64_t most_rows = n <= kFusedGatherTokens ? n : kFusedGatherRows + n * kFusedGatherPercent / 100;
+    const bool big_gather = total > ctx->heads * most_rows;
     if (fusable && !big_gather)
         return launch_fused(ctx, K, V, n, n_sink, ctx->plan.d_offsets, scores, indices, K_out, V_out, st) == hipSuccess
                    ? CURDKV_OK : CURDKV_ERR_HIP;

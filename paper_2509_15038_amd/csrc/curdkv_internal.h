@@ -16,7 +16,8 @@ constexpr int kMaxColBlocks = 4;       // r padded to 32, 64 or 128
 constexpr int kMaxBlocksPerHead = 256; // partial sums kept per (layer, group): one head can have a workgroup per compute unit
 constexpr int kTileTokens = 32;        // tokens per wave tile
 constexpr int kCompactRowsPerBlock = 128;  // output rows per entry of the gather's table of heads
-constexpr int kFusedGatherMaxPercent = 11;  // curdkv_compress: share of rows kept up to which the fused kernel also gathers
+constexpr int kFusedGatherTokens = 2048;       // curdkv_compress: heads up to which the fused kernel always gathers,
+constexpr int kFusedGatherRows = 800, kFusedGatherPercent = 9;   // longer ones: up to so many rows kept, and so much of the head more
 
 struct BlockInfo {                     // for gather block b, whose first output row is b*128:
     int64_t head_end;                  //   offsets[head + 1]

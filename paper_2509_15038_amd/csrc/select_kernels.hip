@@ -498,10 +498,8 @@ static hipError_t launch_reg(const curdkv_ctx* ctx, float* scores, int32_t n, in
 // gather kernel's many small workgroups make up for its launch: half kept of 64 heads of 8192 tokens (262144 rows)
 // 106.4 -> 105.6, of 128 heads 185.9 -> 190.6; a tenth of 64 heads of 32768 (209664) 241.8 -> 242.5: hence 512 rows a unit.
 // The split selection, which comes second, is behind up to the longest head this holds, as long as the rows are few: a tenth kept, this
-// and split, r = 20, 1 head of 24577 tokens 19.4 and 25.3, of 32768 22.0 and 26.6; 8 of 32768 40.5 and 43.5; 16 of 32768 67.5 and 71.0; 24 of 28000
-// 84.9 and 86.9.  From there to 32 heads the two are level: r = 64, 24 of 32768 102.8 and 104.2, 32 of 28000 115.0 and 116.2, of 32768 132.6 and 132.8; r = 20,
-// 24 of 32768 101.0 and 101.2, 32 of 32768 131.2 and 130.4 (this reads 2.5 % more there, every workgroup its head's products); heads of one
-// value 159.8 and 186.6.  Half kept, separate kernels and split, 194.1 and 192.5.
+// and split, r = 64, 1 head of 32768 tokens 22.2 and 26.3; 4 of 32768 29.6 and 31.0; 8 of 24000 33.8 and 38.0, of 32768 44.9 and 49.1; 16 of 24000 51.6 and 55.6, of 32768
+// 66.9 and 68.4; 24 of 32768 92.6 and 93.3, 32 of 24000 88.7 and 90.7, of 32768 116.8 and 116.5; r = 20, 115.9 and 116.0.
 // Smaller workgroups for shorter heads give nothing (256 threads: 1024 tokens 9.9, 8192 tokens 21.7).
 constexpr int64_t kGatherMaxTokens = 32 * kSelThreads;             // what a workgroup's registers and LDS hold
 constexpr int64_t kGatherRowsPerUnit = 512;

@@ -72,7 +72,7 @@ def _check_scores(heads, n, dtype, r, source, projection):
 # one call: the kernel that does everything (few rows kept of as many heads as units), scores by it and separate kernels, the selection
 # that gathers, the split selection with histograms from the scoring; a quarter and more kept, where the end of the scan goes through the caches,
 # is a walk in two parts.  The rows kept are found again
-@pytest.mark.parametrize("heads,n,r,keep,dtype", [(256, 2049, 64, 0.1, "bf16"), (256, 2500, 20, 0.05, "bf16"), (256, 2111, 64, 0.5, "bf16"), (25, 16411, 64, 0.1, "bf16"),
+@pytest.mark.parametrize("heads,n,r,keep,dtype", [(256, 2048, 64, 0.9, "bf16"), (256, 2047, 20, 0.5, "bf16"), (256, 2049, 64, 0.1, "bf16"), (256, 2500, 20, 0.05, "bf16"), (256, 2111, 64, 0.5, "bf16"), (25, 16411, 64, 0.1, "bf16"),
                                                   (25, 16411, 20, 0.3, "bf16"), (160, 2600, 20, 0.4, "bf16"), (6, 70001, 20, 0.1, "bf16"), (6, 70001, 64, 0.5, "bf16"),
                                                   (40, 40001, 128, 0.05, "bf16"), (8, 49217, 128, 0.6, "bf16"), (100, 4133, 20, 0.1, "fp32"), (4, 70001, 32, 0.4, "fp32"),
                                                   (256, 1009, 20, 0.5, "fp32")])
