@@ -115,6 +115,9 @@ struct SelectGather {
     int64_t total;                     // rows kept, all heads
     bool done;
 };
+// The largest budget is at most a quarter above the average (max_budget < 0: not known).  Otherwise the workgroups that gather a head's rows are spread over
+// all XCDs: 4 heads of 99162 tokens, half kept, Dirichlet budgets, split_emit_kernel 39.2 us so, 50.5 with two XCDs a head.
+inline bool even_budgets(const curdkv_ctx* ctx, int64_t max_budget, int64_t total) { return max_budget >= 0 && max_budget * ctx->heads * 4 <= total * 5; }
 hipError_t launch_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
                          const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
                          int scale_blocks = 0, bool write_scaled = true,

@@ -396,9 +396,10 @@ static bool few_tokens(const curdkv_ctx* ctx, int64_t n, bool running) {
 // of the same call finds its rows there.  us, kept in the caches and streamed, three caches in turn, r = 64: curdkv_scores of 8 heads of
 // 24576 tokens (101 MB) 22.2 and 23.2, of 32768 (134) 31.2 and 29.0, of 65536 53.8 and 47.8; appends of 768 tokens to 256 heads (101) 19.8 and
 // 20.6, of 1024 28.7 and 26.9; one call, a tenth kept, 8 heads of 8192 17.3 and 19.2, of 32768 (134) 44.8 and 45.4, of 40960 (168) 57.7 and 54.7, half
-// kept (168, the end of the scan left in the caches) 75.9 and 78.6, 32 heads of 12288 (201) 81.6 and 79.1.  Large: 256 heads of 32768 703 and 624, of 131072, r = 128,
+// kept (168, the end of the scan left in the caches) 75.9 and 78.6, 32 heads of 12288 (201) 81.6 and 79.1, 4 of 99162 (203) 88.2 and 95.7, 8 of 65536 (268) 110.6 and
+// 108.3.  Large: 256 heads of 32768 703 and 624, of 131072, r = 128,
 // 2858 and 2578.
-constexpr int64_t kStreamBytes = 120000000, kStreamBytesReread = 160000000, kStreamBytesRereadMany = 200000000;
+constexpr int64_t kStreamBytes = 120000000, kStreamBytesReread = 160000000, kStreamBytesRereadMany = 256000000;
 // Where a quarter of the rows or more are gathered afterwards, the end of the scan still goes through the caches: so much of it as
 // the gather then finds there.  One call, half kept, nothing left, 128, 192 and 256 MB, us: 32 heads of 16384, r = 64, 103.9, 100.4, 109.0 and 110.7 (all
 // kept in the caches 105.7); 256 of 32768 1326, 1304, 1309, 1311; fp32, r = 32, 8 heads of 32768 120.3, 109.7, 110.5, 113.0 (all 111.8), three tenths kept 101.2,

@@ -390,14 +390,10 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const float*
                                                                 int32_t n, int32_t n_sink, const int64_t* __restrict__ offsets,
                                                                 int32_t* __restrict__ indices, const float* __restrict__ partial,
                                                                 int scale_blocks, int share, GatherArgs ga,
-                                                                const Threshold* __restrict__ known) {
+                                                                const Threshold* __restrict__ known, int heads_x) {
     extern __shared__ int32_t stage[];             // [n]
     __shared__ SelectShared<kSelThreads, KPT> sm;
-    // Workgroups are dealt to the eight XCDs one by one: with the heads along x, those of a head, which all read the same products, meet in one L2
-    // (heads in eights; in two for fours).  One call, us, before and after: 32 heads of 32768 tokens 121.6 and 119.0, 16 of 20000 46.1 and 44.7, 8 of 8192 17.8
-    // and 17.7.  Up to 2048 tokens, where there is little to fetch, shares along x are better: 16 heads of 863 tokens 13.4 and 13.7, 128 of 950 in fp32 49.3 and 49.9.
-    constexpr bool kHeadsX = KPT > 2;
-    const int head = kHeadsX ? blockIdx.x : blockIdx.y, x0 = kHeadsX ? blockIdx.y : blockIdx.x, shares = kHeadsX ? gridDim.y : gridDim.x;
+    const int head = heads_x ? blockIdx.x : blockIdx.y, x0 = heads_x ? blockIdx.y : blockIdx.x, shares = heads_x ? gridDim.y : gridDim.x;
     const int tid = threadIdx.x;
     raw += (size_t)head * n;
     const double mine = head_partial(partial + (size_t)head * kMaxBlocksPerHead, scale_blocks);
@@ -529,9 +525,14 @@ static hipError_t launch_gather(const curdkv_ctx* ctx, const float* raw, float* 
     const int64_t shares = max_budget < 0 ? places : (max_budget + share - 1) / share;
     if (max_budget < 0) share = 0;
     const GatherArgs ga{(const u32x4*)g.K, (const u32x4*)g.V, (u32x4*)g.K_out, (u32x4*)g.V_out};
-    const dim3 grid = KPT > 2 ? dim3((unsigned)ctx->heads, (unsigned)shares) : dim3((unsigned)shares, (unsigned)ctx->heads);   // as the kernel reads it
+    // Workgroups are dealt to the eight XCDs one by one: with the heads along x, those of a head, which all read the same products, meet in one L2
+    // (heads in eights; in two for fours).  One call, us, before and after: 32 heads of 32768 tokens 121.6 and 119.0, 16 of 20000 46.1 and 44.7, 8 of 8192 17.8
+    // and 17.7.  Up to 2048 tokens, where there is little to fetch, shares along x are better: 16 heads of 863 tokens 13.4 and 13.7, 128 of 950 in fp32 49.3 and
+    // 49.9; and where the budgets are uneven, as a large one's rows would go through one XCD (even_budgets).
+    const bool heads_x = KPT > 2 && even_budgets(ctx, max_budget, g.total);
+    const dim3 grid = heads_x ? dim3((unsigned)ctx->heads, (unsigned)shares) : dim3((unsigned)shares, (unsigned)ctx->heads);
     select_gather_kernel<KPT, ROW_U4><<<grid, kSelThreads, (size_t)n * 4, stream>>>(
-        raw, scores, n, n_sink, d_offsets, indices, ctx->d_partial, scale_blocks, (int)share, ga, known);
+        raw, scores, n, n_sink, d_offsets, indices, ctx->d_partial, scale_blocks, (int)share, ga, known, heads_x ? 1 : 0);
     return hipGetLastError();
 }
 

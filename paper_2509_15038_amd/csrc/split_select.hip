@@ -165,7 +165,7 @@ __device__ __forceinline__ uint32_t wave_find(const uint32_t (&c)[PER], uint32_t
 template <bool KNOWN>
 __global__ __launch_bounds__(kSplitThreads) void split_flag_kernel(SplitArgs a) {
     __shared__ uint32_t exps[256], fine[64], found[2];
-    const int head = blockIdx.x, x0 = blockIdx.y;  // (a head's workgroups, which read the same data, in one L2: select_gather_kernel)
+    const int head = blockIdx.x, x0 = blockIdx.y;  // (a head's workgroups, which read the same data, in one L2: launch_gather)
     const int tid = threadIdx.x, lane = tid & 63;
     const int32_t n = a.n, s = a.n_sink < n ? a.n_sink : n;
     const int64_t o0 = a.offsets[head], o1 = a.offsets[head + 1];
@@ -338,10 +338,10 @@ __device__ __forceinline__ void pick_digit(uint32_t* hist, uint32_t* digit, uint
 // the head's rows by the workgroups, listed kSplitShare at a time where it copies them.
 template <int ROW_U4, bool KNOWN>
 __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, int32_t* __restrict__ indices, int share,
-                                                                   GatherArgs ga) {
+                                                                   GatherArgs ga, int heads_x) {
     __shared__ EmitShared sm;
     __shared__ int32_t stage[ROW_U4 ? kSplitShare : 1];
-    const int head = blockIdx.x, x0 = blockIdx.y;  // (a head's workgroups, which read the same data, in one L2: select_gather_kernel)
+    const int head = heads_x ? blockIdx.x : blockIdx.y, x0 = heads_x ? blockIdx.y : blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int32_t n = a.n, s = a.n_sink < n ? a.n_sink : n;
     const int64_t o0 = a.offsets[head], o1 = a.offsets[head + 1];
@@ -363,7 +363,8 @@ __global__ __launch_bounds__(kSplitThreads) void split_emit_kernel(SplitArgs a, 
     const HeadScale scale = head_scale(head_partial(a.partial + (size_t)head * kMaxBlocksPerHead, scale_blocks), scale_blocks, n);
     const float* sc = a.scores + (size_t)head * n;
     const int32_t k = (int32_t)(o1 - o0);
-    if (KNOWN) share = (k + (int)gridDim.y - 1) / (int)gridDim.y;
+    const int shares = (int)(heads_x ? gridDim.y : gridDim.x);
+    if (KNOWN) share = (k + shares - 1) / shares;
     const int32_t begin = (int32_t)x0 * share;
     const int32_t end = begin + share < k ? begin + share : k;     // output rows begin .. end-1 are this workgroup's
     uint32_t m;
@@ -694,7 +695,9 @@ hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, 
         shares = (ctx->num_cu * (with_gather ? 2 : 1) + ctx->heads - 1) / ctx->heads;
         share = 0;
     }
-    const dim3 grid((unsigned)ctx->heads, (unsigned)(shares > 0 ? shares : 1));
+    const bool heads_x = !with_gather || even_budgets(ctx, max_budget, gather->total);    // as in launch_gather (select_kernels.hip)
+    const unsigned each = (unsigned)(shares > 0 ? shares : 1);
+    const dim3 grid = heads_x ? dim3((unsigned)ctx->heads, each) : dim3(each, (unsigned)ctx->heads);
     GatherArgs ga{};
     if (with_gather) {
         ga = GatherArgs{(const u32x4*)gather->K, (const u32x4*)gather->V, (u32x4*)gather->K_out, (u32x4*)gather->V_out};
@@ -702,9 +705,9 @@ hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, 
     }
     auto emit = [&](auto known) {
         constexpr bool KNOWN = decltype(known)::value;
-        if (!with_gather) split_emit_kernel<0, KNOWN><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga);
-        else if (ctx->cfg.dtype == CURDKV_DTYPE_BF16) split_emit_kernel<16, KNOWN><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga);
-        else split_emit_kernel<32, KNOWN><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga);
+        if (!with_gather) split_emit_kernel<0, KNOWN><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga, heads_x ? 1 : 0);
+        else if (ctx->cfg.dtype == CURDKV_DTYPE_BF16) split_emit_kernel<16, KNOWN><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga, heads_x ? 1 : 0);
+        else split_emit_kernel<32, KNOWN><<<grid, kSplitThreads, 0, stream>>>(a, indices, (int)share, ga, heads_x ? 1 : 0);
     };
     if (max_budget < 0) emit(std::true_type{});
     else emit(std::false_type{});
