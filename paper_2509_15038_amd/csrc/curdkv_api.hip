@@ -215,6 +215,7 @@ int curdkv_create(curdkv_ctx** out, const curdkv_config* cfg) {
     }
     try {
         ctx->plan.cached.assign((size_t)ctx->heads + 1, 0);
+        ctx->sketch_outside.assign((size_t)ctx->heads, 0);
     } catch (...) {
         release(ctx);
         return CURDKV_ERR_OOM;
@@ -254,7 +255,13 @@ int curdkv_set_sketch(curdkv_ctx* ctx, int32_t layer, int32_t head, const float*
     std::memcpy(G, G_host, count * sizeof(float));
     round_to_storage(G, count, ctx->cfg.dtype);
     if (hipDeviceSynchronize() != hipSuccess) { std::free(G); return CURDKV_ERR_HIP; }
-    const int rc = upload_sketch(ctx, layer * ctx->cfg.kv_heads + head, G);
+    const int group = layer * ctx->cfg.kv_heads + head;
+    const int rc = upload_sketch(ctx, group, G);
+    if (rc == CURDKV_OK) {
+        const uint8_t outside = sketch_splits(G, count) ? 0 : 1;
+        ctx->sketches_outside += outside - ctx->sketch_outside[group];
+        ctx->sketch_outside[group] = outside;
+    }
     std::free(G);
     return rc;
 }

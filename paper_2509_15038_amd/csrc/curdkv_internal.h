@@ -65,6 +65,8 @@ struct curdkv_ctx {
     float* d_scores_ws = nullptr;      // [heads, max_tokens], allocated when curdkv_compress needs it
     int lds_limit = 0;                 // max dynamic LDS per workgroup, bytes
     int num_cu = 0;
+    std::vector<uint8_t> sketch_outside;   // per (layer, group): a sketch of the caller's that sketch_splits refuses,
+    int sketches_outside = 0;              // and how many there are
     curdkv::Plan plan;
 };
 
@@ -73,6 +75,7 @@ namespace curdkv {
 // sketch_host.cpp
 void sketch_values(const curdkv_config& cfg, int layer, int head, float* G /*[d*r], rounded*/);
 void round_to_storage(float* G, size_t count, int dtype);
+bool sketch_splits(const float* G, size_t count);
 // Pack row-major G[d][r] (already rounded) into the A-operand layout of one head.
 void pack_sketch(const curdkv_config& cfg, int col_blocks, const float* G, void* packed);
 size_t packed_elems(int col_blocks);

@@ -249,11 +249,13 @@ __global__ __launch_bounds__(256) void fold_kernel(const float* __restrict__ sq,
 // (eight waves a compute unit) and the waves' shares, whole groups of 64, differ little, else in fp32.  There HBM waits for neither the matrix units nor the splitting, while the fp32 units are busy 55 %
 // of the time and one wave a SIMD does not hide the rest.  curdkv_scores, r = 20, us, fp32 units and split: 8 heads of 4096 tokens 19.0 and 25.0, of 8192 22.7 and
 // 25.5, of 16384 (64 tokens a wave) 35.6 and 31.9, of 20000 (64 or 128) 41.1 and 41.5, of 24000 45.7 and 43.5, of 32768 60.5 and 59.2, of 65536 106.4 and 95.5; 64 of 16384 198.9 and 178.1; 112 of
-// 10007 211.2 and 197.2; 256 of 512 35.5 and 31.8, of 16384 727 and 685.  Wider sketches are bound by the matrix units' power: streaming gives them
+// 10007 211.2 and 197.2; 256 of 512 35.5 and 31.8, of 16384 727 and 685.  A sketch of the caller's that the split parts do not hold (sketch_splits) stays
+// with the fp32 units.  Wider sketches are bound by the matrix units' power: streaming gives them
 // nothing (64 heads of 16384, r = 64, 222.4 and 221.1).
 static bool f32_split(const curdkv_ctx* ctx, int64_t n) {
     if (ctx->cfg.dtype != CURDKV_DTYPE_F32 || ctx->cfg.no_projection) return false;
     if (ctx->col_blocks > 1) return true;
+    if (ctx->sketches_outside > 0) return false;
     const int64_t waves = (int64_t)ctx->num_cu * ShapeF32<2, true>::kWaves;
     if (ctx->heads * n < waves * 64) return false;
     const int64_t groups = (n + 63) / 64, places = waves / ctx->heads > 1 ? waves / ctx->heads : 1;

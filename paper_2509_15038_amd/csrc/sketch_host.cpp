@@ -44,6 +44,17 @@ void round_to_storage(float* G, size_t count, int dtype) {
     for (size_t i = 0; i < count; ++i) G[i] = bf16_bits_to_float(bf16_bits_rne(G[i]));
 }
 
+// Whether three bf16 parts (split_bf16 in scan_device.h) stand for every element as well as the float does, whatever the rows are.  From 2^-90 up
+// to far below bf16's largest number the parts are exact.  A row's elements below 2^-110 lose up to 2^-126 each, which elements of at
+// most 2^20 keep below 2^-99 in a coordinate: less than a rounding of any coordinate whose square is an fp32 number.  (Generated sketches lie within.)
+bool sketch_splits(const float* G, size_t count) {
+    for (size_t i = 0; i < count; ++i) {
+        const float size = std::fabs(G[i]);
+        if (size != 0.f && !(size >= 0x1p-90f && size <= 0x1p20f)) return false;
+    }
+    return true;
+}
+
 void sketch_values(const curdkv_config& cfg, int layer, int head, float* G) {
     const uint64_t d = static_cast<uint64_t>(cfg.head_dim);
     const uint64_t r = static_cast<uint64_t>(cfg.sketch_dim);

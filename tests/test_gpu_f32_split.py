@@ -108,3 +108,47 @@ def test_rows_and_sketches_of_any_size(r, rows):
                 assert np.isnan(raw[0, 0, 77]) and np.all(np.isposinf(raw[0, 0, [64, 130, 2084] if r != 33 else [64]]))
             raw[0, 0, [64, 77, 130, 2084]] = want[[64, 77, 130, 2084]] = 0
         assert np.all(np.abs(raw[i, j] - want) <= ELEMENT_TOL * want), (i, j)
+
+
+# Plain fp32 products round a coordinate's sum once per 4 of them, 32 times instead of 24 of a finer sum: a score of 20 to 32 columns errs by
+# 2e-7 at root mean square, seven times that over the 130000 scores compared, and twice that again for rows that lean on few coordinates ("largest": on one).
+PLAIN_TOL = 48 * 2.0 ** -24
+
+
+# Up to 32 columns the split products are taken from a number of tokens on only: what plain fp32 products give for a caller's own sketch, at fewer
+# tokens as well, they give there (128 heads of 1024 tokens and 64 of 3001 are beyond, 128 of 1023 are not).
+@pytest.mark.parametrize("heads,n", [(128, 1023), (128, 1024), (64, 3001)])
+@pytest.mark.parametrize("kind", ["tiny rows", "tiny sketch", "infinite", "largest"])
+def test_sketches_beyond_the_parts(heads, n, kind):
+    """Rows of 2^-120 under a sketch of 2^75, and rows of 2^70 under one of 2^-115, to the tolerance of any rows; a sketch with an infinity makes every score
+    infinite, one with the largest float leaves them finite."""
+    import torch
+    r = 32
+    rng = np.random.default_rng(heads)
+    K = rng.standard_normal((heads, n, 128)).astype(np.float32)
+    G = (rng.standard_normal((128, r)) / np.sqrt(r)).astype(np.float32)
+    if kind == "tiny rows":
+        K, G = K * np.float32(2.0 ** -120), G * np.float32(2.0 ** 75)
+    elif kind == "tiny sketch":
+        K, G = K * np.float32(2.0 ** 70), G * np.float32(2.0 ** -115)
+    else:
+        G[17, 3] = np.inf if kind == "infinite" else np.finfo(np.float32).max
+        K[..., 17] *= np.float32(2.0 ** -120)
+    with B.Context(heads, 1, 4, 128, r, "fp32", n, 1, "k") as ctx:
+        ctx.set_sketch(heads // 2, 0, G)
+        dK = torch.from_numpy(K).cuda()
+        raw, sums = torch.full((heads, n), float("nan"), device="cuda"), torch.zeros((heads,), dtype=torch.float64, device="cuda")
+        ctx.scores_append(dK, dK, n, 0, n, raw, sums)
+        got = raw[heads // 2].cpu().numpy()
+        ctx.set_sketch(heads // 2, 0, np.ones((128, r), np.float32))        # in range again
+        ctx.scores_append(dK, dK, n, 0, n, raw, sums)
+        ones = raw[heads // 2].cpu().numpy()
+    rows = K[heads // 2].astype(np.float64)
+    if kind == "infinite":
+        assert np.all(np.isposinf(got))
+    else:
+        want = ((rows @ G.astype(np.float64)) ** 2).sum(1)
+        assert np.all(np.abs(got - want) <= PLAIN_TOL * want)
+    if kind in ("infinite", "largest"):
+        want = r * rows.sum(1) ** 2
+        assert np.linalg.norm(ones - want) <= NORM_TOL * np.linalg.norm(want)
