@@ -364,9 +364,25 @@ constexpr int64_t kFewF32Tokens = 16384, kFewF32Steps = 6, kFewBf16Tokens = 8192
 // 26.4 and 23.0 (9), 256 of 128 23.2 and 21.4 (8), 16 of 3000 25.0 and 24.5 (12).  curdkv_scores_append: bf16, r = 20, 8 of 2048 8.5 and 7.1, r = 64 9.0 and
 // 8.1; fp32, r = 20, 8 of 2500 18.3 and 11.0.  Wider fp32 sketches would gain as much (r = 64, 8 of 2500 30.2 and 23.4), but the split products of the other kernel err
 // less than the plain ones here.
-struct FewLoad { int heads, load; };
-constexpr FewLoad kFewLoadBf16[3] = {{64, 6}, {32, 4}, {32, 3}};   // up to 32, 64 and 128 columns
-constexpr FewLoad kFewLoadF32 = {256, 10};                         // up to 32 columns
+// fp32 in more heads than half the units: where one tensor is scored, or a running sum is wanted, the other kernel's one workgroup a head ends sooner (and adds
+// the sum by itself): curdkv_scores_append, r = 20, 256 heads of 128 tokens, keys alone 8.2 and 12.4, 224 of 128 7.9 and 11.3, 200 of 160 8.6 and 11.1, both tensors 256 of 65
+// 11.6 and 13.6, 224 of 128 12.6 and 13.6; curdkv_scores, keys alone, 256 of 128 10.6 and 12.9, 200 of 160 10.3 and 11.5, but both tensors 16.4 and 14.5, 16.8 and 14.4; up to
+// 128 heads this one is ahead either way (128 of 160, keys alone, 8.5 and 7.0).
+constexpr int kFewHeadsBf16 = 64, kFewLoadBf16 = 6;              // up to 32 columns
+constexpr int kFewHeadsBf16Mid = 32, kFewLoadBf16Mid = 4;        // up to 64
+constexpr int kFewHeadsBf16Wide = 32, kFewLoadBf16Wide = 3;      // up to 128
+constexpr int kFewHeadsF32 = 256, kFewLoadF32 = 10;              // up to 32 columns
+
+static bool few_by_load(const curdkv_ctx* ctx, int64_t load, bool running) {
+    if (ctx->cfg.dtype == CURDKV_DTYPE_F32) {
+        if (ctx->col_blocks > 1 || load > kFewLoadF32) return false;
+        const bool one_less = running || ctx->cfg.score_source != CURDKV_SCORE_KV;
+        return ctx->heads <= (one_less ? ctx->num_cu / 2 : kFewHeadsF32);
+    }
+    if (ctx->col_blocks == 1) return ctx->heads <= kFewHeadsBf16 && load <= kFewLoadBf16;
+    if (ctx->col_blocks == 2) return ctx->heads <= kFewHeadsBf16Mid && load <= kFewLoadBf16Mid;
+    return ctx->heads <= kFewHeadsBf16Wide && load <= kFewLoadBf16Wide;
+}
 
 // running: a running sum is wanted (curdkv_scores_append).
 static bool few_tokens(const curdkv_ctx* ctx, int64_t n, bool running) {
@@ -375,10 +391,8 @@ static bool few_tokens(const curdkv_ctx* ctx, int64_t n, bool running) {
     const int64_t most = f32 ? kFewF32Tokens : kFewBf16Tokens / (ctx->heads > ctx->num_cu / 4 ? ctx->col_blocks : 1);
     const int64_t steps = (n + 15) / 16, blocks = few_blocks_per_head(ctx, n, running);
     if (n * ctx->heads > most || steps > (f32 ? kFewF32Steps : kFewBf16Steps) * blocks) {
-        if (f32 && ctx->col_blocks > 1) return false;
-        const FewLoad limit = f32 ? kFewLoadF32 : kFewLoadBf16[ctx->col_blocks == 1 ? 0 : ctx->col_blocks == 2 ? 1 : 2];
         const int64_t load = (steps + blocks - 1) / blocks * ((blocks * ctx->heads + ctx->num_cu - 1) / ctx->num_cu);
-        if (ctx->heads > limit.heads || load > limit.load) return false;
+        if (!few_by_load(ctx, load, running)) return false;
     }
     // bf16, two steps of a wide sketch: the other kernel's waves hold all of it and take 32 tokens at once.  8 heads, r = 20 /
     // 64 / 128, replayed graph: 32 tokens 3.6 -> 3.4 / 3.9 -> 4.3 / 4.7 -> 6.3, 16 tokens 3.5 -> 3.0 / 3.8 -> 3.5 / 4.5 -> 4.6, 8

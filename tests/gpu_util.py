@@ -38,6 +38,37 @@ def to_host(t, dtype: str) -> np.ndarray:
     return t.cpu().numpy()
 
 
+def launches(call):
+    """(kernel, template arguments, grid) of every launch that `call` makes, in order, from a captured graph of it: where a test has to
+    know which kernel ran.  Make the same call once before (no upload or allocation is captured)."""
+    import ctypes
+    import torch
+
+    class Node(ctypes.Structure):                       # hipKernelNodeParams
+        _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
+                    ("params", ctypes.c_void_p), ("shared", ctypes.c_uint)]
+
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    handle, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(handle, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(handle, nodes, ctypes.byref(count)) == 0
+    out = []
+    for node in nodes:
+        p = Node()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        name = hip.hipKernelNameRefByPtr(ctypes.c_void_p(p.func), None).decode()
+        found = re.match(r"_ZN6curdkv(\d+)", name)
+        assert found, name
+        end = found.end() + int(found.group(1))
+        out.append((name[found.end():end], tuple(int(x) for x in re.findall(r"L[a-z](\d+)E", name[end:])), tuple(p.grid)))
+    return out
+
+
 class Guarded:
     """A device buffer with canary elements before and after it: a kernel that writes outside
     the buffer it was given (an overrun past the last group, an offset gone negative) changes
