@@ -345,12 +345,18 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     // 717 / 785 / 813 / 855 / 924 / 1050; 16384 at 12 / 15 % 411 / 438 and 420 / 441; 12000 at 10 / 16 / 20 % 295 / 326 / 356 and 300 / 329 / 351; 8000 at
     // 15 / 25 % 216 / 252 and 221 / 253; 4096 at 20 / 30 / 40 % 122 / 142 / 161 and 126 / 142 / 157; 2048 at 20 / 50 / 80 % 71 / 94 / 118 and 79 / 103 / 126; 1000 at
     // 20 / 90 % 34 / 58 and 39 / 64; 300 at 50 % 18 and 23.
+    // Those are equal budgets.  A head that keeps more than the average copies its rows while other units are done, 8 to 17 us per 512 rows more.  Dirichlet budgets within
+    // layers of 8 heads, average and largest: 2048 tokens 102 / 444 61 and 65, 204 / 888 68 and 69, 409 / 1780 83 and 78, 614 / 2048 90 and 86; 1000 tokens 200 / 870 41.0 and 40.6; 3000 tokens
+    // 150 / 653 80 and 78, 600 / 2612 122 and 96; 6000 tokens 600 / 2612 179 and 159; 16384 tokens 819 / 3565 413 and 382, 1638 / 7131 483 and 406.
     const bool fusable = fused_applicable(ctx, n);
     const int64_t most_rows = n <= kFusedGatherTokens ? n : kFusedGatherRows + n * kFusedGatherPercent / 100;
-    const bool big_gather = total > ctx->heads * most_rows;
-    if (fusable && !big_gather)
+    const int64_t more_rows = max_budget - total / ctx->heads;
+    const bool big_gather = total > ctx->heads * most_rows || more_rows > (n <= kFusedGatherTokens ? kFusedUnevenRows : kFusedUnevenRowsLong);
+    const auto all_fused = [&] {
         return launch_fused(ctx, K, V, n, n_sink, ctx->plan.d_offsets, scores, indices, K_out, V_out, st) == hipSuccess
                    ? CURDKV_OK : CURDKV_ERR_HIP;
+    };
+    if (fusable && !big_gather) return all_fused();
     const bool scores_wanted = scores != nullptr;
     const bool together = !fusable && select_gather_applicable(ctx, n, total);
     const bool split = !fusable && !together && split_applicable(ctx, n, true), with_hist = split && split_counts_in_scan(ctx, n);
@@ -359,7 +365,7 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
             hipMalloc((void**)&ctx->d_scores_ws, (size_t)ctx->heads * (size_t)ctx->cfg.max_tokens * sizeof(float)) != hipSuccess) {
             (void)hipGetLastError();
             ctx->d_scores_ws = nullptr;
-            return CURDKV_ERR_OOM;
+            return fusable ? all_fused() : CURDKV_ERR_OOM;      // (the one kernel needs no scratch)
         }
         scores = ctx->d_scores_ws;
     }

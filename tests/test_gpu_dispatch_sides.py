@@ -150,3 +150,33 @@ def test_one_call_with_more_rows_than_the_split_gathers(dtype):
             ctx.compress(Kd, Vd, n, budgets, s, off, sc, ix, Ko, Vo)
             ctx.compress(Kd, Vd, n, budgets, s, off, None, ix2, Ko2, Vo2)
             assert torch.equal(ix, ix2) and torch.equal(Ko, Ko2) and torch.equal(Vo, Vo2)
+
+
+LONG_FROM = gu.limit("curdkv_internal.h", "kFusedGatherTokens")
+UNEVEN, UNEVEN_LONG = gu.limit("curdkv_internal.h", "kFusedUnevenRows"), gu.limit("curdkv_internal.h", "kFusedUnevenRowsLong")
+
+
+# budgets whose largest is a row beyond what one workgroup copies alone, and not; the average is within the fused kernel's limit in all
+@pytest.mark.parametrize("n,average,more,fused", [(LONG_FROM, 300, UNEVEN, True), (LONG_FROM, 300, UNEVEN + 1, False), (1111, 500, UNEVEN + 1, False), (700, 300, 400, True),
+                                                  (LONG_FROM + 1, 300, UNEVEN_LONG, True), (LONG_FROM + 1, 300, UNEVEN_LONG + 1, False)])
+def test_fused_gather_of_uneven_budgets(n, average, more, fused):
+    import torch
+    heads, s = torch.cuda.get_device_properties(0).multi_processor_count, 4
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    K = torch.randn((heads, n, 128), generator=g, device="cuda").to(torch.bfloat16)
+    V = (torch.randn((heads, n, 128), generator=g, device="cuda") * torch.randn((heads, n, 1), generator=g, device="cuda").exp()).to(torch.bfloat16)
+    budgets = np.full((heads,), average, np.int32)
+    budgets[5] += more
+    budgets[7] -= min(more, average)
+    budgets[9] -= more - min(more, average)                                # the average stays
+    with B.Context(1, heads, 4, 128, 64, "bf16", n, SEED) as ctx:
+        sc, ix, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, s, "bf16", one_call=True)
+        names = [name for name, _, _ in gu.launches(lambda: ctx.compress(K, V, n, budgets, s, off, sc, ix, Ko, Vo))]
+        torch.cuda.synchronize()
+    assert (names == ["fused_kernel"]) == fused and names[0] == "fused_kernel", names
+    sc, rows = sc.cpu().numpy().astype(np.float64), ix.long()
+    for h in (0, 5, 7, 9, heads - 1):
+        mine = slice(int(off[h]), int(off[h + 1]))
+        assert np.array_equal(rows[mine].cpu().numpy(), orc.select(sc[h], int(budgets[h]), s)), h
+        assert torch.equal(Ko[mine], K[h, rows[mine]]) and torch.equal(Vo[mine], V[h, rows[mine]]), h
