@@ -380,7 +380,7 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     // back), which saves the separate pass over the scores
     int bph = 0;
     if (launch_scores(ctx, K, V, n, together ? ctx->d_raw_ws : scores, st, /*normalise=*/false, &bph, 0, 0, nullptr, false, nullptr,
-                      with_hist, n_sink, /*kept=*/total) != hipSuccess) return CURDKV_ERR_HIP;
+                      with_hist, n_sink, /*kept=*/total, /*uneven=*/together && !even_budgets(ctx, max_budget, total)) != hipSuccess) return CURDKV_ERR_HIP;
     SelectGather gather{K, V, K_out, V_out, total, false};
     if (together)
         return launch_select_gather(ctx, ctx->d_raw_ws, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st, bph, gather) == hipSuccess

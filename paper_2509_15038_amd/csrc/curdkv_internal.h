@@ -88,10 +88,10 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
                          float* scores, hipStream_t stream, bool normalise = true,
                          int* blocks_per_head = nullptr, int64_t out_stride = 0, int64_t out_offset = 0,
                          double* sums = nullptr, bool restart = false, bool* summed = nullptr,
-                         bool with_hist = false, int32_t n_sink = 0, int64_t kept = 0);
+                         bool with_hist = false, int32_t n_sink = 0, int64_t kept = 0, bool uneven = false);
 // with_hist: every workgroup also leaves its counts of the products of tokens n_sink and up for the
 // split selection (split_select.hip), which must apply to n.
-// kept: rows that the call reads again to gather them.
+// kept: rows that the call reads again to gather them; uneven: by select_gather_kernel, from budgets that even_budgets refuses.
 // sums (device, [heads]) given: where one block scores a whole head, the kernel itself adds the
 // head's total to sums[head] (after zeroing it if `restart`) and *summed is set; otherwise the
 // caller adds the partial sums (launch_accumulate).

@@ -428,9 +428,15 @@ static int64_t scan_bytes(const curdkv_ctx* ctx, int64_t n) {
 
 static bool many_kept(const curdkv_ctx* ctx, int64_t n, int64_t kept) { return kept * 4 >= ctx->heads * n; }
 
-static bool stream_rows(const curdkv_ctx* ctx, int64_t n, int64_t kept) {
-    return ctx->cfg.dtype == CURDKV_DTYPE_BF16 &&
-           scan_bytes(ctx, n) > (many_kept(ctx, n, kept) ? kStreamBytesRereadMany : kept > 0 ? kStreamBytesReread : kStreamBytes);
+// Where select_gather_kernel gathers uneven budgets, its workgroups that copy the large one's rows wait longer for those that come from HBM: from 256 MB on, and
+// fp32 of one tensor, whose other tensor's rows come from there anyway, always.  One call, 20 % kept, caches and streamed, Dirichlet budgets within layers of 8: 112 heads
+// of 3487 tokens (200 MB) 68.0 and 74.6, 32 of 12207 74.1 and 77.4, 64 of 6103 in turn with writing them 136.7 and 146.9; one head of 8 with nearly all rows: 64 of 6103 68.9 and 76.2, of 7812
+// (256 MB) 86.6 and 95.7, 32 of 17700 (290 MB) 104.3 and 110.6 (240 MB and more behind 270 MB of other traffic are ahead streamed, Dirichlet budgets: 32 of 14648 106.9 and 93.2); fp32, r = 20, 112
+// of 1744 (200 MB) 75.0 and 82.6, 64 of 3052 75.6 and 80.9, 64 of 4090 (268 MB) 91.5 and 97.1, and behind other traffic 112.0 and 100.4.
+static bool stream_rows(const curdkv_ctx* ctx, int64_t n, int64_t kept, bool uneven) {
+    if (ctx->cfg.dtype == CURDKV_DTYPE_F32)
+        return ctx->col_blocks == 1 && f32_split(ctx, n) && !(uneven && ctx->cfg.score_source == CURDKV_SCORE_KV && scan_bytes(ctx, n) <= kStreamBytesRereadMany);
+    return scan_bytes(ctx, n) > (many_kept(ctx, n, kept) || uneven ? kStreamBytesRereadMany : kept > 0 ? kStreamBytesReread : kStreamBytes);
 }
 
 int stay_share(const curdkv_ctx* ctx, int64_t n, int64_t kept) {
@@ -447,10 +453,10 @@ hipError_t configure_kernels(curdkv_ctx* ctx) {
 hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n,
                          float* scores, hipStream_t stream, bool normalise, int* blocks_per_head,
                          int64_t out_stride, int64_t out_offset, double* sums, bool restart,
-                         bool* summed, bool with_hist, int32_t n_sink, int64_t kept) {
+                         bool* summed, bool with_hist, int32_t n_sink, int64_t kept, bool uneven) {
     if (out_stride <= 0) out_stride = n;
     const bool few = few_tokens(ctx, n, sums != nullptr) && !with_hist;
-    const bool stream_past = stream_rows(ctx, n, kept);
+    const bool stream_past = stream_rows(ctx, n, kept, uneven);
     const int bph = few ? few_blocks_per_head(ctx, n, sums != nullptr) : pick_blocks_per_head(ctx, n, stream_past, with_hist ? split_hists(ctx) : kMaxBlocksPerHead);
     if (blocks_per_head) *blocks_per_head = bph;
     if (bph != 1) sums = nullptr;                 // several blocks per head: the caller adds the partials
@@ -499,8 +505,12 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
             };
             if constexpr (CB > 2) launch_f32(std::true_type{}, std::false_type{});
             else if constexpr (PROJ) {
-                if (f32_split(ctx, n)) launch_f32(std::true_type{}, std::true_type{});
-                else launch_f32(std::false_type{}, std::false_type{});
+                const bool parts = f32_split(ctx, n);
+                if (parts && stream_past) launch_f32(std::true_type{}, std::true_type{});
+                else if constexpr (SRC == kSrcKV && !COUNT) {        // (stream_rows: parts that are not streamed are for select_gather_kernel)
+                    if (parts) launch_f32(std::true_type{}, std::false_type{});
+                    else launch_f32(std::false_type{}, std::false_type{});
+                } else launch_f32(std::false_type{}, std::false_type{});
             } else launch_f32(std::false_type{}, std::false_type{});
         }
     };

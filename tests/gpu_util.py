@@ -65,7 +65,8 @@ def launches(call):
         found = re.match(r"_ZN6curdkv(\d+)", name)
         assert found, name
         end = found.end() + int(found.group(1))
-        out.append((name[found.end():end], tuple(int(x) for x in re.findall(r"L[a-z](\d+)E", name[end:])), tuple(p.grid)))
+        values = re.match(r"I((?:L[a-z]\d+E)+)E", name[end:])
+        out.append((name[found.end():end], tuple(int(x) for x in re.findall(r"L[a-z](\d+)E", values.group(1))) if values else (), tuple(p.grid)))
     return out
 
 

@@ -92,3 +92,33 @@ def test_one_call(heads, n, r, keep, dtype):
         gu.check_scores(sc[i].cpu().numpy(), lt, str(i))
         gu.check_selection(rows.cpu().numpy().astype(np.int64), lt, int(budgets[i]), 4, str(i))
         assert torch.equal(Ko[off[i]:off[i + 1]], K[i][rows.long()]) and torch.equal(Vo[off[i]:off[i + 1]], V[i][rows.long()])
+
+
+# Budgets around what counts as even (the largest a quarter above the average), gathered by the selection kernel: rows past the caches from the lower limit
+# on where they are, with the heads along the grid's x, and from the upper one on where they are not, with the shares along x.  fp32 over the bf16 units both ways
+@pytest.mark.parametrize("heads,n,dtype", [(64, 6103, "bf16"), (64, 7900, "bf16"), (32, 9700, "bf16"), (112, 1744, "fp32"), (64, 4090, "fp32")])
+@pytest.mark.parametrize("more", [0, 1])
+def test_one_call_at_the_edge_of_even_budgets(heads, n, dtype, more):
+    import torch
+    average, s = 400, 4
+    bytes_read = heads * n * 128 * (2 if dtype == "bf16" else 4) * 2
+    K, V = _cache(heads, n, dtype, n)
+    budgets = np.full((heads,), average, np.int32)
+    budgets[3] += average // 4 + more
+    budgets[9] -= average // 4 + more
+    even = int(budgets.max()) * heads * 4 <= int(budgets.sum()) * 5
+    assert even == (more == 0)
+    with B.Context(heads, 1, 4, 128, 20, dtype, n, SEED) as ctx:
+        sc, ix, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, s, dtype, one_call=True)
+        scan, select = gu.launches(lambda: ctx.compress(K, V, n, budgets, s, off, sc, ix, Ko, Vo))
+    past = bytes_read > (LIMIT_REREAD if even else LIMIT_REREAD_MANY)
+    assert scan[:2] == (("scores_bf16_kernel", (2, 0, 1, 0, int(past))) if dtype == "bf16" else ("scores_f32_kernel", (2, 0, 1, 0, 1, int(even or past))))
+    assert select[0] == "select_gather_kernel"
+    if n > 2048:
+        assert (select[2][0] == heads) == even
+    for i in (0, 3, 9, heads - 1):
+        rows = ix[off[i]:off[i + 1]]
+        lt = _want(K, V, i, 20, dtype, "kv", True)
+        gu.check_scores(sc[i].cpu().numpy(), lt, str(i))
+        gu.check_selection(rows.cpu().numpy().astype(np.int64), lt, int(budgets[i]), s, str(i))
+        assert torch.equal(Ko[off[i]:off[i + 1]], K[i][rows.long()]) and torch.equal(Vo[off[i]:off[i + 1]], V[i][rows.long()])
