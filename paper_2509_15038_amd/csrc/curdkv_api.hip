@@ -282,7 +282,7 @@ int curdkv_scores(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, floa
     // all-zero offsets make it stop after the scores.
     if (fused_applicable(ctx, n))
         return launch_fused(ctx, K, V, n, 0, ctx->d_zero_offsets, scores, nullptr, nullptr, nullptr,
-                            (hipStream_t)stream) == hipSuccess ? CURDKV_OK : CURDKV_ERR_HIP;
+                            (hipStream_t)stream, /*kept=*/0) == hipSuccess ? CURDKV_OK : CURDKV_ERR_HIP;
     return launch_scores(ctx, K, V, n, scores, (hipStream_t)stream) == hipSuccess ? CURDKV_OK
                                                                                   : CURDKV_ERR_HIP;
 }
@@ -353,7 +353,7 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     const int64_t more_rows = max_budget - total / ctx->heads;
     const bool big_gather = total > ctx->heads * most_rows || more_rows > (n <= kFusedGatherTokens ? kFusedUnevenRows : kFusedUnevenRowsLong);
     const auto all_fused = [&] {
-        return launch_fused(ctx, K, V, n, n_sink, ctx->plan.d_offsets, scores, indices, K_out, V_out, st) == hipSuccess
+        return launch_fused(ctx, K, V, n, n_sink, ctx->plan.d_offsets, scores, indices, K_out, V_out, st, total) == hipSuccess
                    ? CURDKV_OK : CURDKV_ERR_HIP;
     };
     if (fusable && !big_gather) return all_fused();
@@ -370,7 +370,7 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
         scores = ctx->d_scores_ws;
     }
     if (fusable) {      // scores from the fused kernel's first phases, then select and gather kernels
-        if (launch_fused(ctx, K, V, n, 0, ctx->d_zero_offsets, scores, nullptr, nullptr, nullptr, st, nullptr, nullptr, stay_share(ctx, n, total)) != hipSuccess ||
+        if (launch_fused(ctx, K, V, n, 0, ctx->d_zero_offsets, scores, nullptr, nullptr, nullptr, st, total) != hipSuccess ||
             launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st) != hipSuccess ||
             launch_compact(ctx, K, V, n, indices, ctx->plan.d_offsets, total, K_out, V_out, st) != hipSuccess)
             return CURDKV_ERR_HIP;
@@ -464,7 +464,7 @@ int curdkv_compress_adaptive(curdkv_ctx* ctx, const void* K, const void* V, int6
     int bph = 0;
     const hipError_t e = fused
         ? launch_fused(ctx, K, V, n, n_sink, ctx->d_zero_offsets, scores, nullptr, nullptr, nullptr, st,
-                       adaptive_hist_buffer(ctx, ctx->d_adaptive_ws), adaptive_coarse_buffer(ctx, ctx->d_adaptive_ws), stay_share(ctx, n, total))
+                       total, adaptive_hist_buffer(ctx, ctx->d_adaptive_ws), adaptive_coarse_buffer(ctx, ctx->d_adaptive_ws))
         : launch_scores(ctx, K, V, n, scores, st, /*normalise=*/!allots, &bph, 0, 0, nullptr, false, nullptr, false, 0, /*kept=*/total);
     if (e != hipSuccess) return CURDKV_ERR_HIP;
     bool planned = false;

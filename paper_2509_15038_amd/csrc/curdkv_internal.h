@@ -95,6 +95,8 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
 // sums (device, [heads]) given: where one block scores a whole head, the kernel itself adds the
 // head's total to sums[head] (after zeroing it if `restart`) and *summed is set; otherwise the
 // caller adds the partial sums (launch_accumulate).
+int64_t scan_bytes(const curdkv_ctx* ctx, int64_t n);                  // that a scan of n tokens a head reads
+bool many_kept(const curdkv_ctx* ctx, int64_t n, int64_t kept);        // a quarter of the rows or more
 // In 256ths: how much of a scan, its end, should leave its rows in the caches for a gather of `kept` rows that follows.
 int stay_share(const curdkv_ctx* ctx, int64_t n, int64_t kept);
 hipError_t launch_accumulate(const curdkv_ctx* ctx, int blocks_per_head, double* sums, bool reset,
@@ -190,7 +192,8 @@ bool fused_applicable(const curdkv_ctx* ctx, int64_t n);
 // and its sums per exponent, for the head-wise budget allocation that follows it.
 hipError_t launch_fused(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n, int32_t n_sink,
                         const int64_t* d_offsets, float* scores, int32_t* indices, void* K_out,
-                        void* V_out, hipStream_t stream, uint32_t* hist_out = nullptr,
-                        uint32_t* coarse_out = nullptr, int stay = 0);
+                        void* V_out, hipStream_t stream, int64_t kept, uint32_t* hist_out = nullptr,
+                        uint32_t* coarse_out = nullptr);
+// kept: rows that the call gathers, by this kernel (indices given) or after it.
 
 }  // namespace curdkv

@@ -26,7 +26,7 @@ constexpr int kFusedThreads = 512;
 constexpr int kFusedWaves = kFusedThreads / 64;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-template <int CB, int KPT, int SRC, bool PROJ>
+template <int CB, int KPT, int SRC, bool PROJ, int MODE>
 __global__ __launch_bounds__(kFusedThreads, 2) void fused_kernel(
     const uint4* __restrict__ K, const uint4* __restrict__ V, const uint4* __restrict__ Gp,
     int32_t n, int32_t n_sink, const int64_t* __restrict__ offsets, float* __restrict__ scores_out,
@@ -51,9 +51,7 @@ __global__ __launch_bounds__(kFusedThreads, 2) void fused_kernel(
         per_wave += per_wave & 1;                  // whole pairs
         const int32_t t_begin = wave * per_wave;
         const int32_t t_end = t_begin + per_wave < tiles ? t_begin + per_wave : tiles;
-        // more than 2048 tokens a head are more rows than the caches hold (fetch in scan_device.h): 256 heads of 2048 tokens (268 MB), a tenth
-        // kept, 63.2 us either way, of 4096, a fifth, 134.6 and streamed 126.5, of 32768, a tenth, 863 and 781; of 1024 33.8 and 35.0
-        acc = scan_tiles<CB, SRC, PROJ, false, (KPT > 4 ? kStreamStay : kStreamNone)>(G, Kh, Vh, n, t_begin, t_end, sc, 0, lane, scan_phase(head, wave), nullptr, 0, stay_tile(t_begin, t_end, stay));
+        acc = scan_tiles<CB, SRC, PROJ, false, MODE>(G, Kh, Vh, n, t_begin, t_end, sc, 0, lane, scan_phase(head, wave), nullptr, 0, stay_tile(t_begin, t_end, stay));
     }
     // ---- 2. sum over the head ----------------------------------------------------------
     acc = wave_sum(acc);
@@ -140,27 +138,41 @@ struct FusedArgs {
     uint32_t* coarse_out;
     hipStream_t stream;
     int stay;                // stay_share
+    bool past;               // rows past the caches (streams_fused)
     int dyn;                 // >= 0: only raise the kernel's dynamic LDS limit to this, no launch
 };
 
-template <int CB, int KPT, int SRC, bool PROJ>
+template <int CB, int KPT, int SRC, bool PROJ, int MODE>
 static hipError_t one(const FusedArgs& a) {
     if (a.dyn >= 0)
-        return hipFuncSetAttribute((const void*)fused_kernel<CB, KPT, SRC, PROJ>,
+        return hipFuncSetAttribute((const void*)fused_kernel<CB, KPT, SRC, PROJ, MODE>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, a.dyn);
     const size_t lds = (((size_t)a.n + 63) & ~(size_t)63) * 4;
-    fused_kernel<CB, KPT, SRC, PROJ><<<dim3((unsigned)a.ctx->heads), kFusedThreads, lds, a.stream>>>(
+    fused_kernel<CB, KPT, SRC, PROJ, MODE><<<dim3((unsigned)a.ctx->heads), kFusedThreads, lds, a.stream>>>(
         (const uint4*)a.K, (const uint4*)a.V, (const uint4*)a.ctx->d_G, a.n, a.n_sink, a.d_offsets,
         a.scores, a.indices, (u32x4*)a.K_out, (u32x4*)a.V_out, a.hist_out, a.coarse_out, a.stay);
     return hipGetLastError();
 }
 
+// 512 * KPT tokens a head and fewer: up to 2048 never past the caches, from 4097 on always (streams_fused), between them either where one tensor is scored
+template <int CB, int KPT, int SRC, bool PROJ>
+static hipError_t by_mode(const FusedArgs& a) {
+    if constexpr (KPT <= 4) return one<CB, KPT, SRC, PROJ, kStreamNone>(a);
+    else if constexpr (KPT == 8 && SRC != kSrcKV) {
+        if (a.dyn >= 0) {
+            const hipError_t e = one<CB, KPT, SRC, PROJ, kStreamNone>(a);
+            if (e != hipSuccess) return e;
+        } else if (!a.past) return one<CB, KPT, SRC, PROJ, kStreamNone>(a);
+    }
+    return one<CB, KPT, SRC, PROJ, kStreamStay>(a);
+}
+
 template <int CB, int KPT, bool PROJ>
 static hipError_t by_source(const FusedArgs& a, int source) {
     switch (source) {
-        case CURDKV_SCORE_KEY: return one<CB, KPT, kSrcK, PROJ>(a);
-        case CURDKV_SCORE_VALUE: return one<CB, KPT, kSrcV, PROJ>(a);
-        default: return one<CB, KPT, kSrcKV, PROJ>(a);
+        case CURDKV_SCORE_KEY: return by_mode<CB, KPT, kSrcK, PROJ>(a);
+        case CURDKV_SCORE_VALUE: return by_mode<CB, KPT, kSrcV, PROJ>(a);
+        default: return by_mode<CB, KPT, kSrcKV, PROJ>(a);
     }
 }
 
@@ -220,11 +232,22 @@ bool fused_applicable(const curdkv_ctx* ctx, int64_t n) {
     return (int64_t)ctx->heads * 10 >= rounds * ctx->num_cu * 9;
 }
 
+// More than 2048 tokens a head are more rows than the caches hold (fetch in scan_device.h), us, kept in the caches and streamed: 256 heads of 2048 tokens (268 MB), a tenth
+// kept, 63.2 either way, of 4096, a fifth, 134.6 and 126.5, of 32768, a tenth, 863 and 781; of 1024 33.8 and 35.0.  One tensor, half as many bytes: keys alone, a twentieth
+// kept, 2049 tokens (134 MB) 37.1 and 34.8, 3000 49.2 and 45.1; but where a quarter or more is kept, up to 180 MB, half and four fifths of 2049 74.2 and 78.0, 95.9 and 100.0, values alone 74.2 and
+// 78.6, 93.9 and 100.1, of 2600 (170 MB) 90.2 and 92.4, 116.8 and 122.6; of 3000 (197 MB) 105.6 and 103.4, 134.6 and 138.7, of 3900 keys alone 135.4 and 129.5, 180.6 and 173.8.
+constexpr int64_t kFusedStreamBytesMany = 180000000;
+
+static bool streams_fused(const curdkv_ctx* ctx, int64_t n, int64_t kept) {
+    return !many_kept(ctx, n, kept) || scan_bytes(ctx, n) > kFusedStreamBytesMany;
+}
+
 hipError_t launch_fused(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n, int32_t n_sink,
                         const int64_t* d_offsets, float* scores, int32_t* indices, void* K_out,
-                        void* V_out, hipStream_t stream, uint32_t* hist_out, uint32_t* coarse_out, int stay) {
+                        void* V_out, hipStream_t stream, int64_t kept, uint32_t* hist_out, uint32_t* coarse_out) {
     if (!coarse_out) hist_out = nullptr;           // the two go together
-    FusedArgs a{ctx, K, V, (int32_t)n, n_sink, d_offsets, scores, indices, K_out, V_out, hist_out, coarse_out, stream, stay, -1};
+    const int stay = indices ? 0 : stay_share(ctx, n, kept);
+    FusedArgs a{ctx, K, V, (int32_t)n, n_sink, d_offsets, scores, indices, K_out, V_out, hist_out, coarse_out, stream, stay, streams_fused(ctx, n, kept), -1};
     return dispatch(a, ctx->col_blocks, keys_per_thread(n), ctx->cfg.score_source, !ctx->cfg.no_projection);
 }
 

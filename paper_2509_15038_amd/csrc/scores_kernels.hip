@@ -422,11 +422,11 @@ constexpr int64_t kStreamBytes = 120000000, kStreamBytesReread = 160000000, kStr
 // 93.5, 94.4, 95.8 (95.3); in bf16 three tenths are level (32 of 16384 87.5 and 87.4).
 constexpr int64_t kStayBytes = 128000000;
 
-static int64_t scan_bytes(const curdkv_ctx* ctx, int64_t n) {
+int64_t scan_bytes(const curdkv_ctx* ctx, int64_t n) {
     return ctx->heads * n * kHeadDim * (ctx->cfg.dtype == CURDKV_DTYPE_BF16 ? 2 : 4) * (ctx->cfg.score_source == CURDKV_SCORE_KV ? 2 : 1);
 }
 
-static bool many_kept(const curdkv_ctx* ctx, int64_t n, int64_t kept) { return kept * 4 >= ctx->heads * n; }
+bool many_kept(const curdkv_ctx* ctx, int64_t n, int64_t kept) { return kept * 4 >= ctx->heads * n; }
 
 // Where select_gather_kernel gathers uneven budgets, its workgroups that copy the large one's rows wait longer for those that come from HBM: from 256 MB on, and
 // fp32 of one tensor, whose other tensor's rows come from there anyway, always.  One call, 20 % kept, caches and streamed, Dirichlet budgets within layers of 8: 112 heads

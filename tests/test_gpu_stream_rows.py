@@ -122,3 +122,38 @@ def test_one_call_at_the_edge_of_even_budgets(heads, n, dtype, more):
         gu.check_scores(sc[i].cpu().numpy(), lt, str(i))
         gu.check_selection(rows.cpu().numpy().astype(np.int64), lt, int(budgets[i]), s, str(i))
         assert torch.equal(Ko[off[i]:off[i + 1]], K[i][rows.long()]) and torch.equal(Vo[off[i]:off[i + 1]], V[i][rows.long()])
+
+
+FUSED_MANY = gu.limit("fused_kernel.hip", "kFusedStreamBytesMany")
+
+
+# one tensor scored, one workgroup a head: few rows kept are streamed from 2049 tokens on, a quarter and more from a number of bytes on; gathered by the
+# same kernel, by kernels of their own, and after budgets allotted on the device
+@pytest.mark.parametrize("source,r,projection", [("k", 64, True), ("v", 20, True), ("v", 64, False)])
+@pytest.mark.parametrize("tokens,keep", [("first", 0.1), ("first", 0.3), ("first", 0.5), ("last", 0.5), ("more", 0.5)])
+def test_one_tensor_by_one_workgroup_a_head(source, r, projection, tokens, keep):
+    import torch
+    heads, s = torch.cuda.get_device_properties(0).multi_processor_count, 4
+    last = FUSED_MANY // (heads * 256)
+    n = {"first": 2049, "last": last, "more": last + 1}[tokens]
+    K, V = _cache(heads, n, "bf16", n + r)
+    budgets = np.full((heads,), int(np.ceil(keep * n)), np.int32)
+    with B.Context(heads, 1, 4, 128, r, "bf16", n, SEED, source, projection) as ctx:
+        sc, ix, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, s, "bf16", one_call=True)
+        scan = gu.launches(lambda: ctx.compress(K, V, n, budgets, s, off, sc, ix, Ko, Vo))[0]
+        torch.cuda.synchronize()
+        args = (4 if r > 32 and projection else 2, 8, 1 if source == "k" else 2, int(projection), 2 if keep < 0.25 or tokens == "more" else 0)
+        assert scan[:2] == ("fused_kernel", args), scan
+        bo, oo = torch.empty((heads,), dtype=torch.int32, device="cuda"), torch.empty((heads + 1,), dtype=torch.int64, device="cuda")
+        sc2, ix2, Ko2, Vo2 = torch.full_like(sc, float("nan")), torch.empty_like(ix), torch.empty_like(Ko), torch.empty_like(Vo)
+        call = lambda: ctx.compress_adaptive(K, V, n, int(budgets[0]), s, 0.2, sc2, bo, oo, ix2, Ko2, Vo2)
+        call()
+        assert gu.launches(call)[0][:2] == scan[:2]
+        torch.cuda.synchronize()
+    assert torch.equal(sc, sc2) and torch.equal(ix, ix2) and torch.equal(Ko, Ko2) and torch.equal(Vo, Vo2)      # (one head a layer: its budget is the layer's)
+    for i in (0, heads // 2, heads - 1):
+        rows = ix[off[i]:off[i + 1]]
+        lt = _want(K, V, i, r, "bf16", source, projection)
+        gu.check_scores(sc[i].cpu().numpy(), lt, str(i))
+        gu.check_selection(rows.cpu().numpy().astype(np.int64), lt, int(budgets[i]), s, str(i))
+        assert torch.equal(Ko[off[i]:off[i + 1]], K[i][rows.long()]) and torch.equal(Vo[off[i]:off[i + 1]], V[i][rows.long()])
