@@ -528,8 +528,10 @@ static hipError_t launch_gather(const curdkv_ctx* ctx, const float* raw, float* 
     // Workgroups are dealt to the eight XCDs one by one: with the heads along x, those of a head, which all read the same products, meet in one L2
     // (heads in eights; in two for fours).  One call, us, before and after: 32 heads of 32768 tokens 121.6 and 119.0, 16 of 20000 46.1 and 44.7, 8 of 8192 17.8
     // and 17.7.  Up to 2048 tokens, where there is little to fetch, shares along x are better: 16 heads of 863 tokens 13.4 and 13.7, 128 of 950 in fp32 49.3 and
-    // 49.9; and where the budgets are uneven, as a large one's rows would go through one XCD (even_budgets).
-    const bool heads_x = KPT > 2 && even_budgets(ctx, max_budget, g.total);
+    // 49.9; and where the budgets are uneven, as a large one's rows would go through one XCD (even_budgets); and up to 8192 tokens, where many rows are kept, whose copying weighs
+    // more than the products: half kept, r = 20, shares and heads along x, 16 heads of 4096 tokens 17.7 and 18.9, 8 of 8192 18.7 and 20.0, 24 of 2500 17.1 and 18.1, 32 of 4096 27.8 and 29.1 (a fifth: 16.1
+    // and 16.1, 17.1 and 17.1, 22.5 and 22.7), of 20000 8 heads 37.9 and 37.7.
+    const bool heads_x = KPT > 2 && even_budgets(ctx, max_budget, g.total) && (KPT > 8 || !many_kept(ctx, n, g.total));
     const dim3 grid = heads_x ? dim3((unsigned)ctx->heads, (unsigned)shares) : dim3((unsigned)shares, (unsigned)ctx->heads);
     select_gather_kernel<KPT, ROW_U4><<<grid, kSelThreads, (size_t)n * 4, stream>>>(
         raw, scores, n, n_sink, d_offsets, indices, ctx->d_partial, scale_blocks, (int)share, ga, known, heads_x ? 1 : 0);

@@ -162,3 +162,20 @@ def test_captured(heads, n):
             for a, b in zip(kept, eager):
                 assert torch.equal(a, b), seed
             assert torch.equal(kept[1], kept[4]), seed
+
+
+# the heads along x, so that a head's workgroups meet in one L2, from 2049 tokens on, and up to 8192 only where fewer than a quarter of the rows are kept
+@pytest.mark.parametrize("heads,n,budget,heads_x", [(12, 2048, 400, False), (12, 2049, 400, True), (12, 4096, 1023, True), (12, 4096, 1024, False), (5, 8192, 4000, False), (5, 8193, 4000, True)])
+def test_order_of_the_grid(heads, n, budget, heads_x):
+    import torch
+    budgets = np.full((heads,), budget, np.int32)
+    K, V = _cache(heads, n, "bf16", 4)
+    with B.Context(1, heads, 4, 128, 20, "bf16", n, 77) as ctx:
+        sc, idx, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, 4, "bf16", one_call=True)
+        name, _, grid = gu.launches(lambda: ctx.compress(K, V, n, budgets, 4, off, sc, idx, Ko, Vo))[-1]
+    assert name == "select_gather_kernel" and grid[1 - heads_x] == heads and grid[int(heads_x)] != heads, grid
+    where = idx.long()
+    for h in range(heads):
+        mine = slice(int(off[h]), int(off[h + 1]))
+        assert np.array_equal(where[mine].cpu().numpy(), orc.select(sc[h].cpu().numpy().astype(np.float64), budget, 4)), h
+        assert torch.equal(Ko[mine], K[0, h, where[mine]]) and torch.equal(Vo[mine], V[0, h, where[mine]]), h
