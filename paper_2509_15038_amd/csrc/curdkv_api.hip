@@ -305,7 +305,7 @@ int curdkv_select(curdkv_ctx* ctx, const float* scores, int64_t n, const int32_t
     if (rc != CURDKV_OK) return rc;
     if (total == 0) return CURDKV_OK;
     if (!indices) return CURDKV_ERR_INVALID_ARG;
-    return launch_select(ctx, const_cast<float*>(scores), n, n_sink, ctx->plan.d_offsets, max_budget, indices,
+    return launch_select(ctx, const_cast<float*>(scores), n, n_sink, ctx->plan.d_offsets, max_budget, total, indices,
                          (hipStream_t)stream) == hipSuccess
                ? CURDKV_OK : CURDKV_ERR_HIP;
 }
@@ -371,7 +371,7 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     }
     if (fusable) {      // scores from the fused kernel's first phases, then select and gather kernels
         if (launch_fused(ctx, K, V, n, 0, ctx->d_zero_offsets, scores, nullptr, nullptr, nullptr, st, total) != hipSuccess ||
-            launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st) != hipSuccess ||
+            launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, max_budget, total, indices, st) != hipSuccess ||
             launch_compact(ctx, K, V, n, indices, ctx->plan.d_offsets, total, K_out, V_out, st) != hipSuccess)
             return CURDKV_ERR_HIP;
         return CURDKV_OK;
@@ -385,7 +385,7 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     if (together)
         return launch_select_gather(ctx, ctx->d_raw_ws, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st, bph, gather) == hipSuccess
                    ? CURDKV_OK : CURDKV_ERR_HIP;
-    if (launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, max_budget, indices, st, bph, scores_wanted, nullptr, &gather,
+    if (launch_select(ctx, scores, n, n_sink, ctx->plan.d_offsets, max_budget, total, indices, st, bph, scores_wanted, nullptr, &gather,
                       with_hist ? bph : 0) != hipSuccess)
         return CURDKV_ERR_HIP;
     if (total == 0 || gather.done) return CURDKV_OK;
@@ -480,7 +480,7 @@ int curdkv_compress_adaptive(curdkv_ctx* ctx, const void* K, const void* V, int6
     if (select_gather_applicable(ctx, n, total))
         return launch_select_gather(ctx, scores, nullptr, n, n_sink, offsets_out, /*max_budget=*/-1, indices, st, 0, gather, known) == hipSuccess
                    ? CURDKV_OK : CURDKV_ERR_HIP;
-    if (launch_select(ctx, scores, n, n_sink, offsets_out, /*max_budget=*/-1, indices, st, 0, true, known, &gather) != hipSuccess)
+    if (launch_select(ctx, scores, n, n_sink, offsets_out, /*max_budget=*/-1, total, indices, st, 0, true, known, &gather) != hipSuccess)
         return CURDKV_ERR_HIP;
     if (gather.done) return CURDKV_OK;
     return launch_compact(ctx, K, V, n, indices, offsets_out, total, K_out, V_out, st, ctx->d_adaptive_blocks) == hipSuccess

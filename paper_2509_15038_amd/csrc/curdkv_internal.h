@@ -110,7 +110,7 @@ hipError_t launch_fold(const curdkv_ctx* ctx, const float* scores_q, int64_t n, 
 // result and writes it back, which is what normalisation followed by selection gives
 // (write_scaled = false: selects on the divided values but leaves `scores` as they are, for
 // callers that do not want the scores).
-// max_budget: the largest of the heads' budgets; negative: they exist on the device only.
+// max_budget: the largest of the heads' budgets; negative: they exist on the device only.  total: their sum.
 // known_thresholds (device, one {key, need} pair per head as the budget allocation leaves them,
 // adaptive_thresholds): heads whose entry is valid skip the search for their threshold.
 // gather given: the selection may copy the kept rows itself; gather->done says whether it has.
@@ -121,11 +121,11 @@ struct SelectGather {
     int64_t total;                     // rows kept, all heads
     bool done;
 };
-// The largest budget is at most a quarter above the average (max_budget < 0: not known).  Otherwise the workgroups that gather a head's rows are spread over
+// The largest budget is at most a quarter above the average (max_budget < 0: not known).  Otherwise the workgroups that gather or list a head's rows are spread over
 // all XCDs: 4 heads of 99162 tokens, half kept, Dirichlet budgets, split_emit_kernel 39.2 us so, 50.5 with two XCDs a head.
 inline bool even_budgets(const curdkv_ctx* ctx, int64_t max_budget, int64_t total) { return max_budget >= 0 && max_budget * ctx->heads * 4 <= total * 5; }
 hipError_t launch_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
-                         const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
+                         const int64_t* d_offsets, int64_t max_budget, int64_t total, int32_t* indices, hipStream_t stream,
                          int scale_blocks = 0, bool write_scaled = true,
                          const void* known_thresholds = nullptr, SelectGather* gather = nullptr, int hists = 0);
 // Few, short heads, one call: selection and gather in one launch.  `raw`: the un-normalised products (ctx->d_raw_ws);
@@ -146,7 +146,7 @@ uint32_t* split_hist(const curdkv_ctx* ctx);           // [heads][split_hists][2
 uint32_t* split_coarse(const curdkv_ctx* ctx);         // [heads][split_hists][256]
 constexpr int kSplitMaxHeads = 128;                    // (layer, group) pairs the split is used for (its workspace takes 9 KB per histogram, 64 per pair up to 32 pairs and 32 beyond, and 32 KB of bitmaps at most: 0.62 or 0.33 MB a pair)
 hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
-                               const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
+                               const int64_t* d_offsets, int64_t max_budget, int64_t total, int32_t* indices, hipStream_t stream,
                                int scale_blocks, bool write_scaled, const void* known_thresholds, SelectGather* gather, int hists);
 bool split_counts_in_scan(const curdkv_ctx* ctx, int64_t n);      // one call: the histograms are launch_scores' to make
 hipError_t launch_compact(const curdkv_ctx* ctx, const void* K, const void* V, int64_t n,

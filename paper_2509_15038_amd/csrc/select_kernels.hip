@@ -581,13 +581,13 @@ hipError_t launch_select_gather(const curdkv_ctx* ctx, const float* raw, float* 
 }
 
 hipError_t launch_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
-                         const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
+                         const int64_t* d_offsets, int64_t max_budget, int64_t total, int32_t* indices, hipStream_t stream,
                          int scale_blocks, bool write_scaled, const void* known_thresholds, SelectGather* gather, int hists) {
     const Threshold* known = static_cast<const Threshold*>(known_thresholds);
     const int32_t n32 = (int32_t)n;
     const int ws = write_scaled ? 1 : 0;
     if (split_applicable(ctx, n, scale_blocks > 0))
-        return launch_split_select(ctx, scores, n, n_sink, d_offsets, max_budget, indices, stream, scale_blocks, write_scaled, known_thresholds, gather, hists);
+        return launch_split_select(ctx, scores, n, n_sink, d_offsets, max_budget, total, indices, stream, scale_blocks, write_scaled, known_thresholds, gather, hists);
     if (n <= 32 * kSelThreads)
         return by_keys_per_thread(n, [&](auto kpt) {
             return launch_reg<decltype(kpt)::value>(ctx, scores, n32, n_sink, d_offsets, indices, stream, scale_blocks, ws, known);

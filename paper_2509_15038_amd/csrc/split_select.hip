@@ -659,7 +659,7 @@ uint32_t* split_coarse(const curdkv_ctx* ctx) { return carve(ctx).coarse; }
 static bool emit_gathers(const curdkv_ctx* ctx, int64_t total) { return total <= (int64_t)ctx->num_cu * 1024; }
 
 hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, int32_t n_sink,
-                               const int64_t* d_offsets, int64_t max_budget, int32_t* indices, hipStream_t stream,
+                               const int64_t* d_offsets, int64_t max_budget, int64_t total, int32_t* indices, hipStream_t stream,
                                int scale_blocks, bool write_scaled, const void* known_thresholds, SelectGather* gather, int hists) {
     SplitArgs a{carve(ctx), scores, (int32_t)n, n_sink, d_offsets, ctx->d_partial, scale_blocks, write_scaled ? 1 : 0, 0, hists,
                 static_cast<const Threshold*>(known_thresholds)};
@@ -695,7 +695,9 @@ hipError_t launch_split_select(const curdkv_ctx* ctx, float* scores, int64_t n, 
         shares = (ctx->num_cu * (with_gather ? 2 : 1) + ctx->heads - 1) / ctx->heads;
         share = 0;
     }
-    const bool heads_x = !with_gather || even_budgets(ctx, max_budget, gather->total);    // as in launch_gather (select_kernels.hip)
+    // As in launch_gather (select_kernels.hip).  Lists alone: where heads of one XCD have the large budgets, half kept, one head of 8 with all rows, us, shares and heads along x, 32 heads
+    // of 109334 tokens 28.2 and 36.5, 128 of 65536 48.0 and 56.9, 16 of 131072 21.4 and 25.0; equal budgets, over 36 sizes, heads along x 5 % ahead.
+    const bool heads_x = even_budgets(ctx, max_budget, total);
     const unsigned each = (unsigned)(shares > 0 ? shares : 1);
     const dim3 grid = heads_x ? dim3((unsigned)ctx->heads, each) : dim3(each, (unsigned)ctx->heads);
     GatherArgs ga{};

@@ -209,3 +209,28 @@ def test_sum_too_small_to_divide_by(heads, n, dtype):
         ctx.scores(K, V, n, sc)
         for x in (two, sc):
             assert bool(torch.isfinite(x[:2]).all()) and int(torch.count_nonzero(x[:2])) == 200
+
+
+# the heads along the grid's x where the budgets are even, the largest at most a quarter above the average; lists alone, and with the rows
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("one_call", [False, True])
+def test_order_of_the_grid(more, one_call):
+    import torch
+    heads, n, average = 6, 40000, 4000
+    budgets = np.full((heads,), average, np.int32)
+    budgets[2] += average // 4 + more
+    budgets[3] -= average // 4 + more
+    g = torch.Generator(device="cuda")
+    g.manual_seed(more)
+    K, V = (torch.randn((1, heads, n, 128), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    with B.Context(1, heads, 4, 128, 20, "bf16", n, 3) as ctx:
+        sc, idx, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, 4, "bf16", one_call=one_call)
+        call = (lambda: ctx.compress(K, V, n, budgets, 4, off, sc, idx, Ko, Vo)) if one_call else (lambda: ctx.select(sc, n, budgets, 4, off, idx))
+        name, args, grid = gu.launches(call)[-1]
+        torch.cuda.synchronize()
+    assert name == "split_emit_kernel" and args[0] == (16 if one_call else 0) and (grid[0] == heads) == (more == 0) and heads in grid, (name, args, grid)
+    where = idx.long()
+    for h in range(heads):
+        mine = slice(int(off[h]), int(off[h + 1]))
+        assert np.array_equal(where[mine].cpu().numpy(), orc.select(sc[h].cpu().numpy().astype(np.float64), int(budgets[h]), 4)), h
+        assert torch.equal(Ko[mine], K[0, h, where[mine]]) and torch.equal(Vo[mine], V[0, h, where[mine]]), h
