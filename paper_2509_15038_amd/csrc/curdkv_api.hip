@@ -347,11 +347,13 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     // 20 / 90 % 34 / 58 and 39 / 64; 300 at 50 % 18 and 23.
     // Those are equal budgets.  A head that keeps more than the average copies its rows while other units are done, 8 to 17 us per 512 rows more.  Dirichlet budgets within
     // layers of 8 heads, average and largest: 2048 tokens 102 / 444 61 and 65, 204 / 888 68 and 69, 409 / 1780 83 and 78, 614 / 2048 90 and 86; 1000 tokens 200 / 870 41.0 and 40.6; 3000 tokens
-    // 150 / 653 80 and 78, 600 / 2612 122 and 96; 6000 tokens 600 / 2612 179 and 159; 16384 tokens 819 / 3565 413 and 382, 1638 / 7131 483 and 406.
+    // 150 / 653 80 and 78, 600 / 2612 122 and 96; 6000 tokens 600 / 2612 179 and 159; 16384 tokens 819 / 3565 413 and 382, 1638 / 7131 483 and 406.  In
+    // several rounds a unit can meet two such heads, or none: 512 heads of 1000 tokens, one head of 8 with nearly all rows, 200 / 1000 87.8 and 75.7, 500 / 1000 110 and 98, of 700 350 / 700 80 and 72, of 512 256 / 512 58 and 55, but Dirichlet budgets 71 and 72 and 49 and 55.
     const bool fusable = fused_applicable(ctx, n);
     const int64_t most_rows = n <= kFusedGatherTokens ? n : kFusedGatherRows + n * kFusedGatherPercent / 100;
     const int64_t more_rows = max_budget - total / ctx->heads;
-    const bool big_gather = total > ctx->heads * most_rows || more_rows > (n <= kFusedGatherTokens ? kFusedUnevenRows : kFusedUnevenRowsLong);
+    const int64_t most_more = ctx->heads > ctx->num_cu ? kFusedUnevenRowsRounds : n <= kFusedGatherTokens ? kFusedUnevenRows : kFusedUnevenRowsLong;
+    const bool big_gather = total > ctx->heads * most_rows || more_rows > most_more;
     const auto all_fused = [&] {
         return launch_fused(ctx, K, V, n, n_sink, ctx->plan.d_offsets, scores, indices, K_out, V_out, st, total) == hipSuccess
                    ? CURDKV_OK : CURDKV_ERR_HIP;

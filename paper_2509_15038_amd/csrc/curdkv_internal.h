@@ -18,7 +18,7 @@ constexpr int kTileTokens = 32;        // tokens per wave tile
 constexpr int kCompactRowsPerBlock = 128;  // output rows per entry of the gather's table of heads
 constexpr int kFusedGatherTokens = 2048;       // curdkv_compress: heads up to which the fused kernel also gathers, whatever is kept on average,
 constexpr int kFusedGatherRows = 800, kFusedGatherPercent = 9;   // longer ones: up to so many rows kept, and so much of the head more;
-constexpr int kFusedUnevenRows = 512, kFusedUnevenRowsLong = 256;    // and a head at most so many more than the average
+constexpr int kFusedUnevenRows = 512, kFusedUnevenRowsLong = 256, kFusedUnevenRowsRounds = 384;    // and a head at most so many more than the average (Rounds: more heads than units)
 
 struct BlockInfo {                     // for gather block b, whose first output row is b*128:
     int64_t head_end;                  //   offsets[head + 1]

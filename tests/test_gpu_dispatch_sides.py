@@ -153,15 +153,16 @@ def test_one_call_with_more_rows_than_the_split_gathers(dtype):
 
 
 LONG_FROM = gu.limit("curdkv_internal.h", "kFusedGatherTokens")
-UNEVEN, UNEVEN_LONG = gu.limit("curdkv_internal.h", "kFusedUnevenRows"), gu.limit("curdkv_internal.h", "kFusedUnevenRowsLong")
+UNEVEN, UNEVEN_LONG, UNEVEN_ROUNDS = (gu.limit("curdkv_internal.h", "kFusedUnevenRows" + which) for which in ("", "Long", "Rounds"))
 
 
 # budgets whose largest is a row beyond what one workgroup copies alone, and not; the average is within the fused kernel's limit in all
-@pytest.mark.parametrize("n,average,more,fused", [(LONG_FROM, 300, UNEVEN, True), (LONG_FROM, 300, UNEVEN + 1, False), (1111, 500, UNEVEN + 1, False), (700, 300, 400, True),
-                                                  (LONG_FROM + 1, 300, UNEVEN_LONG, True), (LONG_FROM + 1, 300, UNEVEN_LONG + 1, False)])
-def test_fused_gather_of_uneven_budgets(n, average, more, fused):
+@pytest.mark.parametrize("rounds,n,average,more,fused", [(1, LONG_FROM, 300, UNEVEN, True), (1, LONG_FROM, 300, UNEVEN + 1, False), (1, 1111, 500, UNEVEN + 1, False), (1, 700, 300, 400, True),
+                                                         (1, LONG_FROM + 1, 300, UNEVEN_LONG, True), (1, LONG_FROM + 1, 300, UNEVEN_LONG + 1, False),
+                                                         (2, 801, 390, UNEVEN_ROUNDS, True), (2, 801, 390, UNEVEN_ROUNDS + 1, False)])
+def test_fused_gather_of_uneven_budgets(rounds, n, average, more, fused):
     import torch
-    heads, s = torch.cuda.get_device_properties(0).multi_processor_count, 4
+    heads, s = rounds * torch.cuda.get_device_properties(0).multi_processor_count, 4
     g = torch.Generator(device="cuda")
     g.manual_seed(n)
     K = torch.randn((heads, n, 128), generator=g, device="cuda").to(torch.bfloat16)
