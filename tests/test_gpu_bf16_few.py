@@ -1,6 +1,6 @@
 """bf16 calls of few tokens in all: workgroups of 16 tokens whose waves share the products.  Scores and
 running sums against the float64 oracle at the edges of the 16-token steps, with one step and several
-per workgroup, and on both sides of the lines where the kernel of longer calls takes over."""
+per workgroup, and around the lines where the kernel of longer calls takes over."""
 import numpy as np
 import pytest
 
@@ -15,8 +15,8 @@ SEED = 0xC0DE0011
 NORM_TOL = 1e-6
 
 
-# one token; edges of a step; two steps in one workgroup and three in three; 64 workgroups of 1 and 4 steps and
-# one step too many; many heads, up to the last sizes of either width and beyond them
+# one token; edges of a step; two steps in one workgroup and three in three; 64 workgroups of 1 and 4 steps and one step more; many heads, around
+# the tokens up to which each width is taken (beyond them a call may be taken by its load: test_gpu_few_load.py asks which kernel runs)
 @pytest.mark.parametrize("n,heads", [(1, 1), (16, 1), (17, 3), (32, 2), (33, 2), (1025, 1), (4096, 1), (4097, 1), (1, 256),
                                      (8, 256), (9, 256), (32, 256), (33, 256), (1024, 8), (1025, 8)])
 @pytest.mark.parametrize("r,source", [(20, "kv"), (33, "v"), (64, "kv"), (128, "k"), (128, "kv")])

@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 
 SEED = 0xC0DE0013
 FEW_F32 = gu.limit("scores_kernels.hip", "kFewF32Tokens")
+FEW_HEADS_F32 = gu.limit("scores_kernels.hip", "kFewHeadsF32")
 SPLIT_HEADS = gu.limit("curdkv_internal.h", "kSplitMaxHeads")
 SPLIT_FROM_ELSE = gu.limit("split_select.hip", "kSplitMinTokensElse")
 GATHER_LONGEST = 32 * gu.limit("select_kernels.hip", "kSelThreads")     # up to here few heads take the selection that gathers
@@ -30,6 +31,8 @@ NORM_TOL = 1e-6
 def test_f32_scores_beyond_the_few(n, r, source):
     import torch
     heads = FEW_F32 // n + 1
+    if r <= 32:                                          # (the kernel for few tokens takes more of these, by its load, in up to so many heads)
+        heads = max(heads, FEW_HEADS_F32 + 1) if n < 1000 else 64
     g = torch.Generator(device="cuda")
     g.manual_seed(n * 512 + r)
     K = torch.randn((heads, n, 128), generator=g, device="cuda") * torch.exp(torch.randn((heads, 1, 128), generator=g, device="cuda"))
@@ -37,6 +40,9 @@ def test_f32_scores_beyond_the_few(n, r, source):
     with B.Context(heads, 1, 4, 128, r, "fp32", n, SEED, source) as ctx:
         out = torch.full((heads, n), float("nan"), device="cuda")
         ctx.scores(K, V, n, out)
+        name, args, _ = gu.launches(lambda: ctx.scores(K, V, n, out))[0]
+        assert name == "scores_f32_kernel" and args[4] == (r > 32), (name, args)
+        torch.cuda.synchronize()
         raw, sums = torch.full((heads, n), float("nan"), device="cuda"), torch.zeros((heads,), dtype=torch.float64, device="cuda")
         ctx.scores_append(K, V, n, 0, n, raw, sums)
         out, raw, sums = out.cpu().numpy(), raw.cpu().numpy().astype(np.float64), sums.cpu().numpy()
@@ -48,20 +54,23 @@ def test_f32_scores_beyond_the_few(n, r, source):
             assert np.linalg.norm(x - want) <= NORM_TOL * np.linalg.norm(want), (n, r, source, i)
 
 
-# (widths without columns of padding, whose zeros make an infinity a NaN in any order)
-@pytest.mark.parametrize("r", [64, 128])
-def test_f32_rows_that_are_not_finite_beyond_the_few(r):
+# (widths without columns of padding, whose zeros make an infinity a NaN in any order; up to 32 columns the split products begin at a number of tokens)
+@pytest.mark.parametrize("r,heads", [(32, 1024), (64, FEW_F32 // 300 + 1), (128, FEW_F32 // 300 + 1)])
+@pytest.mark.parametrize("source", ["kv", "k", "v"])
+def test_f32_rows_that_are_not_finite_beyond_the_few(r, heads, source):
     import torch
     n = 300
-    heads = FEW_F32 // n + 1
     g = torch.Generator(device="cuda")
     g.manual_seed(r)
     K, V = torch.randn((heads, n, 128), generator=g, device="cuda"), torch.randn((heads, n, 128), generator=g, device="cuda")
 
     def raw_scores():
-        with B.Context(heads, 1, 4, 128, r, "fp32", n, SEED) as ctx:
+        with B.Context(heads, 1, 4, 128, r, "fp32", n, SEED, source) as ctx:
             raw, sums = torch.full((heads, n), -1.0, device="cuda"), torch.zeros((heads,), dtype=torch.float64, device="cuda")
-            ctx.scores_append(K, V, n, 0, n, raw, sums)
+            call = lambda: ctx.scores_append(K, V, n, 0, n, raw, sums)
+            call()
+            name, args, _ = gu.launches(call)[0]
+            assert name == "scores_f32_kernel" and args[4] == 1, (name, args)
             return raw.cpu().numpy()
 
     clean = raw_scores()
@@ -70,9 +79,44 @@ def test_f32_rows_that_are_not_finite_beyond_the_few(r):
     V[1, 77, 100] = float("nan")
     V[1, 299, 0] = -float("inf")
     raw = raw_scores()
-    assert np.all(np.isposinf(raw[1, [5, 130, 299]])) and np.isnan(raw[1, 77])
-    clean[1, [5, 77, 130, 299]] = raw[1, [5, 77, 130, 299]] = 0.0
+    infinite, nan = [j for j, of in ((5, "k"), (130, "k"), (299, "v")) if of in source], [77] if "v" in source else []
+    assert np.all(np.isposinf(raw[1, infinite])) and np.all(np.isnan(raw[1, nan]))
+    clean[1, infinite + nan] = raw[1, infinite + nan] = 0.0
     assert np.array_equal(raw, clean)
+
+
+# rows that the bf16 parts do not hold, scored again after the walk, where the scan also counts for the split selection
+@pytest.mark.parametrize("r", [32, 64])
+def test_one_call_with_rows_at_the_top_of_the_range(r):
+    """A channel of the largest floats under a sketch of 2^-80: the rows' first parts are infinite, their scores are not, and are the largest."""
+    import torch
+    heads, n, s = 4, 70001, 4
+    g = torch.Generator(device="cuda")
+    g.manual_seed(r)
+    K = torch.randn((heads, n, 128), generator=g, device="cuda")
+    V = torch.randn((heads, n, 128), generator=g, device="cuda") * torch.randn((heads, n, 1), generator=g, device="cuda").exp()
+    K[..., 17] = 0
+    top = torch.tensor([3, 4, 63, 64, 30000, 30031, 44444, n - 1], device="cuda")
+    K[1, top, 17] = float(np.finfo(np.float32).max)
+    K[3, top, 17] = -float(np.finfo(np.float32).max)
+    G = np.stack([orc.sketch(SEED, 0, h, heads, 128, r, "fp32") for h in range(heads)])
+    G[:, 17] = np.sign(G[:, 17]) * 2.0 ** -80
+    budgets = np.array([n // 10, n // 10, n // 3, 9], np.int32)
+    with B.Context(1, heads, 4, 128, r, "fp32", n, SEED) as ctx:
+        for h in range(heads):
+            ctx.set_sketch(0, h, G[h].astype(np.float32))
+        sc, ix, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, s, "fp32", one_call=True)
+        name, args, _ = gu.launches(lambda: ctx.compress(K, V, n, budgets, s, off, sc, ix, Ko, Vo))[0]
+        torch.cuda.synchronize()
+    assert name == "scores_f32_kernel" and args[3:5] == (1, 1), (name, args)
+    for h in range(heads):
+        lt = orc.scores(K[h].double().cpu().numpy(), V[h].double().cpu().numpy(), G[h])
+        rows = ix[off[h]:off[h + 1]].cpu().numpy().astype(np.int64)
+        gu.check_scores(sc[h].cpu().numpy(), lt, str(h))
+        gu.check_selection(rows, lt, int(budgets[h]), s, str(h))
+        if h in (1, 3):
+            assert np.isin(top.cpu().numpy(), rows).sum() >= (8 if h == 1 else 5)          # (of head 3 five beside the sinks, of which 3 is one)
+        assert torch.equal(Ko[off[h]:off[h + 1]], K[h, rows]) and torch.equal(Vo[off[h]:off[h + 1]], V[h, rows])
 
 
 def _full_bin(rng, n, in_bin):

@@ -1,6 +1,6 @@
 """fp32 calls of few tokens in all: workgroups of 16 tokens whose waves share the products.  Scores
 and running sums against the float64 oracle at the edges of the 16-token steps, with one step and
-several per workgroup, on both sides of the lines where the other kernels take over, and the
+several per workgroup, around the lines where the other kernels take over, and the
 other kernels on rows that are not finite at a size that is theirs."""
 import numpy as np
 import pytest
@@ -17,8 +17,8 @@ SEED = 0xC0DE0009
 NORM_TOL = 1e-6
 
 
-# one token; edges of a step; 64 workgroups of 1, 2 and 6 steps (the last ones short or empty); one
-# step too many (the other kernel); many heads, up to the last size and beyond it
+# one token; edges of a step; 64 workgroups of 1, 2 and 6 steps (the last ones short or empty), and one step more; many heads, around the tokens up to which
+# every width is taken (beyond them, (65, 256) and (2049, 8), r = 20 is by its load, and the wider ones are not: test_gpu_few_load.py asks which kernel runs)
 @pytest.mark.parametrize("n,heads", [(1, 1), (16, 1), (17, 3), (1024, 1), (1025, 1), (6144, 1), (6145, 1),
                                      (1, 256), (33, 256), (64, 256), (65, 256), (2048, 8), (2049, 8)])
 @pytest.mark.parametrize("r,source", [(20, "kv"), (33, "kv"), (64, "k"), (128, "kv"), (128, "v")])

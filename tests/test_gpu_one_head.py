@@ -16,8 +16,8 @@ pytestmark = pytest.mark.gpu
 SCORE_TOL, SUM_TOL = {20: 48 * 2.0 ** -24, 64: 24 * 2.0 ** -24, 128: 24 * 2.0 ** -24}, 1e-6
 
 
-# A wave has two 32-token tiles at least: 256 workgroups from 65536 tokens on.  (8192, 24576 + 1: the few-token kernel's
-# and the split selection's lines; 2 heads of 3000 and 3 of 3000: its workgroups are as many as units, or 64 a head)
+# A wave has two 32-token tiles at least: 256 workgroups from 65536 tokens on.  (8192: tokens that the few-token kernel takes whatever its load, 24576 + 1: the split
+# selection's line; 2 heads of 3000 and 3 of 3000: the few-token kernel's workgroups are as many as units, or 64 a head)
 @pytest.mark.parametrize("heads,n", [(2, 3000), (3, 3000), (1, 4096), (1, 8192), (1, 8193), (1, 16640), (1, 24577), (2, 24577), (1, 40001), (2, 49153), (1, 65537), (2, 100003), (1, 131072), (1, 131073)])
 @pytest.mark.parametrize("r,dtype", [(20, "bf16"), (128, "bf16"), (20, "fp32"), (64, "fp32")])
 def test_scores_sums_and_selection(heads, n, r, dtype):
