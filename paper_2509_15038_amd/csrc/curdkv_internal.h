@@ -97,8 +97,9 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
 // caller adds the partial sums (launch_accumulate).
 int64_t scan_bytes(const curdkv_ctx* ctx, int64_t n);                  // that a scan of n tokens a head reads
 bool many_kept(const curdkv_ctx* ctx, int64_t n, int64_t kept);        // a quarter of the rows or more
-// In 256ths: how much of a scan, its end, should leave its rows in the caches for a gather of `kept` rows that follows.
-int stay_share(const curdkv_ctx* ctx, int64_t n, int64_t kept);
+// In 256ths: how much of a streamed scan, at its start and at its end, goes through the caches all the same; kept: rows that a gather reads afterwards; one_workgroup: scans a head.
+struct CachedShares { int start, end; };
+CachedShares cached_shares(const curdkv_ctx* ctx, int64_t n, int64_t kept, bool one_workgroup);
 hipError_t launch_accumulate(const curdkv_ctx* ctx, int blocks_per_head, double* sums, bool reset,
                              hipStream_t stream);
 hipError_t launch_normalise_sums(const curdkv_ctx* ctx, const float* raw, const double* sums,

@@ -31,7 +31,7 @@ __global__ __launch_bounds__(kFusedThreads, 2) void fused_kernel(
     const uint4* __restrict__ K, const uint4* __restrict__ V, const uint4* __restrict__ Gp,
     int32_t n, int32_t n_sink, const int64_t* __restrict__ offsets, float* __restrict__ scores_out,
     int32_t* __restrict__ indices, u32x4* __restrict__ K_out, u32x4* __restrict__ V_out,
-    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, int stay) {
+    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, CachedShares cached) {
     extern __shared__ float sc[];                  // [n rounded up to 64]; later int32 stage[n]
     __shared__ SelectShared<kFusedThreads, KPT> sm;
     __shared__ float wsum[kFusedWaves];
@@ -51,7 +51,7 @@ __global__ __launch_bounds__(kFusedThreads, 2) void fused_kernel(
         per_wave += per_wave & 1;                  // whole pairs
         const int32_t t_begin = wave * per_wave;
         const int32_t t_end = t_begin + per_wave < tiles ? t_begin + per_wave : tiles;
-        acc = scan_tiles<CB, SRC, PROJ, false, MODE>(G, Kh, Vh, n, t_begin, t_end, sc, 0, lane, scan_phase(head, wave), nullptr, 0, stay_tile(t_begin, t_end, stay));
+        acc = scan_tiles<CB, SRC, PROJ, false, MODE>(G, Kh, Vh, n, t_begin, t_end, sc, 0, lane, scan_phase(head, wave), nullptr, 0, cached_tiles(t_begin, t_end, cached));
     }
     // ---- 2. sum over the head ----------------------------------------------------------
     acc = wave_sum(acc);
@@ -137,7 +137,7 @@ struct FusedArgs {
     uint32_t* hist_out;
     uint32_t* coarse_out;
     hipStream_t stream;
-    int stay;                // stay_share
+    CachedShares cached;
     bool past;               // rows past the caches (streams_fused)
     int dyn;                 // >= 0: only raise the kernel's dynamic LDS limit to this, no launch
 };
@@ -150,7 +150,7 @@ static hipError_t one(const FusedArgs& a) {
     const size_t lds = (((size_t)a.n + 63) & ~(size_t)63) * 4;
     fused_kernel<CB, KPT, SRC, PROJ, MODE><<<dim3((unsigned)a.ctx->heads), kFusedThreads, lds, a.stream>>>(
         (const uint4*)a.K, (const uint4*)a.V, (const uint4*)a.ctx->d_G, a.n, a.n_sink, a.d_offsets,
-        a.scores, a.indices, (u32x4*)a.K_out, (u32x4*)a.V_out, a.hist_out, a.coarse_out, a.stay);
+        a.scores, a.indices, (u32x4*)a.K_out, (u32x4*)a.V_out, a.hist_out, a.coarse_out, a.cached);
     return hipGetLastError();
 }
 
@@ -164,7 +164,7 @@ static hipError_t by_mode(const FusedArgs& a) {
             if (e != hipSuccess) return e;
         } else if (!a.past) return one<CB, KPT, SRC, PROJ, kStreamNone>(a);
     }
-    return one<CB, KPT, SRC, PROJ, kStreamStay>(a);
+    return one<CB, KPT, SRC, PROJ, kStreamParts>(a);
 }
 
 template <int CB, int KPT, bool PROJ>
@@ -246,8 +246,8 @@ hipError_t launch_fused(const curdkv_ctx* ctx, const void* K, const void* V, int
                         const int64_t* d_offsets, float* scores, int32_t* indices, void* K_out,
                         void* V_out, hipStream_t stream, int64_t kept, uint32_t* hist_out, uint32_t* coarse_out) {
     if (!coarse_out) hist_out = nullptr;           // the two go together
-    const int stay = indices ? 0 : stay_share(ctx, n, kept);
-    FusedArgs a{ctx, K, V, (int32_t)n, n_sink, d_offsets, scores, indices, K_out, V_out, hist_out, coarse_out, stream, stay, streams_fused(ctx, n, kept), -1};
+    const CachedShares cached = cached_shares(ctx, n, indices ? 0 : kept, /*one_workgroup=*/true);
+    FusedArgs a{ctx, K, V, (int32_t)n, n_sink, d_offsets, scores, indices, K_out, V_out, hist_out, coarse_out, stream, cached, streams_fused(ctx, n, kept), -1};
     return dispatch(a, ctx->col_blocks, keys_per_thread(n), ctx->cfg.score_source, !ctx->cfg.no_projection);
 }
 

@@ -44,8 +44,9 @@ union Chunk {           // 16 bytes of a token row: 8 bf16
 // 2 GB by 1024 such waves, us: half lines 95.6 and 357, non-temporal 94.8 and 362; whole lines 95.1 and 357, non-temporal 81.8 and 312 (6.9 TB/s).
 // The loads of 16 rows come in pairs (a, b) of 128 bytes a row: for a, lanes (tok, q) take 16-byte piece q of row tok (tok < 8) or q + 4 of row tok - 8,
 // for b the same of rows 8..15; settle_pair then exchanges between the halves of every 16 lanes, three register moves a word.
-// A scan that gathers many rows afterwards leaves those of its end in the caches: kStreamStay.
-constexpr int kStreamNone = 0, kStreamAll = 1, kStreamStay = 2;
+// Parts of a streamed scan go through the caches all the same, by ordinary loads of whole lines (kStreamParts, CachedShares): a large one's start, to push out what was written
+// just before, and the end of one that gathers many rows afterwards.
+constexpr int kStreamNone = 0, kStreamAll = 1, kStreamParts = 2;
 
 template <bool STREAM>
 __device__ __forceinline__ int load_row(int tok, int which) { return STREAM ? (tok & 7) + 8 * which : tok; }
@@ -149,6 +150,13 @@ __device__ __forceinline__ uint32_t scan_phase(int head, int wave_of_head) {
     return (uint32_t)head * 5u + (uint32_t)wave_of_head * 3u;
 }
 
+struct CachedTiles { int32_t start_to, end_from; };             // of a wave's walk, in its order: those before start_to and from end_from on
+
+__device__ __forceinline__ CachedTiles cached_tiles(int32_t begin, int32_t end, CachedShares share) {
+    const int64_t len = begin < end ? end - begin : 0;
+    return {begin + (int32_t)((len * share.start) >> 8), end - (int32_t)((len * share.end) >> 8)};
+}
+
 // The walk over tiles [t_begin, t_end) of one wave, shared by the storage types: two tile
 // buffers, tiles taken in pairs.
 //   load_tile(Tile&, tile, check, how)  issues the loads of one tile; check = std::true_type clamps
@@ -156,17 +164,17 @@ __device__ __forceinline__ uint32_t scan_phase(int head, int wave_of_head) {
 //                                   tiles known to lie entirely below n: no clamping, no
 //                                   predicate, hence no branch, which keeps the steady-state
 //                                   loop one basic block so that the compiler's wait counts let
-//                                   loads stay in flight; how = std::false_type (kStreamStay, from
-//                                   tile stay_from of the walk on): rows that are to stay in the caches;
+//                                   loads stay in flight; how = std::false_type (kStreamParts, `cached`):
+//                                   rows that go through the caches;
 //   compute_tile(Tile&, slot)       scores the tile, once per load of it, as first (0) or second (1) of its pair;
 //   store_pair(tile, check)         puts the pair's 64 scores away (tile = its first tile).
 // t_begin must be even, and t_end even or equal to ceil(n/32): a missing second tile is taken
 // to lie beyond n.
 template <int MODE, class Tile, class Load, class Compute, class Store>
-__device__ __forceinline__ void walk_tiles(int32_t n, int32_t t_begin, int32_t t_end, uint32_t phase, int32_t stay_from,
+__device__ __forceinline__ void walk_tiles(int32_t n, int32_t t_begin, int32_t t_end, uint32_t phase, CachedTiles cached,
                                            Load load_tile, Compute compute_tile, Store store_pair) {
     const std::true_type checked, past;
-    const std::false_type unchecked, stay;
+    const std::false_type unchecked, through;
     if (t_begin < t_end) {
         Tile ra, rb;
         const int32_t full = n / kTileTokens;                   // tiles with all 32 rows below n
@@ -208,22 +216,18 @@ __device__ __forceinline__ void walk_tiles(int32_t n, int32_t t_begin, int32_t t
                 store_pair(at(t), checked);                     // an absent second tile lies beyond n
             }
         };
-        if constexpr (MODE == kStreamStay) {                    // (a kernel of its own: the code of both ways costs short scans 3 %)
-            steady(stay_from < t_steady ? stay_from : t_steady, past);
-            if (stay_from < t_end) {
-                steady(t_steady, stay);
-                finish(stay);
+        if constexpr (MODE == kStreamParts) {                   // (a kernel of its own: the code of both ways costs short scans 3 %)
+            steady(cached.start_to < t_steady ? cached.start_to : t_steady, through);
+            steady(cached.end_from < t_steady ? cached.end_from : t_steady, past);
+            if (cached.end_from < t_end) {
+                steady(t_steady, through);
+                finish(through);
             } else finish(past);
         } else {
             steady(t_steady, past);
             finish(past);
         }
     }
-}
-
-// The first tile, in the order of the walk, whose rows stay in the caches where a wave streams tiles [begin, end): the last share / 256 of them.
-__device__ __forceinline__ int32_t stay_tile(int32_t begin, int32_t end, int share) {
-    return begin < end ? end - (int32_t)(((int64_t)(end - begin) * share) >> 8) : end;
 }
 
 // COUNT: every score is also counted in `hist` (raw_hist_count), those of the first n_sink rows as nothing:
@@ -233,7 +237,7 @@ template <int CB, int SRC = kSrcKV, bool PROJ = true, bool COUNT = false, int MO
 __device__ __forceinline__ float scan_tiles(const SketchRegs<CB>& G, const uint4* __restrict__ Kh,
                                             const uint4* __restrict__ Vh, int32_t n, int32_t t_begin,
                                             int32_t t_end, float* lds_rows, int32_t row0, int lane,
-                                            uint32_t phase, uint32_t* hist, int32_t n_sink, int32_t stay_from) {
+                                            uint32_t phase, uint32_t* hist, int32_t n_sink, CachedTiles cached) {
     constexpr bool STREAM = MODE != kStreamNone;
     const int tok = lane & 15, q = lane >> 4;
     float acc_sum = 0.f;
@@ -311,7 +315,7 @@ __device__ __forceinline__ float scan_tiles(const SketchRegs<CB>& G, const uint4
             acc_sum += pend;
         }
     };
-    walk_tiles<MODE, TileRegs>(n, t_begin, t_end, phase, stay_from, load_tile, compute_tile, store_pair);
+    walk_tiles<MODE, TileRegs>(n, t_begin, t_end, phase, cached, load_tile, compute_tile, store_pair);
     return acc_sum;
 }
 
@@ -416,7 +420,7 @@ __device__ __forceinline__ float scan_tiles_f32(const SketchF32<CB>& G, const fl
             acc_sum += pend;
         }
     };
-    walk_tiles<kStreamNone, TileRegsF32>(n, t_begin, t_end, phase, t_end, load_tile, compute_tile, store_pair);
+    walk_tiles<kStreamNone, TileRegsF32>(n, t_begin, t_end, phase, CachedTiles{}, load_tile, compute_tile, store_pair);
     return acc_sum;
 }
 
@@ -630,7 +634,7 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
                                                 const float4* __restrict__ Vh,
                                                 int32_t n, int32_t t_begin, int32_t t_end, float* lds_rows,
                                                 int32_t row0, int lane, uint32_t phase, uint32_t* hist,
-                                                int32_t n_sink, int32_t stay_from) {
+                                                int32_t n_sink, CachedTiles cached) {
     const int tok = lane & 15, q = lane >> 4;
     const int32_t groups = (t_end - t_begin + 1) >> 1;          // of 64 tokens
     if (groups <= 0) return 0.f;
@@ -708,8 +712,9 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
     const int32_t base = t_begin * kTileTokens;
     int32_t g = rot;
     load(base + g * 64, std::bool_constant<STREAM>{});
-    auto walk = [&](int32_t from, int32_t to, auto how) {       // groups from .. to-1 of the walk
-        for (int32_t i = from; i < to; ++i) {
+    int32_t i = 0;
+    auto walk = [&](int32_t to, auto how) {                     // groups i .. to-1 of the walk
+        for (; i < to; ++i) {
             const int32_t first = base + g * 64;
             g = g + 1 == groups ? 0 : g + 1;
             step(0, first + 16, how);
@@ -726,13 +731,17 @@ __device__ __forceinline__ float scan_tiles_f32_split(const bf16x8* gs, const fl
             }
         }
     };
-    int32_t past = 0;                                           // groups whose rows do not stay in the caches
     if constexpr (STREAM) {
-        past = (stay_from - t_begin) >> 1;
-        past = past < 0 ? 0 : past < groups ? past : groups;
-        walk(0, past, std::true_type{});
-    }
-    walk(past, groups, std::false_type{});
+        auto group = [&](int32_t tile) { const int32_t to = (tile - t_begin) >> 1; return to < groups ? to : groups; };
+        int32_t until = group(cached.start_to);
+        const int32_t past_to = group(cached.end_from);
+#pragma clang loop unroll(disable)
+        for (int part = 0; part < 2; ++part) {                  // as in walk_tiles
+            walk(until, std::false_type{});
+            walk(past_to, std::true_type{});
+            until = groups;
+        }
+    } else walk(groups, std::false_type{});
     if (__any(acc_sum != acc_sum)) {                            // some row is not a number: do those again
         acc_sum = 0.f;
         for (int32_t j = base; j < base + groups * 64; j += 64) {

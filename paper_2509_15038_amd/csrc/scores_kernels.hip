@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
     const uint4* __restrict__ K, const uint4* __restrict__ V, const uint4* __restrict__ Gp,
     float* __restrict__ scores, float* __restrict__ partial, int64_t n, int blocks_per_head,
     int64_t out_stride, int64_t out_offset, double* __restrict__ sums, int restart,
-    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, int hists, int32_t n_sink, int stay) {
+    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, int hists, int32_t n_sink, CachedShares share) {
     constexpr int kStageTiles = Stage<CB>::kTiles;
     __shared__ float stage[4][kStageTiles * kTileTokens];
     __shared__ uint32_t hist[COUNT ? kRawHistWords : 1];
@@ -80,14 +80,14 @@ __global__ __launch_bounds__(256, (CB <= 4 ? 2 : 1)) void scores_bf16_kernel(
     float* sh = scores + (size_t)head * out_stride + out_offset;   // score of row j goes to sh[j]
     float* mine = stage[wave];
     float acc_sum = 0.f;
-    const int32_t stay_from = stay_tile(t_begin, t_end, stay);
+    const CachedTiles cached = cached_tiles(t_begin, t_end, share);
     for (int32_t seg = t_begin; seg < t_end; seg += kStageTiles) {
         const int32_t seg_end = seg + kStageTiles < t_end ? seg + kStageTiles : t_end;
         const int32_t r0 = seg * kTileTokens;
         acc_sum += scan_tiles<CB, SRC, PROJ, COUNT, MODE>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane,
                                                    // (streamed rows gain nothing from different starts here: 32 heads of 32768 tokens 89.7 us with, 89.0 without, appends of
                                                    // 1024 tokens to 256 heads 24.5 and 23.5; the kernel of one workgroup a head does, 256 of 32768 623 and 630)
-                                                   MODE == kStreamNone ? scan_phase(head, blk * 4 + wave) : 0u, hist, n_sink, stay_from);
+                                                   MODE == kStreamNone ? scan_phase(head, blk * 4 + wave) : 0u, hist, n_sink, cached);
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
         for (int32_t r = r0 + lane; r < r1; r += 64) sh[r] = mine[r - r0];
     }
@@ -113,7 +113,7 @@ __global__ __launch_bounds__((ShapeF32<CB, SPLIT>::kWaves * 64), (SPLIT ? 2 : 1)
     const float4* __restrict__ K, const float4* __restrict__ V, const float4* __restrict__ Gp,
     float* __restrict__ scores, float* __restrict__ partial, int64_t n, int blocks_per_head,
     int64_t out_stride, int64_t out_offset, double* __restrict__ sums, int restart,
-    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, int hists, int32_t n_sink, int stay) {
+    uint32_t* __restrict__ hist_out, uint32_t* __restrict__ coarse_out, int hists, int32_t n_sink, CachedShares share) {
     constexpr int kWaves = ShapeF32<CB, SPLIT>::kWaves;
     constexpr int kStageTiles = ShapeF32<CB, SPLIT>::kTiles;
     __shared__ float stage[kWaves][kStageTiles * kTileTokens];
@@ -150,12 +150,12 @@ __global__ __launch_bounds__((ShapeF32<CB, SPLIT>::kWaves * 64), (SPLIT ? 2 : 1)
     float* sh = scores + (size_t)head * out_stride + out_offset;
     float* mine = stage[wave];
     float acc_sum = 0.f;
-    const int32_t stay_from = stay_tile(t_begin, t_end, stay);
+    const CachedTiles cached = cached_tiles(t_begin, t_end, share);
     for (int32_t seg = t_begin; seg < t_end; seg += kStageTiles) {
         const int32_t seg_end = seg + kStageTiles < t_end ? seg + kStageTiles : t_end;
         const int32_t r0 = seg * kTileTokens;
         const uint32_t phase = scan_phase(head, blk * kWaves + wave);
-        if constexpr (SPLIT) acc_sum += scan_tiles_f32_split<CB, SRC, COUNT, STREAM>(gs, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink, stay_from);
+        if constexpr (SPLIT) acc_sum += scan_tiles_f32_split<CB, SRC, COUNT, STREAM>(gs, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink, cached);
         else acc_sum += scan_tiles_f32<CB, SRC, PROJ, COUNT>(G, Kh, Vh, n32, seg, seg_end, mine, r0, lane, phase, hist, n_sink);
         const int32_t r1 = seg_end * kTileTokens < n32 ? seg_end * kTileTokens : n32;
         for (int32_t r = r0 + lane; r < r1; r += 64) sh[r] = mine[r - r0];
@@ -439,10 +439,18 @@ static bool stream_rows(const curdkv_ctx* ctx, int64_t n, int64_t kept, bool une
     return scan_bytes(ctx, n) > (many_kept(ctx, n, kept) || uneven ? kStreamBytesRereadMany : kept > 0 ? kStreamBytesReread : kStreamBytes);
 }
 
-int stay_share(const curdkv_ctx* ctx, int64_t n, int64_t kept) {
-    if (!many_kept(ctx, n, kept)) return 0;
-    const int64_t share = kStayBytes * 256 / scan_bytes(ctx, n);
-    return (int)(share < 256 ? share : 256);
+// What the kernel before has just written lies dirty in the Infinity Cache, and every non-temporal read of such a line writes it back. Where one workgroup takes long over a head
+// those writes trickle in among the reads of the whole scan; rows read by ordinary loads at its start push the lines out at once (e^-(bytes / 256 MB) of them are left: it does not
+// evict the oldest). One call, a tenth kept, K and V written just before: us, all through the caches, streamed, and streamed after 800 MB: 256 heads of 32768 tokens 909, 995 and
+// 863, of 20000 592, 609 and 575, 224 of 32768 830, 853 and 828, 448 1601, 1667 and 1594, r = 128 256 934, 972 and 950, fp32, r = 20, of 24576 1352, 1443 and 1269. With other caches read before, 256 of 32768 take
+// 848, 782 and 785, between calls of the same kind 856, 781 and 793, behind other writes 879, 797 and 816. Of fewer bytes a head the streamed scan is ahead by itself (256 of 16384 505
+// and 502, keys alone of 32768 579 and 503), of more as well (of 65536 1831 and 1775, after 600 MB 1806; fp32 of 32768 1807 and 1791), and with several workgroups a head (128 of 32768 509 and 509, 64 311 and 272).
+constexpr int64_t kStartBytes = 800000000, kStartHeadBytes = 10000000, kStartHeadBytesMost = 26000000;
+
+CachedShares cached_shares(const curdkv_ctx* ctx, int64_t n, int64_t kept, bool one_workgroup) {
+    const int64_t bytes = scan_bytes(ctx, n), head = bytes / ctx->heads;
+    const auto part = [&](int64_t of) { return (int)(of < bytes ? of * 256 / bytes : 256); };
+    return {one_workgroup && head >= kStartHeadBytes && head <= kStartHeadBytesMost ? part(kStartBytes) : 0, many_kept(ctx, n, kept) ? part(kStayBytes) : 0};
 }
 
 hipError_t configure_kernels(curdkv_ctx* ctx) {
@@ -470,7 +478,7 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
     }
     uint32_t* hist = with_hist ? split_hist(ctx) : nullptr;
     uint32_t* coarse = with_hist ? split_coarse(ctx) : nullptr;
-    const int stay = stay_share(ctx, n, kept);
+    const CachedShares share = cached_shares(ctx, n, kept, bph == 1);
     const dim3 grid((unsigned)(ctx->heads * bph));
     float* part = ctx->d_partial;
     auto launch = [&](auto cb, auto src, auto proj, auto count) {
@@ -491,17 +499,17 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
             auto launch_bf16 = [&](auto past) {
                 scores_bf16_kernel<CB, SRC, PROJ, COUNT, decltype(past)::value><<<grid, 256, 0, stream>>>(
                     (const uint4*)K, (const uint4*)V, (const uint4*)ctx->d_G, scores, part, n, bph, out_stride, out_offset, sums, rs,
-                    hist, coarse, hists, n_sink, stay);
+                    hist, coarse, hists, n_sink, share);
             };
             if (!stream_past) launch_bf16(std::integral_constant<int, kStreamNone>{});
-            else if (stay == 0) launch_bf16(std::integral_constant<int, kStreamAll>{});
-            else launch_bf16(std::integral_constant<int, kStreamStay>{});
+            else if (share.start == 0 && share.end == 0) launch_bf16(std::integral_constant<int, kStreamAll>{});
+            else launch_bf16(std::integral_constant<int, kStreamParts>{});
         } else {
             auto launch_f32 = [&](auto split, auto past) {
                 constexpr bool SPLIT = decltype(split)::value;
                 scores_f32_kernel<CB, SRC, PROJ, COUNT, SPLIT, decltype(past)::value><<<grid, ShapeF32<CB, SPLIT>::kWaves * 64, 0, stream>>>(
                     (const float4*)K, (const float4*)V, (const float4*)ctx->d_G, scores, part, n, bph, out_stride, out_offset, sums, rs,
-                    hist, coarse, hists, n_sink, stay);
+                    hist, coarse, hists, n_sink, share);
             };
             if constexpr (CB > 2) launch_f32(std::true_type{}, std::false_type{});
             else if constexpr (PROJ) {

@@ -157,3 +157,38 @@ def test_one_tensor_by_one_workgroup_a_head(source, r, projection, tokens, keep)
         gu.check_scores(sc[i].cpu().numpy(), lt, str(i))
         gu.check_selection(rows.cpu().numpy().astype(np.int64), lt, int(budgets[i]), s, str(i))
         assert torch.equal(Ko[off[i]:off[i + 1]], K[i][rows.long()]) and torch.equal(Vo[off[i]:off[i + 1]], V[i][rows.long()])
+
+
+START = gu.limit("scores_kernels.hip", "kStartHeadBytes")
+
+
+# one workgroup takes long over a head: the start of its scan goes through the caches, from a number of bytes a head on, then the rows go past them, and at the end through them again
+# where many are kept; by the kernel that does everything, by it and separate kernels, and by the general ones
+@pytest.mark.parametrize("heads,r,keep,dtype,source", [(256, 64, 0.05, "bf16", "kv"), (256, 20, 0.5, "bf16", "kv"), (200, 20, 0.1, "bf16", "kv"), (200, 64, 0.4, "bf16", "kv"), (256, 128, 0.1, "bf16", "kv"),
+                                                       (256, 20, 0.1, "fp32", "kv"), (256, 32, 0.4, "fp32", "kv")])
+@pytest.mark.parametrize("side", ["below", "from"])
+def test_the_start_of_a_long_scan(heads, r, keep, dtype, source, side):
+    import torch
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    heads, s = heads * units // 256, 4
+    row = 128 * (2 if dtype == "bf16" else 4) * (2 if source == "kv" else 1)
+    n = (START - 1) // row + (side == "from")
+    assert (n * row >= START) == (side == "from")
+    K, V = _cache(heads, n, dtype, n + r)
+    budgets = np.full((heads,), int(keep * n), np.int32)
+    with B.Context(heads, 1, 4, 128, r, dtype, n, SEED, source) as ctx:
+        sc, ix, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, s, dtype, one_call=True)
+        name, args, grid = gu.launches(lambda: ctx.compress(K, V, n, budgets, s, off, sc, ix, Ko, Vo))[0]
+        torch.cuda.synchronize()
+    assert grid[0] == heads, (name, grid)                       # one workgroup a head
+    if name == "scores_bf16_kernel":
+        assert args[4] == (2 if side == "from" or keep >= 0.25 else 1), args
+    else:
+        assert name == ("fused_kernel" if dtype == "bf16" else "scores_f32_kernel") and args[4:] == ((2,) if dtype == "bf16" else (1, 1)), (name, args)
+    for i in (0, heads // 2, heads - 1):
+        rows = ix[off[i]:off[i + 1]]
+        lt = _want(K, V, i, r, dtype, source, True)
+        gu.check_scores(sc[i].cpu().numpy(), lt, str(i))
+        assert np.linalg.norm(sc[i].cpu().numpy() - lt) <= NORM_TOL * np.linalg.norm(lt), i
+        gu.check_selection(rows.cpu().numpy().astype(np.int64), lt, int(budgets[i]), s, str(i))
+        assert torch.equal(Ko[off[i]:off[i + 1]], K[i][rows.long()]) and torch.equal(Vo[off[i]:off[i + 1]], V[i][rows.long()])
