@@ -225,9 +225,9 @@ bool fused_applicable(const curdkv_ctx* ctx, int64_t n) {
     const size_t lds = (((size_t)n + 63) & ~(size_t)63) * 4 + sizeof(SelectShared<kFusedThreads, 64>) + 1024;
     if (lds > (size_t)ctx->lds_limit) return false;
     // One workgroup per head and one workgroup per CU at a time: the heads go through the chip
-    // in rounds of num_cu, and a last round that is mostly empty costs a full scan time.  Measured
-    // at n = 32768: 256, 512, 768 heads are faster fused; 128, 288, 384, 640 heads are faster
-    // with the general kernels, 192 is a tie.
+    // in rounds of num_cu, and a last round that is mostly empty costs a full scan time.  One call, a tenth kept, us, general kernels and fused: 32768 tokens, 128 heads 422 and 620, 192 669 and
+    // 651, 224 724 and 706, 240 788 and 754, 256 836 and 797, 288 1007 and 1312, 384 1292 and 1365, 461 1514 and 1472, 512 1676 and 1635, 640 2153 and 2169, 768 2478 and 2427; 8192 tokens, 192 heads 160
+    // and 161, 240 197 and 191, 384 337 and 343, 512 424 and 406, 768 657 and 615; 2048 tokens, 192 51.6 and 50.7, 240 61.4 and 59.7, 288 73.8 and 98.4, 512 116 and 119, 768 177 and 178.
     const int64_t rounds = (ctx->heads + ctx->num_cu - 1) / ctx->num_cu;
     return (int64_t)ctx->heads * 10 >= rounds * ctx->num_cu * 9;
 }

@@ -271,12 +271,10 @@ static bool f32_split(const curdkv_ctx* ctx, int64_t n) {
 // the number of workgroups a unit gets times their length, and ties go to the fewer, longer
 // ones (measured at n = 32768, scoring and normalisation: 32 heads 8 per head, 64 heads 4,
 // 128 heads 2; 2 to 5 % faster than filling two workgroups per unit).
-// One exception, measured at n = 32768 with the two-per-unit kernel: where one workgroup per
-// head already puts four waves on three quarters of the compute units (192 or 224 heads of
-// 256, or 448 of 512 places), HBM is saturated by those alone, and one long-lived workgroup per
-// head, writing its scores in two bursts, beats any split by 2.5-3.5 % although units stay idle
-// (192 heads: 562 us against 576 for four per head; 224: 649 against 671; 448: 1305 against
-// 1338).
+// One exception, with the two-per-unit kernel: where one workgroup per head already puts four waves on three
+// quarters of the compute units (192 or 224 heads of 256, or 448 of 512 places), HBM is saturated by those alone, and one long-lived workgroup per
+// head, writing its scores in two bursts at most, beats any split although units stay idle. curdkv_scores, us, one and several per head: 192 heads of 4096 tokens 68.8 and 71.6, of 16384 246.8
+// and 264.1, of 32768 527.5 and 523.2; 208 259.7 and 291.8, 553.6 and 602.1; 224 77.8 and 82.4, 276.5 and 326.3, 596.3 and 616.7; 448 of 8192 297.7 and 319.6, of 32768 1215 and 1258.
 static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n, bool streams, int64_t most_blocks = kMaxBlocksPerHead) {
     const int64_t tiles = (n + kTileTokens - 1) / kTileTokens;
     const bool wide = ctx->cfg.dtype == CURDKV_DTYPE_BF16 && ctx->col_blocks > 2 && !ctx->cfg.no_projection;

@@ -491,8 +491,8 @@ static hipError_t launch_reg(const curdkv_ctx* ctx, float* scores, int32_t n, in
 // Which calls take it.  One call, separate kernels -> this, us: 1 head of 1024 tokens (fp32) 12.1 -> 10.2, of 4096 15.4 -> 13.4; 8 heads of
 // 2048 tokens, 30 % kept, 16.7 -> 14.6, of 8192, 20 %, 20.8 -> 18.1, of 24000, 60 %, 54.9 -> 49.8; 32 heads of 4096, 20 %, 27.4 -> 24.1,
 // of 16384, 10 %, 72.8 -> 70.5; 64 heads of 8192, 10 %, 74.6 -> 71.3; 128 heads of 2048, 10 %, 40.6 -> 38.5.  With more rows the
-// gather kernel's many small workgroups make up for its launch: half kept of 64 heads of 8192 tokens (262144 rows)
-// 106.4 -> 105.6, of 128 heads 185.9 -> 190.6; a tenth of 64 heads of 32768 (209664) 241.8 -> 242.5: hence 512 rows a unit.
+// gather kernel's many small workgroups make up for its launch: 64 heads of 8192 tokens, 35 % kept (183488 rows), 88.4 -> 87.5, half (262144) 100.7 -> 98.4, 70 % 113.8 -> 115.1,
+// 128 heads of 8192, 20 % (209664), 132.8 -> 137.2, 64 of 16384, 20 %, 131.7 -> 135.1: hence 512 rows a unit.
 // The split selection, which comes second, is behind up to the longest head this holds, as long as the rows are few: a tenth kept, this
 // and split, r = 64, 1 head of 32768 tokens 22.2 and 26.3; 4 of 32768 29.6 and 31.0; 8 of 24000 33.8 and 38.0, of 32768 44.9 and 49.1; 16 of 24000 51.6 and 55.6, of 32768
 // 66.9 and 68.4; 24 of 32768 92.6 and 93.3, 32 of 24000 88.7 and 90.7, of 32768 116.8 and 116.5; r = 20, 115.9 and 116.0.
