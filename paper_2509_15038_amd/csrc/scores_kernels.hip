@@ -426,15 +426,17 @@ int64_t scan_bytes(const curdkv_ctx* ctx, int64_t n) {
 
 bool many_kept(const curdkv_ctx* ctx, int64_t n, int64_t kept) { return kept * 4 >= ctx->heads * n; }
 
-// Where select_gather_kernel gathers uneven budgets, its workgroups that copy the large one's rows wait longer for those that come from HBM: from 256 MB on, and
-// fp32 of one tensor, whose other tensor's rows come from there anyway, always.  One call, 20 % kept, caches and streamed, Dirichlet budgets within layers of 8: 112 heads
+// Where select_gather_kernel gathers uneven budgets, its workgroups that copy the large one's rows wait longer for those that come from HBM: from 256 MB on.  One call, 20 % kept, caches and streamed, Dirichlet budgets within layers of 8: 112 heads
 // of 3487 tokens (200 MB) 68.0 and 74.6, 32 of 12207 74.1 and 77.4, 64 of 6103 in turn with writing them 136.7 and 146.9; one head of 8 with nearly all rows: 64 of 6103 68.9 and 76.2, of 7812
-// (256 MB) 86.6 and 95.7, 32 of 17700 (290 MB) 104.3 and 110.6 (240 MB and more behind 270 MB of other traffic are ahead streamed, Dirichlet budgets: 32 of 14648 106.9 and 93.2); fp32, r = 20, 112
-// of 1744 (200 MB) 75.0 and 82.6, 64 of 3052 75.6 and 80.9, 64 of 4090 (268 MB) 91.5 and 97.1, and behind other traffic 112.0 and 100.4.
+// (256 MB) 86.6 and 95.7, 32 of 17700 (290 MB) 104.3 and 110.6 (240 MB and more behind 270 MB of other traffic are ahead streamed, Dirichlet budgets: 32 of 14648 106.9 and 93.2).
+// fp32 over the bf16 units: past the caches by any size for scores alone (r = 20, 8 heads of 16384 tokens, three in turn, 34.9 and 35.4, behind other writes 45.7 and 35.8; keys alone 22.2 and 21.2); a call that
+// gathers from 256 MB on, whatever its budgets: 20 % kept, 8 of 24000 (197 MB), one cache again, in turn, behind reads, 64.3 and 70.3, 68.3 and 72.4, 68.4 and 73.9 (fp32 units, caches, 67, 70 and 70.5), just written 77.5 and 74.0, behind other writes
+// 84.5 and 73.2; 32 of 4096 43.4 and 48.0, 46.5 and 48.8, 47.1 and 51.0; 200 of 1000 61 and 67, 67.9 and 68, 68.9 and 70.4; a tenth kept, 8 of 16384 42.3 and 46.3, 45.9 and 47.6, 47.1 and 48.8, keys alone 33.1
+// and 31.9, 35.2 and 34.1, 35.6 and 35.4, of 32768 54.2 and 58.0, 60.3 and 60.2, 60.8 and 61.1; 268 MB, 8 of 32768, 76 and 82, 84 and 85, 85 and 86, behind other writes 105 and 85.
 static bool stream_rows(const curdkv_ctx* ctx, int64_t n, int64_t kept, bool uneven) {
-    if (ctx->cfg.dtype == CURDKV_DTYPE_F32)
-        return ctx->col_blocks == 1 && f32_split(ctx, n) && !(uneven && ctx->cfg.score_source == CURDKV_SCORE_KV && scan_bytes(ctx, n) <= kStreamBytesRereadMany);
-    return scan_bytes(ctx, n) > (many_kept(ctx, n, kept) || uneven ? kStreamBytesRereadMany : kept > 0 ? kStreamBytesReread : kStreamBytes);
+    const int64_t bytes = scan_bytes(ctx, n);
+    if (ctx->cfg.dtype == CURDKV_DTYPE_F32) return ctx->col_blocks == 1 && f32_split(ctx, n) && (kept == 0 || bytes > kStreamBytesRereadMany);
+    return bytes > (many_kept(ctx, n, kept) || uneven ? kStreamBytesRereadMany : kept > 0 ? kStreamBytesReread : kStreamBytes);
 }
 
 // What the kernel before has just written lies dirty in the Infinity Cache, and every non-temporal read of such a line writes it back. Where one workgroup takes long over a head
@@ -511,12 +513,9 @@ hipError_t launch_scores(const curdkv_ctx* ctx, const void* K, const void* V, in
             };
             if constexpr (CB > 2) launch_f32(std::true_type{}, std::false_type{});
             else if constexpr (PROJ) {
-                const bool parts = f32_split(ctx, n);
-                if (parts && stream_past) launch_f32(std::true_type{}, std::true_type{});
-                else if constexpr (SRC == kSrcKV && !COUNT) {        // (stream_rows: parts that are not streamed are for select_gather_kernel)
-                    if (parts) launch_f32(std::true_type{}, std::false_type{});
-                    else launch_f32(std::false_type{}, std::false_type{});
-                } else launch_f32(std::false_type{}, std::false_type{});
+                if (!f32_split(ctx, n)) launch_f32(std::false_type{}, std::false_type{});
+                else if (stream_past) launch_f32(std::true_type{}, std::true_type{});
+                else launch_f32(std::true_type{}, std::false_type{});
             } else launch_f32(std::false_type{}, std::false_type{});
         }
     };

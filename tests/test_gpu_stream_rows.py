@@ -112,7 +112,7 @@ def test_one_call_at_the_edge_of_even_budgets(heads, n, dtype, more):
         sc, ix, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, s, dtype, one_call=True)
         scan, select = gu.launches(lambda: ctx.compress(K, V, n, budgets, s, off, sc, ix, Ko, Vo))
     past = bytes_read > (LIMIT_REREAD if even else LIMIT_REREAD_MANY)
-    assert scan[:2] == (("scores_bf16_kernel", (2, 0, 1, 0, int(past))) if dtype == "bf16" else ("scores_f32_kernel", (2, 0, 1, 0, 1, int(even or past))))
+    assert scan[:2] == (("scores_bf16_kernel", (2, 0, 1, 0, int(past))) if dtype == "bf16" else ("scores_f32_kernel", (2, 0, 1, 0, 1, int(bytes_read > LIMIT_REREAD_MANY))))
     assert select[0] == "select_gather_kernel"
     if n > 2048:
         assert (select[2][0] == heads) == even
@@ -188,6 +188,30 @@ def test_the_start_of_a_long_scan(heads, r, keep, dtype, source, side):
     for i in (0, heads // 2, heads - 1):
         rows = ix[off[i]:off[i + 1]]
         lt = _want(K, V, i, r, dtype, source, True)
+        gu.check_scores(sc[i].cpu().numpy(), lt, str(i))
+        assert np.linalg.norm(sc[i].cpu().numpy() - lt) <= NORM_TOL * np.linalg.norm(lt), i
+        gu.check_selection(rows.cpu().numpy().astype(np.int64), lt, int(budgets[i]), s, str(i))
+        assert torch.equal(Ko[off[i]:off[i + 1]], K[i][rows.long()]) and torch.equal(Vo[off[i]:off[i + 1]], V[i][rows.long()])
+
+
+# up to 32 columns of an fp32 cache: rows of a call that gathers stay in the caches up to a number of bytes; gathered by the selection, by the split selection that has its counts
+# from the scoring and by a kernel of its own, one tensor scored and both, to whole and ragged groups
+@pytest.mark.parametrize("heads,n,r,source,keep", [(128, 1024, 20, "kv", 0.1), (8, 24000, 32, "kv", 0.2), (8, 24011, 20, "k", 0.1), (16, 16301, 20, "v", 0.2), (3, 65001, 32, "kv", 0.1), (5, 60001, 20, "k", 0.4),
+                                                   (100, 2099, 20, "kv", 0.7), (256, 1009, 20, "v", 0.1)])
+def test_one_call_of_narrow_sketches_in_fp32(heads, n, r, source, keep):
+    import torch
+    bytes_read, s = heads * n * 512 * (2 if source == "kv" else 1), 4
+    assert bytes_read <= LIMIT_REREAD_MANY
+    K, V = _cache(heads, n, "fp32", n + r)
+    budgets = np.full((heads,), int(keep * n), np.int32)
+    with B.Context(heads, 1, 4, 128, r, "fp32", n, SEED, source) as ctx:
+        sc, ix, Ko, Vo, off = gu.run_path(ctx, K, V, n, budgets, s, "fp32", one_call=True)
+        name, args, _ = gu.launches(lambda: ctx.compress(K, V, n, budgets, s, off, sc, ix, Ko, Vo))[0]
+        torch.cuda.synchronize()
+    assert (name, args) == ("scores_f32_kernel", (2, {"kv": 0, "k": 1, "v": 2}[source], 1, int(n > 24576), 1, 0)), (name, args)
+    for i in (0, heads // 2, heads - 1):
+        rows = ix[off[i]:off[i + 1]]
+        lt = _want(K, V, i, r, "fp32", source, True)
         gu.check_scores(sc[i].cpu().numpy(), lt, str(i))
         assert np.linalg.norm(sc[i].cpu().numpy() - lt) <= NORM_TOL * np.linalg.norm(lt), i
         gu.check_selection(rows.cpu().numpy().astype(np.int64), lt, int(budgets[i]), s, str(i))
