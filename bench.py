@@ -35,7 +35,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E, vendor figure
 FP32_MFMA_PEAK_TFLOPS = 157.3     # MI355X, dense fp32 matrix rate
 BF16_MFMA_PEAK_TFLOPS = 2500.0    # MI355X, dense bf16 matrix rate
-FUSED_GATHER_MAX_PERCENT = 11     # curdkv_compress: above this share of rows kept, the fused kernel only scores
+FUSED_GATHER_MAX_PERCENT = 10     # curdkv_compress: above this share of rows kept, the fused kernel only scores
 
 
 def algorithmic_bytes(cfg, budgets, source="kv"):

@@ -341,8 +341,8 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     // Beyond, the stand-alone gather kernel (many small workgroups, 32 waves per compute unit)
     // moves rows enough faster than the fused kernel's last phase (one long-lived workgroup of 8
     // waves per unit), and finds those of the scan's end in the Infinity Cache, to pay for two more launches and a
-    // selection from memory.  One call for 256 heads, us, fused and as separate kernels: 32768 tokens at keep 5 / 10 / 12 / 15 / 20 / 30 % 700 / 779 / 813 / 865 / 944 / 1114 and
-    // 717 / 785 / 813 / 855 / 924 / 1050; 16384 at 12 / 15 % 411 / 438 and 420 / 441; 12000 at 10 / 16 / 20 % 295 / 326 / 356 and 300 / 329 / 351; 8000 at
+    // selection from memory.  One call for 256 heads, us, fused and as separate kernels: 32768 tokens at keep 5 / 10 / 12 / 15 / 20 / 30 % 718 / 798 / 829 / 882 / 961 / 1127 and
+    // 728 / 796 / 823 / 863 / 930 / 1063; 20000 at 5 / 10 / 13 / 16 / 20 % 451 / 500 / 533 / 563 / 602 and 457 / 498 / 522 / 546 / 579 (scans whose start goes through the caches); 16384 at 12 / 15 % 411 / 438 and 420 / 441; 12000 at 10 / 16 / 20 % 295 / 326 / 356 and 300 / 329 / 351; 8000 at
     // 15 / 25 % 216 / 252 and 221 / 253; 4096 at 20 / 30 / 40 % 122 / 142 / 161 and 126 / 142 / 157; 2048 at 20 / 50 / 80 % 71 / 94 / 118 and 79 / 103 / 126; 1000 at
     // 20 / 90 % 34 / 58 and 39 / 64; 300 at 50 % 18 and 23.
     // Those are equal budgets.  A head that keeps more than the average copies its rows while other units are done, 8 to 17 us per 512 rows more.  Dirichlet budgets within
@@ -350,7 +350,8 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     // 150 / 653 80 and 78, 600 / 2612 122 and 96; 6000 tokens 600 / 2612 179 and 159; 16384 tokens 819 / 3565 413 and 382, 1638 / 7131 483 and 406.  In
     // several rounds a unit can meet two such heads, or none: 512 heads of 1000 tokens, one head of 8 with nearly all rows, 200 / 1000 87.8 and 75.7, 500 / 1000 110 and 98, of 700 350 / 700 80 and 72, of 512 256 / 512 58 and 55, but Dirichlet budgets 71 and 72 and 49 and 55.
     const bool fusable = fused_applicable(ctx, n);
-    const int64_t most_rows = n <= kFusedGatherTokens ? n : kFusedGatherRows + n * kFusedGatherPercent / 100;
+    const bool cached_start = cached_shares(ctx, n, /*kept=*/0, /*one_workgroup=*/true).start > 0;
+    const int64_t most_rows = n <= kFusedGatherTokens ? n : cached_start ? n / kFusedGatherLongShare : kFusedGatherRows + n * kFusedGatherPercent / 100;
     const int64_t more_rows = max_budget - total / ctx->heads;
     const int64_t most_more = ctx->heads > ctx->num_cu ? kFusedUnevenRowsRounds : n <= kFusedGatherTokens ? kFusedUnevenRows : kFusedUnevenRowsLong;
     const bool big_gather = total > ctx->heads * most_rows || more_rows > most_more;

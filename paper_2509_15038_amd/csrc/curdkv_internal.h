@@ -17,7 +17,8 @@ constexpr int kMaxBlocksPerHead = 256; // partial sums kept per (layer, group): 
 constexpr int kTileTokens = 32;        // tokens per wave tile
 constexpr int kCompactRowsPerBlock = 128;  // output rows per entry of the gather's table of heads
 constexpr int kFusedGatherTokens = 2048;       // curdkv_compress: heads up to which the fused kernel also gathers, whatever is kept on average,
-constexpr int kFusedGatherRows = 800, kFusedGatherPercent = 9;   // longer ones: up to so many rows kept, and so much of the head more;
+constexpr int kFusedGatherRows = 800, kFusedGatherPercent = 9;   // longer ones: up to so many rows kept, and so much of the head more,
+constexpr int kFusedGatherLongShare = 10;                        // or, where the scan's start goes through the caches (cached_shares), a tenth of it;
 constexpr int kFusedUnevenRows = 512, kFusedUnevenRowsLong = 256, kFusedUnevenRowsRounds = 384;    // and a head at most so many more than the average (Rounds: more heads than units)
 
 struct BlockInfo {                     // for gather block b, whose first output row is b*128:

@@ -233,7 +233,7 @@ bool fused_applicable(const curdkv_ctx* ctx, int64_t n) {
 }
 
 // More than 2048 tokens a head are more rows than the caches hold (fetch in scan_device.h), us, kept in the caches and streamed: 256 heads of 2048 tokens (268 MB), a tenth
-// kept, 63.2 either way, of 4096, a fifth, 134.6 and 126.5, of 32768, a tenth, 863 and 781; of 1024 33.8 and 35.0.  One tensor, half as many bytes: keys alone, a twentieth
+// kept, 63.2 either way, of 4096, a fifth, 134.6 and 126.5, of 32768, a tenth, 863 and 781 (795 after a start through the caches, cached_shares); of 1024 33.8 and 35.0.  One tensor, half as many bytes: keys alone, a twentieth
 // kept, 2049 tokens (134 MB) 37.1 and 34.8, 3000 49.2 and 45.1; but where a quarter or more is kept, up to 180 MB, half and four fifths of 2049 74.2 and 78.0, 95.9 and 100.0, values alone 74.2 and
 // 78.6, 93.9 and 100.1, of 2600 (170 MB) 90.2 and 92.4, 116.8 and 122.6; of 3000 (197 MB) 105.6 and 103.4, 134.6 and 138.7, of 3900 keys alone 135.4 and 129.5, 180.6 and 173.8.
 constexpr int64_t kFusedStreamBytesMany = 180000000;

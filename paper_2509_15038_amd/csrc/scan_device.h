@@ -231,8 +231,8 @@ __device__ __forceinline__ void walk_tiles(int32_t n, int32_t t_begin, int32_t t
 }
 
 // COUNT: every score is also counted in `hist` (raw_hist_count), those of the first n_sink rows as nothing:
-// one LDS atomic per 64 tokens, and the histogram written at the end (scan of 32 heads of 32768 tokens 95.4 us without,
-// 99.7 with it, which saves a pass over the scores).
+// one LDS atomic per 64 tokens, and the histogram written at the end (scan of 32 heads of 40000 tokens 114.7 us without,
+// 116.4 with it, of 8 of 131072 84.0 and 84.8, which saves a pass over the scores).
 template <int CB, int SRC = kSrcKV, bool PROJ = true, bool COUNT = false, int MODE = kStreamNone>
 __device__ __forceinline__ float scan_tiles(const SketchRegs<CB>& G, const uint4* __restrict__ Kh,
                                             const uint4* __restrict__ Vh, int32_t n, int32_t t_begin,

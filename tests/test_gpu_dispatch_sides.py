@@ -197,13 +197,17 @@ def test_one_call_with_more_rows_than_the_split_gathers(dtype):
 
 
 LONG_FROM = gu.limit("curdkv_internal.h", "kFusedGatherTokens")
+SHARE = gu.limit("curdkv_internal.h", "kFusedGatherLongShare")
+CACHED_FROM = gu.limit("scores_kernels.hip", "kStartHeadBytes") // 512 + 1
 UNEVEN, UNEVEN_LONG, UNEVEN_ROUNDS = (gu.limit("curdkv_internal.h", "kFusedUnevenRows" + which) for which in ("", "Long", "Rounds"))
 
 
-# budgets whose largest is a row beyond what one workgroup copies alone, and not; the average is within the fused kernel's limit in all
+# budgets whose largest is a row beyond what one workgroup copies alone, and not, the average within the fused kernel's limit; equal ones on both sides of that limit, where the scan's start
+# goes through the caches and where it does not
 @pytest.mark.parametrize("rounds,n,average,more,fused", [(1, LONG_FROM, 300, UNEVEN, True), (1, LONG_FROM, 300, UNEVEN + 1, False), (1, 1111, 500, UNEVEN + 1, False), (1, 700, 300, 400, True),
                                                          (1, LONG_FROM + 1, 300, UNEVEN_LONG, True), (1, LONG_FROM + 1, 300, UNEVEN_LONG + 1, False),
-                                                         (2, 801, 390, UNEVEN_ROUNDS, True), (2, 801, 390, UNEVEN_ROUNDS + 1, False)])
+                                                         (2, 801, 390, UNEVEN_ROUNDS, True), (2, 801, 390, UNEVEN_ROUNDS + 1, False),
+                                                         (1, CACHED_FROM, CACHED_FROM // SHARE, 0, True), (1, CACHED_FROM, CACHED_FROM // SHARE + 1, 0, False), (1, CACHED_FROM - 1, CACHED_FROM // SHARE + 1, 0, True)])
 def test_fused_gather_of_uneven_budgets(rounds, n, average, more, fused):
     import torch
     heads, s = rounds * torch.cuda.get_device_properties(0).multi_processor_count, 4
