@@ -275,6 +275,9 @@ static bool f32_split(const curdkv_ctx* ctx, int64_t n) {
 // quarters of the compute units (192 or 224 heads of 256, or 448 of 512 places), HBM is saturated by those alone, and one long-lived workgroup per
 // head, writing its scores in two bursts at most, beats any split although units stay idle. curdkv_scores, us, one and several per head: 192 heads of 4096 tokens 68.8 and 71.6, of 16384 246.8
 // and 264.1, of 32768 527.5 and 523.2; 208 259.7 and 291.8, 553.6 and 602.1; 224 77.8 and 82.4, 276.5 and 326.3, 596.3 and 616.7; 448 of 8192 297.7 and 319.6, of 32768 1215 and 1258.
+// Scans whose start would go through the caches (cached_shares) take it from four fifths on, below 257 heads: one call, a tenth kept, in turn, just written, behind other writes, 192 heads of 20000 tokens 425,
+// 478, 446 and 402, 429, 408, of 32768 667, 755, 677 and 654, 695, 669, 200 689, 766, 697 and 684, 720, 696, 208 703, 787, 712 and 746, 789, 768, 224 751, 836, 764 and 769, 827, 797, 448 1490, 1574,
+// 1511 and 1530, 1640, 1596.
 static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n, bool streams, int64_t most_blocks = kMaxBlocksPerHead) {
     const int64_t tiles = (n + kTileTokens - 1) / kTileTokens;
     const bool wide = ctx->cfg.dtype == CURDKV_DTYPE_BF16 && ctx->col_blocks > 2 && !ctx->cfg.no_projection;
@@ -303,7 +306,8 @@ static int pick_blocks_per_head(const curdkv_ctx* ctx, int64_t n, bool streams, 
     if (lo < 1) lo = 1;
     if (!wide && !f32 && lo <= 2 && ctx->heads <= 2 * (int64_t)ctx->num_cu) {
         const int64_t in_last = ctx->heads - (ctx->heads > ctx->num_cu ? ctx->num_cu : 0);   // heads in the last round
-        if (in_last * 4 >= 3 * (int64_t)ctx->num_cu) return 1;
+        const bool later = ctx->heads <= ctx->num_cu && cached_shares(ctx, n, 0, true).start > 0;
+        if (later ? in_last * 5 >= 4 * (int64_t)ctx->num_cu : in_last * 4 >= 3 * (int64_t)ctx->num_cu) return 1;
     }
     // (up to one workgroup per place where the heads are few: 8 heads of 131072 tokens 105 us on 184 units, 99 on 256;
     // curdkv_scores of 1 head of 131072 tokens 34.6 us with 64 workgroups, 18.3 with 256, in fp32 77.1 and 36.8)
