@@ -364,11 +364,14 @@ int curdkv_compress(curdkv_ctx* ctx, const void* K, const void* V, int64_t n, co
     const bool together = !fusable && select_gather_applicable(ctx, n, total);
     const bool split = !fusable && !together && split_applicable(ctx, n, true), with_hist = split && split_counts_in_scan(ctx, n);
     if (!scores && !together) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (!ctx->d_scores_ws && fusable && hipStreamIsCapturing(st, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone)
+            return all_fused();                                 // (which needs no scratch: a capture cannot have any allocated)
         if (!ctx->d_scores_ws &&
             hipMalloc((void**)&ctx->d_scores_ws, (size_t)ctx->heads * (size_t)ctx->cfg.max_tokens * sizeof(float)) != hipSuccess) {
             (void)hipGetLastError();
             ctx->d_scores_ws = nullptr;
-            return fusable ? all_fused() : CURDKV_ERR_OOM;      // (the one kernel needs no scratch)
+            return fusable ? all_fused() : CURDKV_ERR_OOM;
         }
         scores = ctx->d_scores_ws;
     }

@@ -229,3 +229,34 @@ def test_fused_gather_of_uneven_budgets(rounds, n, average, more, fused):
         mine = slice(int(off[h]), int(off[h + 1]))
         assert np.array_equal(rows[mine].cpu().numpy(), orc.select(sc[h], int(budgets[h]), s)), h
         assert torch.equal(Ko[mine], K[h, rows[mine]]) and torch.equal(Vo[mine], V[h, rows[mine]]), h
+
+
+def test_uneven_budgets_captured_before_any_scratch_for_scores():
+    """The call with scores has uploaded the offsets; the same without scores is captured before it has ever run: by the one kernel, which allocates nothing."""
+    import torch
+    heads, n, s = torch.cuda.get_device_properties(0).multi_processor_count, 1024, 4
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    K = torch.randn((heads, n, 128), generator=g, device="cuda").to(torch.bfloat16)
+    V = (torch.randn((heads, n, 128), generator=g, device="cuda") * torch.randn((heads, n, 1), generator=g, device="cuda").exp()).to(torch.bfloat16)
+    budgets = np.full((heads,), 200, np.int32)
+    budgets[3] += UNEVEN + 1
+    off = np.concatenate([[0], np.cumsum(budgets, dtype=np.int64)])
+    with B.Context(1, heads, 4, 128, 64, "bf16", n, SEED) as ctx:
+        sc = torch.empty((heads, n), dtype=torch.float32, device="cuda")
+        ix = torch.empty((int(off[-1]),), dtype=torch.int32, device="cuda")
+        Ko, Vo = torch.empty((int(off[-1]), 128), dtype=K.dtype, device="cuda"), torch.empty((int(off[-1]), 128), dtype=K.dtype, device="cuda")
+        ix2, Ko2, Vo2 = torch.empty_like(ix), torch.empty_like(Ko), torch.empty_like(Vo)
+        ctx.compress(K, V, n, budgets, s, off, sc, ix, Ko, Vo)
+        torch.cuda.synchronize()
+        assert [name for name, _, _ in gu.launches(lambda: ctx.compress(K, V, n, budgets, s, off, None, ix2, Ko2, Vo2))] == ["fused_kernel"]
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            ctx.compress(K, V, n, budgets, s, off, None, ix2, Ko2, Vo2)
+        for _ in range(3):
+            for t in (ix2, Ko2, Vo2):
+                t.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(ix, ix2) and torch.equal(Ko, Ko2) and torch.equal(Vo, Vo2)
+        del graph
